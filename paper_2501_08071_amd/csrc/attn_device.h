@@ -6,12 +6,7 @@
 
 namespace attn_device {
 
-// plain maxima, without the quiet-NaN canonicalisation the C library semantics would add
-__device__ __forceinline__ float vmax(float a, float b) {
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
+// plain maximum of three (vmax in gfx950_common.h: of two)
 __device__ __forceinline__ float vmax3(float a, float b, float c) {
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));

@@ -4,7 +4,7 @@
 // Matrix-core kernel (K % 32 == 0, N % 8 == 0):
 //   * a workgroup of four wavefronts (2 x 2) owns a 64 TM x 64 TN tile of c, a wavefront 32 TM x 32 TN of
 //     it as TM x TN accumulator blocks of v_mfma_f32_32x32x16; TM = TN = 2 (128 x 128) when that gives
-//     the chip enough tiles, else 1 (64 x 64);
+//     the chip enough tiles, else 1 (64 x 64); problems with enough tiles of 256 x 256: gemm_lrelu_wide_kernel;
 //   * computed transposed, c^T = b^T a^T: the first operand is a 32 x 16 piece of b^T, fetched from the
 //     row-major b tile in LDS with transposing reads (ds_read_b64_tr_b16), the second 16 contiguous bytes
 //     of a row of a; a lane then holds four consecutive n of one row m of c, and the tile of c goes out
@@ -12,9 +12,6 @@
 //   * K runs in steps of 32 through four LDS stages; tiles come straight from global memory into LDS
 //     (global_load_lds_dwordx4, 16 bytes per lane, 1 KiB of consecutive LDS per instruction), three
 //     stages ahead, with the bank-conflict swizzle applied to the global address of each lane;
-//   * the 256 x 256 tile has eight wavefronts, two per SIMD, in two groups that alternate between reading a
-//     block's operands from LDS and issuing its matrix instructions, one phase apart: the matrix pipe of a
-//     SIMD is fed by one wavefront while the other waits for the barrier, for LDS and for its loads;
 //   * rows past M repeat the last row and column chunks past N the last chunk (results masked at the
 //     store), so the loop has no edge cases.
 // Small problems (at most 256 tiles of 32 x 32, K >= 256): 32 x 32 tiles with K split over the four wavefronts of
@@ -28,9 +25,6 @@
 #include "gemm_launch.h"
 #include "gfx950_common.h"
 
-#ifndef GEMM_PINGPONG
-#define GEMM_PINGPONG 1   // eight-wavefront tiles: two groups of wavefronts alternate operand reads and matrix instructions
-#endif
 #ifndef GEMM_NST
 #define GEMM_NST 4   // LDS stages of 32 in K; GEMM_NST - 1 of them in flight ahead of the one in use
 #endif
@@ -50,6 +44,28 @@ template <int CHUNKS>
 __device__ __forceinline__ constexpr int swz_b(int row) {
     return CHUNKS >= 16 ? (((row & 3) << 2) | ((row >> 2) & 3))   // the low four chunk bits = 256 bytes = all banks
                         : ((((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1));
+}
+
+// Workgroup -> tile.  Workgroup b runs on XCD b % 8, each with an L2 of its own, so every XCD takes a contiguous run of
+// the tile list, and the list goes through GEMM_GROUP_M tile rows at a time, column by column: the workgroups that an
+// XCD runs together then cover a compact block of c (4 x 8 tiles when it holds 32) and share both their rows of a and
+// their columns of b.
+#ifndef GEMM_GROUP_M
+#define GEMM_GROUP_M 4
+#endif
+struct TileIndex {
+    int bi, tm, tn;
+};
+__device__ __forceinline__ TileIndex tile_of_workgroup(int tiles_m, int tiles_n) {
+    const int total = (int)gridDim.x, b = (int)blockIdx.x;
+    const int q = total >> 3, r = total & 7, x = b & 7;
+    const int c = x * q + (x < r ? x : r) + (b >> 3);
+    const int per = tiles_m * tiles_n;
+    const int bi = c / per, t = c - bi * per;
+    const int g = t / (GEMM_GROUP_M * tiles_n), u = t - g * (GEMM_GROUP_M * tiles_n);
+    const int left = tiles_m - g * GEMM_GROUP_M, rows = left < GEMM_GROUP_M ? left : GEMM_GROUP_M;
+    const int tn = u / rows;
+    return {bi, g * GEMM_GROUP_M + (u - tn * rows), tn};
 }
 
 __device__ __forceinline__ float leaky(float t, float slope) { return t >= 0.f ? t : slope * t; }
@@ -89,10 +105,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     const int l32 = lane & 31, h = lane >> 5;
     const int wm = wave % WM, wn = wave / WM;
 
-    const int bx = blockIdx.x;
-    const int tn_i = bx % tiles_n;
-    const int tm_i = (bx / tiles_n) % tiles_m;
-    const int bi = bx / (tiles_n * tiles_m);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n);
     const int m0 = tm_i * BM, n0 = tn_i * BN;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -185,79 +198,36 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
             for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = E::mfma(o.b[tn], o.a[tm], acc[tn][tm]);
     };
 
-    if constexpr (NW == 8 && GEMM_PINGPONG) {
-        // Eight wavefronts, two per SIMD: two groups (0-3 and 4-7; w and w + 4 share a SIMD) run the same
-        // sequence of phases one phase apart, a barrier between phases.  In its read phase L(k) a wavefront
-        // fetches all operands of block k from LDS into registers; in its matrix phase M(k) it issues the
-        // block's matrix instructions and nothing else: on every SIMD one wavefront feeds the matrix pipe while
-        // the other waits for the barrier, for LDS and for its loads.  Slot 2k: first group L(k), second
-        // M(k-1); slot 2k+1: first group M(k), second L(k).  Block k is read in slots 2k and 2k+1 and those
-        // reads are used up in slots 2k+1 and 2k+2: its stage takes block k + NST in slot 2k+3, from the first
-        // group in its M(k+1) and from the second in its L(k+1).  Every wavefront has its share of block k in
-        // LDS before the barrier that opens slot 2k: all but the loads of the NST-2 later blocks.
-        const bool grp1 = wave >= NW / 2;
-        Ops ops[2];
-        wait_tile_loads<(NST - 2) * IPS>();
-        __syncthreads();
-        if (grp1) asm volatile("s_barrier" ::: "memory");
-        auto step = [&](int kb, auto phase) {
-            constexpr int PH = decltype(phase)::value;
-            wait_tile_loads<(NST - 2) * IPS>();
-            asm volatile("s_barrier" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            read_ops(ops[0], PH * STAGE, 0);
-            read_ops(ops[1], PH * STAGE, 1);
-            if (grp1) issue(kb + NST - 1, (PH + NST - 1) % NST);
-            __builtin_amdgcn_sched_barrier(0);
-            wait_tile_loads<(NST - 2) * IPS>();
-            asm volatile("s_barrier" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(ops[0]);
-            __builtin_amdgcn_sched_barrier(0);
-            if (!grp1) issue(kb + NST - 1, (PH + NST - 1) % NST);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(ops[1]);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        static_assert(NST >= 3, "one block in use, at least two in flight");
-        for (int k0 = 0; k0 < nk; k0 += NST) {
-            [&]<int... PH>(std::integer_sequence<int, PH...>) {
-                ((k0 + PH < nk ? step(k0 + PH, std::integral_constant<int, PH>{}) : (void)0), ...);
-            }(std::make_integer_sequence<int, NST>{});
-        }
-        if (!grp1) asm volatile("s_barrier" ::: "memory");   // the first group's last one
-    } else {
-        // Block kb: its first k step runs on operands read during block kb-1 (`ahead`), its second on operands
-        // read under the first, and under the second the first operands of block kb+1 are read: the matrix
-        // pipe never waits for an LDS round trip behind a barrier.  For that, block kb+1 must be complete one
-        // barrier early: every wavefront checks its share of it before the barrier of block kb.
-        Ops ahead;
-        wait_tile_loads<(NST - 2) * IPS>();
-        __syncthreads();
-        read_ops(ahead, 0, 0);
-        auto step = [&](int kb, auto phase) {
-            constexpr int PH = decltype(phase)::value;
-            // blocks up to kb+1 have landed when at most the loads of the NST-3 later blocks are still out
-            wait_tile_loads<(NST - 3) * IPS>();
-            asm volatile("s_barrier" ::: "memory");
-            // ... for everybody, and everybody is done with block kb-1: its stage takes block kb+NST-1
-            issue(kb + NST - 1, (PH + NST - 1) % NST);
-            Ops second;
-            read_ops(second, PH * STAGE, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(ahead);
-            __builtin_amdgcn_sched_barrier(0);
-            read_ops(ahead, ((PH + 1) % NST) * STAGE, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(second);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        static_assert(NST >= 3, "one block in use, one read ahead, at least one in flight");
-        for (int k0 = 0; k0 < nk; k0 += NST) {
-            [&]<int... PH>(std::integer_sequence<int, PH...>) {
-                ((k0 + PH < nk ? step(k0 + PH, std::integral_constant<int, PH>{}) : (void)0), ...);
-            }(std::make_integer_sequence<int, NST>{});
-        }
+    // Block kb: its first k step runs on operands read during block kb-1 (`ahead`), its second on operands
+    // read under the first, and under the second the first operands of block kb+1 are read: the matrix
+    // pipe never waits for an LDS round trip behind a barrier.  For that, block kb+1 must be complete one
+    // barrier early: every wavefront checks its share of it before the barrier of block kb.
+    Ops ahead;
+    wait_tile_loads<(NST - 2) * IPS>();
+    __syncthreads();
+    read_ops(ahead, 0, 0);
+    auto step = [&](int kb, auto phase) {
+        constexpr int PH = decltype(phase)::value;
+        // blocks up to kb+1 have landed when at most the loads of the NST-3 later blocks are still out
+        wait_tile_loads<(NST - 3) * IPS>();
+        asm volatile("s_barrier" ::: "memory");
+        // ... for everybody, and everybody is done with block kb-1: its stage takes block kb+NST-1
+        issue(kb + NST - 1, (PH + NST - 1) % NST);
+        Ops second;
+        read_ops(second, PH * STAGE, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(ahead);
+        __builtin_amdgcn_sched_barrier(0);
+        read_ops(ahead, ((PH + 1) % NST) * STAGE, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        multiply(second);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    static_assert(NST >= 3, "one block in use, one read ahead, at least one in flight");
+    for (int k0 = 0; k0 < nk; k0 += NST) {
+        [&]<int... PH>(std::integer_sequence<int, PH...>) {
+            ((k0 + PH < nk ? step(k0 + PH, std::integral_constant<int, PH>{}) : (void)0), ...);
+        }(std::make_integer_sequence<int, NST>{});
     }
     wait_tile_loads<0>();   // the repeated loads of the last steps must not outlive the workgroup's LDS
 
@@ -295,6 +265,191 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 }
 
 
+// Large problems: 256 x 256 tiles, four wavefronts (2 x 2), one per SIMD with the whole register file, 128 x 128 of c
+// per wavefront.
+// What bounds it: the clock, which the chip lowers with the switching activity of the matrix pipes and of what feeds
+// them (1.4 to 1.8 GHz here).  So the kernel is laid out for energy per operation:
+//   * v_mfma_f32_16x16x32: on N(0,1) operands and nothing else to do the chip sustains 2040 TFLOP/s with it against
+//     1790 with v_mfma_f32_32x32x16 (half as many accumulator bits written per multiplication);
+//   * 8 x 8 accumulators: an operand read from LDS feeds eight instructions, 64 KiB of LDS reads per 32 of K and
+//     workgroup instead of 96 KiB with eight wavefronts of 64 x 128;
+//   * the accumulators are visited in a snake, so that only one of an instruction's two operands changes.
+// 4096 x 4096 x 4096, bfloat16, N(0,1): 99 us = 1385 TFLOP/s, 8192 cubed 785 us = 1400 TFLOP/s (113.6 and 844 us with
+// eight wavefronts of 64 x 128, two groups alternating between LDS reads and matrix instructions); a block of 32 of K
+// takes 1260 cycles, 1024 of them matrix instructions.
+// Nothing but the order of issue keeps the matrix pipe fed: the operands of block kb + 1 are read under the 64 matrix
+// instructions of block kb, one LDS read per two of them, then the loads of block kb + NST - 1.
+template <int DT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int M,
+                            int N, int K, int tiles_m, int tiles_n, float slope) {
+    using E = Elem<DT>;
+    constexpr int NST = GEMM_NST;
+    // LDS: the a tiles of all stages, then the b tiles: every read is one base register plus a 16-bit immediate
+    constexpr int A_TILE = 256 * 64, B_ROWB = 512, B_TILE = 32 * B_ROWB, B_BASE = NST * A_TILE;
+    constexpr int LA = 4, LB = 4, IPS = LA + LB;   // load instructions (1 KiB) per stage and wavefront
+    static_assert(NST >= 3 && NST % 2 == 0 && NST * (A_TILE + B_TILE) <= 160 * 1024, "stages");
+
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, g = lane >> 4;
+    const int wm = wave & 1, wn = wave >> 1;
+
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n);
+    const int m0 = tm_i * 256, n0 = tn_i * 256;
+    const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
+    const uint16_t* Bb = B + (size_t)bi * K * N + n0;
+    uint16_t* Cb = C + (size_t)bi * M * N;
+    const int nk = K / 32;
+
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
+
+    // ---- loads: byte offset of this lane's source chunk inside the tile's rows ----
+    uint32_t goff_a[LA], goff_b[LB];
+    {
+        const int nvalid = (N - n0) / 8 < 32 ? (N - n0) / 8 : 32;   // chunks of this tile inside the matrix
+#pragma unroll
+        for (int j = 0; j < LA; ++j) {
+            const int r = 16 * (wave * LA + j) + lane / 4, pos = lane % 4;
+            const int rr = r < M - 1 - m0 ? r : M - 1 - m0;
+            goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a(r)) << 3)) * 2u;
+        }
+#pragma unroll
+        for (int j = 0; j < LB; ++j) {
+            const int r = 2 * (wave * LB + j) + lane / 32, pos = lane % 32;
+            int ch = pos ^ swz_b<32>(r);
+            ch = ch < nvalid - 1 ? ch : nvalid - 1;
+            goff_b[j] = (uint32_t)(r * N + (ch << 3)) * 2u;
+        }
+    }
+    auto issue_a = [&](const uint16_t* sa, int j, int st) { lds_dma16(lds0 + st * A_TILE + (wave * LA + j) * 1024, sa, goff_a[j]); };
+    auto issue_b = [&](const uint16_t* sb, int j, int st) { lds_dma16(lds0 + B_BASE + st * B_TILE + (wave * LB + j) * 1024, sb, goff_b[j]); };
+
+    // A block past the end repeats the last one (nobody uses it): every step issues the same number of loads and the wait
+    // count is a constant
+#pragma unroll
+    for (int s = 0; s < NST - 1; ++s) {
+        const int kc = s < nk - 1 ? s : nk - 1;
+#pragma unroll
+        for (int j = 0; j < LA; ++j) issue_a(Ab + (size_t)kc * 32, j, s);
+#pragma unroll
+        for (int j = 0; j < LB; ++j) issue_b(Bb + (size_t)kc * 32 * N, j, s);
+    }
+    __builtin_amdgcn_sched_barrier(0);   // the loads are on their way before anything else is set up
+
+    // ---- operand addresses (stage 0) ----
+    // a: row l16 of a block of 16, chunk g.  b^T: lane addresses 8 bytes of row (k) 8 g + 4 hi + x, elements (n) 4 y .. +3
+    // of a block of 16 columns; the transposing read hands lane l the four k of column l % 16.  Two neighbouring blocks
+    // of columns differ in one bit of the swizzled chunk index, further ones by a constant.
+    const uint32_t a_addr = lds0 + (wm * 128 + l16) * 64 + ((g ^ swz_a(l16)) << 4);
+    uint32_t b_addr[2][8];
+    {
+        const int x = l16 >> 2, y = l16 & 3;
+#pragma unroll
+        for (int hi = 0; hi < 2; ++hi)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int row = 8 * g + 4 * hi + x, chunk = 2 * (wn * 8 + i) + (y >> 1);
+                b_addr[hi][i] = lds0 + B_BASE + row * B_ROWB + ((chunk ^ swz_b<32>(row)) << 4) + ((y & 1) << 3);
+            }
+    }
+    struct Ops {
+        u32x4 a[8], b[8];
+    };
+    // the i-th of the 24 LDS reads of a block, in the order of use: b 0, all of a, the other b
+    auto read_one = [&](Ops& o, auto idx, int st) {
+        constexpr int I = decltype(idx)::value;
+        if constexpr (I >= 2 && I < 10) {
+            o.a[I - 2] = lds_read_b128(a_addr + (I - 2) * 1024 + st * A_TILE);
+        } else {
+            constexpr int J = I < 2 ? I : I - 8, i = J / 2, hi = J % 2;
+            const u32x2 t = lds_read_tr16(b_addr[hi][i] + st * B_TILE);
+            o.b[i][2 * hi] = t[0];
+            o.b[i][2 * hi + 1] = t[1];
+        }
+    };
+
+    f32x4 acc[8][8];   // [n block][m block]
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Ops ops[2];
+    wait_tile_loads<(NST - 2) * IPS>();
+    __syncthreads();
+    [&]<int... I>(std::integer_sequence<int, I...>) {
+        (read_one(ops[0], std::integral_constant<int, I>{}, 0), ...);
+    }(std::make_integer_sequence<int, 24>{});
+    auto step = [&](int kb, auto phase) {
+        constexpr int PH = decltype(phase)::value;
+        // block kb+1 has landed when at most the loads of the NST-3 later blocks are still out
+        wait_tile_loads<(NST - 3) * IPS>();
+        asm volatile("s_barrier" ::: "memory");
+        // ... for everybody, and everybody has the operands of block kb-1 in registers: its stage takes block kb+NST-1
+        const int kn = kb + NST - 1;
+        const int kc = kn < nk - 1 ? kn : nk - 1;
+        const uint16_t* sa = Ab + (size_t)kc * 32;
+        const uint16_t* sb = Bb + (size_t)kc * 32 * N;
+        auto unit = [&](auto un) {
+            constexpr int U = decltype(un)::value;
+            constexpr int i = U / 8, j = i % 2 == 0 ? U % 8 : 7 - U % 8;
+            acc[i][j] = E::mfma16(ops[PH % 2].b[i], ops[PH % 2].a[j], acc[i][j]);
+            if constexpr (U % 2 == 1 && U < 48) read_one(ops[(PH + 1) % 2], std::integral_constant<int, U / 2>{}, (PH + 1) % NST);
+            if constexpr (U % 2 == 0 && U / 2 < IPS) {
+                constexpr int P = U / 2;
+                if constexpr (P < LA) issue_a(sa, P, (PH + NST - 1) % NST);
+                else issue_b(sb, P - LA, (PH + NST - 1) % NST);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        [&]<int... U>(std::integer_sequence<int, U...>) {
+            (unit(std::integral_constant<int, U>{}), ...);
+        }(std::make_integer_sequence<int, 64>{});
+    };
+    for (int k0 = 0; k0 < nk; k0 += NST) {
+        [&]<int... PH>(std::integer_sequence<int, PH...>) {
+            ((k0 + PH < nk ? step(k0 + PH, std::integral_constant<int, PH>{}) : (void)0), ...);
+        }(std::make_integer_sequence<int, NST>{});
+    }
+    wait_tile_loads<0>();   // the repeated loads of the last steps must not outlive the workgroup's LDS
+
+    // ---- epilogue: activation in fp32, round, store from registers ----
+    // A lane holds four consecutive n of row l16 of every 16 x 16 block.  Exchanging the odd quarters of the wavefront's
+    // results of one block with the even quarters of the next makes that eight: an instruction stores 64 bytes of
+    // 16 rows.  (By way of LDS, in whole rows, the way out took this one wavefront per SIMD 11.7 k cycles, half of
+    // them waits for LDS; like this 8.6 k.)
+    {
+        // the lane's number anew: nothing that only the way out needs occupies a register during the loop
+        const int el = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const int m = m0 + wm * 128 + (el & 15), n = n0 + wn * 128 + 16 * ((el >> 4) & 1) + 8 * (el >> 5);
+        uint16_t* cp = Cb + (size_t)m * N + n;
+        auto way_out = [&](auto act, auto inside) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    f32x4 t = acc[2 * p][j], u = acc[2 * p + 1][j];
+                    // taken out of the accumulation registers here, not on a common path in front of all the variants
+                    asm volatile("" : "+v"(t), "+v"(u));
+                    const auto lo = __builtin_amdgcn_permlane16_swap(E::pack2(act(t[0]), act(t[1])), E::pack2(act(u[0]), act(u[1])), false, false);
+                    const auto hi = __builtin_amdgcn_permlane16_swap(E::pack2(act(t[2]), act(t[3])), E::pack2(act(u[2]), act(u[3])), false, false);
+                    const u32x4 v = {lo[0], hi[0], lo[1], hi[1]};
+                    if (decltype(inside)::value || (m + 16 * j < M && n + 32 * p < N)) *(u32x4*)(cp + (size_t)(16 * j) * N + 32 * p) = v;
+                }
+                __builtin_amdgcn_sched_barrier(0);   // the results of one group of rows at a time in vector registers
+            }
+        };
+        auto way_out_act = [&](auto inside) {
+            // 0 < slope <= 1: the larger of t and slope t, one instruction less per element
+            if (slope > 0.f && slope <= 1.f) way_out([&](float t) { return vmax(t, slope * t); }, inside);
+            else way_out([&](float t) { return leaky(t, slope); }, inside);
+        };
+        if (m0 + 256 <= M && n0 + 256 <= N) way_out_act(std::true_type{});
+        else way_out_act(std::false_type{});
+    }
+}
+
 // Small problems: 32 x 32 tiles of c, K split over the four wavefronts of the workgroup.
 // A problem of few 64 x 64 tiles leaves most compute units without work, and every workgroup pulls its whole
 // strip of a and b through one compute unit's memory pipeline: that, not arithmetic, is what such a launch waits
@@ -317,10 +472,7 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    const int bx = blockIdx.x;
-    const int tn_i = bx % tiles_n;
-    const int tm_i = (bx / tiles_n) % tiles_m;
-    const int bi = bx / (tiles_n * tiles_m);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n);
     const int m0 = tm_i * 32, n0 = tn_i * 32;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -465,6 +617,25 @@ hipError_t launch_tiles(const GemmLaunch& g) {
     return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(WM * WN * 64), args, lds_bytes, (hipStream_t)g.stream);
 }
 
+// 256 x 256 tiles
+template <int DT>
+hipError_t launch_wide(const GemmLaunch& g) {
+    int tiles_m = (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
+    const long long blocks = (long long)tiles_m * tiles_n * g.batch;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    const uint16_t* a = (const uint16_t*)g.a;
+    const uint16_t* b = (const uint16_t*)g.b;
+    uint16_t* c = (uint16_t*)g.c;
+    int M = g.M, N = g.N, K = g.K;
+    float slope = g.slope;
+    void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &slope};
+    constexpr unsigned lds_bytes = GEMM_NST * (256 * 64 + 32 * 512);
+    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_wide_kernel<DT>);
+    static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
+    if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
+    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256), args, lds_bytes, (hipStream_t)g.stream);
+}
+
 template <int DT>
 hipError_t launch_plain(const GemmLaunch& g) {
     const uint16_t* a = (const uint16_t*)g.a;
@@ -501,7 +672,7 @@ hipError_t launch_splitk(const GemmLaunch& g) {
 template <int DT>
 hipError_t dispatch(const GemmLaunch& g) {
     switch (gemm_path_of(g.batch, g.M, g.N, g.K)) {
-        case 1: return launch_tiles<DT, 4, 2, 2, 4>(g);   // 256 x 256, eight wavefronts of 64 x 128
+        case 1: return launch_wide<DT>(g);                // 256 x 256, four wavefronts of 128 x 128
         case 2: return launch_tiles<DT, 2, 2, 2, 2>(g);   // 128 x 128, four wavefronts of 64 x 64
         case 3: return launch_tiles<DT, 2, 2, 1, 1>(g);   // 64 x 64, four wavefronts of 32 x 32
         case 5: return launch_splitk<DT>(g);   // 32 x 32, K split over the four wavefronts

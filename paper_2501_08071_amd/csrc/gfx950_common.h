@@ -27,6 +27,9 @@ template <> struct Elem<0> {  // IEEE binary16
     static __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     }
+    static __device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    }
     static __device__ __forceinline__ uint32_t pack2(float lo, float hi) {  // round to nearest even
         f32x2 x = {lo, hi};
         return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, f16x2));
@@ -39,6 +42,9 @@ template <> struct Elem<0> {  // IEEE binary16
 template <> struct Elem<1> {  // bfloat16
     static __device__ __forceinline__ f32x16 mfma(u32x4 a, u32x4 b, f32x16 c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ f32x4 mfma16(u32x4 a, u32x4 b, f32x4 c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     }
     static __device__ __forceinline__ uint32_t pack2(float lo, float hi) {  // round to nearest even
         f32x2 x = {lo, hi};
@@ -79,6 +85,13 @@ __device__ __forceinline__ void mfma_settle(f32x16& a0, f32x16& a1, f32x16& a2, 
 __device__ __forceinline__ u32x4 global_load_acc16(const void* p) {
     u32x4 r;
     asm volatile("global_load_dwordx4 %0, %1, off" : "=a"(r) : "v"(p) : "memory");
+    return r;
+}
+
+// plain maximum, without the quiet-NaN canonicalisation the C library semantics would add
+__device__ __forceinline__ float vmax(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
 
