@@ -1,7 +1,7 @@
 // Fused GEMM + LeakyReLU for gfx950 (the paper's mmLeakyReLu, Table 2): c = f(a b), a [M,K], b [K,N]
 // row-major, 16-bit in and out, fp32 accumulation.
 //
-// Matrix-core kernel (K % 32 == 0, N % 8 == 0):
+// Matrix-core kernel (K % 8 == 0, N % 8 == 0):
 //   * a workgroup of four wavefronts (2 x 2) owns a 64 TM x 64 TN tile of c, a wavefront 32 TM x 32 TN of
 //     it as TM x TN accumulator blocks of v_mfma_f32_32x32x16; TM = TN = 2 (128 x 128) when that gives
 //     the chip enough tiles, else 1 (64 x 64); problems with enough tiles of 256 x 256: gemm_lrelu_wide_kernel;
@@ -16,7 +16,8 @@
 //     store), so the loop has no edge cases.
 // Small problems (at most 256 tiles of 32 x 32, K >= 256): 32 x 32 tiles with K split over the four wavefronts of
 // the workgroup, see gemm_lrelu_splitk_kernel.
-// Plain kernel (any shape): one thread per element of c, fp32 fused multiply-adds in the order of k.
+// K % 32 != 0: the same kernels with the last block cut (K % 8 == 0), or, where rows of a or b do not start at 16-byte
+// aligned addresses, the 32 x 32 kernel with its loads through registers.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -25,8 +26,18 @@
 #include "gemm_launch.h"
 #include "gfx950_common.h"
 
+// LDS stages of 32 in K; all but one of them in flight ahead of the one in use.  64 x 64 tiles: a block is two matrix
+// instructions per wavefront, so the loads' latency shows: 4 x 512 x 512 x 2048 takes 14.5 us with four stages, 11.2 with
+// six; more than six leave fewer workgroups on a compute unit (2 x 777 x 1000 x 1024: 11.5 us with six, 14.1 with
+// twelve).  128 x 128 tiles: 2048 cubed 21.7 us with four and six, 22.4 with eight.
+#ifndef GEMM_NST128
+#define GEMM_NST128 4
+#endif
+#ifndef GEMM_NST64
+#define GEMM_NST64 6
+#endif
 #ifndef GEMM_NST
-#define GEMM_NST 4   // LDS stages of 32 in K; GEMM_NST - 1 of them in flight ahead of the one in use
+#define GEMM_NST 4   // the same for 256 x 256 tiles (all that LDS holds)
 #endif
 
 namespace {
@@ -56,16 +67,19 @@ __device__ __forceinline__ constexpr int swz_b(int row) {
 struct TileIndex {
     int bi, tm, tn;
 };
+__device__ __forceinline__ TileIndex tile_in_list(int bi, int t, int tiles_m, int tiles_n) {
+    const int g = t / (GEMM_GROUP_M * tiles_n), u = t - g * (GEMM_GROUP_M * tiles_n);
+    const int left = tiles_m - g * GEMM_GROUP_M, rows = left < GEMM_GROUP_M ? left : GEMM_GROUP_M;
+    const int tn = u / rows;
+    return {bi, g * GEMM_GROUP_M + (u - tn * rows), tn};
+}
 __device__ __forceinline__ TileIndex tile_of_workgroup(int tiles_m, int tiles_n) {
     const int total = (int)gridDim.x, b = (int)blockIdx.x;
     const int q = total >> 3, r = total & 7, x = b & 7;
     const int c = x * q + (x < r ? x : r) + (b >> 3);
     const int per = tiles_m * tiles_n;
-    const int bi = c / per, t = c - bi * per;
-    const int g = t / (GEMM_GROUP_M * tiles_n), u = t - g * (GEMM_GROUP_M * tiles_n);
-    const int left = tiles_m - g * GEMM_GROUP_M, rows = left < GEMM_GROUP_M ? left : GEMM_GROUP_M;
-    const int tn = u / rows;
-    return {bi, g * GEMM_GROUP_M + (u - tn * rows), tn};
+    const int bi = c / per;
+    return tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
 }
 
 __device__ __forceinline__ float leaky(float t, float slope) { return t >= 0.f ? t : slope * t; }
@@ -73,21 +87,21 @@ __device__ __forceinline__ float leaky(float t, float slope) { return t >= 0.f ?
 extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
 // dynamic LDS of a kernel instance: the stages of the loop, or (if larger) the padded blocks of c on their way out
-template <int WM, int WN, int TM, int TN>
+template <int WM, int WN, int TM, int TN, int NST>
 struct GemmLds {
-    static constexpr int STAGES = GEMM_NST * (32 * TM * WM * 64 + 32 * 2 * 32 * TN * WN);
+    static constexpr int STAGES = NST * (32 * TM * WM * 64 + 32 * 2 * 32 * TN * WN);
     static constexpr int OUT = WM * WN * (32 * TM) * (64 * TN + 16);
     static constexpr int BYTES = STAGES > OUT ? STAGES : OUT;
     static_assert(BYTES <= 160 * 1024, "LDS");
 };
 
-template <int DT, int WM, int WN, int TM, int TN>
+template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                         uint16_t* __restrict__ C, int M, int N, int K, int tiles_m,
                                                         int tiles_n, float slope) {
     using E = Elem<DT>;
     constexpr int NW = WM * WN;               // wavefronts, WM x WN over the tile
-    constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN, NST = GEMM_NST;
+    constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     constexpr int A_TILE = BM * 64;          // BM rows of 32 elements
     constexpr int B_ROWB = 2 * BN;           // bytes per row of the b tile
     constexpr int B_TILE = 32 * B_ROWB;      // 32 rows (k) of BN elements
@@ -110,17 +124,19 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
     uint16_t* Cb = C + (size_t)bi * M * N;
-    const int nk = K / 32;
+    const int nk = (K + 31) / 32;
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
 
     // ---- loads: byte offset of this lane's source chunk inside the tile's rows ----
-    uint32_t goff_a[LA], goff_b[LB];
+    const int kr = K - 32 * (nk - 1);   // valid k of the last block (KTAIL: 8, 16 or 24, else 32)
+    uint32_t goff_a[LA], goff_b[LB], tail_a[LA], tail_b[LB];   // tail: the same for the last block, chunks past K replaced
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
         const int r = 16 * (wave * LA + j) + lane / 4, pos = lane % 4;
         const int rr = r < M - 1 - m0 ? r : M - 1 - m0;
         goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a(r)) << 3)) * 2u;
+        if constexpr (KTAIL) tail_a[j] = 8 * (pos ^ swz_a(r)) < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
     }
     {
         const int nvalid = (N - n0) / 8 < BN / 8 ? (N - n0) / 8 : BN / 8;   // chunks of this tile inside the matrix
@@ -130,6 +146,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
             int ch = pos ^ swz_b<B_LPR>(r);
             ch = ch < nvalid - 1 ? ch : nvalid - 1;
             goff_b[j] = (uint32_t)(r * N + (ch << 3)) * 2u;
+            if constexpr (KTAIL) tail_b[j] = (uint32_t)((r < kr ? r : 0) * N + (ch << 3)) * 2u;
         }
     }
     // k block kb into stage st; a block past the end repeats the last one (nobody reads it): every step
@@ -138,10 +155,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
         const int kc = kb < nk - 1 ? kb : nk - 1;
         const uint16_t* sa = Ab + (size_t)kc * 32;
         const uint16_t* sb = Bb + (size_t)kc * 32 * N;
+        const bool tail = KTAIL && kc == nk - 1;
 #pragma unroll
-        for (int j = 0; j < LA; ++j) lds_dma16(lds0 + st * STAGE + (wave * LA + j) * 1024, sa, goff_a[j]);
+        for (int j = 0; j < LA; ++j) lds_dma16(lds0 + st * STAGE + (wave * LA + j) * 1024, sa, tail ? tail_a[j] : goff_a[j]);
 #pragma unroll
-        for (int j = 0; j < LB; ++j) lds_dma16(lds0 + st * STAGE + A_TILE + (wave * LB + j) * 1024, sb, goff_b[j]);
+        for (int j = 0; j < LB; ++j) lds_dma16(lds0 + st * STAGE + A_TILE + (wave * LB + j) * 1024, sb, tail ? tail_b[j] : goff_b[j]);
     };
 
     // ---- operand addresses (stage 0, k step 0 of the b tile) ----
@@ -191,6 +209,15 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
             o.b[tn] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
     };
+    // the last block of a K that is not a multiple of 32: both operands' k past the end become zero (whatever was
+    // loaded in their place may be infinite)
+    auto cut_tail = [&](Ops& o, int ks) {
+        const bool past = 16 * ks + 8 * h >= kr;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) o.a[tm] = past ? u32x4{0u, 0u, 0u, 0u} : o.a[tm];
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) o.b[tn] = past ? u32x4{0u, 0u, 0u, 0u} : o.b[tn];
+    };
     auto multiply = [&](const Ops& o) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
@@ -215,6 +242,10 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
         issue(kb + NST - 1, (PH + NST - 1) % NST);
         Ops second;
         read_ops(second, PH * STAGE, 1);
+        if (KTAIL && kb == nk - 1) {
+            cut_tail(ahead, 0);
+            cut_tail(second, 1);
+        }
         __builtin_amdgcn_sched_barrier(0);
         multiply(ahead);
         __builtin_amdgcn_sched_barrier(0);
@@ -240,7 +271,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     __syncthreads();
     {
         constexpr int RW = 32 * TM, RB = 64 * TN, RS = RB + 16;
-        static_assert(NW * RW * RS <= GemmLds<WM, WN, TM, TN>::BYTES, "LDS for the way out");
+        static_assert(NW * RW * RS <= GemmLds<WM, WN, TM, TN, NST>::BYTES, "LDS for the way out");
         uint8_t* reg = smem + wave * (RW * RS);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
@@ -279,7 +310,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 // takes 1260 cycles, 1024 of them matrix instructions.
 // Nothing but the order of issue keeps the matrix pipe fed: the operands of block kb + 1 are read under the 64 matrix
 // instructions of block kb, one LDS read per two of them, then the loads of block kb + NST - 1.
-template <int DT>
+template <int DT, bool KTAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int M,
                             int N, int K, int tiles_m, int tiles_n, float slope) {
@@ -301,12 +332,13 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
     uint16_t* Cb = C + (size_t)bi * M * N;
-    const int nk = K / 32;
+    const int nk = (K + 31) / 32;
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
 
     // ---- loads: byte offset of this lane's source chunk inside the tile's rows ----
-    uint32_t goff_a[LA], goff_b[LB];
+    const int kr = K - 32 * (nk - 1);   // valid k of the last block (KTAIL: 8, 16 or 24, else 32)
+    uint32_t goff_a[LA], goff_b[LB], tail_a[LA], tail_b[LB];   // tail: the same for the last block, chunks past K replaced
     {
         const int nvalid = (N - n0) / 8 < 32 ? (N - n0) / 8 : 32;   // chunks of this tile inside the matrix
 #pragma unroll
@@ -314,6 +346,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
             const int r = 16 * (wave * LA + j) + lane / 4, pos = lane % 4;
             const int rr = r < M - 1 - m0 ? r : M - 1 - m0;
             goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a(r)) << 3)) * 2u;
+            if constexpr (KTAIL) tail_a[j] = 8 * (pos ^ swz_a(r)) < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
         }
 #pragma unroll
         for (int j = 0; j < LB; ++j) {
@@ -321,10 +354,16 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
             int ch = pos ^ swz_b<32>(r);
             ch = ch < nvalid - 1 ? ch : nvalid - 1;
             goff_b[j] = (uint32_t)(r * N + (ch << 3)) * 2u;
+            if constexpr (KTAIL) tail_b[j] = (uint32_t)((r < kr ? r : 0) * N + (ch << 3)) * 2u;
         }
     }
-    auto issue_a = [&](const uint16_t* sa, int j, int st) { lds_dma16(lds0 + st * A_TILE + (wave * LA + j) * 1024, sa, goff_a[j]); };
-    auto issue_b = [&](const uint16_t* sb, int j, int st) { lds_dma16(lds0 + B_BASE + st * B_TILE + (wave * LB + j) * 1024, sb, goff_b[j]); };
+    // load instruction j of block kc's tile of a / of b
+    auto issue_a = [&](int kc, int j, int st) {
+        lds_dma16(lds0 + st * A_TILE + (wave * LA + j) * 1024, Ab + (size_t)kc * 32, KTAIL && kc == nk - 1 ? tail_a[j] : goff_a[j]);
+    };
+    auto issue_b = [&](int kc, int j, int st) {
+        lds_dma16(lds0 + B_BASE + st * B_TILE + (wave * LB + j) * 1024, Bb + (size_t)kc * 32 * N, KTAIL && kc == nk - 1 ? tail_b[j] : goff_b[j]);
+    };
 
     // A block past the end repeats the last one (nobody uses it): every step issues the same number of loads and the wait
     // count is a constant
@@ -332,9 +371,9 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     for (int s = 0; s < NST - 1; ++s) {
         const int kc = s < nk - 1 ? s : nk - 1;
 #pragma unroll
-        for (int j = 0; j < LA; ++j) issue_a(Ab + (size_t)kc * 32, j, s);
+        for (int j = 0; j < LA; ++j) issue_a(kc, j, s);
 #pragma unroll
-        for (int j = 0; j < LB; ++j) issue_b(Bb + (size_t)kc * 32 * N, j, s);
+        for (int j = 0; j < LB; ++j) issue_b(kc, j, s);
     }
     __builtin_amdgcn_sched_barrier(0);   // the loads are on their way before anything else is set up
 
@@ -389,8 +428,14 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
         // ... for everybody, and everybody has the operands of block kb-1 in registers: its stage takes block kb+NST-1
         const int kn = kb + NST - 1;
         const int kc = kn < nk - 1 ? kn : nk - 1;
-        const uint16_t* sa = Ab + (size_t)kc * 32;
-        const uint16_t* sb = Bb + (size_t)kc * 32 * N;
+        if (KTAIL && kb == nk - 1) {   // both operands' k past the end become zero (what was loaded there may be infinite)
+            const bool past = 8 * g >= kr;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                ops[PH % 2].a[i] = past ? u32x4{0u, 0u, 0u, 0u} : ops[PH % 2].a[i];
+                ops[PH % 2].b[i] = past ? u32x4{0u, 0u, 0u, 0u} : ops[PH % 2].b[i];
+            }
+        }
         auto unit = [&](auto un) {
             constexpr int U = decltype(un)::value;
             constexpr int i = U / 8, j = i % 2 == 0 ? U % 8 : 7 - U % 8;
@@ -398,8 +443,8 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
             if constexpr (U % 2 == 1 && U < 48) read_one(ops[(PH + 1) % 2], std::integral_constant<int, U / 2>{}, (PH + 1) % NST);
             if constexpr (U % 2 == 0 && U / 2 < IPS) {
                 constexpr int P = U / 2;
-                if constexpr (P < LA) issue_a(sa, P, (PH + NST - 1) % NST);
-                else issue_b(sb, P - LA, (PH + NST - 1) % NST);
+                if constexpr (P < LA) issue_a(kc, P, (PH + NST - 1) % NST);
+                else issue_b(kc, P - LA, (PH + NST - 1) % NST);
             }
             __builtin_amdgcn_sched_barrier(0);
         };
@@ -458,56 +503,47 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
 // the loop: what a wavefront loads only that wavefront reads), accumulates a 32 x 32 partial result in two
 // independent accumulators, and at the end the four partial results meet in LDS: wavefront q adds up, activates
 // and stores columns 8q .. 8q+7 of the tile.
+//
+// LOAD 0: K % 32 == 0 and N % 8 == 0; 1: K % 8 == 0 and N % 8 == 0, the last block is cut; both load straight into LDS.
+// LOAD 2: any K and N.  Rows of a and b then start at any even address, and loads into LDS need 4-byte aligned ones:
+// the blocks go through registers, 16 unaligned bytes per lane, two blocks ahead, and from there into two LDS stages.
+// Elements past the end of a row are the next row's and fall under the masks of k and n; only what would pass the end
+// of the whole matrix is read element by element.  (777 x 1001 x 1003: 16.2 us; one thread per element of c: 350 us.)
 #ifndef GEMM_SK_NST
 #define GEMM_SK_NST 4   // LDS stages per wavefront (4 KiB each); more gained nothing and a larger LDS request starts later
 #endif
-template <int DT>
+template <int DT, int LOAD>
 __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                                uint16_t* __restrict__ C, int M, int N, int K, int tiles_m,
-                                                               int tiles_n, float slope) {
+                                                               int tiles_n, long long total, float slope) {
     using E = Elem<DT>;
     constexpr int NST = GEMM_SK_NST, STAGE = 4096, IPS = 4;
+    constexpr bool KTAIL = LOAD != 0;
     static_assert(NST >= 3 && 4 * NST * STAGE <= 160 * 1024 && (NST - 2) * IPS <= 63, "stages");
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n);
+    TileIndex ti;
+    if (gridDim.y == 1) {
+        ti = tile_of_workgroup(tiles_m, tiles_n);
+    } else {   // more tiles than a grid's x takes: in the list's order, surplus workgroups repeat the last tile
+        long long c = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+        c = c < total ? c : total - 1;
+        const int per = tiles_m * tiles_n, b = (int)(c / per);
+        ti = tile_in_list(b, (int)(c - (long long)b * per), tiles_m, tiles_n);
+    }
+    const auto [bi, tm_i, tn_i] = ti;
     const int m0 = tm_i * 32, n0 = tn_i * 32;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
     uint16_t* Cb = C + (size_t)bi * M * N;
-    const int nk = K / 32;
+    const int nk = (K + 31) / 32;
+    const int kr = K - 32 * (nk - 1);   // valid k of the last block
     const int mine = nk > wave ? (nk - wave + 3) / 4 : 0;   // k blocks of this wavefront: wave, wave + 4, ...
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
     const uint32_t ldsw = lds0 + wave * (NST * STAGE);
-    // loads: instruction j covers rows 16 j .. 16 j + 15 of a tile (64 bytes each); lane = row * 4 + chunk position
-    uint32_t goff_a[2], goff_b[2];
-    {
-        const int nvalid = (N - n0) / 8 < 4 ? (N - n0) / 8 : 4;   // 16-byte chunks of this tile inside the matrix
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int r = 16 * j + lane / 4, pos = lane % 4;
-            const int rr = r < M - 1 - m0 ? r : M - 1 - m0;
-            goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a(r)) << 3)) * 2u;
-            int ch = pos ^ swz_a(r);
-            ch = ch < nvalid - 1 ? ch : nvalid - 1;
-            goff_b[j] = (uint32_t)(r * N + (ch << 3)) * 2u;
-        }
-    }
-    // the i-th block of this wavefront into stage st; past its last block the last one again (nobody reads it):
-    // every step issues the same number of loads.  A wavefront without blocks issues nothing.
-    auto issue = [&](int i, int st) {
-        if (mine == 0) return;
-        const int kb = wave + 4 * (i < mine - 1 ? i : mine - 1);
-        const uint16_t* sa = Ab + (size_t)kb * 32;
-        const uint16_t* sb = Bb + (size_t)kb * 32 * N;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) lds_dma16(ldsw + st * STAGE + j * 1024, sa, goff_a[j]);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) lds_dma16(ldsw + st * STAGE + 2048 + j * 1024, sb, goff_b[j]);
-    };
     // operands (stage 0): a: row l32, chunk 2 ks + h; b^T: 8 bytes of row (k) 8 h + 4 hi + x, elements 16 g1 + 4 y .. +3
     uint32_t a_addr[2], b_addr[2];
 #pragma unroll
@@ -526,31 +562,137 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[ks][r] = 0.f;
 
-#pragma unroll
-    for (int s = 0; s < NST - 1; ++s) issue(s, s);
-    auto step = [&](int i, auto phase) {
-        constexpr int PH = decltype(phase)::value;
-        // block i has landed when at most the loads of the NST-2 later blocks are still out
-        wait_tile_loads<(NST - 2) * IPS>();
+    // the operands of the block in the stage at st_bytes, and their matrix instructions; kb: which block it is
+    auto use_stage = [&](int st_bytes, int kb) {
         u32x4 a[2], b[2];
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) {
-            a[ks] = lds_read_b128(a_addr[ks] + PH * STAGE);
-            const u32x2 lo = lds_read_tr16(b_addr[0] + PH * STAGE + ks * 16 * 64);
-            const u32x2 hi = lds_read_tr16(b_addr[1] + PH * STAGE + ks * 16 * 64);
+            a[ks] = lds_read_b128(a_addr[ks] + st_bytes);
+            const u32x2 lo = lds_read_tr16(b_addr[0] + st_bytes + ks * 16 * 64);
+            const u32x2 hi = lds_read_tr16(b_addr[1] + st_bytes + ks * 16 * 64);
             b[ks] = u32x4{lo[0], lo[1], hi[0], hi[1]};
+        }
+        // the last block: both operands' k past the end become zero (whatever was loaded in their place may be infinite)
+        if (KTAIL && kb == nk - 1) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                const int valid = kr - 16 * ks - 8 * h;   // of the eight k in this lane's operand
+#pragma unroll
+                for (int d = 0; d < 4; ++d) {
+                    const uint32_t keep = 2 * d + 2 <= valid ? 0xffffffffu : 2 * d + 1 <= valid ? 0xffffu : 0u;
+                    a[ks][d] &= keep;
+                    b[ks][d] &= keep;
+                }
+            }
         }
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) acc[ks] = E::mfma(b[ks], a[ks], acc[ks]);
-        // the operands are in registers: the stage takes this wavefront's block i + NST - 1
-        issue(i + NST - 1, (PH + NST - 1) % NST);
     };
-    for (int i0 = 0; i0 < mine; i0 += NST) {
-        [&]<int... PH>(std::integer_sequence<int, PH...>) {
-            ((i0 + PH < mine ? step(i0 + PH, std::integral_constant<int, PH>{}) : (void)0), ...);
-        }(std::make_integer_sequence<int, NST>{});
+
+    if constexpr (LOAD != 2) {
+        // loads: instruction j covers rows 16 j .. 16 j + 15 of a tile (64 bytes each); lane = row * 4 + chunk position
+        uint32_t goff_a[2], goff_b[2], tail_a[2], tail_b[2];   // tail: the same for the last block, chunks past K replaced
+        {
+            const int nvalid = (N - n0) / 8 < 4 ? (N - n0) / 8 : 4;   // 16-byte chunks of this tile inside the matrix
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int r = 16 * j + lane / 4, pos = lane % 4;
+                const int rr = r < M - 1 - m0 ? r : M - 1 - m0;
+                goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a(r)) << 3)) * 2u;
+                int ch = pos ^ swz_a(r);
+                if constexpr (KTAIL) tail_a[j] = 8 * ch < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
+                ch = ch < nvalid - 1 ? ch : nvalid - 1;
+                goff_b[j] = (uint32_t)(r * N + (ch << 3)) * 2u;
+                if constexpr (KTAIL) tail_b[j] = (uint32_t)((r < kr ? r : 0) * N + (ch << 3)) * 2u;
+            }
+        }
+        // the i-th block of this wavefront into stage st; past its last block the last one again (nobody reads it):
+        // every step issues the same number of loads.  A wavefront without blocks issues nothing.
+        auto issue = [&](int i, int st) {
+            if (mine == 0) return;
+            const int kb = wave + 4 * (i < mine - 1 ? i : mine - 1);
+            const bool tail = KTAIL && kb == nk - 1;
+            const uint16_t* sa = Ab + (size_t)kb * 32;
+            const uint16_t* sb = Bb + (size_t)kb * 32 * N;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) lds_dma16(ldsw + st * STAGE + j * 1024, sa, tail ? tail_a[j] : goff_a[j]);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) lds_dma16(ldsw + st * STAGE + 2048 + j * 1024, sb, tail ? tail_b[j] : goff_b[j]);
+        };
+#pragma unroll
+        for (int s = 0; s < NST - 1; ++s) issue(s, s);
+        auto step = [&](int i, auto phase) {
+            constexpr int PH = decltype(phase)::value;
+            // block i has landed when at most the loads of the NST-2 later blocks are still out
+            wait_tile_loads<(NST - 2) * IPS>();
+            use_stage(PH * STAGE, wave + 4 * i);
+            // the operands are in registers: the stage takes this wavefront's block i + NST - 1
+            issue(i + NST - 1, (PH + NST - 1) % NST);
+        };
+        for (int i0 = 0; i0 < mine; i0 += NST) {
+            [&]<int... PH>(std::integer_sequence<int, PH...>) {
+                ((i0 + PH < mine ? step(i0 + PH, std::integral_constant<int, PH>{}) : (void)0), ...);
+            }(std::make_integer_sequence<int, NST>{});
+        }
+        wait_tile_loads<0>();   // the repeated loads of the last steps must have landed before LDS is used again
+    } else {
+        // lane = row * 4 + chunk as above, the swizzle applied to the LDS address
+        const int r0 = lane / 4, ch = lane % 4;
+        const uint32_t w_addr[2] = {ldsw + r0 * 64 + ((ch ^ swz_a(r0)) << 4), ldsw + (16 + r0) * 64 + ((ch ^ swz_a(16 + r0)) << 4)};
+        // 16 bytes from element `off` of a matrix of `size` elements; what lies past its end reads as zero
+        auto load8 = [](const uint16_t* base, size_t off, size_t size) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (off + 8 <= size) {
+                __builtin_memcpy(&v, base + off, 16);   // an unaligned 16-byte load
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (off + e < size) v[e / 2] |= (uint32_t)base[off + e] << (16 * (e % 2));
+            }
+            return v;
+        };
+        const uint16_t* Ai = A + (size_t)bi * M * K;
+        const uint16_t* Bi = B + (size_t)bi * K * N;
+        const size_t size_a = (size_t)M * K, size_b = (size_t)K * N;
+        size_t row_a[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int r = m0 + 16 * j + r0;
+            row_a[j] = (size_t)(r < M ? r : M - 1) * K + 8 * ch;
+        }
+        struct Blk {
+            u32x4 a[2], b[2];
+        };
+        auto load = [&](Blk& x, int i) {
+            const int kb = wave + 4 * i;
+            if (i >= mine) return;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) x.a[j] = load8(Ai, row_a[j] + 32 * (size_t)kb, size_a);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const int k = 32 * kb + 16 * j + r0;
+                x.b[j] = load8(Bi, (size_t)(k < K ? k : K - 1) * N + n0 + 8 * ch, size_b);
+            }
+        };
+        Blk x[2];
+        load(x[0], 0);
+        load(x[1], 1);
+        auto step = [&](int i, auto phase) {
+            constexpr int PH = decltype(phase)::value;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                *(LDS_AS u32x4*)(uintptr_t)(w_addr[j] + PH * STAGE) = x[PH].a[j];
+                *(LDS_AS u32x4*)(uintptr_t)(w_addr[j] + PH * STAGE + 2048) = x[PH].b[j];
+            }
+            load(x[PH], i + 2);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // only this wavefront reads what it wrote
+            use_stage(PH * STAGE, wave + 4 * i);
+        };
+        for (int i0 = 0; i0 < mine; i0 += 2) {
+            step(i0, std::integral_constant<int, 0>{});
+            if (i0 + 1 < mine) step(i0 + 1, std::integral_constant<int, 1>{});
+        }
     }
-    wait_tile_loads<0>();   // the repeated loads of the last steps must have landed before LDS is used again
     __syncthreads();
     // the partial results meet: [wavefront][group of four registers][lane] as 16 bytes each
     {
@@ -572,36 +714,26 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
         }
         // registers 4 q .. 4 q + 3 of lane (l32, h) are c[m0 + l32][n0 + 8 q + 4 h .. + 3]
         const int m = m0 + l32, n = n0 + 8 * wave + 4 * h;
-        if (m < M && n < N) {
-            const u32x2 v = {E::pack2(leaky(t[0], slope), leaky(t[1], slope)), E::pack2(leaky(t[2], slope), leaky(t[3], slope))};
-            *(u32x2*)(Cb + (size_t)m * N + n) = v;
+        const u32x2 v = {E::pack2(leaky(t[0], slope), leaky(t[1], slope)), E::pack2(leaky(t[2], slope), leaky(t[3], slope))};
+        uint16_t* cp = Cb + (size_t)m * N + n;
+        if constexpr (LOAD != 2) {
+            if (m < M && n < N) *(u32x2*)cp = v;
+        } else if (m < M) {
+            if (n + 4 <= N) {
+                __builtin_memcpy(cp, &v, 8);   // an unaligned 8-byte store
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (n + e < N) cp[e] = (uint16_t)(v[e / 2] >> (16 * (e % 2)));
+            }
         }
     }
 }
 
-// any shape: one thread per element of c
-template <int DT>
-__global__ __launch_bounds__(256) void gemm_lrelu_plain_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
-                                                              uint16_t* __restrict__ C, long long total, int M, int N, int K,
-                                                              float slope) {
-    using E = Elem<DT>;
-    for (long long idx = (long long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long long)gridDim.x * 256) {
-        const int n = (int)(idx % N);
-        const long long bm = idx / N;          // batch * M + m
-        const long long bi = bm / M;
-        const uint16_t* a = A + (size_t)bm * K;
-        const uint16_t* b = B + (size_t)bi * K * N + n;
-        float t = 0.f;
-        for (int k = 0; k < K; ++k) t = __builtin_fmaf(E::widen(a[k]), E::widen(b[(size_t)k * N]), t);
-        const uint32_t p = E::pack2(leaky(t, slope), 0.f);
-        C[idx] = (uint16_t)(p & 0xFFFFu);
-    }
-}
-
-template <int DT, int WM, int WN, int TM, int TN>
+template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
 hipError_t launch_tiles(const GemmLaunch& g) {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-    constexpr unsigned lds_bytes = (unsigned)GemmLds<WM, WN, TM, TN>::BYTES;
+    constexpr unsigned lds_bytes = (unsigned)GemmLds<WM, WN, TM, TN, NST>::BYTES;
     int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
     const long long blocks = (long long)tiles_m * tiles_n * g.batch;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
@@ -611,14 +743,14 @@ hipError_t launch_tiles(const GemmLaunch& g) {
     int M = g.M, N = g.N, K = g.K;
     float slope = g.slope;
     void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &slope};
-    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN>);
+    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN, NST, KTAIL>);
     static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
     if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
     return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(WM * WN * 64), args, lds_bytes, (hipStream_t)g.stream);
 }
 
 // 256 x 256 tiles
-template <int DT>
+template <int DT, bool KTAIL>
 hipError_t launch_wide(const GemmLaunch& g) {
     int tiles_m = (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
     const long long blocks = (long long)tiles_m * tiles_n * g.batch;
@@ -630,54 +762,45 @@ hipError_t launch_wide(const GemmLaunch& g) {
     float slope = g.slope;
     void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &slope};
     constexpr unsigned lds_bytes = GEMM_NST * (256 * 64 + 32 * 512);
-    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_wide_kernel<DT>);
+    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_wide_kernel<DT, KTAIL>);
     static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
     if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
     return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256), args, lds_bytes, (hipStream_t)g.stream);
 }
 
-template <int DT>
-hipError_t launch_plain(const GemmLaunch& g) {
-    const uint16_t* a = (const uint16_t*)g.a;
-    const uint16_t* b = (const uint16_t*)g.b;
-    uint16_t* c = (uint16_t*)g.c;
-    long long total = (long long)g.batch * g.M * g.N;
-    int M = g.M, N = g.N, K = g.K;
-    float slope = g.slope;
-    const long long groups = (total + 255) / 256;
-    const unsigned grid = (unsigned)(groups < 65536 ? groups : 65536);
-    void* args[] = {&a, &b, &c, &total, &M, &N, &K, &slope};
-    return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_lrelu_plain_kernel<DT>), dim3(grid), dim3(256), args, 0,
-                           (hipStream_t)g.stream);
-}
-
-
-template <int DT>
+template <int DT, int LOAD>
 hipError_t launch_splitk(const GemmLaunch& g) {
     int tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32;
-    const long long blocks = (long long)tiles_m * tiles_n * g.batch;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    long long blocks = (long long)tiles_m * tiles_n * g.batch;
+    constexpr long long X = 1 << 22;   // a dimension of the grid holds fewer than 2^32 threads
+    const unsigned gx = (unsigned)(blocks < X ? blocks : X), gy = (unsigned)((blocks + gx - 1) / gx);
+    if (gy > 65535u) return hipErrorInvalidConfiguration;
     const uint16_t* a = (const uint16_t*)g.a;
     const uint16_t* b = (const uint16_t*)g.b;
     uint16_t* c = (uint16_t*)g.c;
     int M = g.M, N = g.N, K = g.K;
     float slope = g.slope;
-    void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &slope};
+    void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &blocks, &slope};
     constexpr unsigned lds_bytes = 4u * GEMM_SK_NST * 4096u;
-    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_splitk_kernel<DT>);
+    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_splitk_kernel<DT, LOAD>);
     static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
     if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
-    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256), args, lds_bytes, (hipStream_t)g.stream);
+    return hipLaunchKernel(fn, dim3(gx, gy), dim3(256), args, lds_bytes, (hipStream_t)g.stream);
+}
+
+template <int DT, bool KTAIL>
+hipError_t launch_tile_size(const GemmLaunch& g) {
+    switch (gemm_tile_of(g.batch, g.M, g.N, g.K)) {
+        case 1: return launch_wide<DT, KTAIL>(g);                              // 256 x 256, four wavefronts of 128 x 128
+        case 2: return launch_tiles<DT, 2, 2, 2, 2, GEMM_NST128, KTAIL>(g);   // 128 x 128, four wavefronts of 64 x 64
+        case 3: return launch_tiles<DT, 2, 2, 1, 1, GEMM_NST64, KTAIL>(g);    // 64 x 64, four wavefronts of 32 x 32
+        default: return launch_splitk<DT, KTAIL ? 1 : 0>(g);                  // 32 x 32, K split over the four wavefronts
+    }
 }
 template <int DT>
 hipError_t dispatch(const GemmLaunch& g) {
-    switch (gemm_path_of(g.batch, g.M, g.N, g.K)) {
-        case 1: return launch_wide<DT>(g);                // 256 x 256, four wavefronts of 128 x 128
-        case 2: return launch_tiles<DT, 2, 2, 2, 2>(g);   // 128 x 128, four wavefronts of 64 x 64
-        case 3: return launch_tiles<DT, 2, 2, 1, 1>(g);   // 64 x 64, four wavefronts of 32 x 32
-        case 5: return launch_splitk<DT>(g);   // 32 x 32, K split over the four wavefronts
-        default: return launch_plain<DT>(g);
-    }
+    if (!gemm_rows_aligned(g.N, g.K)) return launch_splitk<DT, 2>(g);
+    return g.K % 32 == 0 ? launch_tile_size<DT, false>(g) : launch_tile_size<DT, true>(g);
 }
 
 }  // namespace

@@ -169,3 +169,48 @@ def test_empty_and_errors(P):
         P.gemm_leakyrelu_fwd(a, torch.ones((32, 8), dtype=torch.float16, device="cuda"))
     with pytest.raises(TypeError):
         P.gemm_leakyrelu_fwd(a.float(), b.float())
+
+
+# K cut in its last block (K % 32 = 8, 16, 24) in every tile size, at the smallest K, at a K of one cut block only and at
+# several; whole and ragged tiles, batches: 64 x 64, 32 x 32 with K split (K >= 256), 128 x 128, 256 x 256
+CUT_K = [(1, 64, 64, 8), (2, 70, 72, 24), (1, 200, 136, 232), (1, 576, 520, 264), (2, 777, 1000, 1000),
+         (1, 33, 8, 264), (3, 200, 136, 360), (1, 97, 72, 2056), (1, 128, 128, 280),
+         (1, 1793, 1800, 40), (2, 1300, 1288, 8), (1, 1792, 1792, 184),
+         (1, 3585, 3592, 8), (1, 3584, 3584, 56), (3, 2100, 2056, 152)]
+# rows that start at unaligned addresses: odd and even K and N, remainders of the 32 x 32 tile and of the 8-element chunk,
+# the matrix's last chunk ending exactly at its end and one element past it, fewer k blocks than wavefronts and more
+UNALIGNED = [(1, 1, 1, 5), (1, 1, 2, 33), (3, 31, 33, 7), (2, 32, 31, 32), (1, 32, 33, 64), (2, 65, 63, 100), (1, 40, 7, 999),
+             (1, 777, 1001, 1003), (4, 130, 257, 131), (1, 5, 4, 4100), (1, 64, 1002, 1500), (1, 9, 3001, 18)]
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("shape", CUT_K + UNALIGNED)
+def test_sizes_that_fit_no_tile(P, shape, dtype):
+    assert P.gemm_path(*shape, dtype) == 4
+    run(P, *shape, dtype)
+
+
+@pytest.mark.parametrize("K,N", [(40, 64), (37, 33)])
+def test_what_lies_past_a_cut_k_is_not_read_into_the_sums(P, K, N):
+    """Rows of a and b next to each other in memory: an infinite element in one row shows in that row of c only."""
+    dt = I.F16
+    M = 48
+    a, b = I.gen_gemm(1, M, N, K, dt)
+    da, db = dev(a, dt), dev(b, dt)
+    da[0, 17, 0] = float("inf")
+    c = P.gemm_leakyrelu_fwd(da, db, 0.5).float()
+    torch.cuda.synchronize()
+    assert torch.isinf(c[0, 17]).all()
+    c[0, 17] = 0.0
+    assert torch.isfinite(c).all()
+
+
+def test_more_tiles_than_one_grid_dimension(P):
+    """2^22 + 3 tiles of 32 x 32: a single column, K = 1, so that c is one exact product per row."""
+    M = ((1 << 22) + 2) * 32 + 5
+    a = (torch.arange(M, device="cuda", dtype=torch.int32) % 1021 - 510).to(torch.float16).reshape(M, 1)
+    b = torch.full((1, 1), 2.0, dtype=torch.float16, device="cuda")
+    c = P.gemm_leakyrelu_fwd(a, b, 0.5)
+    exp = torch.where(a >= 0, a * 2.0, a)
+    torch.cuda.synchronize()
+    assert torch.equal(c, exp)
