@@ -41,8 +41,8 @@ typedef enum {
  *   y        DEVICE pointer, [n_rows, n_cols] contiguous, elements of `dtype`.  Written.
  *            May be the same buffer as x (a row is read completely before it is written).
  *   n_rows   any number of rows >= 0; 0 is an empty input: nothing is launched.
- *   n_cols   row length, 1 .. 2^24.  Rows of up to 16384 elements with n_cols % 8 == 0 stay in
- *            registers between the read and the write; other lengths are read three times.
+ *   n_cols   row length, 1 .. 2^24.  Rows of 8 to 65536 elements stay in registers between the read and
+ *            the write (fastest with n_cols % 8 == 0: aligned accesses); other lengths are read three times.
  *   dtype    rowops_dtype_t of x and y.
  *   stream   hipStream_t to enqueue on (NULL = the default stream).
  *
@@ -60,16 +60,17 @@ int softmax_rows_fwd(const void* x, void* y, long long n_rows, int n_cols, int d
  *   w        DEVICE pointer, [d] weight, elements of `dtype`.  Read only.
  *   y        DEVICE pointer, [n_rows, d] contiguous, elements of `dtype`.  Written.  May be x.
  *   n_rows   >= 0; 0 launches nothing.
- *   d        row length, 1 .. 2^24.  With d % 8 == 0 and d <= 16384 a row stays in registers (several
- *            rows per wavefront when d <= 256); other lengths are read twice.
+ *   d        row length, 1 .. 2^24.  A row of 8 to 65536 elements stays in registers (several rows per
+ *            wavefront when d <= 256); other lengths are read twice.
  *   eps      added to the mean of squares under the root; finite, >= 0.
  *   dtype, stream, ownership, errors: as above.
  */
 int rmsnorm_fwd(const void* x, const void* w, void* y, long long n_rows, int d, float eps, int dtype,
                 void* stream);
 
-/* Which code path serves rows of this length: 1 = the row stays in registers (one read), 2 = the
- * general path (several reads), 0 = the length or dtype is not accepted.  op: 0 softmax, 1 rmsnorm. */
+/* The kind of row length: 1 = a multiple of 8 up to 16384 (aligned accesses, one read), 2 = any other
+ * (unaligned, or longer; one read from 8 to 65536 elements, else several), 0 = the length or dtype is
+ * not accepted.  op: 0 softmax, 1 rmsnorm. */
 int rowops_path(int op, int row_len, int dtype);
 
 /* Static, NUL-terminated description of a status code; never NULL. */

@@ -2,34 +2,29 @@
 //
 // Both are bound by HBM: every element is read once and written once, 4 bytes of traffic per element
 // and a handful of fp32 operations.  So the whole design is about the memory side:
-//   * a row stays in registers between its read and its write (rows of up to 16384 elements whose
-//     length is a multiple of 8): one pass over HBM, not two or three;
+//   * a row of 8 to 65536 elements stays in registers between its read and its write: one pass over
+//     HBM, not two or three;
 //   * every lane moves 16 bytes per instruction and neighbouring lanes neighbouring addresses, so a
-//     wavefront's load or store is 1 KiB of whole 128-byte lines;
+//     wavefront's load or store is 1 KiB of consecutive bytes (whole 128-byte lines where the row length
+//     is a multiple of 8);
 //   * short rows (rmsnorm over a head dimension of 64 is 128 bytes) share a wavefront, TPR lanes per
 //     row, so that the instruction stays 1 KiB wide; long rows take a whole workgroup;
-//   * reductions run across the TPR lanes with cross-lane moves, across the four wavefronts of a
-//     workgroup through 32 bytes of LDS.
-// Rows of any other length go through a general path that reads the row two (rmsnorm) or three
-// (softmax) times with 2-byte accesses.
+//   * reductions run across the TPR lanes with cross-lane moves, across the wavefronts of a
+//     workgroup through LDS.
+// Rows shorter than 8 or longer than 65536 elements go through a general path that reads the row two
+// (rmsnorm) or three (softmax) times with 2-byte accesses.
 #include <hip/hip_runtime.h>
 #include <cstdint>
 
+#include "gfx950_common.h"
 #include "rowops_launch.h"
 
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;   // at any even address
 
 constexpr float LOG2E = 1.4426950408889634f;
-
-// row groups per step (all loads first): rows within a wavefront / rows that take a workgroup with 1 or 2 chunks
-#ifndef ROWOPS_U_SHORT
-#define ROWOPS_U_SHORT 4
-#endif
-#ifndef ROWOPS_U_LONG
-#define ROWOPS_U_LONG 2
-#endif
 
 template <int DT>
 __device__ __forceinline__ float widen(uint16_t b) {
@@ -39,10 +34,12 @@ __device__ __forceinline__ float widen(uint16_t b) {
 // round to nearest even into the 16-bit type (finite values; binary16 overflows to infinity)
 template <int DT>
 __device__ __forceinline__ uint16_t narrow(float f) {
-    if (DT == 0) return __builtin_bit_cast(uint16_t, (_Float16)f);
-    const uint32_t u = __builtin_bit_cast(uint32_t, f);
-    return (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+    return (uint16_t)gfx950::Elem<DT>::pack2(f, 0.f);
 }
+// 16 bytes of a row
+__device__ __forceinline__ u32x4 load16(const uint16_t* p) { return *(const u32x4_any*)p; }
+// The result is not read again here: non-temporal, it does not displace the lines of the rows still to be read.
+__device__ __forceinline__ void store16(uint16_t* p, u32x4 v) { __builtin_nontemporal_store(v, (u32x4_any*)p); }
 template <int DT>
 __device__ __forceinline__ void widen8(const u32x4& p, float (&f)[8]) {
 #pragma unroll
@@ -55,65 +52,94 @@ template <int DT>
 __device__ __forceinline__ u32x4 narrow8(const float (&f)[8]) {
     u32x4 p;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = (uint32_t)narrow<DT>(f[2 * i]) | ((uint32_t)narrow<DT>(f[2 * i + 1]) << 16);
+    for (int i = 0; i < 4; ++i) p[i] = gfx950::Elem<DT>::pack2(f[2 * i], f[2 * i + 1]);
     return p;
 }
 
 struct Max {
-    static __device__ __forceinline__ float op(float a, float b) { return a > b ? a : b; }
+    static __device__ __forceinline__ float op(float a, float b) { return gfx950::vmax(a, b); }
 };
 struct Sum {
     static __device__ __forceinline__ float op(float a, float b) { return a + b; }
 };
 
-// Reduction over the TPR threads that share a row (TPR <= 64: lanes of one wavefront; TPR == 256: the
+// Reduction over the TPR threads that share a row (TPR <= 64: lanes of one wavefront; TPR > 64: the
 // whole workgroup, `red` holds one float per wavefront and row), of U independent rows at once.  Every
 // thread gets the results.
 template <class R, int TPR, int U>
-__device__ __forceinline__ void reduce_rows(float (&v)[U], float (*red)[4]) {
+__device__ __forceinline__ void reduce_rows(float (&v)[U], float (*red)[TPR > 64 ? TPR / 64 : 1]) {
     constexpr int W = TPR < 64 ? TPR : 64;
 #pragma unroll
     for (int off = W / 2; off >= 1; off >>= 1)
 #pragma unroll
         for (int u = 0; u < U; ++u) v[u] = R::op(v[u], __shfl_xor(v[u], off, 64));
-    if constexpr (TPR == 256) {
+    if constexpr (TPR > 64) {
+        constexpr int NW = TPR / 64;
         if ((threadIdx.x & 63) == 0) {
 #pragma unroll
             for (int u = 0; u < U; ++u) red[u][threadIdx.x >> 6] = v[u];
         }
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = R::op(R::op(red[u][0], red[u][1]), R::op(red[u][2], red[u][3]));
+        for (int u = 0; u < U; ++u) {
+            float t[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) t[w] = red[u][w];
+#pragma unroll
+            for (int h = NW / 2; h >= 1; h >>= 1)
+#pragma unroll
+                for (int w = 0; w < h; ++w) t[w] = R::op(t[2 * w], t[2 * w + 1]);
+            v[u] = t[0];
+        }
     }
 }
 
 // Registers path.  OP 0: softmax, 1: rmsnorm.  TPR threads share a row, each holds CH chunks of 8
 // elements: chunk c of thread t covers elements 8 (c TPR + t) .. +7, so the TPR threads of a row read
-// 16 TPR consecutive bytes per instruction.  256 / TPR rows per workgroup at a time, and U such groups
+// 16 TPR consecutive bytes per instruction.  BLOCK / TPR rows per workgroup at a time, and U such groups
 // per step, all their loads issued before the first is used: the bytes in flight are what hides the
 // latency of HBM.
-template <int DT, int OP, int TPR, int CH, int U>
-__global__ __launch_bounds__(256) void rowop_reg_kernel(const uint16_t* x, const uint16_t* __restrict__ w,
-                                                       uint16_t* y, long long n_rows, int n, float eps) {
-    constexpr int RPW = 256 / TPR;
-    __shared__ float red[2][U][4];
+// TAIL: the row length is at least 8 but no multiple of it.  Rows then start at any even address (the
+// accesses are unaligned, which costs a 128-byte line more per KiB), and the last chunk of a row moves back
+// to the row's last eight elements: its first `dup` ones are also the previous chunk's, are left out of
+// the sums, and are stored twice with the same value.
+// Measured (binary16, inputs changing; the copy of a large tensor runs at 5200 GB/s): softmax 4096 x 4095 12.1 us =
+// 5500 GB/s (general path: 28), 2048 x 32768 50 us (general path: 166), rmsnorm 39999 x 999 26 us (93),
+// 2097152 x 64 96 us = 5580 GB/s (100.6 with ordinary stores), 40000 x 1000 26 us (32 with ordinary stores).
+template <int DT, int OP, int TPR, int CH, int U, bool TAIL>
+__global__ __launch_bounds__(TPR > 64 ? TPR : 256) void rowop_reg_kernel(const uint16_t* x, const uint16_t* __restrict__ w,
+                                                                         uint16_t* y, long long n_rows, int n, float eps) {
+    constexpr int BLOCK = TPR > 64 ? TPR : 256, RPW = BLOCK / TPR;
+    __shared__ float red[2][U][TPR > 64 ? TPR / 64 : 1];
     const int t = threadIdx.x % TPR, rin = threadIdx.x / TPR;
-    const int c8 = n >> 3;
+    const int c8 = TAIL ? (n + 7) >> 3 : n >> 3;
+    // element offset of a chunk, and how many of its leading elements belong to the chunk before it
+    auto offset = [&](int chunk) { return TAIL && chunk == c8 - 1 ? n - 8 : 8 * chunk; };
+    auto dup = [&](int chunk) { return TAIL && chunk == c8 - 1 ? 8 * c8 - n : 0; };
+    auto sum8 = [&](int chunk, float s, auto term) {
+        if (TAIL && chunk == c8 - 1) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s = i >= dup(chunk) ? term(i, s) : s;
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s = term(i, s);
+        }
+        return s;
+    };
 
-    float wf[OP == 1 ? CH : 1][8];
+    u32x4 wr[OP == 1 ? CH : 1];
     if constexpr (OP == 1) {
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             const int chunk = c * TPR + t;
-            u32x4 p = {0u, 0u, 0u, 0u};
-            if (chunk < c8) p = *(const u32x4*)(w + 8 * (size_t)chunk);
-            widen8<DT>(p, wf[c]);
+            wr[c] = u32x4{0u, 0u, 0u, 0u};
+            if (chunk < c8) wr[c] = load16(w + offset(chunk));
         }
     }
 
     int turn = 0;   // which of the two LDS slots the next workgroup-wide reduction uses
     for (long long row0 = (long long)blockIdx.x * (RPW * U); row0 < n_rows; row0 += (long long)gridDim.x * (RPW * U)) {
-        float v[U][CH][8];
+        u32x4 raw[U][CH];
         bool ok[U][CH];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -123,20 +149,29 @@ __global__ __launch_bounds__(256) void rowop_reg_kernel(const uint16_t* x, const
             for (int c = 0; c < CH; ++c) {
                 const int chunk = c * TPR + t;
                 ok[u][c] = row < n_rows && chunk < c8;
-                u32x4 p = {0u, 0u, 0u, 0u};
-                if (ok[u][c]) p = *(const u32x4*)(xr + 8 * (size_t)chunk);
-                widen8<DT>(p, v[u][c]);
+                // outside the row: zeros do not count in rmsnorm's sum, minus infinity neither in softmax's
+                constexpr uint32_t NONE = OP == 1 ? 0u : DT == 0 ? 0xfc00fc00u : 0xff80ff80u;
+                raw[u][c] = u32x4{NONE, NONE, NONE, NONE};
+                if (ok[u][c]) raw[u][c] = load16(xr + offset(chunk));
             }
         }
+        auto store_row = [&](int u, int c, const float (&f)[8]) {
+            if (ok[u][c]) store16(y + (size_t)(row0 + u * RPW + rin) * n + offset(c * TPR + t), narrow8<DT>(f));
+        };
         if constexpr (OP == 0) {
+            float v[U][CH][8];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c < CH; ++c) widen8<DT>(raw[u][c], v[u][c]);
             float m[U], s[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                m[u] = -3.0e38f;   // below every finite 16-bit value
+                m[u] = v[u][0][0];
 #pragma unroll
                 for (int c = 0; c < CH; ++c)
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) m[u] = ok[u][c] && v[u][c][i] > m[u] ? v[u][c][i] : m[u];
+                    for (int i = 0; i < 8; ++i) m[u] = gfx950::vmax(m[u], v[u][c][i]);
             }
             reduce_rows<Max, TPR, U>(m, red[turn]);
             turn ^= 1;
@@ -144,12 +179,11 @@ __global__ __launch_bounds__(256) void rowop_reg_kernel(const uint16_t* x, const
             for (int u = 0; u < U; ++u) {
                 s[u] = 0.f;
 #pragma unroll
-                for (int c = 0; c < CH; ++c)
+                for (int c = 0; c < CH; ++c) {
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        v[u][c][i] = ok[u][c] ? __builtin_amdgcn_exp2f((v[u][c][i] - m[u]) * LOG2E) : 0.f;
-                        s[u] += v[u][c][i];
-                    }
+                    for (int i = 0; i < 8; ++i) v[u][c][i] = __builtin_amdgcn_exp2f((v[u][c][i] - m[u]) * LOG2E);
+                    s[u] = sum8(c * TPR + t, s[u], [&](int i, float s) { return s + v[u][c][i]; });
+                }
             }
             reduce_rows<Sum, TPR, U>(s, red[turn]);
             turn ^= 1;
@@ -157,9 +191,11 @@ __global__ __launch_bounds__(256) void rowop_reg_kernel(const uint16_t* x, const
             for (int u = 0; u < U; ++u) {
                 const float inv = 1.0f / s[u];
 #pragma unroll
-                for (int c = 0; c < CH; ++c)
+                for (int c = 0; c < CH; ++c) {
 #pragma unroll
                     for (int i = 0; i < 8; ++i) v[u][c][i] *= inv;
+                    store_row(u, c, v[u][c]);
+                }
             }
         } else {
             float ss[U];
@@ -167,9 +203,11 @@ __global__ __launch_bounds__(256) void rowop_reg_kernel(const uint16_t* x, const
             for (int u = 0; u < U; ++u) {
                 ss[u] = 0.f;
 #pragma unroll
-                for (int c = 0; c < CH; ++c)
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) ss[u] = __builtin_fmaf(v[u][c][i], v[u][c][i], ss[u]);   // masked chunks hold zeros
+                for (int c = 0; c < CH; ++c) {
+                    float f[8];
+                    widen8<DT>(raw[u][c], f);
+                    ss[u] = sum8(c * TPR + t, ss[u], [&](int i, float s) { return __builtin_fmaf(f[i], f[i], s); });
+                }
             }
             reduce_rows<Sum, TPR, U>(ss, red[turn]);
             turn ^= 1;
@@ -177,17 +215,16 @@ __global__ __launch_bounds__(256) void rowop_reg_kernel(const uint16_t* x, const
             for (int u = 0; u < U; ++u) {
                 const float r = 1.0f / __builtin_sqrtf(ss[u] / (float)n + eps);
 #pragma unroll
-                for (int c = 0; c < CH; ++c)
+                for (int c = 0; c < CH; ++c) {
+                    // widened again: held as they came, a row and its weights take half the registers
+                    float f[8], g[8];
+                    widen8<DT>(raw[u][c], f);
+                    widen8<DT>(wr[c], g);
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) v[u][c][i] = v[u][c][i] * r * wf[c][i];
+                    for (int i = 0; i < 8; ++i) f[i] = f[i] * r * g[i];
+                    store_row(u, c, f);
+                }
             }
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            uint16_t* yr = y + (size_t)(row0 + u * RPW + rin) * n;
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-                if (ok[u][c]) *(u32x4*)(yr + 8 * (size_t)(c * TPR + t)) = narrow8<DT>(v[u][c]);
         }
     }
 }
@@ -235,11 +272,12 @@ __global__ __launch_bounds__(256) void rowop_gen_kernel(const uint16_t* x, const
     }
 }
 
-template <int DT, int OP, int TPR, int CH, int U>
+template <int DT, int OP, int TPR, int CH, int U, bool TAIL>
 hipError_t launch_reg(const RowopLaunch& a) {
-    constexpr int RPW = (256 / TPR) * U;
+    constexpr int BLOCK = TPR > 64 ? TPR : 256, RPW = (BLOCK / TPR) * U;
+    constexpr long long FIT = 2048LL * 256 / BLOCK;   // 2048 threads per compute unit: all that fit, then a stride
     long long groups = (a.n_rows + RPW - 1) / RPW;
-    const unsigned grid = (unsigned)(groups < 2048 ? groups : 2048);   // 8 workgroups per compute unit (all that fit), then a stride
+    const unsigned grid = (unsigned)(groups < FIT ? groups : FIT);
     const uint16_t* x = (const uint16_t*)a.x;
     const uint16_t* w = (const uint16_t*)a.w;
     uint16_t* y = (uint16_t*)a.y;
@@ -247,8 +285,8 @@ hipError_t launch_reg(const RowopLaunch& a) {
     int n = a.n;
     float eps = a.eps;
     void* args[] = {&x, &w, &y, &n_rows, &n, &eps};
-    return hipLaunchKernel(reinterpret_cast<const void*>(&rowop_reg_kernel<DT, OP, TPR, CH, U>), dim3(grid), dim3(256), args, 0,
-                           (hipStream_t)a.stream);
+    return hipLaunchKernel(reinterpret_cast<const void*>(&rowop_reg_kernel<DT, OP, TPR, CH, U, TAIL>), dim3(grid), dim3(BLOCK), args,
+                           0, (hipStream_t)a.stream);
 }
 
 template <int DT, int OP>
@@ -265,25 +303,53 @@ hipError_t launch_gen(const RowopLaunch& a) {
                            (hipStream_t)a.stream);
 }
 
+// Threads per row, chunks per thread and rows per step by row length and number of rows: many rows want bytes in flight
+// per thread and few barriers, few rows want as many wavefronts as there can be.  All times in microseconds.
+// Rows within a wavefront: four groups per step where that still makes 1024 workgroups, else one (softmax 8192 x 256:
+// 2.8 with one, 3.5 with four; rmsnorm 131072 x 64: 6.5 and 6.0).
+template <int DT, int OP, int TPR, int CH, bool TAIL>
+hipError_t launch_short(const RowopLaunch& a) {
+    return a.n_rows >= 1024LL * 4 * (256 / TPR) ? launch_reg<DT, OP, TPR, CH, 4, TAIL>(a) : launch_reg<DT, OP, TPR, CH, 1, TAIL>(a);
+}
+
+template <int DT, int OP, bool TAIL>
+hipError_t dispatch_reg(const RowopLaunch& a) {
+    const int c8 = (a.n + 7) / 8;   // 16-byte chunks per row
+    const long long rows = a.n_rows;
+    if (c8 <= 8) return launch_short<DT, OP, 8, 1, TAIL>(a);
+    if (c8 <= 16) return launch_short<DT, OP, 16, 1, TAIL>(a);
+    if (c8 <= 32) return launch_short<DT, OP, 32, 1, TAIL>(a);
+    if (c8 <= 64) return launch_short<DT, OP, 64, 1, TAIL>(a);
+    // two chunks for a wavefront, not one for four: 65536 x 515 takes 26, not 57
+    if (c8 <= 128) return launch_short<DT, OP, 64, 2, TAIL>(a);
+    // rmsnorm 30000 x 1601: 34 with 64 threads a row, 37 with 256; softmax 512 x 2048 would have half the workgroups
+    if (c8 <= 256) return rows >= 4096 ? launch_reg<DT, OP, 64, 4, 1, TAIL>(a) : launch_reg<DT, OP, 256, 1, 1, TAIL>(a);
+    // softmax 512 x 4096: 3.6 with two rows per step, 3.1 with one; rmsnorm 16384 x 4095: 51 and 56
+    if (c8 <= 512) return rows >= 8192 ? launch_reg<DT, OP, 256, 2, 2, TAIL>(a) : launch_reg<DT, OP, 256, 2, 1, TAIL>(a);
+    if (c8 <= 1024) {
+        // rmsnorm 500 x 8192: 3.3 with 512 threads, 3.9 with 1024, 4.5 with 256; 8000 x 8191: 55, 48 and 51; softmax
+        // 8000 x 8191: 57, 54 and 50
+        if (rows < 2048) return launch_reg<DT, OP, 512, 2, 1, TAIL>(a);
+        if constexpr (OP == 0) return launch_reg<DT, OP, 256, 4, 2, TAIL>(a);
+        else return launch_reg<DT, OP, 1024, 1, 1, TAIL>(a);
+    }
+    if (c8 <= 2048) {
+        // rmsnorm 100 x 16384: 3.3 with 1024 threads, 5.9 with 256; 4000 x 16384: 47 and 52; softmax 4000 x 9001: 32 and 26
+        if (OP == 0 && rows >= 2048) return launch_reg<DT, OP, 256, 8, 1, TAIL>(a);
+        return launch_reg<DT, OP, 1024, 2, 1, TAIL>(a);
+    }
+    if (c8 <= 4096) return launch_reg<DT, OP, 1024, 4, 1, TAIL>(a);
+    return launch_reg<DT, OP, 1024, 8, 1, TAIL>(a);   // c8 <= 8192 = ROWOPS_MAX_REG_ROW / 8
+}
 template <int DT, int OP>
 hipError_t dispatch(const RowopLaunch& a) {
-    if (rowop_path_of(a.n) != 1) return launch_gen<DT, OP>(a);
-    const int c8 = a.n / 8;   // 16-byte chunks per row
-    constexpr int US = ROWOPS_U_SHORT, UL = ROWOPS_U_LONG;
-    if (c8 <= 8) return launch_reg<DT, OP, 8, 1, US>(a);
-    if (c8 <= 16) return launch_reg<DT, OP, 16, 1, US>(a);
-    if (c8 <= 32) return launch_reg<DT, OP, 32, 1, US>(a);
-    if (c8 <= 64) return launch_reg<DT, OP, 64, 1, US>(a);
-    if (c8 <= 256) return launch_reg<DT, OP, 256, 1, UL>(a);
-    if (c8 <= 512) return launch_reg<DT, OP, 256, 2, UL>(a);
-    if (c8 <= 1024) return launch_reg<DT, OP, 256, 4, 1>(a);
-    return launch_reg<DT, OP, 256, 8, 1>(a);   // c8 <= 2048 = ROWOPS_MAX_REG_ROW / 8
+    if (a.n < 8 || a.n > ROWOPS_MAX_REG_ROW) return launch_gen<DT, OP>(a);
+    return a.n % 8 == 0 ? dispatch_reg<DT, OP, false>(a) : dispatch_reg<DT, OP, true>(a);
 }
 
 }  // namespace
 
 hipError_t rowop_launch(const RowopLaunch& a) {
-    static_assert(ROWOPS_MAX_REG_ROW == 256 * 8 * 8, "the longest registers-path row is 256 threads x 8 chunks x 8 elements");
     if (a.dtype == 0) return a.op == 0 ? dispatch<0, 0>(a) : dispatch<0, 1>(a);
     return a.op == 0 ? dispatch<1, 0>(a) : dispatch<1, 1>(a);
 }

@@ -14,9 +14,9 @@ struct RowopLaunch {
     void* stream;
 };
 
-constexpr int ROWOPS_MAX_REG_ROW = 16384;   // longest row kept in registers between its read and its write
+constexpr int ROWOPS_MAX_REG_ROW = 65536;   // longest row kept in registers between its read and its write (1024 threads x 8 chunks x 8)
 
-// 1 = registers path, 2 = general path
-inline int rowop_path_of(int n) { return (n % 8 == 0 && n <= ROWOPS_MAX_REG_ROW) ? 1 : 2; }
+// 1 = rows of up to 16384 elements that start at 16-byte aligned addresses, 2 = other lengths
+inline int rowop_path_of(int n) { return (n % 8 == 0 && n <= 16384) ? 1 : 2; }
 
 hipError_t rowop_launch(const RowopLaunch& a);

@@ -184,3 +184,30 @@ def test_side_stream_and_repeatability(P):
     torch.cuda.synchronize()
     assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     check(host_bits(a), R.softmax_rows(xb, dt), dt, "softmax side stream")
+
+
+# (rows, length): the last chunk of a row moved back over 1 .. 7 elements, a row of one or two chunks; every choice of
+# threads per row, on either side of the number of rows that decides (1024 workgroups of four steps, 4096, 8192, 2048
+# rows) with a ragged last step; the longest row kept in registers and the first one that is not
+@pytest.mark.parametrize("op", ["softmax", "rmsnorm"])
+@pytest.mark.parametrize("n_rows,n", [(37, 8 + i) for i in range(1, 8)] + [
+    (131072 + 5, 33), (131071, 33), (32768 + 3, 257), (16384 + 1, 511), (16384 + 3, 1023), (37, 1025), (4096 + 1, 1027),
+    (4095, 1030), (8192 + 1, 2050), (8191, 2051), (2048 + 1, 4100), (2047, 4097), (2048 + 1, 8196), (2047, 8193), (3, 16391),
+    (300, 32767), (3, 65535), (3, 65529), (2, 65536), (2, 65537)])
+def test_row_kernel_choices(P, op, n_rows, n):
+    dt = I.BF16 if (n_rows + n) % 2 else I.F16
+    g = torch.Generator().manual_seed(n_rows * 131 + n)
+    x = (torch.randn(n_rows, n, generator=g) * 2).to(TDT[dt])
+    w = torch.randn(n, generator=g).to(TDT[dt])
+    # a guard row after the tensor and a guard value before it: nothing outside may be written
+    buf = torch.full(((n_rows + 1) * n + 8,), 7.0, dtype=TDT[dt], device="cuda")
+    y = buf[8:8 + n_rows * n].view(n_rows, n)
+    xd, wd = x.cuda(), w.cuda()
+    P.softmax_rows_fwd(xd, y=y) if op == "softmax" else P.rmsnorm_fwd(xd, wd, 1e-6, y=y)
+    torch.cuda.synchronize()
+    x64 = x.cuda().double()
+    ref = torch.softmax(x64, 1) if op == "softmax" else x64 / (x64.square().mean(1, keepdim=True) + 1e-6).sqrt() * wd.double()
+    err = (y.double() - ref).abs() - (REL[dt] * ref.abs() + FLOOR[dt])
+    assert err.max().item() <= 0, (op, n_rows, n, err.max().item())
+    assert torch.equal(buf[:8].cpu(), torch.full((8,), 7.0, dtype=TDT[dt]))
+    assert (buf[8 + n_rows * n:] == 7.0).all()
