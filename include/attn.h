@@ -89,7 +89,7 @@ const char *attn_status_str(int status);
 /*
  * Name of the kernel attn_fwd launches for this very problem (the symbol a
  * profiler reports; it depends on B and H because small problems take the
- * instance with half the wavefronts, see attn_launch_rows), or NULL if
+ * instance with half the query rows, see attn_launch_rows), or NULL if
  * unsupported.  A string constant: no HIP call, safe from any thread.
  */
 const char *attn_kernel_name(int B, int H, int S, int D, int dtype, int causal);
@@ -103,7 +103,8 @@ int attn_tile_keys(int D, int dtype, int causal);
 
 /*
  * Query rows per workgroup attn_fwd uses for this very problem: attn_tile_rows, or half of it (the
- * same kernel with half the wavefronts, "..., 4>" in its name) when the problem has so few tiles
+ * same kernel with half the query rows, "..., 4>" in its name; from a few hundred keys on the one that
+ * splits the keys between two halves of its wavefronts, "attn_fwd_halves_kernel") when the problem has so few tiles
  * that the larger ones would leave half of the chip idle.  0 if unsupported.
  */
 int attn_launch_rows(int B, int H, int S, int D, int dtype, int causal);

@@ -35,14 +35,14 @@ extern "C" const char* attn_status_str(int status) {
 // The names a profiler reports, one string constant per instance (nothing is built at run time).
 #define ATTN_STR2(x) #x
 #define ATTN_STR(x) ATTN_STR2(x)
-#define ATTN_NAME(DT, DD, CZ, NWS) "attn_fwd_kernel<" #DT ", " #DD ", " #CZ ", " NWS ">"
-#define ATTN_NAMES_NW(NWS)                                                                              \
-    {{{ATTN_NAME(0, 32, false, NWS), ATTN_NAME(0, 32, true, NWS)},                                      \
-      {ATTN_NAME(0, 64, false, NWS), ATTN_NAME(0, 64, true, NWS)},                                      \
-      {ATTN_NAME(0, 128, false, NWS), ATTN_NAME(0, 128, true, NWS)}},                                   \
-     {{ATTN_NAME(1, 32, false, NWS), ATTN_NAME(1, 32, true, NWS)},                                      \
-      {ATTN_NAME(1, 64, false, NWS), ATTN_NAME(1, 64, true, NWS)},                                      \
-      {ATTN_NAME(1, 128, false, NWS), ATTN_NAME(1, 128, true, NWS)}}}
+#define ATTN_NAME(FN, DT, DD, CZ, NWS) FN "<" #DT ", " #DD ", " #CZ ", " NWS ">"
+#define ATTN_NAMES_NW(FN, NWS)                                                                            \
+    {{{ATTN_NAME(FN, 0, 32, false, NWS), ATTN_NAME(FN, 0, 32, true, NWS)},                                      \
+      {ATTN_NAME(FN, 0, 64, false, NWS), ATTN_NAME(FN, 0, 64, true, NWS)},                                      \
+      {ATTN_NAME(FN, 0, 128, false, NWS), ATTN_NAME(FN, 0, 128, true, NWS)}},                                   \
+     {{ATTN_NAME(FN, 1, 32, false, NWS), ATTN_NAME(FN, 1, 32, true, NWS)},                                      \
+      {ATTN_NAME(FN, 1, 64, false, NWS), ATTN_NAME(FN, 1, 64, true, NWS)},                                      \
+      {ATTN_NAME(FN, 1, 128, false, NWS), ATTN_NAME(FN, 1, 128, true, NWS)}}}
 #if ATTN_NW == 8
 #define ATTN_NW_FULL_STR "8"
 #define ATTN_NW_HALF_STR "4"
@@ -53,7 +53,9 @@ extern "C" const char* attn_status_str(int status) {
 #error "attn_kernel_name: add the strings for this ATTN_NW"
 #endif
 namespace {
-const char* const kKernelNames[2][2][3][2] = {ATTN_NAMES_NW(ATTN_NW_FULL_STR), ATTN_NAMES_NW(ATTN_NW_HALF_STR)};
+const char* const kKernelNames[3][2][3][2] = {ATTN_NAMES_NW("attn_fwd_kernel", ATTN_NW_FULL_STR),
+                                               ATTN_NAMES_NW("attn_fwd_kernel", ATTN_NW_HALF_STR),
+                                               ATTN_NAMES_NW("attn_fwd_halves_kernel", ATTN_NW_HALF_STR)};
 const char* const kRows64Names[2][2] = {{"attn_fwd_rows64_kernel<0, 128, false>", "attn_fwd_rows64_kernel<0, 128, true>"},
                                         {"attn_fwd_rows64_kernel<1, 128, false>", "attn_fwd_rows64_kernel<1, 128, true>"}};
 }  // namespace
@@ -61,8 +63,9 @@ const char* const kRows64Names[2][2] = {{"attn_fwd_rows64_kernel<0, 128, false>"
 extern "C" const char* attn_kernel_name(int B, int H, int S, int D, int dtype, int causal) {
     if (B <= 0 || H <= 0 || !attn_supported(S, D, dtype, causal)) return nullptr;
     if (attn_takes_rows64((long long)B * H, S, D)) return kRows64Names[dtype][causal != 0];
-    const int half = attn_pick_nw((long long)B * H, S) == ATTN_NW ? 0 : 1;
-    return kKernelNames[half][dtype][D == 32 ? 0 : D == 64 ? 1 : 2][causal != 0];
+    const long long bh = (long long)B * H;
+    const int mode = attn_pick_nw(bh, S) == ATTN_NW ? 0 : attn_splits_keys(bh, S, D) ? 2 : 1;
+    return kKernelNames[mode][dtype][D == 32 ? 0 : D == 64 ? 1 : 2][causal != 0];
 }
 
 extern "C" int attn_tile_rows(int D, int dtype, int causal) {

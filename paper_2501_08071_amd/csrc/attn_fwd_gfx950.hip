@@ -6,7 +6,8 @@
 // (Sections 2.4, 3.5).  Here that order is set by hand for CDNA4.
 //
 // Work split
-//   workgroup = NW wavefronts, each owning 32 consecutive query rows of one (b,h);
+//   workgroup = NR groups of 32 consecutive query rows of one (b,h), a wavefront for each -- or, in the workgroups of half
+//   the rows that small problems take, two: one for either half of the keys of every block (added up at the end);
 //   K/V stream through LDS in blocks of BC keys shared by the whole workgroup (64 in the
 //   alternating-phase loop, 32 in the interleaved one).
 //
@@ -59,23 +60,27 @@ __device__ __forceinline__ void wait_block_loads() { wait_lds_dma<N>(); }
 
 extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
-template <int DT, int D, bool CAUSAL, int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(ATTN_WPE, ATTN_WPE)))
-void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
-                     void* __restrict__ o, float* __restrict__ lse, int S, int BH, int nqt, float c_arg,
-                     uint32_t qsign, int o16) {
+template <int DT, int D, bool CAUSAL, int NR, int KP>
+__device__ __forceinline__
+void attn_fwd_body(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                   void* __restrict__ o, float* __restrict__ lse, int S, int BH, int nqt, float c_arg,
+                   uint32_t qsign, int o16) {
     using E = Elem<DT>;
     // Row sum of the weights.  By one fp32 addition per weight, or -- binary16 at D = 64 -- from the rounded weights, two
     // per dot instruction.  A dot instruction issued while the other wavefront of the SIMD streams matrix instructions
     // waits for a gap in that stream (measured: include/probe.h, probe_issue_share), so it only pays where the vector
     // phase outlasts the other wavefront's matrix phase and the dot instructions can stand at its end: D = 64.
     constexpr bool SUM_DOT = ATTN_F16_SUM_DOT != 0 && DT == 0 && D == 64;
-    constexpr int BR = NW * 32;        // query rows per workgroup, 32 per wavefront
+    // The wavefronts stand in KP parts of NR: wavefront w owns the query rows 32 (w % NR) .. of the workgroup and, of every
+    // key block, the keys BCW (w / NR) ..; what the parts have accumulated is put together at the end.
+    constexpr int NW = NR * KP;
+    constexpr int BR = NR * 32;        // query rows per workgroup, 32 per wavefront
     // keys per block: 32, or 64 (D = 128) and 128 (D = 64) in the alternating-phase loop (a phase then has more work
     // between its two barriers; half as many buffers, each larger)
-    constexpr int BC = attn_block_keys(D);
-    constexpr int NSUB = BC / 32;      // 32-key sub-blocks (one accumulator tile of S each)
-    constexpr int NBUF = attn_buffers(D);   // LDS buffers per tensor (a power of two); block k lives in buffer k % NBUF
+    constexpr int BC = attn_block_keys(D, KP);
+    constexpr int BCW = BC / KP;       // ... of which a wavefront works on this many
+    constexpr int NSUB = BCW / 32;     // 32-key sub-blocks (one accumulator tile of S each)
+    constexpr int NBUF = attn_buffers(D, KP);   // LDS buffers per tensor (a power of two); block k lives in buffer k % NBUF
     // Two loop structures (see below): D = 128 and 64 alternate matrix and vector phases between two
     // groups of wavefronts; D = 32, where the vector work far outweighs the matrix work, interleaves both
     // in every wavefront.
@@ -96,7 +101,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     constexpr int IPT = BC / RPI;      // such instructions per block and tensor
     constexpr int IPW = IPT >= NW ? IPT / NW : 1;   // ... per loading wavefront
     constexpr int LOADERS = IPT / IPW;              // wavefronts that issue loads
-    static_assert((BC == 32 || (PP && (BC == 64 || (BC == 128 && D == 64)))) && IPT % IPW == 0 && LOADERS <= NW, "load split");
+    static_assert((BC == 32 * KP || (PP && (BC == 64 || (BC == 128 && D == 64)))) && BCW % 32 == 0 && IPT % IPW == 0 && LOADERS <= NW, "load split");
     // LDS: K buffers 0..NBUF-1 | V buffers 0..NBUF-1
 
     const float c = c_arg;
@@ -105,6 +110,8 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31;
     const int h = lane >> 5;
+    const int part = KP == 1 ? 0 : wave / NR;         // which keys of a block
+    const int rgrp = KP == 1 ? wave : wave % NR;      // which query rows of the tile
 
     // Workgroup -> tile.  Workgroups are handed to the eight XCDs in turn (workgroup b runs on XCD b % 8,
     // each with an L2 of its own), in the order of their number.  The (b,h) pairs are therefore dealt out
@@ -129,7 +136,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         if (CAUSAL) qt = nqt - 1 - qt;
     }
     const int q0 = qt * BR;
-    const int qw0 = q0 + 32 * wave;          // first query row of this wavefront
+    const int qw0 = q0 + 32 * rgrp;          // first query row of this wavefront
     const int qrow = qw0 + l32;              // this lane's query row (may lie beyond S on the last tile)
     const int qrow_ld = qrow < S ? qrow : S - 1;
 
@@ -144,11 +151,8 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // ragged last block of the sequence (which may not exist: then kd == nblk).  Later blocks of the
     // workgroup are masked entirely for it.
     const int nfull = S / BC;
-    auto first_masked = [&](int w) {
-        const int d = CAUSAL ? (q0 + 32 * w) / BC : nfull;
-        return d < nfull ? d : nfull;
-    };
-    const int kd = first_masked(wave);
+    // (the first block whose share of this wavefront ends beyond the keys that all its rows see)
+    const int kd = ((CAUSAL && qw0 < S ? qw0 : S) - (part + 1) * BCW + BC) / BC;
     const int last_max = nblk - 1;   // the last block any wavefront of the workgroup works on
 
     // ---- direct-to-LDS block loads ----
@@ -225,7 +229,10 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     for (int i = 0; i < DB; ++i)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[i][r] = 0.f;
-    float m_run = -INFINITY;   // reference maximum (base-2 units) everything accumulated so far was taken against
+    // A wavefront that sees a part of the keys only may find all of its first keys masked.  Its reference then starts
+    // from a floor between the masked logits (-3e38) and any real one, so that their weights are zeros (finite for every c).
+    const float m_floor = KP == 1 ? -INFINITY : -2.9e38f * fminf(c, 1.0f);
+    float m_run = m_floor;     // reference maximum (base-2 units) everything accumulated so far was taken against
     float l_run = 0.f;         // this lane's share of the running row sum
     float m_ref;               // main loop: reference maximum of the block in hand
 
@@ -233,7 +240,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // K operand of step ks: row l32 of the block, source chunk 2 ks + h
     uint32_t kaddr[KSTEPS];
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) kaddr[ks] = lds0 + l32 * ROWB + (((2 * ks + h) ^ swz<D>(l32)) << 4);
+    for (int ks = 0; ks < KSTEPS; ++ks) kaddr[ks] = lds0 + (part * BCW + l32) * ROWB + (((2 * ks + h) ^ swz<D>(l32)) << 4);
     // V^T operand of (t, half hi, block i): lane addresses 8 bytes of row 16 t + 8 hi + 4 h + x,
     // elements 32 i + 16 g1 + 4 y .. +3, where x = (lane%16)/4, y = lane%4, g1 = (lane/16)%2
     uint32_t vaddr[2][DB];
@@ -244,12 +251,12 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #pragma unroll
             for (int i = 0; i < DB; ++i) {
                 const int chunk = 4 * i + 2 * g1 + (y >> 1);
-                vaddr[hi][i] = lds0 + NBUF * BLKB + (8 * hi + 4 * h + x) * ROWB +
+                vaddr[hi][i] = lds0 + NBUF * BLKB + (part * BCW + 8 * hi + 4 * h + x) * ROWB +
                                ((chunk ^ swz<D>(8 * hi + 4 * h + x)) << 4) + ((y & 1) << 3);
             }
     }
 
-    constexpr int NT = BC / 16;                      // 16-key steps of the second product
+    constexpr int NT = BCW / 16;                     // 16-key steps of the second product
     constexpr int NU = NSUB * KSTEPS + NT * DB;      // matrix instructions (units, operand fetches) per block
     auto fetch_v = [&](int VB, int tt, int i) {
         u32x2 lo = lds_read_tr16(vaddr[0][i] + VB * BLKB + 16 * tt * ROWB);
@@ -339,7 +346,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                 // A block cut by the causal diagonal or by the end of the sequence: masked logits become
                 // -3e38 (times c >= 1e-30 that is far below any real logit and the weight comes out as an
                 // exact 0); past the diagonal that is all of them and the phase changes nothing.
-                const int lim = (CAUSAL ? qrow_ld : S - 1) - kb * BC - 4 * h;
+                const int lim = (CAUSAL ? qrow_ld : S - 1) - kb * BC - part * BCW - 4 * h;
 #pragma unroll
                 for (int sub = 0; sub < NSUB; ++sub)
 #pragma unroll
@@ -405,7 +412,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
 #pragma unroll
         for (int tt = 0; tt < NT; ++tt) pf[tt] = u32x4{0u, 0u, 0u, 0u};
-        m_ref = -INFINITY;
+        m_ref = m_floor;
         const bool grp1 = wave >= NW / 2;
         // prologue: K(0), the first load, has to be there for the first operand reads
         wait_block_loads<(KAHEAD + VAHEAD - 1) * IPW>();
@@ -449,10 +456,15 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #pragma unroll
                 for (int i = 0; i < DB; ++i) acc_o[i] = E::mfma(a[tt][i], pf[tt], acc_o[i]);
         };
-        // Under the causal mask a wavefront is done with its diagonal block kd: every later block of the
-        // workgroup is masked entirely for it.  In the time of block kd+1 it adds the second product of
-        // block kd; from then on it only issues its share of the block loads and keeps the barriers.
-        const int last_w = CAUSAL && kd < last_max ? kd : last_max;
+        // Under the causal mask a wavefront is done with the block of its diagonal, last_w: every later block of the
+        // workgroup is masked entirely for it.  In the time of block last_w + 1 it adds the second product of
+        // block last_w; from then on it only issues its share of the block loads and keeps the barriers.
+        // (A wavefront whose share of block 0 is masked entirely goes through it with zero weights.)
+        int last_w = last_max;
+        if constexpr (CAUSAL) {
+            const int d = qw0 + 31 < part * BCW ? 0 : (qw0 + 31 - part * BCW) / BC;   // its last block with a key it sees
+            last_w = d < last_max ? d : last_max;
+        }
         for (int k0 = 0; k0 <= last_w; k0 += NBUF) {
             [&]<int... PH>(std::integer_sequence<int, PH...>) {
                 ((k0 + PH <= last_w ? block(k0 + PH, std::integral_constant<int, PH>{}) : (void)0), ...);
@@ -508,7 +520,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                 // A block cut by the causal diagonal or by the end of the sequence: masked logits become
                 // -3e38 (times c >= 1e-30 that is far below any real logit and the weight comes out as an
                 // exact 0), and the reference maximum is taken again, over what is left.
-                const int lim = (CAUSAL ? qrow_ld : S - 1) - kb * BC - 4 * h;
+                const int lim = (CAUSAL ? qrow_ld : S - 1) - kb * BC - part * BCW - 4 * h;
                 float m = -3.0e38f;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
@@ -634,6 +646,7 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #pragma unroll
             for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s_a[r]);
             m_ref = fmaxf(mx, other_half(mx)) * c;   // the first reference: the true maxima of block 0
+            if constexpr (KP > 1) m_ref = fmaxf(m_ref, m_floor);
 #pragma unroll
             for (int u = 0; u < FETCH; ++u) pre[u] = lds_read_b128(kaddr[u] + (1 & (NBUF - 1)) * BLKB);
         }
@@ -656,7 +669,50 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     }
 
     // ---- epilogue: O = acc / l, lse = ln 2 * (m + log2 l) ----
-    const float l_tot = l_run + other_half(l_run);
+    float l_tot = l_run + other_half(l_run);
+    if constexpr (KP > 1) {
+        // Parts 1 .. KP-1 leave their accumulators, row sums and references in LDS (a region of 32 D + 64 + 64 floats
+        // per wavefront, lane beside lane), part 0 adds them up in the order of the parts, against the largest reference.
+        // The block buffers are free once every wavefront's loads have landed and all have come here.
+        constexpr int REG = 32 * D * 4 + 512;
+        static_assert((KP - 1) * NR * REG <= 2 * NBUF * BLKB, "the parts' accumulators fit the block buffers");
+        wait_block_loads<0>();
+        __syncthreads();
+        if (part > 0) {
+            uint8_t* reg = smem + (wave - NR) * REG;
+#pragma unroll
+            for (int i = 0; i < DB; ++i)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *(f32x4*)(reg + ((4 * i + g) * 64 + lane) * 16) =
+                        f32x4{acc_o[i][4 * g], acc_o[i][4 * g + 1], acc_o[i][4 * g + 2], acc_o[i][4 * g + 3]};
+            *(float*)(reg + 128 * D + lane * 4) = l_tot;
+            *(float*)(reg + 128 * D + 256 + lane * 4) = m_run;
+        }
+        __syncthreads();
+        if (part > 0) return;
+        float m_all = m_run;
+#pragma unroll
+        for (int p = 1; p < KP; ++p) m_all = fmaxf(m_all, *(const float*)(smem + ((p - 1) * NR + rgrp) * REG + 128 * D + 256 + lane * 4));
+        const float own = __builtin_amdgcn_exp2f(m_run - m_all);
+        l_tot *= own;
+        rescale_o(own);
+#pragma unroll
+        for (int p = 1; p < KP; ++p) {
+            const uint8_t* reg = smem + ((p - 1) * NR + rgrp) * REG;
+            const float f = __builtin_amdgcn_exp2f(*(const float*)(reg + 128 * D + 256 + lane * 4) - m_all);
+            l_tot = fmaf(f, *(const float*)(reg + 128 * D + lane * 4), l_tot);
+#pragma unroll
+            for (int i = 0; i < DB; ++i)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4 y = *(const f32x4*)(reg + ((4 * i + g) * 64 + lane) * 16);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc_o[i][4 * g + e] = fmaf(f, y[e], acc_o[i][4 * g + e]);
+                }
+        }
+        m_run = m_all;
+    }
     const float inv = 1.0f / l_tot;
     if (o16 == 0) {
         // Single precision O.  A lane holds 4 consecutive elements of its own row: stored from there, one
@@ -699,9 +755,28 @@ void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     }
 }
 
-template <int DT, int D, bool CAUSAL, int NW>
+template <int DT, int D, bool CAUSAL, int NR>
+__global__ __launch_bounds__(NR * 64) __attribute__((amdgpu_waves_per_eu(ATTN_WPE, ATTN_WPE)))
+void attn_fwd_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                     void* __restrict__ o, float* __restrict__ lse, int S, int BH, int nqt, float c_arg,
+                     uint32_t qsign, int o16) {
+    attn_fwd_body<DT, D, CAUSAL, NR, 1>(q, k, v, o, lse, S, BH, nqt, c_arg, qsign, o16);
+}
+// Two wavefronts for every 32 query rows, each with half of the keys of every block.  For problems of fewer workgroups than
+// compute units: a SIMD then has two wavefronts instead of one, and the serial chain over the keys is half as long.
+// Measured (binary16, us, one part -> two): D = 32, 4 heads x 4096 43.3 -> 29.0; D = 64 40.6 -> 32.2; D = 128 63.9 -> 47.2
+// (causal 43.6 -> 29.1, 41.3 -> 31.8, 63.3 -> 45.5); bound by the chain of phases and barriers of the workgroups' one round.
+template <int DT, int D, bool CAUSAL, int NR>
+__global__ __launch_bounds__(NR * 2 * 64) __attribute__((amdgpu_waves_per_eu(ATTN_WPE, ATTN_WPE)))
+void attn_fwd_halves_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+                            void* __restrict__ o, float* __restrict__ lse, int S, int BH, int nqt, float c_arg,
+                            uint32_t qsign, int o16) {
+    attn_fwd_body<DT, D, CAUSAL, NR, 2>(q, k, v, o, lse, S, BH, nqt, c_arg, qsign, o16);
+}
+
+template <int DT, int D, bool CAUSAL, int NR, int KP>
 hipError_t launch(const AttnLaunch& a) {
-    constexpr int BR = NW * 32;
+    constexpr int BR = NR * 32;
     const int nqt = (a.S + BR - 1) / BR;
     const long long blocks = (long long)nqt * a.BH;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
@@ -717,11 +792,13 @@ hipError_t launch(const AttnLaunch& a) {
     // the launch status is taken from the call itself: the thread's "last error" may hold a stale
     // value left by an unrelated earlier runtime call of the host program
     // NBUF K and NBUF V block buffers, and 4 KB per wavefront for the way out of the output tile
-    constexpr unsigned lds_bytes = 2u * attn_buffers(D) * attn_block_keys(D) * 2u * D + NW * 4096u;
-    const void* fn = reinterpret_cast<const void*>(&attn_fwd_kernel<DT, D, CAUSAL, NW>);
+    constexpr unsigned lds_bytes = 2u * attn_buffers(D, KP) * attn_block_keys(D, KP) * 2u * D + NR * 4096u;
+    const void* fn;
+    if constexpr (KP == 1) fn = reinterpret_cast<const void*>(&attn_fwd_kernel<DT, D, CAUSAL, NR>);
+    else fn = reinterpret_cast<const void*>(&attn_fwd_halves_kernel<DT, D, CAUSAL, NR>);
     static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
     if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
-    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(NW * 64), args, lds_bytes, (hipStream_t)a.stream);
+    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(NR * KP * 64), args, lds_bytes, (hipStream_t)a.stream);
 }
 
 }  // namespace
@@ -731,9 +808,15 @@ hipError_t attn_launch(const AttnLaunch& a) {
     // (a negative scale, folded into the sign of q, stays with the 32-row kernel: this one keeps q where no vector
     // instruction reaches it)
     if (attn_takes_rows64(a.BH, a.S, a.D) && a.qsign == 0) return attn_launch_rows64(a);
+    const bool full = attn_pick_nw(a.BH, a.S) == ATTN_NW, halves = attn_splits_keys(a.BH, a.S, a.D);
 #define ATTN_CASE(DT, DD, CZ)                                       \
-    if (a.dtype == DT && a.D == DD && (a.causal != 0) == CZ)     \
-        return attn_pick_nw(a.BH, a.S) == ATTN_NW ? launch<DT, DD, CZ, ATTN_NW>(a) : launch<DT, DD, CZ, ATTN_NW / 2>(a);
+    if (a.dtype == DT && a.D == DD && (a.causal != 0) == CZ) {   \
+        if (full) return launch<DT, DD, CZ, ATTN_NW, 1>(a);         \
+        if constexpr (attn_can_split(DD)) {                         \
+            if (halves) return launch<DT, DD, CZ, ATTN_NW / 2, 2>(a);   \
+        }                                                           \
+        return launch<DT, DD, CZ, ATTN_NW / 2, 1>(a);               \
+    }
     ATTN_CASE(0, 32, false)
     ATTN_CASE(0, 32, true)
     ATTN_CASE(1, 32, false)

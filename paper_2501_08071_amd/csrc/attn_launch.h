@@ -62,8 +62,11 @@
 
 // Which loop a head dimension runs, the keys per inner-loop block and the LDS buffers per tensor that go with it.
 constexpr bool attn_alternating(int D) { return ATTN_PINGPONG != 0 && (D == 128 || D == 64); }
-constexpr int attn_block_keys(int D) { return attn_alternating(D) ? (D == 64 ? ATTN_PP_KEYS_D64 : ATTN_PP_KEYS) : ATTN_BC; }
-constexpr int attn_buffers(int D) { return attn_block_keys(D) * D > 32 * 128 ? ATTN_NBUF / 2 : ATTN_NBUF; }   // blocks of more than 8 KiB: half as many (128 KiB in all with the shipped blocks, D = 128 and 64)
+// (the interleaved loop works on 32 keys at a time: each part of a workgroup brings 32 of its own)
+constexpr int attn_block_keys(int D, int parts = 1) { return attn_alternating(D) ? (D == 64 ? ATTN_PP_KEYS_D64 : ATTN_PP_KEYS) : ATTN_BC * parts; }
+constexpr int attn_buffers(int D, int parts = 1) { return attn_block_keys(D, parts) * D > 32 * 128 ? ATTN_NBUF / 2 : ATTN_NBUF; }   // blocks of more than 8 KiB: half as many (128 KiB in all with the shipped blocks, D = 128 and 64)
+// Can the keys of a block be split between two halves of the wavefronts (32 keys for each at least)?
+constexpr bool attn_can_split(int D) { return attn_alternating(D) ? attn_block_keys(D) >= 64 : D == 32; }
 
 static_assert(ATTN_PP_KEYS == 32 || ATTN_PP_KEYS == 64, "block size of the alternating-phase loop");
 static_assert(ATTN_PP_KEYS_D64 == 32 || ATTN_PP_KEYS_D64 == 64 || ATTN_PP_KEYS_D64 == 128, "block size of the alternating-phase loop at D = 64");
@@ -77,6 +80,14 @@ static_assert(ATTN_PP_KEYS_D64 == 32 || ATTN_PP_KEYS_D64 == 64 || ATTN_PP_KEYS_D
 inline int attn_pick_nw(long long BH, int S) {
     const long long tiles = BH * ((S + 32 * ATTN_NW - 1) / (32 * ATTN_NW));
     return tiles <= ATTN_SMALL_TILES ? ATTN_NW / 2 : ATTN_NW;
+}
+
+// Workgroups of half the rows: are the keys split too?  What it costs is the final addition (and, in it, the wait for loads
+// nobody reads): worth it from a few blocks on.  Measured, us without -> with: D = 32, 8 heads: S = 64 3.5 -> 4.0, 200
+// 5.2 -> 5.2, 333 6.5 -> 6.0, 512 7.8 -> 6.5; D = 64: S = 128 (one block) 5.9 -> 5.8, 200 7.9 -> 7.0, 512 9.2 -> 8.3;
+// D = 128: S = 128 7.2 -> 8.3, 333 causal 10.9 -> 10.9, 512 12.7 -> 11.9, 2048 35.2 -> 27.9.
+inline bool attn_splits_keys(long long BH, int S, int D) {
+    return attn_can_split(D) && attn_pick_nw(BH, S) != ATTN_NW && S > (D == 128 ? 384 : D == 64 ? 128 : 256);
 }
 
 struct AttnLaunch {

@@ -55,6 +55,25 @@ def test_small_problems_take_half_size_workgroups():
     assert P.attn_launch_rows(2, 32, 4096, 128, BF16, True) == 256 and P.attn_launch_rows(4, 16, 1024, 64, F16, False) == 256
 
 
+# Half-size workgroups that split the keys of every block between two halves of their wavefronts.  Lengths at the first it
+# is done for, at the edges of a half (32 keys at D = 32 and 128, 64 at D = 64) and of a block, with logits that differ between
+# the halves by far more than a weight can hold, so that one half's sums vanish in the final addition: first the one, then the other.
+@pytest.mark.parametrize("loud", [0, 1])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S,D", [(257, 32), (288, 32), (319, 32), (385, 128), (416, 128), (449, 128), (129, 64), (192, 64), (321, 64)])
+def test_key_halves(S, D, causal, loud):
+    assert "halves" in P.attn_kernel_name(1, 2, S, D, BF16, causal) and P.attn_launch_rows(1, 2, S, D, BF16, causal) == 128
+    q, k, v = I.gen_tensors(1, 2, S, D, BF16, workload_id=900 + S)
+    half = 64 if D == 64 else 32
+    quiet = (np.arange(S) // half) % 2 != loud
+    # the exponent field lowered by 6 (a factor of 1/64) for the quiet half's keys, raised by 3 (8) for the others
+    step = np.where(quiet[None, None, :, None], -6, 3)
+    k = np.where(((k >> 7) & 0xFF) > 16, k.astype(np.int64) + step * 128, k).astype(np.uint16)
+    # among the scales one at which masked logits overflow
+    for scale in (1 / math.sqrt(D), 3.0, 1e-4):
+        check_full(q, k, v, BF16, causal, scale, f"S{S} D{D} causal{causal} loud{loud} scale{scale}")
+
+
 def test_workload_1_full():
     w = I.workload(1)
     q, k, v = I.gen_inputs(w)
