@@ -124,7 +124,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
     uint16_t* Cb = C + (size_t)bi * M * N;
-    const int nk = (K + 31) / 32;
+    const int nk = gemm_pieces(K, 32);
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
 
@@ -332,7 +332,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
     uint16_t* Cb = C + (size_t)bi * M * N;
-    const int nk = (K + 31) / 32;
+    const int nk = gemm_pieces(K, 32);
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
 
@@ -538,7 +538,7 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
     uint16_t* Cb = C + (size_t)bi * M * N;
-    const int nk = (K + 31) / 32;
+    const int nk = gemm_pieces(K, 32);
     const int kr = K - 32 * (nk - 1);   // valid k of the last block
     const int mine = nk > wave ? (nk - wave + 3) / 4 : 0;   // k blocks of this wavefront: wave, wave + 4, ...
 
@@ -719,7 +719,7 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
         if constexpr (LOAD != 2) {
             if (m < M && n < N) *(u32x2*)cp = v;
         } else if (m < M) {
-            if (n + 4 <= N) {
+            if (n <= N - 4) {   // (n + 4 overflows where N is near 2^31)
                 __builtin_memcpy(cp, &v, 8);   // an unaligned 8-byte store
             } else {
 #pragma unroll
@@ -734,7 +734,7 @@ template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
 hipError_t launch_tiles(const GemmLaunch& g) {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
     constexpr unsigned lds_bytes = (unsigned)GemmLds<WM, WN, TM, TN, NST>::BYTES;
-    int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+    int tiles_m = gemm_pieces(g.M, BM), tiles_n = gemm_pieces(g.N, BN);
     const long long blocks = (long long)tiles_m * tiles_n * g.batch;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const uint16_t* a = (const uint16_t*)g.a;
@@ -752,7 +752,7 @@ hipError_t launch_tiles(const GemmLaunch& g) {
 // 256 x 256 tiles
 template <int DT, bool KTAIL>
 hipError_t launch_wide(const GemmLaunch& g) {
-    int tiles_m = (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
+    int tiles_m = gemm_pieces(g.M, 256), tiles_n = gemm_pieces(g.N, 256);
     const long long blocks = (long long)tiles_m * tiles_n * g.batch;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
     const uint16_t* a = (const uint16_t*)g.a;
@@ -770,7 +770,7 @@ hipError_t launch_wide(const GemmLaunch& g) {
 
 template <int DT, int LOAD>
 hipError_t launch_splitk(const GemmLaunch& g) {
-    int tiles_m = (g.M + 31) / 32, tiles_n = (g.N + 31) / 32;
+    int tiles_m = gemm_pieces(g.M, 32), tiles_n = gemm_pieces(g.N, 32);
     long long blocks = (long long)tiles_m * tiles_n * g.batch;
     constexpr long long X = 1 << 22;   // a dimension of the grid holds fewer than 2^32 threads
     const unsigned gx = (unsigned)(blocks < X ? blocks : X), gy = (unsigned)((blocks + gx - 1) / gx);

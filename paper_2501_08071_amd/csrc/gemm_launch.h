@@ -12,6 +12,9 @@ struct GemmLaunch {
     void* stream;
 };
 
+// Pieces of t that cover x, for any x >= 0 (x + t - 1 would overflow where x is near 2^31).
+constexpr int gemm_pieces(int x, int t) { return x / t + (x % t != 0); }
+
 // Tiles of c for a problem whose rows are 16-byte aligned: 1: 256 x 256, 2: 128 x 128, 3: 64 x 64, 5: 32 x 32 with K
 // split over the wavefronts of a workgroup.  The largest tile that still gives three quarters of the 256 compute units
 // a workgroup; a problem that fits the chip in one round of 32 x 32 tiles and has a K worth splitting takes those.
@@ -19,7 +22,7 @@ struct GemmLaunch {
 #define GEMM_SK_TILES 256
 #endif
 inline int gemm_tile_of(int batch, int M, int N, int K) {
-    auto tiles = [&](int t) { return (long long)batch * ((M + t - 1) / t) * ((N + t - 1) / t); };
+    auto tiles = [&](int t) { return (long long)batch * gemm_pieces(M, t) * gemm_pieces(N, t); };
     if (tiles(32) <= GEMM_SK_TILES && K >= 256) return 5;
     return tiles(256) >= 192 ? 1 : tiles(128) >= 192 ? 2 : 3;
 }

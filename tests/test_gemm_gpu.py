@@ -214,3 +214,15 @@ def test_more_tiles_than_one_grid_dimension(P):
     exp = torch.where(a >= 0, a * 2.0, a)
     torch.cuda.synchronize()
     assert torch.equal(c, exp)
+
+
+@pytest.mark.parametrize("along", ["M", "N"])
+def test_the_longest_row_and_column(P, along):
+    """M or N = 2^31 - 1: one exact product per element of c."""
+    n = 2 ** 31 - 1
+    x = (torch.arange(1021, device="cuda", dtype=torch.int32) - 510).to(torch.float16).repeat(n // 1021 + 1)[:n]
+    one = torch.ones((1, 1), dtype=torch.float16, device="cuda")
+    c = P.gemm_leakyrelu_fwd(x.reshape(n, 1), one, 0.5) if along == "M" else P.gemm_leakyrelu_fwd(one, x.reshape(1, n), 0.5)
+    exp = torch.where(x >= 0, x, x * 0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(c.reshape(n), exp)
