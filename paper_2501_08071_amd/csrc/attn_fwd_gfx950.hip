@@ -230,8 +230,10 @@ void attn_fwd_body(const uint16_t* __restrict__ q, const uint16_t* __restrict__ 
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc_o[i][r] = 0.f;
     // A wavefront that sees a part of the keys only may find all of its first keys masked.  Its reference then starts
-    // from a floor between the masked logits (-3e38) and any real one, so that their weights are zeros (finite for every c).
-    const float m_floor = KP == 1 ? -INFINITY : -2.9e38f * fminf(c, 1.0f);
+    // from a floor just above the masked logits (-3e38 c), so that their weights are zeros, and finite for every c: at most
+    // the largest finite number below zero, which is the floor where nothing is masked.  Real logits lie above it.
+    constexpr float LOWEST = -3.402823466e38f;
+    const float m_floor = KP == 1 ? -INFINITY : kd > last_max ? LOWEST : fmaxf(-2.99999e38f * c, LOWEST);
     float m_run = m_floor;     // reference maximum (base-2 units) everything accumulated so far was taken against
     float l_run = 0.f;         // this lane's share of the running row sum
     float m_ref;               // main loop: reference maximum of the block in hand

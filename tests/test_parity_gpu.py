@@ -74,6 +74,19 @@ def test_key_halves(S, D, causal, loud):
         check_full(q, k, v, BF16, causal, scale, f"S{S} D{D} causal{causal} loud{loud} scale{scale}")
 
 
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S,D", [(320, 32), (300, 32), (256, 64), (300, 64), (448, 128), (450, 128)])
+def test_key_halves_with_logits_near_the_lowest_number(S, D, causal):
+    """Every logit -2^127 (exact products only, so that the weights are exact): far below the floor that a half with masked
+    keys starts from unless that floor follows the scale.  Whole and cut last blocks."""
+    assert "halves" in P.attn_kernel_name(1, 2, S, D, BF16, causal)
+    _, _, v = I.gen_tensors(1, 2, S, D, BF16, workload_id=901)
+    q, k = np.zeros_like(v), np.zeros_like(v)
+    q[..., 0] = (64 + 127) << 7              # 2^64
+    k[..., 0] = 0x8000 | ((63 + 127) << 7)   # -2^63
+    check_full(q, k, v, BF16, causal, 1.25, f"S{S} D{D} causal{causal} logits -2^127")
+
+
 def test_workload_1_full():
     w = I.workload(1)
     q, k, v = I.gen_inputs(w)
