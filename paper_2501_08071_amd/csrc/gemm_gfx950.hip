@@ -57,10 +57,9 @@ __device__ __forceinline__ constexpr int swz_b(int row) {
                         : ((((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1));
 }
 
-// Workgroup -> tile.  Workgroup b runs on XCD b % 8, each with an L2 of its own, so every XCD takes a contiguous run of
-// the tile list, and the list goes through GEMM_GROUP_M tile rows at a time, column by column: the workgroups that an
-// XCD runs together then cover a compact block of c (4 x 8 tiles when it holds 32) and share both their rows of a and
-// their columns of b.
+// Workgroup -> tile.  Every XCD takes a contiguous run of the tile list (gemm_list_position), and the list goes through
+// GEMM_GROUP_M tile rows at a time, column by column: the workgroups that an XCD runs together then cover a compact block
+// of c (4 x 8 tiles when it holds 32) and share both their rows of a and their columns of b.
 #ifndef GEMM_GROUP_M
 #define GEMM_GROUP_M 4
 #endif
@@ -73,13 +72,17 @@ __device__ __forceinline__ TileIndex tile_in_list(int bi, int t, int tiles_m, in
     const int tn = u / rows;
     return {bi, g * GEMM_GROUP_M + (u - tn * rows), tn};
 }
-__device__ __forceinline__ TileIndex tile_of_workgroup(int tiles_m, int tiles_n) {
-    const int total = (int)gridDim.x, b = (int)blockIdx.x;
-    const int q = total >> 3, r = total & 7, x = b & 7;
-    const int c = x * q + (x < r ? x : r) + (b >> 3);
+__device__ __forceinline__ TileIndex tile_of_workgroup(int tiles_m, int tiles_n, long long total) {
     const int per = tiles_m * tiles_n;
-    const int bi = c / per;
-    return tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
+    if (gridDim.y == 1) {
+        const int c = gemm_list_position((int)blockIdx.x, (int)gridDim.x), bi = c / per;
+        return tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
+    }
+    long long b = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    b = b < total ? b : total - 1;   // surplus workgroups repeat the last one's tile
+    const long long c = gemm_list_position(b, total);
+    const int bi = (int)(c / per);
+    return tile_in_list(bi, (int)(c - (long long)bi * per), tiles_m, tiles_n);
 }
 
 __device__ __forceinline__ float leaky(float t, float slope) { return t >= 0.f ? t : slope * t; }
@@ -98,7 +101,7 @@ struct GemmLds {
 template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                         uint16_t* __restrict__ C, int M, int N, int K, int tiles_m,
-                                                        int tiles_n, float slope) {
+                                                        int tiles_n, long long total, float slope) {
     using E = Elem<DT>;
     constexpr int NW = WM * WN;               // wavefronts, WM x WN over the tile
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
@@ -119,7 +122,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     const int l32 = lane & 31, h = lane >> 5;
     const int wm = wave % WM, wn = wave / WM;
 
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, total);
     const int m0 = tm_i * BM, n0 = tn_i * BN;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -313,7 +316,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 template <int DT, bool KTAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int M,
-                            int N, int K, int tiles_m, int tiles_n, float slope) {
+                            int N, int K, int tiles_m, int tiles_n, long long total, float slope) {
     using E = Elem<DT>;
     constexpr int NST = GEMM_NST;
     // LDS: the a tiles of all stages, then the b tiles: every read is one base register plus a 16-bit immediate
@@ -327,7 +330,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave & 1, wn = wave >> 1;
 
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, total);
     const int m0 = tm_i * 256, n0 = tn_i * 256;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -524,16 +527,7 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    TileIndex ti;
-    if (gridDim.y == 1) {
-        ti = tile_of_workgroup(tiles_m, tiles_n);
-    } else {   // more tiles than a grid's x takes: in the list's order, surplus workgroups repeat the last tile
-        long long c = (long long)blockIdx.y * gridDim.x + blockIdx.x;
-        c = c < total ? c : total - 1;
-        const int per = tiles_m * tiles_n, b = (int)(c / per);
-        ti = tile_in_list(b, (int)(c - (long long)b * per), tiles_m, tiles_n);
-    }
-    const auto [bi, tm_i, tn_i] = ti;
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, total);
     const int m0 = tm_i * 32, n0 = tn_i * 32;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -730,62 +724,38 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
     }
 }
 
-template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
-hipError_t launch_tiles(const GemmLaunch& g) {
-    constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-    constexpr unsigned lds_bytes = (unsigned)GemmLds<WM, WN, TM, TN, NST>::BYTES;
-    int tiles_m = gemm_pieces(g.M, BM), tiles_n = gemm_pieces(g.N, BN);
-    const long long blocks = (long long)tiles_m * tiles_n * g.batch;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+// one workgroup of `threads` per tile of bm x bn; `told` as announce_lds has it
+hipError_t launch_grid(const GemmLaunch& g, const void* fn, int bm, int bn, int threads, unsigned lds_bytes, std::atomic<uint64_t>& told) {
+    GemmGrid grid = gemm_grid_of(g.batch, g.M, g.N, bm, bn);
+    if (grid.y > 65535u) return hipErrorInvalidConfiguration;
     const uint16_t* a = (const uint16_t*)g.a;
     const uint16_t* b = (const uint16_t*)g.b;
     uint16_t* c = (uint16_t*)g.c;
     int M = g.M, N = g.N, K = g.K;
     float slope = g.slope;
-    void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &slope};
-    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN, NST, KTAIL>);
-    static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
+    void* args[] = {&a, &b, &c, &M, &N, &K, &grid.tiles_m, &grid.tiles_n, &grid.total, &slope};
     if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
-    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(WM * WN * 64), args, lds_bytes, (hipStream_t)g.stream);
+    return hipLaunchKernel(fn, dim3(grid.x, grid.y), dim3(threads), args, lds_bytes, (hipStream_t)g.stream);
+}
+
+template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
+hipError_t launch_tiles(const GemmLaunch& g) {
+    static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
+    return launch_grid(g, reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN, NST, KTAIL>), 32 * TM * WM, 32 * TN * WN,
+                       WM * WN * 64, (unsigned)GemmLds<WM, WN, TM, TN, NST>::BYTES, told);
 }
 
 // 256 x 256 tiles
 template <int DT, bool KTAIL>
 hipError_t launch_wide(const GemmLaunch& g) {
-    int tiles_m = gemm_pieces(g.M, 256), tiles_n = gemm_pieces(g.N, 256);
-    const long long blocks = (long long)tiles_m * tiles_n * g.batch;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const uint16_t* a = (const uint16_t*)g.a;
-    const uint16_t* b = (const uint16_t*)g.b;
-    uint16_t* c = (uint16_t*)g.c;
-    int M = g.M, N = g.N, K = g.K;
-    float slope = g.slope;
-    void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &slope};
-    constexpr unsigned lds_bytes = GEMM_NST * (256 * 64 + 32 * 512);
-    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_wide_kernel<DT, KTAIL>);
-    static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
-    if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
-    return hipLaunchKernel(fn, dim3((unsigned)blocks), dim3(256), args, lds_bytes, (hipStream_t)g.stream);
+    static std::atomic<uint64_t> told{0};
+    return launch_grid(g, reinterpret_cast<const void*>(&gemm_lrelu_wide_kernel<DT, KTAIL>), 256, 256, 256, GEMM_NST * (256 * 64 + 32 * 512), told);
 }
 
 template <int DT, int LOAD>
 hipError_t launch_splitk(const GemmLaunch& g) {
-    int tiles_m = gemm_pieces(g.M, 32), tiles_n = gemm_pieces(g.N, 32);
-    long long blocks = (long long)tiles_m * tiles_n * g.batch;
-    constexpr long long X = 1 << 22;   // a dimension of the grid holds fewer than 2^32 threads
-    const unsigned gx = (unsigned)(blocks < X ? blocks : X), gy = (unsigned)((blocks + gx - 1) / gx);
-    if (gy > 65535u) return hipErrorInvalidConfiguration;
-    const uint16_t* a = (const uint16_t*)g.a;
-    const uint16_t* b = (const uint16_t*)g.b;
-    uint16_t* c = (uint16_t*)g.c;
-    int M = g.M, N = g.N, K = g.K;
-    float slope = g.slope;
-    void* args[] = {&a, &b, &c, &M, &N, &K, &tiles_m, &tiles_n, &blocks, &slope};
-    constexpr unsigned lds_bytes = 4u * GEMM_SK_NST * 4096u;
-    const void* fn = reinterpret_cast<const void*>(&gemm_lrelu_splitk_kernel<DT, LOAD>);
-    static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
-    if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
-    return hipLaunchKernel(fn, dim3(gx, gy), dim3(256), args, lds_bytes, (hipStream_t)g.stream);
+    static std::atomic<uint64_t> told{0};
+    return launch_grid(g, reinterpret_cast<const void*>(&gemm_lrelu_splitk_kernel<DT, LOAD>), 32, 32, 256, 4u * GEMM_SK_NST * 4096u, told);
 }
 
 template <int DT, bool KTAIL>

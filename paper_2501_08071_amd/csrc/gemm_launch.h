@@ -36,4 +36,27 @@ inline int gemm_path_of(int batch, int M, int N, int K) {
     return gemm_rows_aligned(N, K) && K % 32 == 0 ? gemm_tile_of(batch, M, N, K) : 4;
 }
 
+// The grid over the tiles of bm x bn of a problem: one workgroup per tile, in two dimensions above GEMM_GRID_X of them (a
+// dimension of a grid holds fewer than 2^32 threads).  The last row of workgroups may be surplus.
+constexpr long long GEMM_GRID_X = 1 << 22;
+struct GemmGrid {
+    int tiles_m, tiles_n;
+    long long total;    // tiles
+    unsigned x, y;      // workgroups, x y >= total; y > 65535: more than a grid holds
+};
+constexpr GemmGrid gemm_grid_of(int batch, int M, int N, int bm, int bn) {
+    const int tm = gemm_pieces(M, bm), tn = gemm_pieces(N, bn);
+    const long long total = (long long)tm * tn * batch;
+    if (total <= GEMM_GRID_X) return {tm, tn, total, (unsigned)total, 1u};
+    return {tm, tn, total, (unsigned)GEMM_GRID_X, (unsigned)((total + GEMM_GRID_X - 1) / GEMM_GRID_X)};
+}
+
+// Workgroup b of `total` -> position in the list of tiles.  Workgroup b runs on XCD b % 8, each with an L2 of its own, so
+// every XCD takes a contiguous run of the list.  I: int where it holds every count, else long long.
+template <class I>
+constexpr I gemm_list_position(I b, I total) {
+    const I q = total >> 3, r = total & 7, x = b & 7;
+    return x * q + (x < r ? x : r) + (b >> 3);
+}
+
 hipError_t gemm_launch(const GemmLaunch& a);

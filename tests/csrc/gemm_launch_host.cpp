@@ -4,4 +4,11 @@
 extern "C" {
 int pieces(int x, int t) { return gemm_pieces(x, t); }
 int tile_of(int batch, int M, int N, int K) { return gemm_tile_of(batch, M, N, K); }
+// tiles_m, tiles_n, total, x, y
+void grid_of(int batch, int M, int N, int bm, int bn, long long* out) {
+    const GemmGrid g = gemm_grid_of(batch, M, N, bm, bn);
+    out[0] = g.tiles_m; out[1] = g.tiles_n; out[2] = g.total; out[3] = g.x; out[4] = g.y;
+}
+int position32(int b, int total) { return gemm_list_position(b, total); }
+long long position64(long long b, long long total) { return gemm_list_position(b, total); }
 }

@@ -19,7 +19,10 @@ def L(tmp_path_factory):
     res = subprocess.run([gxx, "-std=c++20", "-O1", "-fwrapv", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-isystem", "/opt/rocm/include",
                           os.path.join(HERE, "csrc", "gemm_launch_host.cpp"), "-o", out], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
-    return ctypes.CDLL(out)
+    lib = ctypes.CDLL(out)
+    lib.position64.argtypes = [ctypes.c_longlong] * 2
+    lib.position64.restype = ctypes.c_longlong
+    return lib
 
 
 @pytest.mark.parametrize("t", [32, 64, 128, 256])
@@ -32,3 +35,31 @@ def test_tile_choice_at_the_largest_sizes(L):
     """Sums of 2^31 - 1 terms, a single row or column of 2^31 - 1 elements: no overflow on the way to a choice."""
     for shape in ((1, 1, 1, TOP), (1, TOP, 1, 1), (1, 1, TOP, 1), (65535, TOP, 1, 1)):
         assert L.tile_of(*shape) in (1, 2, 3, 5)
+
+
+def grid_of(L, *args):
+    out = (ctypes.c_longlong * 5)()
+    L.grid_of(*args, out)
+    return list(out)
+
+
+@pytest.mark.parametrize("batch,M,N,t", [(1, 1, 1, 64), (3, 70, 130, 64), (65535, 1, 64 * 65, 64), (16, 2 ** 28, 8, 256), (1, TOP, 1, 32),
+                                         (65535, 4, 1 << 20, 256), (4, 32, 32 << 20, 32)])
+def test_grid_holds_every_tile(L, batch, M, N, t):
+    """No dimension of 2^32 threads or more, and no more than one surplus row of workgroups."""
+    tm, tn, total, x, y = grid_of(L, batch, M, N, t, t)
+    assert (tm, tn) == (-(-M // t), -(-N // t)) and total == tm * tn * batch
+    assert x * 256 < 2 ** 32 and y <= 65535 and x * y >= total > x * (y - 1)
+    assert y == 1 or x % 8 == 0        # a workgroup's number modulo 8 is its XCD also in the second dimension
+
+
+@pytest.mark.parametrize("total", [1, 7, 8, 9, 31, 32, 100, 257])
+def test_list_positions_are_a_permutation(L, total):
+    assert sorted(L.position32(b, total) for b in range(total)) == list(range(total))
+    assert [L.position64(b, total) for b in range(total)] == [L.position32(b, total) for b in range(total)]
+
+
+def test_list_positions_above_2_to_the_31(L):
+    total = 2 ** 33 + 5
+    got = [L.position64(b, total) for b in (0, 7, 8, total - 1)]
+    assert got == [0, 7 * (total // 8) + 5, 1, 4 * (total // 8) + 4 + total // 8]
