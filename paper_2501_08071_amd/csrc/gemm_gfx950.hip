@@ -57,32 +57,18 @@ __device__ __forceinline__ constexpr int swz_b(int row) {
                         : ((((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1));
 }
 
-// Workgroup -> tile.  Every XCD takes a contiguous run of the tile list (gemm_list_position), and the list goes through
-// GEMM_GROUP_M tile rows at a time, column by column: the workgroups that an XCD runs together then cover a compact block
-// of c (4 x 8 tiles when it holds 32) and share both their rows of a and their columns of b.
-#ifndef GEMM_GROUP_M
-#define GEMM_GROUP_M 4
-#endif
-struct TileIndex {
-    int bi, tm, tn;
-};
-__device__ __forceinline__ TileIndex tile_in_list(int bi, int t, int tiles_m, int tiles_n) {
-    const int g = t / (GEMM_GROUP_M * tiles_n), u = t - g * (GEMM_GROUP_M * tiles_n);
-    const int left = tiles_m - g * GEMM_GROUP_M, rows = left < GEMM_GROUP_M ? left : GEMM_GROUP_M;
-    const int tn = u / rows;
-    return {bi, g * GEMM_GROUP_M + (u - tn * rows), tn};
-}
-__device__ __forceinline__ TileIndex tile_of_workgroup(int tiles_m, int tiles_n, long long total) {
+// Workgroup -> tile: gemm_list_position, then gemm_tile_in_list
+__device__ __forceinline__ GemmTile tile_of_workgroup(int tiles_m, int tiles_n, long long total) {
     const int per = tiles_m * tiles_n;
     if (gridDim.y == 1) {
         const int c = gemm_list_position((int)blockIdx.x, (int)gridDim.x), bi = c / per;
-        return tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
+        return gemm_tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
     }
     long long b = (long long)blockIdx.y * gridDim.x + blockIdx.x;
     b = b < total ? b : total - 1;   // surplus workgroups repeat the last one's tile
     const long long c = gemm_list_position(b, total);
     const int bi = (int)(c / per);
-    return tile_in_list(bi, (int)(c - (long long)bi * per), tiles_m, tiles_n);
+    return gemm_tile_in_list(bi, (int)(c - (long long)bi * per), tiles_m, tiles_n);
 }
 
 __device__ __forceinline__ float leaky(float t, float slope) { return t >= 0.f ? t : slope * t; }

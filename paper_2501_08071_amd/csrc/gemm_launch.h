@@ -59,4 +59,24 @@ constexpr I gemm_list_position(I b, I total) {
     return x * q + (x < r ? x : r) + (b >> 3);
 }
 
+// Position t in matrix bi's list of tiles -> tile.  The list goes through GEMM_GROUP_M tile rows at a time, column by column:
+// the workgroups that an XCD runs together then cover a compact block of c (4 x 8 tiles when it holds 32) and share both
+// their rows of a and their columns of b.  The last group takes the remainder too, GEMM_GROUP_M to 2 GEMM_GROUP_M - 1 rows: a
+// last group of one row would give an XCD 32 columns of b to read (288 x 4096 x 2240, five rows of tiles: 19.7 us with
+// groups of 4 and 1, 16.7 us with one of 5).
+#ifndef GEMM_GROUP_M
+#define GEMM_GROUP_M 4
+#endif
+struct GemmTile {
+    int bi, tm, tn;
+};
+constexpr GemmTile gemm_tile_in_list(int bi, int t, int tiles_m, int tiles_n) {
+    const int last = tiles_m > GEMM_GROUP_M ? tiles_m / GEMM_GROUP_M - 1 : 0;   // number of the last group
+    int g = t / (GEMM_GROUP_M * tiles_n);
+    g = g < last ? g : last;
+    const int u = t - g * GEMM_GROUP_M * tiles_n, rows = g < last ? GEMM_GROUP_M : tiles_m - last * GEMM_GROUP_M;
+    const int tn = u / rows;
+    return {bi, g * GEMM_GROUP_M + (u - tn * rows), tn};
+}
+
 hipError_t gemm_launch(const GemmLaunch& a);

@@ -11,4 +11,8 @@ void grid_of(int batch, int M, int N, int bm, int bn, long long* out) {
 }
 int position32(int b, int total) { return gemm_list_position(b, total); }
 long long position64(long long b, long long total) { return gemm_list_position(b, total); }
+int tile_in_list(int t, int tiles_m, int tiles_n) {
+    const GemmTile g = gemm_tile_in_list(0, t, tiles_m, tiles_n);
+    return g.tm * tiles_n + g.tn;
+}
 }

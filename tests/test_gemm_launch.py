@@ -63,3 +63,15 @@ def test_list_positions_above_2_to_the_31(L):
     total = 2 ** 33 + 5
     got = [L.position64(b, total) for b in (0, 7, 8, total - 1)]
     assert got == [0, 7 * (total // 8) + 5, 1, 4 * (total // 8) + 4 + total // 8]
+
+
+@pytest.mark.parametrize("tiles_m,tiles_n", [(1, 1), (3, 7), (4, 5), (5, 64), (7, 9), (8, 8), (9, 40), (11, 3), (16, 16), (1, 300), (300, 1)])
+def test_every_tile_once_in_compact_blocks(L, tiles_m, tiles_n):
+    order = [L.tile_in_list(t, tiles_m, tiles_n) for t in range(tiles_m * tiles_n)]
+    assert sorted(order) == list(range(tiles_m * tiles_n))
+    # 32 neighbours in the list (what an XCD runs together) touch few rows and columns: never a run along one row
+    # of tiles where there are more rows to choose from
+    for s in range(0, len(order) - 31, 32):
+        rows = {i // tiles_n for i in order[s:s + 32]}
+        cols = {i % tiles_n for i in order[s:s + 32]}
+        assert tiles_m < 4 or tiles_n == 1 or len(rows) + len(cols) <= 20, (s, len(rows), len(cols))
