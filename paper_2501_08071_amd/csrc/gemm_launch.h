@@ -52,11 +52,19 @@ constexpr GemmGrid gemm_grid_of(int batch, int M, int N, int bm, int bn) {
 }
 
 // Workgroup b of `total` -> position in the list of tiles.  Workgroup b runs on XCD b % 8, each with an L2 of its own, so
-// every XCD takes a contiguous run of the list.  I: int where it holds every count, else long long.
+// every XCD takes a contiguous run of the list.  Where that takes more than two rounds of the 256 compute units, XCD x starts an x-th
+// of the way through its run: the runs often begin a power of two of bytes of c apart, and eight XCDs at the same place of
+// theirs would write to the same memory channels (8192 x 8192, K = 64, bfloat16: 47 us in step, 36 us like this; K = 2048: 231
+// and 212; one and two rounds: within 3 % either way).  I: int where it holds every count, else long long.
 template <class I>
 constexpr I gemm_list_position(I b, I total) {
-    const I q = total >> 3, r = total & 7, x = b & 7;
-    return x * q + (x < r ? x : r) + (b >> 3);
+    const I q = total >> 3, r = total & 7, x = b & 7, len = q + (x < r);
+    I j = b >> 3;
+    if (total > 512) {
+        j += (x * len) >> 3;
+        j = j < len ? j : j - len;
+    }
+    return x * q + (x < r ? x : r) + j;
 }
 
 // Position t in matrix bi's list of tiles -> tile.  The list goes through GEMM_GROUP_M tile rows at a time, column by column:

@@ -53,16 +53,26 @@ def test_grid_holds_every_tile(L, batch, M, N, t):
     assert y == 1 or x % 8 == 0        # a workgroup's number modulo 8 is its XCD also in the second dimension
 
 
-@pytest.mark.parametrize("total", [1, 7, 8, 9, 31, 32, 100, 257])
+@pytest.mark.parametrize("total", [1, 7, 8, 9, 31, 32, 100, 257, 512, 513, 514, 1024, 1025, 4099])
 def test_list_positions_are_a_permutation(L, total):
     assert sorted(L.position32(b, total) for b in range(total)) == list(range(total))
     assert [L.position64(b, total) for b in range(total)] == [L.position32(b, total) for b in range(total)]
 
 
 def test_list_positions_above_2_to_the_31(L):
-    total = 2 ** 33 + 5
-    got = [L.position64(b, total) for b in (0, 7, 8, total - 1)]
-    assert got == [0, 7 * (total // 8) + 5, 1, 4 * (total // 8) + 4 + total // 8]
+    total = 2 ** 33 + 5                    # runs of 2^30 + 1 for XCD 0 to 4, of 2^30 for the others
+    start = [x * 2 ** 30 + min(x, 5) for x in range(9)]
+    for b in (0, 1, 7, 8, 12, total - 8, total - 1):
+        x = b % 8
+        run = start[x + 1] - start[x]
+        assert L.position64(b, total) == start[x] + (b // 8 + x * run // 8) % run
+
+
+def test_many_rounds_do_not_march_in_step(L):
+    """8192 x 8192 in tiles of 256: at any time the XCDs are in different columns of tiles."""
+    total = 32 * 32
+    for b in range(0, total, 8):
+        assert len({L.tile_in_list(L.position32(b + x, total), 32, 32) % 32 for x in range(8)}) == 8
 
 
 @pytest.mark.parametrize("tiles_m,tiles_n", [(1, 1), (3, 7), (4, 5), (5, 64), (7, 9), (8, 8), (9, 40), (11, 3), (16, 16), (1, 300), (300, 1)])
