@@ -17,14 +17,18 @@ constexpr int gemm_pieces(int x, int t) { return x / t + (x % t != 0); }
 
 // Tiles of c for a problem whose rows are 16-byte aligned: 1: 256 x 256, 2: 128 x 128, 3: 64 x 64, 5: 32 x 32 with K
 // split over the wavefronts of a workgroup.  The largest tile that still gives three quarters of the 256 compute units
-// a workgroup; a problem that fits the chip in one round of 32 x 32 tiles and has a K worth splitting takes those.
+// a workgroup, and that is not more than half empty: a tile costs the same however little of it lies inside c (us with 256,
+// 128, 64: 1024 x 8 x 64, K = 40, 30 8.8 5.1; 4096 x 16 x 16, K = 64, 95 28 12; 262144 x 64, K = 64, 30 20 15; 262144 x 128, K = 64, 37
+// 27 35; K = 2048 the same way).  A problem that fits the chip in one round of 32 x 32 tiles and has a K worth splitting
+// takes those.
 #ifndef GEMM_SK_TILES
 #define GEMM_SK_TILES 256
 #endif
 inline int gemm_tile_of(int batch, int M, int N, int K) {
     auto tiles = [&](int t) { return (long long)batch * gemm_pieces(M, t) * gemm_pieces(N, t); };
     if (tiles(32) <= GEMM_SK_TILES && K >= 256) return 5;
-    return tiles(256) >= 192 ? 1 : tiles(128) >= 192 ? 2 : 3;
+    const int side = M < N ? M : N;
+    return side > 128 && tiles(256) >= 192 ? 1 : side > 64 && tiles(128) >= 192 ? 2 : 3;
 }
 
 // Do the rows of a and b start at 16-byte aligned addresses (and stay within 32-bit offsets inside a tile)?  Then

@@ -226,3 +226,26 @@ def test_the_longest_row_and_column(P, along):
     exp = torch.where(x >= 0, x, x * 0.5)
     torch.cuda.synchronize()
     assert torch.equal(c.reshape(n), exp)
+
+
+# many matrices of which no side fills the larger tiles, at the edges of 64 and 128
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("shape,path", [((200, 8, 64, 64), 3), ((200, 64, 200, 32), 3), ((200, 65, 136, 96), 2), ((200, 130, 128, 32), 2),
+                                        ((200, 129, 136, 64), 1)])
+def test_narrow_matrices(P, shape, path, dtype):
+    assert P.gemm_path(*shape, dtype) == path
+    run(P, *shape, dtype)
+
+
+def test_more_tiles_than_one_grid_dimension_in_the_tile_kernels(P):
+    """65535 matrices of one row and 65 tiles of 64 columns: 2^22 + 65471 tiles.  Every c is one element of b, exact."""
+    batch, N, K = 65535, 64 * 65, 32
+    assert P.gemm_path(batch, 1, N, K, I.F16) == 3
+    row = ((torch.arange(batch, device="cuda", dtype=torch.int32)[:, None] * 13 + torch.arange(N, device="cuda", dtype=torch.int32)[None, :]) % 1021 - 510).to(torch.float16)
+    b = torch.zeros((batch, K, N), dtype=torch.float16, device="cuda")
+    b[:, 5, :] = row
+    a = torch.zeros((batch, 1, K), dtype=torch.float16, device="cuda")
+    a[:, 0, 5] = 1.0
+    c = P.gemm_leakyrelu_fwd(a, b, 0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(c[:, 0, :], torch.where(row >= 0, row, row * 0.5))

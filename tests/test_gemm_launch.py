@@ -85,3 +85,10 @@ def test_every_tile_once_in_compact_blocks(L, tiles_m, tiles_n):
         rows = {i // tiles_n for i in order[s:s + 32]}
         cols = {i % tiles_n for i in order[s:s + 32]}
         assert tiles_m < 4 or tiles_n == 1 or len(rows) + len(cols) <= 20, (s, len(rows), len(cols))
+
+
+@pytest.mark.parametrize("shape,tile", [((1024, 8, 64, 64), 3), ((4096, 64, 1024, 64), 3), ((4096, 65, 1024, 64), 2), ((4096, 128, 1024, 64), 2),
+                                        ((4096, 129, 1024, 64), 1), ((4096, 129, 128, 64), 2), ((1, 1 << 20, 8, 32), 3), ((1, 1 << 20, 72, 32), 2),
+                                        ((1, 1 << 20, 136, 32), 1), ((1, 3584, 3584, 32), 1)])
+def test_tiles_are_not_more_than_half_empty(L, shape, tile):
+    assert L.tile_of(*shape) == tile
