@@ -9,9 +9,9 @@
 //     row-major b tile in LDS with transposing reads (ds_read_b64_tr_b16), the second 16 contiguous bytes
 //     of a row of a; a lane then holds four consecutive n of one row m of c, and the tile of c goes out
 //     through LDS so that the stores write whole rows of it;
-//   * K runs in steps of 32 through four LDS stages; tiles come straight from global memory into LDS
-//     (global_load_lds_dwordx4, 16 bytes per lane, 1 KiB of consecutive LDS per instruction), three
-//     stages ahead, with the bank-conflict swizzle applied to the global address of each lane;
+//   * K runs in steps of 32 through four LDS stages (64 x 64 tiles: four or six); tiles come straight from
+//     global memory into LDS (global_load_lds_dwordx4, 16 bytes per lane, 1 KiB of consecutive LDS per
+//     instruction), all stages but one ahead, with the bank-conflict swizzle applied to the global address of each lane;
 //   * rows past M repeat the last row and column chunks past N the last chunk (results masked at the
 //     store), so the loop has no edge cases.
 // Small problems (at most 256 tiles of 32 x 32, K >= 256): 32 x 32 tiles with K split over the four wavefronts of
@@ -26,15 +26,10 @@
 #include "gemm_launch.h"
 #include "gfx950_common.h"
 
-// LDS stages of 32 in K; all but one of them in flight ahead of the one in use.  64 x 64 tiles: a block is two matrix
-// instructions per wavefront, so the loads' latency shows: 4 x 512 x 512 x 2048 takes 14.5 us with four stages, 11.2 with
-// six; more than six leave fewer workgroups on a compute unit (2 x 777 x 1000 x 1024: 11.5 us with six, 14.1 with
-// twelve).  128 x 128 tiles: 2048 cubed 21.7 us with four and six, 22.4 with eight.
+// LDS stages of 32 in K; all but one of them in flight ahead of the one in use.  128 x 128 tiles: 2048 cubed 21.7 us with four
+// and six, 22.4 with eight.  64 x 64 tiles take four or six (gemm_deep).
 #ifndef GEMM_NST128
 #define GEMM_NST128 4
-#endif
-#ifndef GEMM_NST64
-#define GEMM_NST64 6
 #endif
 #ifndef GEMM_NST
 #define GEMM_NST 4   // the same for 256 x 256 tiles (all that LDS holds)
@@ -749,7 +744,8 @@ hipError_t launch_tile_size(const GemmLaunch& g) {
     switch (gemm_tile_of(g.batch, g.M, g.N, g.K)) {
         case 1: return launch_wide<DT, KTAIL>(g);                              // 256 x 256, four wavefronts of 128 x 128
         case 2: return launch_tiles<DT, 2, 2, 2, 2, GEMM_NST128, KTAIL>(g);   // 128 x 128, four wavefronts of 64 x 64
-        case 3: return launch_tiles<DT, 2, 2, 1, 1, GEMM_NST64, KTAIL>(g);    // 64 x 64, four wavefronts of 32 x 32
+        case 3:                                                               // 64 x 64, four wavefronts of 32 x 32
+            return gemm_deep(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 2, 2, 1, 1, 6, KTAIL>(g) : launch_tiles<DT, 2, 2, 1, 1, 4, KTAIL>(g);
         default: return launch_splitk<DT, KTAIL ? 1 : 0>(g);                  // 32 x 32, K split over the four wavefronts
     }
 }

@@ -31,6 +31,17 @@ inline int gemm_tile_of(int batch, int M, int N, int K) {
     return side > 128 && tiles(256) >= 192 ? 1 : side > 64 && tiles(128) >= 192 ? 2 : 3;
 }
 
+// 64 x 64 tiles: six LDS stages instead of four?  A block is two matrix instructions per wavefront, so the loads' latency
+// shows where K is long (us with four and six: 1000 x 1000 x 2048 15.7 12.5, 4 x 512 x 512 x 2048 14.5 11.2, 300 x 1400 x 640 5.8
+// 5.4); with a short K the loads that run ahead are waste and the larger LDS leaves fewer workgroups on a compute unit (1024 x 64
+// x 64, K = 64, 6.7 7.8; 32768 x 64 x 384 7.6 8.1; 1000 x 1000 x 128 3.67 3.75).  Between, operands that an XCD's L2 does not
+// hold, with at most one workgroup per compute unit, want the depth too (64 x 9000 x 320 4.8 4.4).
+inline bool gemm_deep(int batch, int M, int N, int K) {
+    if (K >= 640) return true;
+    const long long tiles = (long long)batch * gemm_pieces(M, 64) * gemm_pieces(N, 64), bytes = 2LL * batch * ((long long)M * K + (long long)K * N);
+    return K >= 288 && tiles <= 256 && bytes > (4 << 20);
+}
+
 // Do the rows of a and b start at 16-byte aligned addresses (and stay within 32-bit offsets inside a tile)?  Then
 // blocks of K go straight from global memory into LDS.
 inline bool gemm_rows_aligned(int N, int K) { return K > 0 && K % 8 == 0 && N % 8 == 0 && K <= (1 << 22) && N <= (1 << 22); }

@@ -249,3 +249,10 @@ def test_more_tiles_than_one_grid_dimension_in_the_tile_kernels(P):
     c = P.gemm_leakyrelu_fwd(a, b, 0.5)
     torch.cuda.synchronize()
     assert torch.equal(c[:, 0, :], torch.where(row >= 0, row, row * 0.5))
+
+
+# 64 x 64 tiles on either side of the line between four and six LDS stages, with a number of k blocks below, at and above them
+@pytest.mark.parametrize("shape", [(1, 64, 8984, 256), (1, 64, 8984, 288), (1, 576, 520, 608), (1, 576, 520, 640), (1, 576, 520, 96), (1, 576, 520, 160),
+                                   (1, 64, 8984, 296), (1, 576, 520, 648)])
+def test_stages_of_small_tiles(P, shape):
+    run(P, *shape, I.BF16)

@@ -92,3 +92,9 @@ def test_every_tile_once_in_compact_blocks(L, tiles_m, tiles_n):
                                         ((1, 1 << 20, 136, 32), 1), ((1, 3584, 3584, 32), 1)])
 def test_tiles_are_not_more_than_half_empty(L, shape, tile):
     assert L.tile_of(*shape) == tile
+
+
+def test_deep_pipelines_are_for_long_sums(L):
+    for shape, want in (((1024, 64, 64, 64), 0), ((1, 1000, 1000, 128), 0), ((1, 32768, 64, 384), 0), ((1, 700, 480, 448), 0), ((1, 300, 1400, 639), 0),
+                        ((1, 64, 9000, 287), 0), ((1, 64, 9000, 288), 1), ((1, 1000, 1000, 640), 1), ((4, 512, 512, 2048), 1)):
+        assert L.deep(*shape) == want, shape
