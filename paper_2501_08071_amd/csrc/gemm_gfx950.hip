@@ -56,7 +56,7 @@ __device__ __forceinline__ constexpr int swz_b(int row) {
 __device__ __forceinline__ GemmTile tile_of_workgroup(int tiles_m, int tiles_n, long long total) {
     const int per = tiles_m * tiles_n;
     if (gridDim.y == 1) {
-        const int c = gemm_list_position((int)blockIdx.x, (int)gridDim.x), bi = c / per;
+        const int c = gemm_list_position((int)blockIdx.x, (int)gridDim.x), bi = (int)gridDim.x == per ? 0 : c / per;   // (a division is 0.05 us)
         return gemm_tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
     }
     long long b = (long long)blockIdx.y * gridDim.x + blockIdx.x;

@@ -95,7 +95,7 @@ struct GemmTile {
 };
 constexpr GemmTile gemm_tile_in_list(int bi, int t, int tiles_m, int tiles_n) {
     const int last = tiles_m > GEMM_GROUP_M ? tiles_m / GEMM_GROUP_M - 1 : 0;   // number of the last group
-    int g = t / (GEMM_GROUP_M * tiles_n);
+    int g = last == 0 ? 0 : t / (GEMM_GROUP_M * tiles_n);
     g = g < last ? g : last;
     const int u = t - g * GEMM_GROUP_M * tiles_n, rows = g < last ? GEMM_GROUP_M : tiles_m - last * GEMM_GROUP_M;
     const int tn = u / rows;
