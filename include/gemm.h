@@ -37,8 +37,9 @@ typedef enum {
  *   b        DEVICE pointer, [batch, K, N] contiguous (N fastest), elements of `dtype`.  Read only.
  *   c        DEVICE pointer, [batch, M, N] contiguous, elements of `dtype`.  Written; must not alias a or b.
  *   batch, M, N, K   any sizes >= 0.  batch, M or N == 0: nothing to compute, nothing is launched.
- *            K == 0: every sum is empty and c is all zeros.  Every shape runs on the matrix cores;
- *            K % 8 == 0 and N % 8 == 0 (rows at 16-byte aligned addresses) is the fast case.
+ *            K == 0: every sum is empty and c is all zeros.  K % 8 == 0 and N % 8 == 0 (rows at
+ *            16-byte aligned addresses) is the fast case; sizes that fit no tile and have few products
+ *            run without the matrix cores, one thread per element of c.
  *   slope    factor of the negative side; any finite value (0.01 in the kernel the paper evaluates).
  *   dtype    gemm_dtype_t of a, b and c.
  *   stream   hipStream_t to enqueue on (NULL = the default stream).
@@ -54,7 +55,7 @@ int gemm_leakyrelu_fwd(const void* a, const void* b, void* c, int batch, int M, 
  * largest that still gives most of the chip a workgroup and is at least half filled by c); 5 = matrix cores with tiles of 32 x 32 and K split over
  * the wavefronts of a workgroup (small problems with K >= 256, the paper's 512 x 512 x 2048 among them); 4 = sizes
  * that fit no tile: K % 32 != 0 or N % 8 != 0 (one of those kernels with the last block of K cut, or the 32 x 32 one
- * with unaligned loads); 0 = the shape or dtype is not accepted. */
+ * with unaligned loads, or one thread per element of c); 0 = the shape or dtype is not accepted. */
 int gemm_path(int batch, int M, int N, int K, int dtype);
 
 /* Static, NUL-terminated description of a status code; never NULL. */

@@ -17,7 +17,8 @@
 // Small problems (at most 256 tiles of 32 x 32, K >= 256): 32 x 32 tiles with K split over the four wavefronts of
 // the workgroup, see gemm_lrelu_splitk_kernel.
 // K % 32 != 0: the same kernels with the last block cut (K % 8 == 0), or, where rows of a or b do not start at 16-byte
-// aligned addresses, the 32 x 32 kernel with its loads through registers.
+// aligned addresses, the 32 x 32 kernel with its loads through registers; either way one thread per element where there are
+// too few products to pay for tiles, see gemm_lrelu_element_kernel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -705,6 +706,41 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
     }
 }
 
+// Any shape, one thread per element of c: the sizes that fit no tile and have too few products to pay for one
+// (gemm_per_element).  Bound by the launch and by the loads of a and b, one element each; fp32 fused multiply-adds in the
+// order of k.
+template <int DT>
+__global__ __launch_bounds__(256) void gemm_lrelu_element_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+                                                                uint16_t* __restrict__ C, long long total, int M, int N, int K,
+                                                                float slope) {
+    using E = Elem<DT>;
+    for (long long idx = (long long)blockIdx.x * 256 + threadIdx.x; idx < total; idx += (long long)gridDim.x * 256) {
+        const int n = (int)(idx % N);
+        const long long bm = idx / N;          // batch * M + m
+        const long long bi = bm / M;
+        const uint16_t* a = A + (size_t)bm * K;
+        const uint16_t* b = B + (size_t)bi * K * N + n;
+        float t = 0.f;
+        for (int k = 0; k < K; ++k) t = __builtin_fmaf(E::widen(a[k]), E::widen(b[(size_t)k * N]), t);
+        const uint32_t p = E::pack2(leaky(t, slope), 0.f);
+        C[idx] = (uint16_t)(p & 0xFFFFu);
+    }
+}
+
+template <int DT>
+hipError_t launch_element(const GemmLaunch& g) {
+    const uint16_t* a = (const uint16_t*)g.a;
+    const uint16_t* b = (const uint16_t*)g.b;
+    uint16_t* c = (uint16_t*)g.c;
+    long long total = (long long)g.batch * g.M * g.N;
+    int M = g.M, N = g.N, K = g.K;
+    float slope = g.slope;
+    const long long groups = (total + 255) / 256;
+    const unsigned grid = (unsigned)(groups < 65536 ? groups : 65536);
+    void* args[] = {&a, &b, &c, &total, &M, &N, &K, &slope};
+    return hipLaunchKernel(reinterpret_cast<const void*>(&gemm_lrelu_element_kernel<DT>), dim3(grid), dim3(256), args, 0, (hipStream_t)g.stream);
+}
+
 // one workgroup of `threads` per tile of bm x bn; `told` as announce_lds has it
 hipError_t launch_grid(const GemmLaunch& g, const void* fn, int bm, int bn, int threads, unsigned lds_bytes, std::atomic<uint64_t>& told) {
     GemmGrid grid = gemm_grid_of(g.batch, g.M, g.N, bm, bn);
@@ -751,8 +787,10 @@ hipError_t launch_tile_size(const GemmLaunch& g) {
 }
 template <int DT>
 hipError_t dispatch(const GemmLaunch& g) {
-    if (!gemm_rows_aligned(g.N, g.K)) return launch_splitk<DT, 2>(g);
-    return g.K % 32 == 0 ? launch_tile_size<DT, false>(g) : launch_tile_size<DT, true>(g);
+    const bool aligned = gemm_rows_aligned(g.N, g.K);
+    if (aligned && g.K % 32 == 0) return launch_tile_size<DT, false>(g);
+    if (gemm_per_element(g.batch, g.M, g.N, g.K)) return launch_element<DT>(g);
+    return aligned ? launch_tile_size<DT, true>(g) : launch_splitk<DT, 2>(g);
 }
 
 }  // namespace

@@ -46,6 +46,34 @@ inline bool gemm_deep(int batch, int M, int N, int K) {
 // blocks of K go straight from global memory into LDS.
 inline bool gemm_rows_aligned(int N, int K) { return K > 0 && K % 8 == 0 && N % 8 == 0 && K <= (1 << 22) && N <= (1 << 22); }
 
+// A size that fits no tile (K % 32 != 0, or rows that are not aligned): one thread per element of c instead?  The tile
+// kernels compute whole tiles and whole blocks of 32 in K and begin with a chain of LDS stages; with few products per element that
+// is mostly waste.  Both times are estimated, in us, from constants fitted to 495 measured sizes of this kind (1 to 70000 in
+// M and N, 1 to 104 in K, 1 to 20000 matrices); the choice is the faster kernel, or within 15 %, for 97 % of them.  Measured, us per
+// element / in tiles: 4000 x 1 x 9, K = 3, 2.4 28; 4000 x 1 x 35, K = 17, 5.1 48; 65537 in N, K = 7, 2.8 15; 33 x 33, K = 1, 2.3 4.7; 1500 x
+// 1500, K = 8, 9.8 12; 1003 x 1003, K = 129, 41 8.2; 65536 x 64, K = 40, 48 9.
+//   one thread per element: a launch and a chain of K loads; or all the elements, with K terms each, and, past the first
+//   line or so of a row of a, one line per thread and term where a row of c is shorter than a wavefront's 64 elements;
+//   tiles: a launch and a workgroup's chain, or all the workgroups.
+inline bool gemm_per_element(int batch, int M, int N, int K) {
+    if (K > 100) return false;
+    const double k = K, elements = 1e-6 * batch * M * N;
+    const double chain = 2.25 + (N < 32 ? 0.06 : 0.08) * k, work = 1.6 + elements * (1.3 + 0.4 * k + (K > 12 ? 3.0 / N * (k - 12) : 0.0));
+    const double each = chain > work ? chain : work;
+    double tiled;
+    if (gemm_rows_aligned(N, K)) {
+        static constexpr double FLOOR[] = {0, 7.0, 4.5, 3.3}, PER_TILE[] = {0, 25e-3, 6.6e-3, 2.7e-3};
+        static constexpr int SIDE[] = {0, 256, 128, 64};
+        const int t = gemm_tile_of(batch, M, N, K);   // not 5: K < 256
+        tiled = 1.5 + PER_TILE[t] * batch * gemm_pieces(M, SIDE[t]) * gemm_pieces(N, SIDE[t]);
+        tiled = tiled > FLOOR[t] ? tiled : FLOOR[t];
+    } else {
+        const double tiles = 1e-3 * batch * gemm_pieces(M, 32) * gemm_pieces(N, 32);
+        tiled = 4.3 + 3.6 * tiles > 5.2 * tiles ? 4.3 + 3.6 * tiles : 5.2 * tiles;
+    }
+    return each < (K > 24 ? 0.9 : 1.0) * tiled;   // the estimate for one thread per element is the less certain one the longer K is
+}
+
 // What gemm_path reports: the tile, or 4 where K is cut in its last block or rows are not aligned.
 inline int gemm_path_of(int batch, int M, int N, int K) {
     return gemm_rows_aligned(N, K) && K % 32 == 0 ? gemm_tile_of(batch, M, N, K) : 4;

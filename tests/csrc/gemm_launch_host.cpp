@@ -16,4 +16,5 @@ int tile_in_list(int t, int tiles_m, int tiles_n) {
     return g.tm * tiles_n + g.tn;
 }
 int deep(int batch, int M, int N, int K) { return gemm_deep(batch, M, N, K); }
+int per_element(int batch, int M, int N, int K) { return gemm_per_element(batch, M, N, K); }
 }

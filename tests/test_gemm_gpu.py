@@ -256,3 +256,13 @@ def test_more_tiles_than_one_grid_dimension_in_the_tile_kernels(P):
                                    (1, 64, 8984, 296), (1, 576, 520, 648)])
 def test_stages_of_small_tiles(P, shape):
     run(P, *shape, I.BF16)
+
+
+# sizes that fit no tile, one thread per element and in tiles on either side of the line between them; more elements than a
+# grid of 65536 workgroups has threads
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("shape", [(40, 1, 9, 3), (1, 33, 33, 28), (1, 33, 33, 38), (1, 5, 7, 33), (1, 5, 7, 45), (300, 8, 64, 8), (300, 8, 64, 24), (3, 300, 305, 8),
+                                   (3, 300, 305, 20), (3, 2400, 2401, 3)])
+def test_per_element_and_tiles(P, shape, dtype):
+    assert P.gemm_path(*shape, dtype) == 4
+    run(P, *shape, dtype, slope=-0.5)

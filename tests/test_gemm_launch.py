@@ -98,3 +98,13 @@ def test_deep_pipelines_are_for_long_sums(L):
     for shape, want in (((1024, 64, 64, 64), 0), ((1, 1000, 1000, 128), 0), ((1, 32768, 64, 384), 0), ((1, 700, 480, 448), 0), ((1, 300, 1400, 639), 0),
                         ((1, 64, 9000, 287), 0), ((1, 64, 9000, 288), 1), ((1, 1000, 1000, 640), 1), ((4, 512, 512, 2048), 1)):
         assert L.deep(*shape) == want, shape
+
+
+def test_few_products_take_one_thread_per_element(L):
+    """Sizes that fit no tile, on either side by a factor in the time measured."""
+    for shape in ((4000, 1, 9, 3), (4000, 1, 35, 17), (1, 1, 65537, 7), (1, 33, 33, 1), (1, 1500, 1500, 8), (16384, 8, 64, 8), (1, 1 << 20, 8, 8),
+                  (1, 5, 7, 0), (1, TOP, 1, 1), (1, 1, TOP, 1)):
+        assert L.per_element(*shape) == 1, shape
+    for shape in ((1, 1003, 1003, 129), (1, 65536, 64, 40), (2, 777, 1000, 1000), (1, 777, 1001, 1003), (1, 1000, 8, 1000), (16384, 33, 64, 40),
+                  (1, 3000, 1500, 3008), (1, 1, 1, TOP)):
+        assert L.per_element(*shape) == 0, shape
