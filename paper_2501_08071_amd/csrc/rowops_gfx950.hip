@@ -38,8 +38,10 @@ __device__ __forceinline__ uint16_t narrow(float f) {
 }
 // 16 bytes of a row
 __device__ __forceinline__ u32x4 load16(const uint16_t* p) { return *(const u32x4_any*)p; }
-// The result is not read again here: non-temporal, it does not displace the lines of the rows still to be read.
-__device__ __forceinline__ void store16(uint16_t* p, u32x4 v) { __builtin_nontemporal_store(v, (u32x4_any*)p); }
+// Ordinary stores.  Non-temporal ones make this kernel faster where x comes from beyond the L2 and y fits it (16 MiB each: 6.6 us
+// instead of 8.4), but whoever reads y next finds it in no cache: a copy of y right after takes 0.3 us (4 MiB) to 11 us (64
+// MiB: 54 us for both instead of 44) longer, and on new buffers of 256 MiB this kernel itself 105 us instead of 94.
+__device__ __forceinline__ void store16(uint16_t* p, u32x4 v) { *(u32x4_any*)p = v; }
 template <int DT>
 __device__ __forceinline__ void widen8(const u32x4& p, float (&f)[8]) {
 #pragma unroll
@@ -103,9 +105,8 @@ __device__ __forceinline__ void reduce_rows(float (&v)[U], float (*red)[TPR > 64
 // accesses are unaligned, which costs a 128-byte line more per KiB), and the last chunk of a row moves back
 // to the row's last eight elements: its first `dup` ones are also the previous chunk's, are left out of
 // the sums, and are stored twice with the same value.
-// Measured (binary16, inputs changing; the copy of a large tensor runs at 5200 GB/s): softmax 4096 x 4095 12.1 us =
-// 5500 GB/s (general path: 28), 2048 x 32768 50 us (general path: 166), rmsnorm 39999 x 999 26 us (93),
-// 2097152 x 64 96 us = 5580 GB/s (100.6 with ordinary stores), 40000 x 1000 26 us (32 with ordinary stores).
+// Measured (us a launch, three sets of buffers in turn; general path, or aligned rows of the kernel before, in brackets): softmax 4097 x
+// 4095 13.6 (32), 2048 x 32768 58 (166), rmsnorm 33588 x 999 27.6 (93), 1048576 x 64 49.1 = 5470 GB/s (50.3), 16777 x 1000 12.0 (13.9).
 template <int DT, int OP, int TPR, int CH, int U, bool TAIL>
 __global__ __launch_bounds__(TPR > 64 ? TPR : 256) void rowop_reg_kernel(const uint16_t* x, const uint16_t* __restrict__ w,
                                                                          uint16_t* y, long long n_rows, int n, float eps) {
@@ -306,7 +307,7 @@ hipError_t launch_gen(const RowopLaunch& a) {
 // Threads per row, chunks per thread and rows per step by row length and number of rows: many rows want bytes in flight
 // per thread and few barriers, few rows want as many wavefronts as there can be.  All times in microseconds.
 // Rows within a wavefront: four groups per step where that still makes 1024 workgroups, else one (softmax 8192 x 256:
-// 2.8 with one, 3.5 with four; rmsnorm 131072 x 64: 6.5 and 6.0).
+// 2.8 with one, 3.5 with four).
 template <int DT, int OP, int TPR, int CH, bool TAIL>
 hipError_t launch_short(const RowopLaunch& a) {
     return a.n_rows >= 1024LL * 4 * (256 / TPR) ? launch_reg<DT, OP, TPR, CH, 4, TAIL>(a) : launch_reg<DT, OP, TPR, CH, 1, TAIL>(a);
