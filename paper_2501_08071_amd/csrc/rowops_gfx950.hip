@@ -328,16 +328,21 @@ hipError_t dispatch_reg(const RowopLaunch& a) {
     // softmax 512 x 4096: 3.6 with two rows per step, 3.1 with one; rmsnorm 16384 x 4095: 51 and 56
     if (c8 <= 512) return rows >= 8192 ? launch_reg<DT, OP, 256, 2, 2, TAIL>(a) : launch_reg<DT, OP, 256, 2, 1, TAIL>(a);
     if (c8 <= 1024) {
-        // rmsnorm 500 x 8192: 3.3 with 512 threads, 3.9 with 1024, 4.5 with 256; 8000 x 8191: 55, 48 and 51; softmax
-        // 8000 x 8191: 57, 54 and 50
-        if (rows < 2048) return launch_reg<DT, OP, 512, 2, 1, TAIL>(a);
-        if constexpr (OP == 0) return launch_reg<DT, OP, 256, 4, 2, TAIL>(a);
-        else return launch_reg<DT, OP, 1024, 1, 1, TAIL>(a);
+        // rmsnorm 512 x 8192: 4.6 with 512 threads, 4.9 with 1024; 2796 x 6000: 11.5 and 13.1; 8192 x 8192: 48.4 and 48.2; unaligned 8193 x
+        // 8191: 58 and 52.  15978 x 4200 leaves half of 1024 threads without work: 56, 51 with 256 and two rows.  softmax 512 x
+        // 8192: 5.1 with 512, 5.7 with 256 and two rows; 3994 x 4200: 15.9 and 14.6; 8193 x 8191: 59 and 52
+        if (rows < (OP == 1 && !TAIL ? 8192 : 2048)) return launch_reg<DT, OP, 512, 2, 1, TAIL>(a);
+        if (OP == 0 || c8 <= 640) return launch_reg<DT, OP, 256, 4, 2, TAIL>(a);
+        if constexpr (OP == 1) return launch_reg<DT, OP, 1024, 1, 1, TAIL>(a);
     }
     if (c8 <= 2048) {
-        // rmsnorm 100 x 16384: 3.3 with 1024 threads, 5.9 with 256; 4000 x 16384: 47 and 52; softmax 4000 x 9001: 32 and 26
-        if (OP == 0 && rows >= 2048) return launch_reg<DT, OP, 256, 8, 1, TAIL>(a);
-        return launch_reg<DT, OP, 1024, 2, 1, TAIL>(a);
+        // softmax 1398 x 12000: 11.5 with 512 threads, 15.9 with 1024, 12.8 with 256; 1198 x 14000: 11.8, 13.7, 12.0; unaligned 1397 x
+        // 9001: 11.2, 15.0, 12.6.  rmsnorm 5592 x 12000: 52.9 with 512, 50.0 with 1024; unaligned 1397 x 9001: 12.0 and 15.0, 209 x 10003: 4.6
+        // and 4.2
+        if constexpr (OP == 0 || TAIL) {
+            if (OP == 0 || rows >= 400) return c8 <= 1536 ? launch_reg<DT, OP, 512, 3, 1, TAIL>(a) : launch_reg<DT, OP, 512, 4, 1, TAIL>(a);
+        }
+        if constexpr (OP == 1) return launch_reg<DT, OP, 1024, 2, 1, TAIL>(a);
     }
     if (c8 <= 4096) return launch_reg<DT, OP, 1024, 4, 1, TAIL>(a);
     return launch_reg<DT, OP, 1024, 8, 1, TAIL>(a);   // c8 <= 8192 = ROWOPS_MAX_REG_ROW / 8

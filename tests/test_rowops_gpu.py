@@ -195,6 +195,18 @@ def test_side_stream_and_repeatability(P):
     (4095, 1030), (8192 + 1, 2050), (8191, 2051), (2048 + 1, 4100), (2047, 4097), (2048 + 1, 8196), (2047, 8193), (3, 16391),
     (300, 32767), (3, 65535), (3, 65529), (2, 65536), (2, 65537)])
 def test_row_kernel_choices(P, op, n_rows, n):
+    check_choice(P, op, n_rows, n)
+
+
+# the lines between 256, 512 and 1024 threads for rows of 4097 to 16384 elements, aligned and not, with full and partly idle threads
+@pytest.mark.parametrize("op", ["softmax", "rmsnorm"])
+@pytest.mark.parametrize("n_rows,n", [(8191, 5120), (8192, 5120), (8192, 5128), (2047, 8192), (2049, 8192), (2048, 5121), (399, 8201), (400, 8201), (401, 12288),
+                                      (401, 12285), (401, 12296), (401, 12289), (2047, 16384), (37, 16383)])
+def test_choices_for_long_rows(P, op, n_rows, n):
+    check_choice(P, op, n_rows, n)
+
+
+def check_choice(P, op, n_rows, n):
     dt = I.BF16 if (n_rows + n) % 2 else I.F16
     g = torch.Generator().manual_seed(n_rows * 131 + n)
     x = (torch.randn(n_rows, n, generator=g) * 2).to(TDT[dt])
