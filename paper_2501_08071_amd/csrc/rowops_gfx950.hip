@@ -128,14 +128,21 @@ __global__ __launch_bounds__(TPR > 64 ? TPR : 256) void rowop_reg_kernel(const u
         return s;
     };
 
-    u32x4 wr[OP == 1 ? CH : 1];
-    if constexpr (OP == 1) {
+    // rmsnorm's weights: held for all the rows of this thread, or, where they would not fit the registers next to a row (1024
+    // threads have 128 each), read again for every row
+    constexpr bool HOLD = OP == 1 && CH < 8;
+    auto weights = [&](int c) {
+        const int chunk = c * TPR + t;
+        int off = offset(chunk);
+        if constexpr (!HOLD) asm volatile("" : "+v"(off));   // computed here, not kept as an address per chunk over the loop
+        u32x4 g = {0u, 0u, 0u, 0u};
+        if (chunk < c8) g = load16(w + off);
+        return g;
+    };
+    u32x4 wr[HOLD ? CH : 1];
+    if constexpr (HOLD) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int chunk = c * TPR + t;
-            wr[c] = u32x4{0u, 0u, 0u, 0u};
-            if (chunk < c8) wr[c] = load16(w + offset(chunk));
-        }
+        for (int c = 0; c < CH; ++c) wr[c] = weights(c);
     }
 
     int turn = 0;   // which of the two LDS slots the next workgroup-wide reduction uses
@@ -220,7 +227,8 @@ __global__ __launch_bounds__(TPR > 64 ? TPR : 256) void rowop_reg_kernel(const u
                     // widened again: held as they came, a row and its weights take half the registers
                     float f[8], g[8];
                     widen8<DT>(raw[u][c], f);
-                    widen8<DT>(wr[c], g);
+                    if constexpr (HOLD) widen8<DT>(wr[c], g);
+                    else widen8<DT>(weights(c), g);
 #pragma unroll
                     for (int i = 0; i < 8; ++i) f[i] = f[i] * r * g[i];
                     store_row(u, c, f);

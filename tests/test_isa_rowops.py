@@ -26,3 +26,10 @@ def test_results_stay_in_the_caches_for_whoever_reads_them_next(isa):
     stores = re.findall(r"^\s*(global_store\w*[^\n]*)", isa, flags=re.M)
     assert len([s for s in stores if s.startswith("global_store_dwordx4")]) >= 100
     assert not [s for s in stores if re.search(r"\bnt\b", s)]
+
+
+def test_rows_stay_in_registers(isa):
+    """No instance keeps any part of a row in scratch memory."""
+    sizes = re.findall(r"\.name:\s+(\S*rowop\S*)\n.*?\.private_segment_fixed_size:\s+(\d+)", isa, flags=re.S)
+    assert len(sizes) >= 100
+    assert not [s for s in sizes if s[1] != "0"]
