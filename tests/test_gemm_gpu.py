@@ -67,7 +67,7 @@ SPLITK_TILES = [(1, 128, 128, 256), (1, 33, 8, 2048), (1, 320, 264, 288), (3, 20
 BIG_TILES = [(1, 1792, 1792, 64), (1, 2048, 1536, 96), (2, 1300, 1288, 128), (1, 1793, 1800, 32)]
 # 256 x 256 tiles (path 1): at least 192 of them; whole and ragged tiles, one and several k blocks, batches
 HUGE_TILES = [(1, 3584, 3584, 64), (1, 3585, 3592, 32), (3, 2100, 2056, 96), (1, 4096, 3072, 160)]
-# the plain kernel (path 4): K not a multiple of 32, N not a multiple of 8, K = 0
+# sizes that fit no tile (path 4): K not a multiple of 32, N not a multiple of 8, K = 0
 PLAIN = [(1, 5, 7, 3), (2, 33, 9, 31), (1, 64, 64, 40), (1, 16, 12, 64), (1, 3, 8, 0), (1, 1, 1, 1)]
 
 
@@ -266,3 +266,42 @@ def test_stages_of_small_tiles(P, shape):
 def test_per_element_and_tiles(P, shape, dtype):
     assert P.gemm_path(*shape, dtype) == 4
     run(P, *shape, dtype, slope=-0.5)
+
+
+# What is loaded in the place of the k past a cut K: chunk 0 of the last block of the same row of a, row 0 of the last
+# block of b (16-byte aligned rows), or the next row's elements (unaligned).  An infinity there, in a or in b, times anything
+# but a zero of its own would be an infinity, times a zero a NaN: with both operands cut it shows in its row or column only.
+# One shape for every tile size, LDS depth and load: 64 x 64 (four and six stages), 128, 256, split K, unaligned.
+CUT_INF = [(1, 300, 1400, 296), (1, 576, 520, 648), (1, 1793, 1800, 40), (1, 3585, 3592, 56), (1, 97, 72, 2056), (1, 128, 128, 280),
+           (1, 200, 203, 333), (1, 65, 63, 100)]
+
+
+@pytest.mark.parametrize("where", ["a", "b"])
+@pytest.mark.parametrize("shape", CUT_INF)
+def test_both_operands_are_cut_past_k(P, shape, where):
+    dt = I.F16
+    batch, M, N, K = shape
+    a, b = I.gen_gemm(*shape, dt)
+    da, db = dev(a, dt), dev(b, dt)
+    da[da == 0] = 1.0
+    db[db == 0] = 1.0
+    last = 32 * ((K - 1) // 32)
+    if where == "a":
+        da[0, 17, last] = float("inf")
+        da[0, 18, 0] = float("inf")      # what follows row 17 where rows are not padded
+    else:
+        db[0, last, 5] = float("inf")
+        db[0, 0, 6] = float("inf")
+    c = P.gemm_leakyrelu_fwd(da, db, 0.5).float()[0]
+    torch.cuda.synchronize()
+    hit = c[17:19] if where == "a" else c[:, 5:7]
+    assert torch.isinf(hit).all()
+    hit.zero_()
+    assert torch.isfinite(c).all()
+
+
+@pytest.mark.parametrize("slope", [0.0, -0.5, 1.0, 2.0])
+@pytest.mark.parametrize("shape", [(1, 3585, 3592, 32), (1, 3585, 3592, 40)])
+def test_slopes_of_large_tiles(P, shape, slope):
+    """256 x 256 tiles inside the matrix and at its edges, with every form of the activation."""
+    run(P, *shape, I.F16, slope=slope)

@@ -74,6 +74,22 @@ def test_key_halves(S, D, causal, loud):
         check_full(q, k, v, BF16, causal, scale, f"S{S} D{D} causal{causal} loud{loud} scale{scale}")
 
 
+# The same in binary16, whose row sums at D = 64 are taken from the rounded weights: the loud half's keys doubled, the quiet
+# half's divided by 64 (all normal numbers: a factor is an exponent step).
+@pytest.mark.parametrize("loud", [0, 1])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S,D", [(257, 32), (319, 32), (385, 128), (449, 128), (129, 64), (192, 64), (321, 64)])
+def test_key_halves_binary16(S, D, causal, loud):
+    assert "halves" in P.attn_kernel_name(1, 2, S, D, F16, causal)
+    q, k, v = I.gen_tensors(1, 2, S, D, F16, workload_id=900 + S)
+    half = 64 if D == 64 else 32
+    quiet = (np.arange(S) // half) % 2 != loud
+    kf = k.view(np.float16) * np.where(quiet[None, None, :, None], np.float16(1 / 64), np.float16(2.0))
+    k = np.ascontiguousarray(kf).view(np.uint16)
+    for scale in (1 / math.sqrt(D), 3.0, 1e-4):
+        check_full(q, k, v, F16, causal, scale, f"binary16 S{S} D{D} causal{causal} loud{loud} scale{scale}")
+
+
 @pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("S,D", [(320, 32), (300, 32), (256, 64), (300, 64), (448, 128), (450, 128)])
 def test_key_halves_with_logits_near_the_lowest_number(S, D, causal):

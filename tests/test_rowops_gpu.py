@@ -47,8 +47,8 @@ def check(y_bits, ref, dtype, what):
     assert np.all(err <= tol), f"{what}: |{got[worst]} - {ref[worst]}| = {err[worst]:.3e} > {tol[worst]:.3e} at {worst}"
 
 
-# row lengths: every registers-path instance (8 .. 64 lanes per row, a workgroup per row with 1, 2, 4, 8
-# chunks per thread), lengths that leave lanes and chunks idle, and general-path lengths (odd, 1, > 16384)
+# row lengths: 8 .. 64 lanes per row, a workgroup per row with 1, 2, 4 chunks per thread, lengths that leave lanes and chunks idle,
+# lengths that are no multiple of 8, or longer than 16384 (what rowops_path calls 2), and, below 8, the general path
 LENGTHS = [8, 16, 24, 64, 72, 128, 200, 256, 264, 512, 520, 1000, 2048, 2056, 4096, 4104, 8192, 8200, 16384,
            1, 2, 7, 9, 63, 1001, 4095, 16392, 20001]
 
@@ -103,8 +103,8 @@ def test_many_rows_stride_over_the_grid(P):
     wb = I.gen_rows(1, 8, dt, tensor_id=1)[0]
     check(host_bits(P.rmsnorm_fwd(dev(xb, dt), dev(wb, dt), 1e-5)), R.rmsnorm_rows(xb, wb, 1e-5, dt), dt, "rmsnorm many rows")
     check(host_bits(P.softmax_rows_fwd(dev(xb, dt))), R.softmax_rows(xb, dt), dt, "softmax many rows")
-    xb = I.gen_rows(8192 + 5, 9, dt)                   # general path, one workgroup per row, > 8192 rows
-    check(host_bits(P.softmax_rows_fwd(dev(xb, dt))), R.softmax_rows(xb, dt), dt, "softmax many rows, general path")
+    xb = I.gen_rows(8192 + 5, 9, dt)                   # unaligned rows of one chunk and one element
+    check(host_bits(P.softmax_rows_fwd(dev(xb, dt))), R.softmax_rows(xb, dt), dt, "softmax many rows of 9")
 
 
 @pytest.mark.parametrize("dtype", [I.F16, I.BF16])
@@ -223,3 +223,54 @@ def check_choice(P, op, n_rows, n):
     assert err.max().item() <= 0, (op, n_rows, n, err.max().item())
     assert torch.equal(buf[:8].cpu(), torch.full((8,), 7.0, dtype=TDT[dt]))
     assert (buf[8 + n_rows * n:] == 7.0).all()
+
+
+# rows that several wavefronts share, with a last chunk that reads and stores elements of the one before it
+@pytest.mark.parametrize("n_rows,n", [(19, 2049), (19, 4095), (3000, 4100), (19, 8193), (5, 12289), (5, 32767), (3, 65535), (19, 8192), (5, 16384)])
+def test_long_rows_in_place(P, n_rows, n):
+    dt = I.BF16
+    xb = I.gen_rows(n_rows, n, dt, mul=2.0)
+    wb = I.gen_rows(1, n, dt, tensor_id=1)[0]
+    for x in (dev(xb, dt), dev(xb, dt)):
+        want = P.softmax_rows_fwd(x)
+        P.softmax_rows_fwd(x, y=x)
+        assert torch.equal(x.view(torch.int16), want.view(torch.int16))
+        x = dev(xb, dt)
+        want = P.rmsnorm_fwd(x, dev(wb, dt), 1e-6)
+        P.rmsnorm_fwd(x, dev(wb, dt), 1e-6, y=x)
+        assert torch.equal(x.view(torch.int16), want.view(torch.int16))
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("n", [5, 8, 9, 64, 100, 515, 1000, 2051, 4096, 8193, 16385, 40000])
+def test_softmax_of_masked_rows(P, n, dtype):
+    """Minus infinity is a mask: zeros there, the others as if it were not (a whole chunk, the first element, the last eight);
+    a row with a NaN is NaN, a row of nothing but minus infinity too, and neither touches its neighbours."""
+    g = torch.Generator().manual_seed(n)
+    x = (torch.randn(9, n, generator=g) * 2).to(TDT[dtype])
+    ninf = float("-inf")
+    x[0, : n // 2] = ninf
+    x[1, n - 1] = ninf
+    x[2, max(0, n - 8):] = ninf if n > 8 else x[2, max(0, n - 8):]
+    x[3, :-1] = ninf
+    x[4, 0] = ninf
+    x[5] = ninf
+    x[6, n // 3] = float("nan")
+    x[7, n - 1] = float("nan")
+    y = P.softmax_rows_fwd(x.cuda()).double().cpu()
+    torch.cuda.synchronize()
+    ref = torch.softmax(x.double(), 1)
+    assert torch.isnan(ref[5:8]).all() and torch.isnan(y[5:8]).all()
+    ok = [0, 1, 2, 3, 4, 8]
+    assert ((y[ok] - ref[ok]).abs() <= REL[dtype] * ref[ok].abs() + FLOOR[dtype]).all()
+    assert (y[0, : n // 2] == 0).all() and y[3, n - 1] == 1.0
+
+
+@pytest.mark.parametrize("n_rows,n", [(8192 + 5, 7), (8192 + 5, 1), (2, 65537), (1, 100001)])
+def test_general_path(P, n_rows, n):
+    """Rows shorter than 8 or longer than 65536 elements, one workgroup per row; more rows than a grid has workgroups."""
+    dt = I.F16
+    xb = I.gen_rows(n_rows, n, dt)
+    wb = I.gen_rows(1, n, dt, tensor_id=1)[0]
+    check(host_bits(P.softmax_rows_fwd(dev(xb, dt))), R.softmax_rows(xb, dt), dt, f"softmax {n_rows} x {n}")
+    check(host_bits(P.rmsnorm_fwd(dev(xb, dt), dev(wb, dt), 1e-5)), R.rmsnorm_rows(xb, wb, 1e-5, dt), dt, f"rmsnorm {n_rows} x {n}")
