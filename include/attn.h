@@ -51,7 +51,7 @@ typedef enum {
  *   causal   0: every key visible; non-zero: key j visible to query i iff j <= i.
  *            Masked keys enter the second product with weight 0, so q, k and v must be
  *            finite everywhere: a non-finite row j of v spoils, next to the rows of O
- *            that see key j, the earlier rows of the same block of 64 keys (0 * Inf).
+ *            that see key j, the earlier rows of the same block of keys (attn_tile_keys of them, 0 * Inf).
  *   scale    multiplies q.k before the softmax; any finite value.
  *   dtype    attn_dtype_t of q, k, v.
  *   stream   hipStream_t to enqueue on (NULL = the default stream).
@@ -61,7 +61,9 @@ typedef enum {
  * instance: that the runtime has been told the instance's LDS size (set once,
  * atomically; calls from several host threads are safe).  The call is asynchronous: outputs are valid
  * once `stream` has been synchronised.  o and lse must not alias q, k or v.
- * All pointers must be 16-byte aligned.
+ * All pointers must be 16-byte aligned.  Runs repeat bit for bit.  The last bits of a row may differ between
+ * problems: which kernel serves one, and in how many parts it adds up a row's keys, depends on B, H and S
+ * (attn_kernel_name).
  *
  * Errors: returns an attn_status_t and never throws or aborts.  Every argument
  * is checked before the first HIP call, so bad arguments are reported on a

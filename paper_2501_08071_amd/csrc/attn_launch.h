@@ -85,7 +85,9 @@ inline int attn_pick_nw(long long BH, int S) {
 // Workgroups of half the rows: are the keys split too?  What it costs is the final addition (and, in it, the wait for loads
 // nobody reads): worth it from a few blocks on.  Measured, us without -> with: D = 32, 8 heads: S = 64 3.5 -> 4.0, 200
 // 5.2 -> 5.2, 333 6.5 -> 6.0, 512 7.8 -> 6.5; D = 64: S = 128 (one block) 5.9 -> 5.8, 200 7.9 -> 7.0, 512 9.2 -> 8.3;
-// D = 128: S = 128 7.2 -> 8.3, 333 causal 10.9 -> 10.9, 512 12.7 -> 11.9, 2048 35.2 -> 27.9.
+// D = 128: S = 128 7.2 -> 8.3, 333 causal 10.9 -> 10.9, 512 12.7 -> 11.9, 2048 35.2 -> 27.9.  Over 488 problems it is done for (1
+// to 128 heads, S up to 16384, with and without the causal mask) the time is 0.63 to 1.01 of the unsplit kernel's, the error
+// of O against 64 bits (97 problems) 0.67 to 1.001 of it.
 inline bool attn_splits_keys(long long BH, int S, int D) {
     return attn_can_split(D) && attn_pick_nw(BH, S) != ATTN_NW && S > (D == 128 ? 384 : D == 64 ? 128 : 256);
 }

@@ -3,8 +3,8 @@
 //
 // Matrix-core kernel (K % 8 == 0, N % 8 == 0):
 //   * a workgroup of four wavefronts (2 x 2) owns a 64 TM x 64 TN tile of c, a wavefront 32 TM x 32 TN of
-//     it as TM x TN accumulator blocks of v_mfma_f32_32x32x16; TM = TN = 2 (128 x 128) when that gives
-//     the chip enough tiles, else 1 (64 x 64); problems with enough tiles of 256 x 256: gemm_lrelu_wide_kernel;
+//     it as TM x TN accumulator blocks of v_mfma_f32_32x32x16; TM = TN = 2 (128 x 128) or 1 (64 x 64); larger
+//     problems: 256 x 256 tiles, gemm_lrelu_wide_kernel; gemm_tile_of chooses;
 //   * computed transposed, c^T = b^T a^T: the first operand is a 32 x 16 piece of b^T, fetched from the
 //     row-major b tile in LDS with transposing reads (ds_read_b64_tr_b16), the second 16 contiguous bytes
 //     of a row of a; a lane then holds four consecutive n of one row m of c, and the tile of c goes out
@@ -284,15 +284,14 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 // Large problems: 256 x 256 tiles, four wavefronts (2 x 2), one per SIMD with the whole register file, 128 x 128 of c
 // per wavefront.
 // What bounds it: the clock, which the chip lowers with the switching activity of the matrix pipes and of what feeds
-// them (1.4 to 1.8 GHz here).  So the kernel is laid out for energy per operation:
-//   * v_mfma_f32_16x16x32: on N(0,1) operands and nothing else to do the chip sustains 2040 TFLOP/s with it against
-//     1790 with v_mfma_f32_32x32x16 (half as many accumulator bits written per multiplication);
-//   * 8 x 8 accumulators: an operand read from LDS feeds eight instructions, 64 KiB of LDS reads per 32 of K and
-//     workgroup instead of 96 KiB with eight wavefronts of 64 x 128;
+// them, and LDS.  So the kernel is laid out for energy per operation:
+//   * v_mfma_f32_16x16x32 with 8 x 8 accumulators: an operand read from LDS feeds eight instructions, 64 KiB of LDS reads
+//     per 32 of K and workgroup instead of 96 KiB with eight wavefronts of 64 x 128;
 //   * the accumulators are visited in a snake, so that only one of an instruction's two operands changes.
-// 4096 x 4096 x 4096, bfloat16, N(0,1): 99 us = 1385 TFLOP/s, 8192 cubed 785 us = 1400 TFLOP/s (113.6 and 844 us with
-// eight wavefronts of 64 x 128, two groups alternating between LDS reads and matrix instructions); a block of 32 of K
-// takes 1260 cycles, 1024 of them matrix instructions.
+// 4096 x 4096 x 4096, N(0,1): 96 to 107 us over the boxes seen = 1290 to 1430 TFLOP/s, 8192 cubed 785 to 801 us = 1370 to
+// 1400 TFLOP/s (113 to 121 and 844 us with eight wavefronts of 64 x 128, two groups alternating between LDS reads and matrix
+// instructions).  A wavefront lives 173.5 k cycles at 4096 cubed: 1260 per block of 32 of K, 1024 of them matrix instructions and
+// about 130 LDS bank conflicts, and 8.6 k for the way out.
 // Nothing but the order of issue keeps the matrix pipe fed: the operands of block kb + 1 are read under the 64 matrix
 // instructions of block kb, one LDS read per two of them, then the loads of block kb + NST - 1.
 template <int DT, bool KTAIL>

@@ -15,9 +15,10 @@ pytestmark = pytest.mark.gpu
 BUILT = [s for s in tune.all_states() if os.path.exists(tune.variant_path(s))]
 
 
-# Small problems take the instances with four wavefronts per workgroup; the wide one has more than 128 tiles and takes the
-# eight-wavefront instance (or, in its state, the kernel with 64 query rows per wavefront), which is what the tuner times
-# on the benchmark workloads; the D = 32 shape runs the interleaved loop (barrier period, operand read-ahead).
+# Small problems take workgroups of 128 rows, with the keys split between two halves of eight wavefronts where the sequence is
+# long enough (517, 640) and four wavefronts where it is not; the wide one has more than 128 tiles and takes the 256-row
+# instance (or, in its state, the kernel with 64 query rows per wavefront), which is what the tuner times on the benchmark
+# workloads; the D = 32 shape runs the interleaved loop (barrier period, operand read-ahead).
 SHAPES = [(1, 2, 300, 128, I.BF16, True), (1, 2, 517, 64, I.F16, False), (1, 1, 640, 128, I.F16, False),
           (3, 43, 300, 128, I.BF16, True), (3, 43, 257, 64, I.F16, True), (1, 2, 300, 32, I.F16, True)]
 
