@@ -38,35 +38,44 @@ CSRC = os.path.join(ROOT, "paper_2501_08071_amd", "csrc")
 # summary under profiles/ that holds the counter values; valid only for the kernel source they were taken
 # with (sha256 over the kernel's sources), otherwise reported as null.
 ATTN_FILES = ("attn_fwd_gfx950.hip", "attn_fwd_rows64_gfx950.hip", "attn_launch.h", "attn_device.h", "gfx950_common.h")
-ROW_FILES = ("rowops_gfx950.hip", "rowops_launch.h")
+ROW_FILES = ("rowops_gfx950.hip", "rowops_launch.h", "gfx950_common.h")
 GEMM_FILES = ("gemm_gfx950.hip", "gemm_launch.h", "gfx950_common.h")
 TRAFFIC = {
-    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 147418 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
-                                      "kernel_sha256": "90cf59d9fbf8f596177c62da2977753833bbabfe9f23af8e242831a8f3448e93",
-                                      "source": "profiles/attn_fwd_kernel_S4096_D128_bf16_causal.md"},
-    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 920443 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
-                                       "kernel_sha256": "90cf59d9fbf8f596177c62da2977753833bbabfe9f23af8e242831a8f3448e93",
-                                       "source": "profiles/attn_fwd_kernel_all_workloads.md"},
-    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98509.6 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
-                                    "kernel_sha256": "90cf59d9fbf8f596177c62da2977753833bbabfe9f23af8e242831a8f3448e93",
-                                    "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
-    "B4_H16_S1024_D64_f16": {"fetch_kib": 12472.7 * 2.0, "write_kib": 16640 * 1.0, "files": ATTN_FILES,
-                             "kernel_sha256": "90cf59d9fbf8f596177c62da2977753833bbabfe9f23af8e242831a8f3448e93",
-                             "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
+    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 147310 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+     "source": "profiles/attn_fwd_kernel_S4096_D128_bf16_causal.md"},
+    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 907667 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+     "source": "profiles/attn_fwd_kernel_all_workloads.md"},
+    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98513.5 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+     "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
+    "B4_H16_S1024_D64_f16": {"fetch_kib": 12459.7 * 2.0, "write_kib": 16640 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+     "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
+    "B1_H4_S4096_D32_f16_paper": {"fetch_kib": 2690.1 * 2.0, "write_kib": 2112 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+     "source": "profiles/attn_fwd_halves_kernel.md"},
     # the row kernels (workload name as rowop_run reports it)
-    "softmax_512x4096_f16 x16 rows": {"fetch_kib": 32802.5 * 2.0, "write_kib": 65536.0 * 1.0, "files": ROW_FILES,
-                                      "kernel_sha256": "efc90703c88cd78fc96c429b78ffe9d0151fd5461670fbd9a3e86f4f176ea240",
-                                      "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
-    "rmsnorm_1x32x4096x64_f16 x16 rows": {"fetch_kib": 131108.0 * 2.0, "write_kib": 262144.0 * 1.0, "files": ROW_FILES,
-                                          "kernel_sha256": "efc90703c88cd78fc96c429b78ffe9d0151fd5461670fbd9a3e86f4f176ea240",
-                                          "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
-    # the GEMM + LeakyReLU kernels (the paper's shape; the 256 x 256 tile's launches)
-    "mmLeakyReLu_1x512x512x2048_f16": {"fetch_kib": 10272.5 * 2.0, "write_kib": 512.0 * 1.0, "files": GEMM_FILES,
-                                       "kernel_sha256": "4621da25a85d63d48a6b552e285a1a26e4d75c798cc8b9d9c8efe85953557683",
-                                       "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 147536.0 * 2.0, "write_kib": 32768.0 * 1.0, "files": GEMM_FILES,
-                                         "kernel_sha256": "4621da25a85d63d48a6b552e285a1a26e4d75c798cc8b9d9c8efe85953557683",
-                                         "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
+    "softmax_512x4096_f16 x16 rows": {"fetch_kib": 32798.0 * 2.0, "write_kib": 65536.0 * 1.0, "files": ROW_FILES,
+     "kernel_sha256": "12992ce88316b0f94604d49962a30775d2c085beaabd0a6ce5e590ceaaaf33d6",
+     "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
+    "rmsnorm_1x32x4096x64_f16 x16 rows": {"fetch_kib": 131106.1 * 2.0, "write_kib": 262144.0 * 1.0, "files": ROW_FILES,
+     "kernel_sha256": "12992ce88316b0f94604d49962a30775d2c085beaabd0a6ce5e590ceaaaf33d6",
+     "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
+    # the GEMM + LeakyReLU kernels (the paper's shapes; the 256 x 256 tile's launches)
+    "mmLeakyReLu_1x512x512x2048_f16": {"fetch_kib": 6183.0 * 2.0, "write_kib": 512.0 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "c66dd7a8350bf7e7d7c3debedf3dedeac66a58127dd592bd93e24fd13054fc0b",
+     "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
+    "bmm_4x512x512x2048_f16": {"fetch_kib": 12333.0 * 2.0, "write_kib": 2048.0 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "c66dd7a8350bf7e7d7c3debedf3dedeac66a58127dd592bd93e24fd13054fc0b",
+     "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
+    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 98447.0 * 2.0, "write_kib": 32768.0 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "c66dd7a8350bf7e7d7c3debedf3dedeac66a58127dd592bd93e24fd13054fc0b",
+     "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
+    "mmLeakyReLu_1x8192x8192x8192_f16": {"fetch_kib": 786691.3 * 2.0, "write_kib": 131072.1 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "c66dd7a8350bf7e7d7c3debedf3dedeac66a58127dd592bd93e24fd13054fc0b",
+     "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
 }
 
 

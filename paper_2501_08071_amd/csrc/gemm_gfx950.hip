@@ -290,8 +290,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 //   * the accumulators are visited in a snake, so that only one of an instruction's two operands changes.
 // 4096 x 4096 x 4096, N(0,1): 96 to 107 us over the boxes seen = 1290 to 1430 TFLOP/s, 8192 cubed 785 to 801 us = 1370 to
 // 1400 TFLOP/s (113 to 121 and 844 us with eight wavefronts of 64 x 128, two groups alternating between LDS reads and matrix
-// instructions).  A wavefront lives 173.5 k cycles at 4096 cubed: 1260 per block of 32 of K, 1024 of them matrix instructions and
-// about 130 LDS bank conflicts, and 8.6 k for the way out.
+// instructions).  A wavefront lives 173.5 k cycles at 4096 cubed: 1260 per block of 32 of K, 1024 of them matrix instructions (130 with
+// an LDS bank conflict), and 8.6 k for the way out.
 // Nothing but the order of issue keeps the matrix pipe fed: the operands of block kb + 1 are read under the 64 matrix
 // instructions of block kb, one LDS read per two of them, then the loads of block kb + NST - 1.
 template <int DT, bool KTAIL>
