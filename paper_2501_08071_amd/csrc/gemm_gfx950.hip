@@ -54,10 +54,12 @@ __device__ __forceinline__ constexpr int swz_b(int row) {
 }
 
 // Workgroup -> tile: gemm_list_position, then gemm_tile_in_list
-__device__ __forceinline__ GemmTile tile_of_workgroup(int tiles_m, int tiles_n, long long total) {
+__device__ __forceinline__ GemmTile tile_of_workgroup(int tiles_m, int tiles_n, int K, long long total) {
     const int per = tiles_m * tiles_n;
     if (gridDim.y == 1) {
-        const int c = gemm_list_position((int)blockIdx.x, (int)gridDim.x), bi = (int)gridDim.x == per ? 0 : c / per;   // (a division is 0.05 us)
+        const int total1 = (int)gridDim.x, b = (int)blockIdx.x;
+        const int c = gemm_in_order(tiles_n, K, total1) ? b : gemm_list_position(b, total1);
+        const int bi = total1 == per ? 0 : c / per;   // (a division is 0.05 us)
         return gemm_tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
     }
     long long b = (long long)blockIdx.y * gridDim.x + blockIdx.x;
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     const int l32 = lane & 31, h = lane >> 5;
     const int wm = wave % WM, wn = wave / WM;
 
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, total);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, K, total);
     const int m0 = tm_i * BM, n0 = tn_i * BN;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -311,7 +313,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave & 1, wn = wave >> 1;
 
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, total);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, K, total);
     const int m0 = tm_i * 256, n0 = tn_i * 256;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -508,7 +510,7 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, total);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup(tiles_m, tiles_n, K, total);
     const int m0 = tm_i * 32, n0 = tn_i * 32;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -777,7 +779,8 @@ hipError_t launch_splitk(const GemmLaunch& g) {
 template <int DT, bool KTAIL>
 hipError_t launch_tile_size(const GemmLaunch& g) {
     switch (gemm_tile_of(g.batch, g.M, g.N, g.K)) {
-        case 1: return launch_wide<DT, KTAIL>(g);                              // 256 x 256, four wavefronts of 128 x 128
+        case 1:                                                                // 256 x 256, eight wavefronts of 64 x 128 or four of 128 x 128
+            return gemm_eight_waves(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 4, 2, 2, 4, 4, KTAIL>(g) : launch_wide<DT, KTAIL>(g);
         case 2: return launch_tiles<DT, 2, 2, 2, 2, GEMM_NST128, KTAIL>(g);   // 128 x 128, four wavefronts of 64 x 64
         case 3:                                                               // 64 x 64, four wavefronts of 32 x 32
             return gemm_deep(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 2, 2, 1, 1, 6, KTAIL>(g) : launch_tiles<DT, 2, 2, 1, 1, 4, KTAIL>(g);

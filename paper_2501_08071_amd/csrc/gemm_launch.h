@@ -42,6 +42,14 @@ inline bool gemm_deep(int batch, int M, int N, int K) {
     return K >= 288 && tiles <= 256 && bytes > (4 << 20);
 }
 
+// 256 x 256 tiles: eight wavefronts of 64 x 128 instead of four of 128 x 128?  Two wavefronts per SIMD start, read and write a
+// tile faster than one, which shows where there are two blocks of K or less and either fewer tiles than compute units or a single
+// column of them (us with eight and four, K = 64: 3584 x 3584 10.6 11.5, 3 x 2048 x 2048 10.5 11.1, 524288 x 256 79 87; K = 32: 9.9
+// 10.6, 9.8 10.3, 69 67; ragged 3500 x 3496, K = 64 11.1 10.9).  4096 x 4096, K = 64: 12.0 11.6; 3500 x 3496, K = 128: 12.5 11.9.
+inline bool gemm_eight_waves(int batch, int M, int N, int K) {
+    return K <= 64 && (N <= 256 || (long long)batch * gemm_pieces(M, 256) * gemm_pieces(N, 256) < 256);
+}
+
 // Do the rows of a and b start at 16-byte aligned addresses (and stay within 32-bit offsets inside a tile)?  Then
 // blocks of K go straight from global memory into LDS.
 inline bool gemm_rows_aligned(int N, int K) { return K > 0 && K % 8 == 0 && N % 8 == 0 && K <= (1 << 22) && N <= (1 << 22); }
@@ -109,6 +117,12 @@ constexpr I gemm_list_position(I b, I total) {
     }
     return x * q + (x < r ? x : r) + j;
 }
+
+// Or one after the other?  With a single column of tiles no two of them share rows of a, and what the XCDs run together is best
+// one stretch of memory, as long as that streaming is what a launch waits for and not the matrix instructions (us in runs /
+// in order: 200 x 256 x 256, K = 64 12.2 11.5, K = 2048 94.4 96.1; 50000 x 256, K = 128 12.8 12.3; 524288 x 256, K = 64 81.6
+// 79.1, K = 256 135 147).
+constexpr bool gemm_in_order(int tiles_n, int K, int total) { return tiles_n == 1 && K <= 512 && (total <= 512 || K <= 64); }
 
 // Position t in matrix bi's list of tiles -> tile.  The list goes through GEMM_GROUP_M tile rows at a time, column by column:
 // the workgroups that an XCD runs together then cover a compact block of c (4 x 8 tiles when it holds 32) and share both

@@ -15,6 +15,8 @@ int tile_in_list(int t, int tiles_m, int tiles_n) {
     const GemmTile g = gemm_tile_in_list(0, t, tiles_m, tiles_n);
     return g.tm * tiles_n + g.tn;
 }
+int in_order(int tiles_n, int K, int total) { return gemm_in_order(tiles_n, K, total); }
+int eight_waves(int batch, int M, int N, int K) { return gemm_eight_waves(batch, M, N, K); }
 int deep(int batch, int M, int N, int K) { return gemm_deep(batch, M, N, K); }
 int per_element(int batch, int M, int N, int K) { return gemm_per_element(batch, M, N, K); }
 }

@@ -271,8 +271,9 @@ def test_per_element_and_tiles(P, shape, dtype):
 # What is loaded in the place of the k past a cut K: chunk 0 of the last block of the same row of a, row 0 of the last
 # block of b (16-byte aligned rows), or the next row's elements (unaligned).  An infinity there, in a or in b, times anything
 # but a zero of its own would be an infinity, times a zero a NaN: with both operands cut it shows in its row or column only.
-# One shape for every tile size, LDS depth and load: 64 x 64 (four and six stages), 128, 256, split K, unaligned.
-CUT_INF = [(1, 300, 1400, 296), (1, 576, 520, 648), (1, 1793, 1800, 40), (1, 3585, 3592, 56), (1, 97, 72, 2056), (1, 128, 128, 280),
+# One shape for every tile size, LDS depth and load: 64 x 64 (four and six stages), 128, 256 (eight and four wavefronts), split
+# K, unaligned.
+CUT_INF = [(1, 300, 1400, 296), (1, 576, 520, 648), (1, 1793, 1800, 40), (1, 3585, 3592, 56), (1, 3585, 3592, 88), (1, 97, 72, 2056), (1, 128, 128, 280),
            (1, 200, 203, 333), (1, 65, 63, 100)]
 
 
@@ -301,7 +302,17 @@ def test_both_operands_are_cut_past_k(P, shape, where):
 
 
 @pytest.mark.parametrize("slope", [0.0, -0.5, 1.0, 2.0])
-@pytest.mark.parametrize("shape", [(1, 3585, 3592, 32), (1, 3585, 3592, 40)])
+@pytest.mark.parametrize("shape", [(1, 3585, 3592, 32), (1, 3585, 3592, 40), (1, 3585, 3592, 96), (1, 3585, 3592, 104)])
 def test_slopes_of_large_tiles(P, shape, slope):
     """256 x 256 tiles inside the matrix and at its edges, with every form of the activation."""
     run(P, *shape, I.F16, slope=slope)
+
+
+# 256 x 256 tiles with eight and with four wavefronts, in one column (ragged and whole, in order and in runs) and as several matrices
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("shape", [(1, 49150, 256, 64), (1, 49150, 248, 24), (1, 49150, 200, 72), (200, 250, 256, 64), (200, 256, 136, 96), (1, 132000, 136, 32),
+                                   (1, 132000, 136, 96)])
+def test_tall_products(P, shape, dtype):
+    if shape[3] % 32 == 0:
+        assert P.gemm_path(*shape, dtype) == 1
+    run(P, *shape, dtype)

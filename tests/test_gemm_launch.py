@@ -108,3 +108,13 @@ def test_few_products_take_one_thread_per_element(L):
     for shape in ((1, 1003, 1003, 129), (1, 65536, 64, 40), (2, 777, 1000, 1000), (1, 777, 1001, 1003), (1, 1000, 8, 1000), (16384, 33, 64, 40),
                   (1, 3000, 1500, 3008), (1, 1, 1, TOP)):
         assert L.per_element(*shape) == 0, shape
+
+
+def test_tall_and_short_products(L):
+    """A single column of tiles goes through memory in order unless the product is long; two wavefronts per SIMD for two blocks
+    of K where the tiles are few or in one column."""
+    for args, want in (((1, 64, 200), 1), ((1, 512, 512), 1), ((1, 513, 200), 0), ((1, 65, 513), 0), ((1, 64, 4096), 1), ((2, 64, 200), 0)):
+        assert L.in_order(*args) == want, args
+    for args, want in (((1, 3584, 3584, 64), 1), ((1, 3584, 3584, 65), 0), ((1, 4096, 4096, 64), 0), ((1, 4096, 3840, 32), 1), ((1, 1 << 20, 256, 64), 1),
+                       ((1, 1 << 20, 264, 64), 0), ((1, 1 << 20, 256, 72), 0), ((200, 256, 256, 8), 1)):
+        assert L.eight_waves(*args) == want, args
