@@ -12,14 +12,15 @@ struct GemmLaunch {
     void* stream;
 };
 
-// Pieces of t that cover x, for any x >= 0 (x + t - 1 would overflow where x is near 2^31).
-constexpr int gemm_pieces(int x, int t) { return x / t + (x % t != 0); }
+// Pieces of t that cover x, for any x >= 0 (as int, x + t - 1 would overflow where x is near 2^31).
+constexpr int gemm_pieces(int x, int t) { return (int)(((unsigned)x + (unsigned)(t - 1)) / (unsigned)t); }
 
 // Tiles of c for a problem whose rows are 16-byte aligned: 1: 256 x 256, 2: 128 x 128, 3: 64 x 64, 5: 32 x 32 with K
 // split over the wavefronts of a workgroup.  The largest tile that still gives three quarters of the 256 compute units
 // a workgroup, and that is not more than half empty: a tile costs the same however little of it lies inside c (us with 256,
 // 128, 64: 1024 x 8 x 64, K = 40, 30 8.8 5.1; 4096 x 16 x 16, K = 64, 95 28 12; 262144 x 64, K = 64, 30 20 15; 262144 x 128, K = 64, 37
-// 27 35; K = 2048 the same way).  A problem that fits the chip in one round of 32 x 32 tiles and has a K worth splitting
+// 27 35; K = 2048 the same way).  Except few rows with a long K, where what counts is how often a is read, once per column of
+// tiles (us with 128 and 64: 4 x 64 x 8192, K = 512 9.5 9.1, 1024 14.6 15.0, 4096 54 69; 232 x 33 x 232, K = 1024 29 33).  A problem that fits the chip in one round of 32 x 32 tiles and has a K worth splitting
 // takes those.
 #ifndef GEMM_SK_TILES
 #define GEMM_SK_TILES 256
@@ -27,8 +28,8 @@ constexpr int gemm_pieces(int x, int t) { return x / t + (x % t != 0); }
 inline int gemm_tile_of(int batch, int M, int N, int K) {
     auto tiles = [&](int t) { return (long long)batch * gemm_pieces(M, t) * gemm_pieces(N, t); };
     if (tiles(32) <= GEMM_SK_TILES && K >= 256) return 5;
-    const int side = M < N ? M : N;
-    return side > 128 && tiles(256) >= 192 ? 1 : side > 64 && tiles(128) >= 192 ? 2 : 3;
+    const int largest = N <= 64 || (M <= 64 && K < 768) ? 64 : N <= 128 || M <= 128 ? 128 : 256;
+    return largest == 256 && tiles(256) >= 192 ? 1 : largest >= 128 && tiles(128) >= 192 ? 2 : 3;
 }
 
 // 64 x 64 tiles: six LDS stages instead of four?  A block is two matrix instructions per wavefront, so the loads' latency
@@ -43,11 +44,13 @@ inline bool gemm_deep(int batch, int M, int N, int K) {
 }
 
 // 256 x 256 tiles: eight wavefronts of 64 x 128 instead of four of 128 x 128?  Two wavefronts per SIMD start, read and write a
-// tile faster than one, which shows where there are two blocks of K or less and either fewer tiles than compute units or a single
-// column of them (us with eight and four, K = 64: 3584 x 3584 10.6 11.5, 3 x 2048 x 2048 10.5 11.1, 524288 x 256 79 87; K = 32: 9.9
-// 10.6, 9.8 10.3, 69 67; ragged 3500 x 3496, K = 64 11.1 10.9).  4096 x 4096, K = 64: 12.0 11.6; 3500 x 3496, K = 128: 12.5 11.9.
+// tile faster than one, which shows where there are two blocks of K or less and either fewer tiles than compute units, all whole,
+// or a single whole column of them (us with eight and four, K = 64: 3584 x 3584 10.6 11.5, 3 x 2048 x 2048 10.5 11.1, 524288 x 256 79
+// 87; K = 32: 9.9 10.6, 9.8 10.3, 69 67; 90000 x 256, K = 32 16.2 17.2).  4096 x 4096, K = 64: 12.0 11.6; 27134 x 480, K = 40 12.6 11.9.
 inline bool gemm_eight_waves(int batch, int M, int N, int K) {
-    return K <= 64 && (N <= 256 || (long long)batch * gemm_pieces(M, 256) * gemm_pieces(N, 256) < 256);
+    if (K > 64 || N % 256 != 0) return false;
+    const long long tiles = (long long)batch * gemm_pieces(M, 256) * (N / 256);
+    return tiles < 256 ? M % 256 == 0 || N == 256 : N == 256 && (K > 32 || tiles <= 512);
 }
 
 // Do the rows of a and b start at 16-byte aligned addresses (and stay within 32-bit offsets inside a tile)?  Then
@@ -103,15 +106,18 @@ constexpr GemmGrid gemm_grid_of(int batch, int M, int N, int bm, int bn) {
 }
 
 // Workgroup b of `total` -> position in the list of tiles.  Workgroup b runs on XCD b % 8, each with an L2 of its own, so
-// every XCD takes a contiguous run of the list.  Where that takes more than two rounds of the 256 compute units, XCD x starts an x-th
-// of the way through its run: the runs often begin a power of two of bytes of c apart, and eight XCDs at the same place of
-// theirs would write to the same memory channels (8192 x 8192, K = 64, bfloat16: 47 us in step, 36 us like this; K = 2048: 231
-// and 212; one and two rounds: within 3 % either way).  I: int where it holds every count, else long long.
+// every XCD takes a contiguous run of the list.  The list goes through c in groups of `group` tiles, column by column: where the
+// runs are whole groups or whole parts of one, the XCDs would be in the same column all the time, in rows of c a multiple of 16 KiB
+// apart, and write to the same memory channels.  XCD x then begins x eighths into its run (8192 x 8192, bfloat16, K = 64: 47 us in
+// step, 36 us like this; K = 2048: 231 and 212; 8028 x 24200, K = 64: 134 and 113), if the launch takes more than two rounds of the 256
+// compute units (else within 3 % either way).  Other runs are out of step already (7203 x 16848, K = 1280: 297 as it is, 311 like
+// this).  group 0: never (32 x 32 tiles: 2 % slower).  I: int where it holds every count, else long long.
 template <class I>
-constexpr I gemm_list_position(I b, I total) {
-    const I q = total >> 3, r = total & 7, x = b & 7, len = q + (x < r);
+constexpr I gemm_list_position(I b, I total, I group) {
+    const I q = total >> 3, r = total & 7, x = b & 7;
     I j = b >> 3;
-    if (total > 512) {
+    if (group > 0 && total > 512 && (q % group == 0 || group % q == 0)) {
+        const I len = q + (x < r);
         j += (x * len) >> 3;
         j = j < len ? j : j - len;
     }
@@ -135,6 +141,7 @@ constexpr bool gemm_in_order(int tiles_n, int K, int total) { return tiles_n == 
 struct GemmTile {
     int bi, tm, tn;
 };
+constexpr int gemm_group(int tiles_m, int tiles_n) { return (tiles_m > GEMM_GROUP_M ? GEMM_GROUP_M : tiles_m) * tiles_n; }
 constexpr GemmTile gemm_tile_in_list(int bi, int t, int tiles_m, int tiles_n) {
     const int last = tiles_m > GEMM_GROUP_M ? tiles_m / GEMM_GROUP_M - 1 : 0;   // number of the last group
     int g = last == 0 ? 0 : t / (GEMM_GROUP_M * tiles_n);

@@ -9,8 +9,8 @@ void grid_of(int batch, int M, int N, int bm, int bn, long long* out) {
     const GemmGrid g = gemm_grid_of(batch, M, N, bm, bn);
     out[0] = g.tiles_m; out[1] = g.tiles_n; out[2] = g.total; out[3] = g.x; out[4] = g.y;
 }
-int position32(int b, int total) { return gemm_list_position(b, total); }
-long long position64(long long b, long long total) { return gemm_list_position(b, total); }
+int position32(int b, int total, int group) { return gemm_list_position(b, total, group); }
+long long position64(long long b, long long total, long long group) { return gemm_list_position(b, total, group); }
 int tile_in_list(int t, int tiles_m, int tiles_n) {
     const GemmTile g = gemm_tile_in_list(0, t, tiles_m, tiles_n);
     return g.tm * tiles_n + g.tn;

@@ -20,7 +20,7 @@ def L(tmp_path_factory):
                           os.path.join(HERE, "csrc", "gemm_launch_host.cpp"), "-o", out], capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
     lib = ctypes.CDLL(out)
-    lib.position64.argtypes = [ctypes.c_longlong] * 2
+    lib.position64.argtypes = [ctypes.c_longlong] * 3
     lib.position64.restype = ctypes.c_longlong
     return lib
 
@@ -53,10 +53,18 @@ def test_grid_holds_every_tile(L, batch, M, N, t):
     assert y == 1 or x % 8 == 0        # a workgroup's number modulo 8 is its XCD also in the second dimension
 
 
+@pytest.mark.parametrize("group", [0, 1, 4, 64, 100, 128, 129, 1000])
 @pytest.mark.parametrize("total", [1, 7, 8, 9, 31, 32, 100, 257, 512, 513, 514, 1024, 1025, 4099])
-def test_list_positions_are_a_permutation(L, total):
-    assert sorted(L.position32(b, total) for b in range(total)) == list(range(total))
-    assert [L.position64(b, total) for b in range(total)] == [L.position32(b, total) for b in range(total)]
+def test_list_positions_are_a_permutation(L, total, group):
+    """Every XCD (number modulo 8) a run of its own, every position once."""
+    pos = [L.position32(b, total, group) for b in range(total)]
+    assert [L.position64(b, total, group) for b in range(total)] == pos
+    end = 0
+    for x in range(min(8, total)):
+        run = sorted(pos[x::8])
+        assert run == list(range(end, end + len(run)))
+        end += len(run)
+    assert end == total
 
 
 def test_list_positions_above_2_to_the_31(L):
@@ -65,14 +73,19 @@ def test_list_positions_above_2_to_the_31(L):
     for b in (0, 1, 7, 8, 12, total - 8, total - 1):
         x = b % 8
         run = start[x + 1] - start[x]
-        assert L.position64(b, total) == start[x] + (b // 8 + x * run // 8) % run
+        assert L.position64(b, total, 0) == start[x] + b // 8
+        for group in (2 ** 10, 2 ** 32):     # whole groups, parts of a group
+            assert L.position64(b, total, group) == start[x] + (b // 8 + x * run // 8) % run
+        assert L.position64(b, total, 1000) == start[x] + b // 8
 
 
-def test_many_rounds_do_not_march_in_step(L):
-    """8192 x 8192 in tiles of 256: at any time the XCDs are in different columns of tiles."""
-    total = 32 * 32
-    for b in range(0, total, 8):
-        assert len({L.tile_in_list(L.position32(b + x, total), 32, 32) % 32 for x in range(8)}) == 8
+@pytest.mark.parametrize("tiles_m,tiles_n", [(32, 32), (32, 33), (32, 95), (64, 32), (16, 64)])
+def test_many_rounds_do_not_march_in_step(L, tiles_m, tiles_n):
+    """Large matrices in tiles of 256: no more than two XCDs in the same column of tiles."""
+    total = tiles_m * tiles_n
+    for b in range(0, total // 8, 8):
+        cols = [L.tile_in_list(L.position32(b + x, total, 4 * tiles_n), tiles_m, tiles_n) % tiles_n for x in range(8)]
+        assert max(cols.count(c) for c in cols) <= 2
 
 
 @pytest.mark.parametrize("tiles_m,tiles_n", [(1, 1), (3, 7), (4, 5), (5, 64), (7, 9), (8, 8), (9, 40), (11, 3), (16, 16), (1, 300), (300, 1)])
@@ -89,7 +102,8 @@ def test_every_tile_once_in_compact_blocks(L, tiles_m, tiles_n):
 
 @pytest.mark.parametrize("shape,tile", [((1024, 8, 64, 64), 3), ((4096, 64, 1024, 64), 3), ((4096, 65, 1024, 64), 2), ((4096, 128, 1024, 64), 2),
                                         ((4096, 129, 1024, 64), 1), ((4096, 129, 128, 64), 2), ((1, 1 << 20, 8, 32), 3), ((1, 1 << 20, 72, 32), 2),
-                                        ((1, 1 << 20, 136, 32), 1), ((1, 3584, 3584, 32), 1)])
+                                        ((1, 1 << 20, 136, 32), 1), ((1, 3584, 3584, 32), 1),
+                                        ((4, 64, 8192, 736), 3), ((4, 64, 8192, 768), 2), ((4, 8192, 64, 4096), 3)])
 def test_tiles_are_not_more_than_half_empty(L, shape, tile):
     assert L.tile_of(*shape) == tile
 
@@ -116,5 +130,6 @@ def test_tall_and_short_products(L):
     for args, want in (((1, 64, 200), 1), ((1, 512, 512), 1), ((1, 513, 200), 0), ((1, 65, 513), 0), ((1, 64, 4096), 1), ((2, 64, 200), 0)):
         assert L.in_order(*args) == want, args
     for args, want in (((1, 3584, 3584, 64), 1), ((1, 3584, 3584, 65), 0), ((1, 4096, 4096, 64), 0), ((1, 4096, 3840, 32), 1), ((1, 1 << 20, 256, 64), 1),
-                       ((1, 1 << 20, 264, 64), 0), ((1, 1 << 20, 256, 72), 0), ((200, 256, 256, 8), 1)):
+                       ((1, 1 << 20, 264, 64), 0), ((1, 1 << 20, 256, 72), 0), ((1, 1 << 20, 256, 32), 0), ((200, 256, 256, 8), 1), ((1, 50000, 256, 64), 1),
+                       ((1, 50000, 512, 64), 0), ((1, 3500, 3584, 64), 0), ((1, 3584, 3496, 64), 0)):
         assert L.eight_waves(*args) == want, args
