@@ -53,20 +53,20 @@ __device__ __forceinline__ constexpr int swz_b(int row) {
                         : ((((row >> 1) & 1) << 2) | (((row >> 2) & 1) << 1) | ((row >> 3) & 1));
 }
 
-// Workgroup -> tile: gemm_list_position or in order, then gemm_tile_in_list.  LARGE: 256 x 256 tiles; the others always go in
-// runs (gained nothing else, and every test here is 0.05 us).
+// Workgroup -> tile: its place in the list (gemm_order_of), then gemm_tile_in_list.  LARGE: 256 x 256 tiles; the others always go in runs.
 template <bool LARGE>
-__device__ __forceinline__ GemmTile tile_of_workgroup(int tiles_m, int tiles_n, int K, long long total) {
-    const int per = tiles_m * tiles_n, group = LARGE ? gemm_group(tiles_m, tiles_n) : 0;
+__device__ __forceinline__ GemmTile tile_of_workgroup(int tiles_m, int tiles_n, long long total, int order) {
+    const int per = tiles_m * tiles_n;
+    const bool apart = LARGE && order == GEMM_RUNS_APART;
     if (gridDim.y == 1) {
         const int total1 = (int)gridDim.x, b = (int)blockIdx.x;
-        const int c = LARGE && gemm_in_order(tiles_n, K, total1) ? b : gemm_list_position(b, total1, group);
+        const int c = LARGE && order == GEMM_IN_ORDER ? b : gemm_list_position(b, total1, apart);
         const int bi = total1 == per ? 0 : c / per;   // (a division is 0.05 us)
         return gemm_tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
     }
     long long b = (long long)blockIdx.y * gridDim.x + blockIdx.x;
     b = b < total ? b : total - 1;   // surplus workgroups repeat the last one's tile
-    const long long c = gemm_list_position(b, total, (long long)group);
+    const long long c = gemm_list_position(b, total, apart);
     const int bi = (int)(c / per);
     return gemm_tile_in_list(bi, (int)(c - (long long)bi * per), tiles_m, tiles_n);
 }
@@ -87,7 +87,7 @@ struct GemmLds {
 template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                         uint16_t* __restrict__ C, int M, int N, int K, int tiles_m,
-                                                        int tiles_n, long long total, float slope) {
+                                                        int tiles_n, long long total, int order, float slope) {
     using E = Elem<DT>;
     constexpr int NW = WM * WN;               // wavefronts, WM x WN over the tile
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
@@ -108,7 +108,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     const int l32 = lane & 31, h = lane >> 5;
     const int wm = wave % WM, wn = wave / WM;
 
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup<BM == 256>(tiles_m, tiles_n, K, total);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup<BM == 256>(tiles_m, tiles_n, total, order);
     const int m0 = tm_i * BM, n0 = tn_i * BN;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 template <int DT, bool KTAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int M,
-                            int N, int K, int tiles_m, int tiles_n, long long total, float slope) {
+                            int N, int K, int tiles_m, int tiles_n, long long total, int order, float slope) {
     using E = Elem<DT>;
     constexpr int NST = GEMM_NST;
     // LDS: the a tiles of all stages, then the b tiles: every read is one base register plus a 16-bit immediate
@@ -315,7 +315,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     const int l16 = lane & 15, g = lane >> 4;
     const int wm = wave & 1, wn = wave >> 1;
 
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup<true>(tiles_m, tiles_n, K, total);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup<true>(tiles_m, tiles_n, total, order);
     const int m0 = tm_i * 256, n0 = tn_i * 256;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -503,7 +503,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
 template <int DT, int LOAD>
 __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                                uint16_t* __restrict__ C, int M, int N, int K, int tiles_m,
-                                                               int tiles_n, long long total, float slope) {
+                                                               int tiles_n, long long total, int order, float slope) {
     using E = Elem<DT>;
     constexpr int NST = GEMM_SK_NST, STAGE = 4096, IPS = 4;
     constexpr bool KTAIL = LOAD != 0;
@@ -512,7 +512,7 @@ __global__ __launch_bounds__(256) void gemm_lrelu_splitk_kernel(const uint16_t* 
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, h = lane >> 5;
-    const auto [bi, tm_i, tn_i] = tile_of_workgroup<false>(tiles_m, tiles_n, K, total);
+    const auto [bi, tm_i, tn_i] = tile_of_workgroup<false>(tiles_m, tiles_n, total, order);
     const int m0 = tm_i * 32, n0 = tn_i * 32;
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
@@ -748,12 +748,13 @@ hipError_t launch_element(const GemmLaunch& g) {
 hipError_t launch_grid(const GemmLaunch& g, const void* fn, int bm, int bn, int threads, unsigned lds_bytes, std::atomic<uint64_t>& told) {
     GemmGrid grid = gemm_grid_of(g.batch, g.M, g.N, bm, bn);
     if (grid.y > 65535u) return hipErrorInvalidConfiguration;
+    int order = bm == 256 ? gemm_order_of(grid, g.N, g.K) : GEMM_RUNS;
     const uint16_t* a = (const uint16_t*)g.a;
     const uint16_t* b = (const uint16_t*)g.b;
     uint16_t* c = (uint16_t*)g.c;
     int M = g.M, N = g.N, K = g.K;
     float slope = g.slope;
-    void* args[] = {&a, &b, &c, &M, &N, &K, &grid.tiles_m, &grid.tiles_n, &grid.total, &slope};
+    void* args[] = {&a, &b, &c, &M, &N, &K, &grid.tiles_m, &grid.tiles_n, &grid.total, &order, &slope};
     if (const hipError_t e = announce_lds(fn, lds_bytes, told); e != hipSuccess) return e;
     return hipLaunchKernel(fn, dim3(grid.x, grid.y), dim3(threads), args, lds_bytes, (hipStream_t)g.stream);
 }

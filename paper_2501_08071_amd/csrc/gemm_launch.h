@@ -111,12 +111,18 @@ constexpr GemmGrid gemm_grid_of(int batch, int M, int N, int bm, int bn) {
 // apart, and write to the same memory channels.  XCD x then begins x eighths into its run (8192 x 8192, bfloat16, K = 64: 47 us in
 // step, 36 us like this; K = 2048: 231 and 212; 8028 x 24200, K = 64: 134 and 113), if the launch takes more than two rounds of the 256
 // compute units (else within 3 % either way).  Other runs are out of step already (7203 x 16848, K = 1280: 297 as it is, 311 like
-// this).  group 0: never (32 x 32 tiles: 2 % slower).  I: int where it holds every count, else long long.
+// this).
+constexpr bool gemm_runs_in_step(long long total, long long group) {
+    const long long q = total >> 3;
+    return total > 512 && (q % group == 0 || group % q == 0);
+}
+
+// apart: as above.  I: int where it holds every count, else long long.
 template <class I>
-constexpr I gemm_list_position(I b, I total, I group) {
+constexpr I gemm_list_position(I b, I total, bool apart) {
     const I q = total >> 3, r = total & 7, x = b & 7;
     I j = b >> 3;
-    if (group > 0 && total > 512 && (q % group == 0 || group % q == 0)) {
+    if (apart) {
         const I len = q + (x < r);
         j += (x * len) >> 3;
         j = j < len ? j : j - len;
@@ -128,7 +134,7 @@ constexpr I gemm_list_position(I b, I total, I group) {
 // one stretch of memory, as long as that streaming is what a launch waits for and not the matrix instructions (us in runs /
 // in order: 200 x 256 x 256, K = 64 12.2 11.5, K = 2048 94.4 96.1; 50000 x 256, K = 128 12.8 12.3; 524288 x 256, K = 64 81.6
 // 79.1, K = 256 135 147).
-constexpr bool gemm_in_order(int tiles_n, int K, int total) { return tiles_n == 1 && K <= 512 && (total <= 512 || K <= 64); }
+constexpr bool gemm_in_order(int N, int K, int total) { return N <= 256 && K <= 512 && (total <= 512 || K <= 64); }
 
 // Position t in matrix bi's list of tiles -> tile.  The list goes through GEMM_GROUP_M tile rows at a time, column by column:
 // the workgroups that an XCD runs together then cover a compact block of c (4 x 8 tiles when it holds 32) and share both
@@ -142,6 +148,12 @@ struct GemmTile {
     int bi, tm, tn;
 };
 constexpr int gemm_group(int tiles_m, int tiles_n) { return (tiles_m > GEMM_GROUP_M ? GEMM_GROUP_M : tiles_m) * tiles_n; }
+// The order of a launch of 256 x 256 tiles (smaller ones always go in runs: nothing else gained there).  Decided once, on the host: a
+// workgroup that does not share its compute unit would pay for every division, about 0.05 us each.
+enum GemmOrder { GEMM_RUNS, GEMM_RUNS_APART, GEMM_IN_ORDER };
+constexpr GemmOrder gemm_order_of(const GemmGrid& g, int N, int K) {
+    return g.y == 1 && gemm_in_order(N, K, (int)g.total) ? GEMM_IN_ORDER : gemm_runs_in_step(g.total, gemm_group(g.tiles_m, g.tiles_n)) ? GEMM_RUNS_APART : GEMM_RUNS;
+}
 constexpr GemmTile gemm_tile_in_list(int bi, int t, int tiles_m, int tiles_n) {
     const int last = tiles_m > GEMM_GROUP_M ? tiles_m / GEMM_GROUP_M - 1 : 0;   // number of the last group
     int g = last == 0 ? 0 : t / (GEMM_GROUP_M * tiles_n);

@@ -9,13 +9,14 @@ void grid_of(int batch, int M, int N, int bm, int bn, long long* out) {
     const GemmGrid g = gemm_grid_of(batch, M, N, bm, bn);
     out[0] = g.tiles_m; out[1] = g.tiles_n; out[2] = g.total; out[3] = g.x; out[4] = g.y;
 }
-int position32(int b, int total, int group) { return gemm_list_position(b, total, group); }
-long long position64(long long b, long long total, long long group) { return gemm_list_position(b, total, group); }
+int position32(int b, int total, int group) { return gemm_list_position(b, total, group > 0 && gemm_runs_in_step(total, group)); }
+long long position64(long long b, long long total, long long group) { return gemm_list_position(b, total, group > 0 && gemm_runs_in_step(total, group)); }
 int tile_in_list(int t, int tiles_m, int tiles_n) {
     const GemmTile g = gemm_tile_in_list(0, t, tiles_m, tiles_n);
     return g.tm * tiles_n + g.tn;
 }
-int in_order(int tiles_n, int K, int total) { return gemm_in_order(tiles_n, K, total); }
+int in_order(int N, int K, int total) { return gemm_in_order(N, K, total); }
+int order_of(int batch, int M, int N, int K) { return gemm_order_of(gemm_grid_of(batch, M, N, 256, 256), N, K); }
 int eight_waves(int batch, int M, int N, int K) { return gemm_eight_waves(batch, M, N, K); }
 int deep(int batch, int M, int N, int K) { return gemm_deep(batch, M, N, K); }
 int per_element(int batch, int M, int N, int K) { return gemm_per_element(batch, M, N, K); }

@@ -127,9 +127,13 @@ def test_few_products_take_one_thread_per_element(L):
 def test_tall_and_short_products(L):
     """A single column of tiles goes through memory in order unless the product is long; two wavefronts per SIMD for two blocks
     of K where the tiles are few or in one column."""
-    for args, want in (((1, 64, 200), 1), ((1, 512, 512), 1), ((1, 513, 200), 0), ((1, 65, 513), 0), ((1, 64, 4096), 1), ((2, 64, 200), 0)):
+    for args, want in (((200, 64, 200), 1), ((256, 512, 512), 1), ((129, 513, 200), 0), ((256, 65, 513), 0), ((256, 64, 4096), 1), ((257, 64, 200), 0)):
         assert L.in_order(*args) == want, args
     for args, want in (((1, 3584, 3584, 64), 1), ((1, 3584, 3584, 65), 0), ((1, 4096, 4096, 64), 0), ((1, 4096, 3840, 32), 1), ((1, 1 << 20, 256, 64), 1),
                        ((1, 1 << 20, 264, 64), 0), ((1, 1 << 20, 256, 72), 0), ((1, 1 << 20, 256, 32), 0), ((200, 256, 256, 8), 1), ((1, 50000, 256, 64), 1),
                        ((1, 50000, 512, 64), 0), ((1, 3500, 3584, 64), 0), ((1, 3584, 3496, 64), 0)):
         assert L.eight_waves(*args) == want, args
+    # in runs, in runs that start apart, one after the other
+    for args, want in (((1, 4096, 4096, 64), 0), ((1, 8192, 8192, 64), 1), ((1, 7203, 16848, 1280), 0), ((200, 256, 256, 64), 2), ((1, 1 << 20, 256, 64), 2),
+                       ((1 << 23, 256, 256, 64), 1)):
+        assert L.order_of(*args) == want, args
