@@ -44,13 +44,21 @@ inline bool gemm_deep(int batch, int M, int N, int K) {
 }
 
 // 256 x 256 tiles: eight wavefronts of 64 x 128 instead of four of 128 x 128?  Two wavefronts per SIMD start, read and write a
-// tile faster than one, which shows where there are two blocks of K or less and either fewer tiles than compute units, all whole,
-// or a single whole column of them (us with eight and four, K = 64: 3584 x 3584 10.6 11.5, 3 x 2048 x 2048 10.5 11.1, 524288 x 256 79
+// tile faster than one, which shows where there are few blocks of K and either fewer tiles than compute units, all whole, or a
+// single whole column of them (us with eight and four, K = 64: 3584 x 3584 10.6 11.5, 3 x 2048 x 2048 10.5 11.1, 524288 x 256 79
 // 87; K = 32: 9.9 10.6, 9.8 10.3, 69 67; 90000 x 256, K = 32 16.2 17.2).  4096 x 4096, K = 64: 12.0 11.6; 27134 x 480, K = 40 12.6 11.9.
+// Up to four blocks of K where at least a sixth of the compute units has no tile (K = 96: 3584 x 3584 11.4 12.2, 256 x 49152 11.3 12.4;
+// K = 128: 12.1 12.7, 11.9 12.8, 1536 x 8192 12.3 12.1; with 240 tiles, 3840 x 4096, 13.2 12.8), eight in a single row of them
+// (256 x 52224, K = 224: 14.1 14.9).
+// And in a single column of tiles with a long K, whole in M, where the launch waits for rows of a from memory and not for the matrix
+// instructions (65536 x 256, K = 1536 62.5 63.8, 2048 90 96, 8192 305 344; 131072 x 256, K = 8192 561 609; 65536 x 136, K = 3072
+// 107 110; but K = 1280: 51.0 51.1, 57000 x 136, K = 4096 130 122, 200 x 256 x 256, K = 4096 174 172, 262144 x 200, K = 2048 295 279).
 inline bool gemm_eight_waves(int batch, int M, int N, int K) {
-    if (K > 64 || N % 256 != 0) return false;
-    const long long tiles = (long long)batch * gemm_pieces(M, 256) * (N / 256);
-    return tiles < 256 ? M % 256 == 0 || N == 256 : N == 256 && (K > 32 || tiles <= 512);
+    const long long tiles = (long long)batch * gemm_pieces(M, 256) * gemm_pieces(N, 256);
+    if (N <= 256 && M >= 1024 && M % 256 == 0 && K >= 1536 && K % 32 == 0) return tiles <= 512;
+    if (N % 256 != 0) return false;
+    if (K > 64) return tiles <= 208 && M % 256 == 0 && K <= (M == 256 ? 256 : 128);
+    return N == 256 ? K == 64 || (K == 32 && tiles <= 448) : tiles < 256 && M % 256 == 0;
 }
 
 // Do the rows of a and b start at 16-byte aligned addresses (and stay within 32-bit offsets inside a tile)?  Then
@@ -132,9 +140,10 @@ constexpr I gemm_list_position(I b, I total, bool apart) {
 
 // Or one after the other?  With a single column of tiles no two of them share rows of a, and what the XCDs run together is best
 // one stretch of memory, as long as that streaming is what a launch waits for and not the matrix instructions (us in runs /
-// in order: 200 x 256 x 256, K = 64 12.2 11.5, K = 2048 94.4 96.1; 50000 x 256, K = 128 12.8 12.3; 524288 x 256, K = 64 81.6
-// 79.1, K = 256 135 147).
-constexpr bool gemm_in_order(int N, int K, int total) { return N <= 256 && K <= 512 && (total <= 512 || K <= 64); }
+// in order: 200 x 256 x 256, K = 32 10.7 10.1, K = 64 12.1 11.5, K = 2048 94.4 96.1; 50000 x 256, K = 128 12.8 12.5).  Past one round of the
+// chip only for whole columns and K = 64 (524288 x 256 81.6 79.1; K = 256 135 147; 56 x 13824 x 184, K = 64 106 114; 30 x 4096 x 256, K = 96
+// 24.4 25.8; 24 x 96512 x 256, K = 16 274 288; 126976 x 256, K = 32 17.9 18.6).
+constexpr bool gemm_in_order(int N, int K, int total) { return N <= 256 && (total <= 256 ? K <= 128 : N == 256 && K == 64); }
 
 // Position t in matrix bi's list of tiles -> tile.  The list goes through GEMM_GROUP_M tile rows at a time, column by column:
 // the workgroups that an XCD runs together then cover a compact block of c (4 x 8 tiles when it holds 32) and share both

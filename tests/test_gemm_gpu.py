@@ -316,3 +316,11 @@ def test_tall_products(P, shape, dtype):
     if shape[3] % 32 == 0:
         assert P.gemm_path(*shape, dtype) == 1
     run(P, *shape, dtype)
+
+
+# Eight wavefronts past two blocks of K: several rows of tiles and a single one, and a single column with a long K
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("shape", [(1, 3584, 3584, 128), (1, 3584, 3584, 104), (1, 256, 49408, 224), (1, 49152, 136, 1536)])
+def test_eight_wavefronts(P, shape, dtype):
+    assert P.gemm_path(*shape, dtype) == (1 if shape[3] % 32 == 0 else 4)
+    run(P, *shape, dtype)

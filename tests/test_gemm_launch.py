@@ -126,12 +126,18 @@ def test_few_products_take_one_thread_per_element(L):
 
 def test_tall_and_short_products(L):
     """A single column of tiles goes through memory in order unless the product is long; two wavefronts per SIMD for two blocks
-    of K where the tiles are few or in one column."""
-    for args, want in (((200, 64, 200), 1), ((256, 512, 512), 1), ((129, 513, 200), 0), ((256, 65, 513), 0), ((256, 64, 4096), 1), ((257, 64, 200), 0)):
+    of K where the tiles are few or in one column, up to four or eight of them with fewer tiles still, and for a long K in one column."""
+    for args, want in (((200, 64, 200), 1), ((256, 128, 256), 1), ((129, 128, 257), 0), ((256, 160, 200), 0), ((256, 64, 4096), 1), ((256, 32, 4096), 0),
+                       ((248, 64, 513), 0), ((257, 64, 200), 0), ((256, 40, 200), 1), ((256, 56, 257), 0)):
         assert L.in_order(*args) == want, args
-    for args, want in (((1, 3584, 3584, 64), 1), ((1, 3584, 3584, 65), 0), ((1, 4096, 4096, 64), 0), ((1, 4096, 3840, 32), 1), ((1, 1 << 20, 256, 64), 1),
-                       ((1, 1 << 20, 264, 64), 0), ((1, 1 << 20, 256, 72), 0), ((1, 1 << 20, 256, 32), 0), ((200, 256, 256, 8), 1), ((1, 50000, 256, 64), 1),
-                       ((1, 50000, 512, 64), 0), ((1, 3500, 3584, 64), 0), ((1, 3584, 3496, 64), 0)):
+    for args, want in (((1, 3584, 3584, 64), 1), ((1, 3584, 3584, 65), 1), ((1, 3584, 3584, 128), 1), ((1, 3584, 3584, 136), 0),
+                       ((1, 4096, 4096, 64), 0), ((1, 4096, 3840, 32), 1), ((1, 1 << 20, 256, 64), 1),
+                       ((1, 1 << 20, 264, 64), 0), ((1, 1 << 20, 256, 72), 0), ((1, 1 << 20, 256, 32), 0), ((1, 1 << 20, 256, 56), 0), ((448, 256, 256, 32), 1), ((449, 256, 256, 32), 0),
+                       ((200, 256, 512, 24), 0), ((100, 256, 512, 24), 1), ((200, 256, 256, 32), 1), ((200, 256, 256, 8), 0), ((1, 50000, 256, 64), 1),
+                       ((1, 50000, 512, 64), 0), ((1, 3500, 3584, 64), 0), ((1, 3584, 3496, 64), 0),
+                       ((1, 256, 53248, 256), 1), ((1, 256, 53504, 256), 0), ((1, 256, 53248, 264), 0), ((1, 3840, 4096, 96), 0), ((208, 256, 256, 72), 1),
+                       ((1, 49152, 136, 1536), 1), ((1, 49152, 256, 1504), 0), ((1, 49152, 256, 2056), 0), ((1, 49100, 256, 2048), 0), ((200, 256, 256, 2048), 0),
+                       ((1, 1 << 17, 200, TOP - 31), 1), ((1, 1 << 18, 200, 2048), 0), ((1, 24576, 512, 8192), 0)):
         assert L.eight_waves(*args) == want, args
     # in runs, in runs that start apart, one after the other
     for args, want in (((1, 4096, 4096, 64), 0), ((1, 8192, 8192, 64), 1), ((1, 7203, 16848, 1280), 0), ((200, 256, 256, 64), 2), ((1, 1 << 20, 256, 64), 2),
