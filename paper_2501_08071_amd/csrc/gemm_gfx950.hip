@@ -62,13 +62,13 @@ __device__ __forceinline__ GemmTile tile_of_workgroup(int tiles_m, int tiles_n, 
         const int total1 = (int)gridDim.x, b = (int)blockIdx.x;
         const int c = LARGE && order == GEMM_IN_ORDER ? b : gemm_list_position(b, total1, apart);
         const int bi = total1 == per ? 0 : c / per;   // (a division is 0.05 us)
-        return gemm_tile_in_list(bi, c - bi * per, tiles_m, tiles_n);
+        return gemm_tile_in_list(bi, c - bi * per, tiles_m, tiles_n, !LARGE);
     }
     long long b = (long long)blockIdx.y * gridDim.x + blockIdx.x;
     b = b < total ? b : total - 1;   // surplus workgroups repeat the last one's tile
     const long long c = gemm_list_position(b, total, apart);
     const int bi = (int)(c / per);
-    return gemm_tile_in_list(bi, (int)(c - (long long)bi * per), tiles_m, tiles_n);
+    return gemm_tile_in_list(bi, (int)(c - (long long)bi * per), tiles_m, tiles_n, !LARGE);
 }
 
 __device__ __forceinline__ float leaky(float t, float slope) { return t >= 0.f ? t : slope * t; }

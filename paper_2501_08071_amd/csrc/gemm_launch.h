@@ -147,9 +147,10 @@ constexpr bool gemm_in_order(int N, int K, int total) { return N <= 256 && (tota
 
 // Position t in matrix bi's list of tiles -> tile.  The list goes through GEMM_GROUP_M tile rows at a time, column by column:
 // the workgroups that an XCD runs together then cover a compact block of c (4 x 8 tiles when it holds 32) and share both
-// their rows of a and their columns of b.  The last group takes the remainder too, GEMM_GROUP_M to 2 GEMM_GROUP_M - 1 rows: a
-// last group of one row would give an XCD 32 columns of b to read (288 x 4096 x 2240, five rows of tiles: 19.7 us with
-// groups of 4 and 1, 16.7 us with one of 5).
+// their rows of a and their columns of b.  join: the last group takes the remainder too, GEMM_GROUP_M to 2 GEMM_GROUP_M - 1 rows;
+// a last group of one row gives an XCD 32 columns of b to read (288 x 4096 x 2240, five rows of 64 x 64 tiles: 19.7 us with
+// groups of 4 and 1, 16.7 us with one of 5).  Not in 256 x 256 tiles: 69 products of 5 to 27 rows of them were 1.2 % slower on average
+// with it (8 x 1792 x 4096, K = 256 57.6 63.2; 1 x 2304 x 25600, K = 256 54.7 60.1, K = 1536 166 174; 8 x 2304 x 4096, K = 1536 226 219).
 #ifndef GEMM_GROUP_M
 #define GEMM_GROUP_M 4
 #endif
@@ -163,8 +164,8 @@ enum GemmOrder { GEMM_RUNS, GEMM_RUNS_APART, GEMM_IN_ORDER };
 constexpr GemmOrder gemm_order_of(const GemmGrid& g, int N, int K) {
     return g.y == 1 && gemm_in_order(N, K, (int)g.total) ? GEMM_IN_ORDER : gemm_runs_in_step(g.total, gemm_group(g.tiles_m, g.tiles_n)) ? GEMM_RUNS_APART : GEMM_RUNS;
 }
-constexpr GemmTile gemm_tile_in_list(int bi, int t, int tiles_m, int tiles_n) {
-    const int last = tiles_m > GEMM_GROUP_M ? tiles_m / GEMM_GROUP_M - 1 : 0;   // number of the last group
+constexpr GemmTile gemm_tile_in_list(int bi, int t, int tiles_m, int tiles_n, bool join) {
+    const int last = tiles_m <= GEMM_GROUP_M ? 0 : join ? tiles_m / GEMM_GROUP_M - 1 : (tiles_m - 1) / GEMM_GROUP_M;   // number of the last group
     int g = last == 0 ? 0 : t / (GEMM_GROUP_M * tiles_n);
     g = g < last ? g : last;
     const int u = t - g * GEMM_GROUP_M * tiles_n, rows = g < last ? GEMM_GROUP_M : tiles_m - last * GEMM_GROUP_M;

@@ -11,8 +11,8 @@ void grid_of(int batch, int M, int N, int bm, int bn, long long* out) {
 }
 int position32(int b, int total, int group) { return gemm_list_position(b, total, group > 0 && gemm_runs_in_step(total, group)); }
 long long position64(long long b, long long total, long long group) { return gemm_list_position(b, total, group > 0 && gemm_runs_in_step(total, group)); }
-int tile_in_list(int t, int tiles_m, int tiles_n) {
-    const GemmTile g = gemm_tile_in_list(0, t, tiles_m, tiles_n);
+int tile_in_list(int t, int tiles_m, int tiles_n, int join) {
+    const GemmTile g = gemm_tile_in_list(0, t, tiles_m, tiles_n, join != 0);
     return g.tm * tiles_n + g.tn;
 }
 int in_order(int N, int K, int total) { return gemm_in_order(N, K, total); }

@@ -84,13 +84,16 @@ def test_many_rounds_do_not_march_in_step(L, tiles_m, tiles_n):
     """Large matrices in tiles of 256: no more than two XCDs in the same column of tiles."""
     total = tiles_m * tiles_n
     for b in range(0, total // 8, 8):
-        cols = [L.tile_in_list(L.position32(b + x, total, 4 * tiles_n), tiles_m, tiles_n) % tiles_n for x in range(8)]
+        cols = [L.tile_in_list(L.position32(b + x, total, 4 * tiles_n), tiles_m, tiles_n, 0) % tiles_n for x in range(8)]
         assert max(cols.count(c) for c in cols) <= 2
 
 
 @pytest.mark.parametrize("tiles_m,tiles_n", [(1, 1), (3, 7), (4, 5), (5, 64), (7, 9), (8, 8), (9, 40), (11, 3), (16, 16), (1, 300), (300, 1)])
 def test_every_tile_once_in_compact_blocks(L, tiles_m, tiles_n):
-    order = [L.tile_in_list(t, tiles_m, tiles_n) for t in range(tiles_m * tiles_n)]
+    apart = [L.tile_in_list(t, tiles_m, tiles_n, 0) for t in range(tiles_m * tiles_n)]
+    assert sorted(apart) == list(range(tiles_m * tiles_n))      # 256 x 256 tiles: the last rows may be a group of their own
+    assert {i // tiles_n for i in apart[:4 * tiles_n]} == set(range(min(4, tiles_m)))
+    order = [L.tile_in_list(t, tiles_m, tiles_n, 1) for t in range(tiles_m * tiles_n)]
     assert sorted(order) == list(range(tiles_m * tiles_n))
     # 32 neighbours in the list (what an XCD runs together) touch few rows and columns: never a run along one row
     # of tiles where there are more rows to choose from
