@@ -65,16 +65,16 @@ TRAFFIC = {
      "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
     # the GEMM + LeakyReLU kernels (the paper's shapes; the 256 x 256 tile's launches)
     "mmLeakyReLu_1x512x512x2048_f16": {"fetch_kib": 6188.0 * 2.0, "write_kib": 512.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "e9a5053e158f97b42e19c685278f2e93358a6942a5da88eac90e5c309ce63746",
+     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "bmm_4x512x512x2048_f16": {"fetch_kib": 12329.0 * 2.0, "write_kib": 2048.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "e9a5053e158f97b42e19c685278f2e93358a6942a5da88eac90e5c309ce63746",
+    "bmm_4x512x512x2048_f16": {"fetch_kib": 12334.5 * 2.0, "write_kib": 2048.0 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 98444.5 * 2.0, "write_kib": 32768.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "e9a5053e158f97b42e19c685278f2e93358a6942a5da88eac90e5c309ce63746",
+    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 98454.5 * 2.0, "write_kib": 32768.0 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "mmLeakyReLu_1x8192x8192x8192_f16": {"fetch_kib": 786632.7 * 2.0, "write_kib": 131073.3 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "e9a5053e158f97b42e19c685278f2e93358a6942a5da88eac90e5c309ce63746",
+    "mmLeakyReLu_1x8192x8192x8192_f16": {"fetch_kib": 786803.6 * 2.0, "write_kib": 131073.6 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
 }
 
