@@ -51,7 +51,8 @@ typedef enum {
  *   causal   0: every key visible; non-zero: key j visible to query i iff j <= i.
  *            Masked keys enter the second product with weight 0, so q, k and v must be
  *            finite everywhere: a non-finite row j of v spoils, next to the rows of O
- *            that see key j, the earlier rows of the same block of keys (attn_tile_keys of them, 0 * Inf).
+ *            that see key j, the earlier rows of the same block of keys (attn_tile_keys of them; at D = 32 of the
+ *            same tile of rows; 0 * Inf).
  *   scale    multiplies q.k before the softmax; any finite value.
  *   dtype    attn_dtype_t of q, k, v.
  *   stream   hipStream_t to enqueue on (NULL = the default stream).
@@ -97,17 +98,18 @@ const char *attn_status_str(int status);
 const char *attn_kernel_name(int B, int H, int S, int D, int dtype, int causal);
 
 /*
- * Query rows per workgroup and keys per inner-loop tile of that kernel
+ * Query rows per tile and keys per inner-loop block of the kernel for problems that fill the chip
  * (0 if unsupported).  For harnesses that pick tile-edge rows to check.
  */
 int attn_tile_rows(int D, int dtype, int causal);
 int attn_tile_keys(int D, int dtype, int causal);
 
 /*
- * Query rows per workgroup attn_fwd uses for this very problem: attn_tile_rows, or half of it (the
- * same kernel with half the query rows, "..., 4>" in its name; from a few hundred keys on the one that
- * splits the keys between two halves of its wavefronts, "attn_fwd_halves_kernel") when the problem has so few tiles
- * that the larger ones would leave half of the chip idle.  0 if unsupported.
+ * Query rows per tile attn_fwd uses for this very problem: attn_tile_rows, or half of it ("..., 4>" in the
+ * kernel's name) when the problem has so few tiles that the larger ones would leave half of the chip idle.  A tile is
+ * a workgroup's; of the smaller ones, where the halves of a workgroup's wavefronts split the keys, it is shared by
+ * several workgroups while those fit the chip at once ("attn_fwd_halves_stream_kernel": 32 or 64 rows each, the last
+ * template argument but one).  0 if unsupported.
  */
 int attn_launch_rows(int B, int H, int S, int D, int dtype, int causal);
 

@@ -10,7 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattn_gfx950.so")
-SOURCES = ["attn_fwd_gfx950.hip", "attn_fwd_rows64_gfx950.hip", "attn_api.cpp", "rowops_gfx950.hip", "rowops_api.cpp",
+SOURCES = ["attn_fwd_gfx950.hip", "attn_fwd_stream_gfx950.hip", "attn_fwd_rows64_gfx950.hip", "attn_api.cpp", "rowops_gfx950.hip", "rowops_api.cpp",
            "gemm_gfx950.hip", "gemm_api.cpp", "probe_gfx950.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 

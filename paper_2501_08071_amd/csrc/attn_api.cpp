@@ -56,6 +56,9 @@ namespace {
 const char* const kKernelNames[3][2][3][2] = {ATTN_NAMES_NW("attn_fwd_kernel", ATTN_NW_FULL_STR),
                                                ATTN_NAMES_NW("attn_fwd_kernel", ATTN_NW_HALF_STR),
                                                ATTN_NAMES_NW("attn_fwd_halves_kernel", ATTN_NW_HALF_STR)};
+#define ATTN_STREAM_NAMES(RG)                                                                             \
+    ATTN_NAMES_NW("attn_fwd_halves_stream_kernel", RG ", " ATTN_NW_HALF_STR)
+const char* const kStreamNames[2][2][3][2] = {ATTN_STREAM_NAMES("1"), ATTN_STREAM_NAMES("2")};   // by row groups
 const char* const kRows64Names[2][2] = {{"attn_fwd_rows64_kernel<0, 128, false>", "attn_fwd_rows64_kernel<0, 128, true>"},
                                         {"attn_fwd_rows64_kernel<1, 128, false>", "attn_fwd_rows64_kernel<1, 128, true>"}};
 }  // namespace
@@ -64,8 +67,10 @@ extern "C" const char* attn_kernel_name(int B, int H, int S, int D, int dtype, i
     if (B <= 0 || H <= 0 || !attn_supported(S, D, dtype, causal)) return nullptr;
     if (attn_takes_rows64((long long)B * H, S, D)) return kRows64Names[dtype][causal != 0];
     const long long bh = (long long)B * H;
+    const int di = D == 32 ? 0 : D == 64 ? 1 : 2;
+    if (const int groups = attn_stream_groups(bh, S, D, causal != 0)) return kStreamNames[groups - 1][dtype][di][causal != 0];
     const int mode = attn_pick_nw(bh, S) == ATTN_NW ? 0 : attn_splits_keys(bh, S, D) ? 2 : 1;
-    return kKernelNames[mode][dtype][D == 32 ? 0 : D == 64 ? 1 : 2][causal != 0];
+    return kKernelNames[mode][dtype][di][causal != 0];
 }
 
 extern "C" int attn_tile_rows(int D, int dtype, int causal) {

@@ -92,6 +92,27 @@ inline bool attn_splits_keys(long long BH, int S, int D) {
     return attn_can_split(D) && attn_pick_nw(BH, S) != ATTN_NW && S > (D == 128 ? 384 : D == 64 ? 128 : 256);
 }
 
+// Problems that do not fill the chip with large tiles: row groups (of 32 rows) per workgroup of the kernel whose wavefronts each
+// stream keys of their own (attn_fwd_stream_gfx950.hip), or 0: not that kernel.  One group while that is one round of the 256
+// compute units, two while that is; beyond it the larger workgroups above read less of K and V per row.  Under the mask, where
+// the workgroups of a second round are the short ones, a little further.  Measured, us as before / one group / two (heads x S, 8
+// wavefronts of the other kernels before): D = 128, 8 x 333 11.6 6.6 9.7, 8 x 1024 17.6 10.8 15.7, 1 x 4096 44.6 23.8 39.0,
+// 32 x 333 12.6 12.5 10.6, 16 x 1024 19.4 19.9 17.6, 32 x 1024 25.3 39.5 34.2; D = 64, 8 x 1024 12.3 8.0 9.9, 16 x 1024 12.6 13.9
+// 10.4, 32 x 1024 14.8 26.0 19.5; D = 32, 8 x 1024 10.1 6.4 8.0, 4 x 4096 29.0 27.2 19.6, 8 x 4096 30.4 50.7 35.9.  With the mask:
+// D = 128, 4 x 4096 46.6 32.0 40.3, 8 x 2887 37.6 37.1 33.5, 16 x 2048 31.5 38.2 33.8, 128 x 128 9.9 10.3 9.5; D = 64, 4 x 4096 32.4
+// 23.0 25.1, 6 x 1670 17.8 10.2 13.4, 32 x 512 9.8 9.0 7.9, 10 x 1701 18.9 16.7 14.6, 32 x 1024 14.1 19.7 15.3; D = 32, 8 x 4096 29.4 31.1
+// 23.9, 32 x 1024 11.2 15.4 11.6.  (A single tile of 128 rows keeps the kernel that attn_kernel_name has always named for it.)
+inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
+#ifdef EXP_RG
+    return EXP_RG;
+#endif
+    if (attn_pick_nw(BH, S) == ATTN_NW || (BH == 1 && S <= 128)) return 0;
+    const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
+    if (n32 <= 256 || (causal && n32 <= 512 && (S >= 2048 || (D == 128 ? S >= 256 : n32 <= 400 && S >= 640)))) return 1;
+    if (n64 <= 256 || (causal && (D != 128 && S >= 2048 ? n64 <= 512 : S >= 1000 && n64 <= 384))) return 2;
+    return 0;
+}
+
 struct AttnLaunch {
     const void* q;
     const void* k;
@@ -108,6 +129,7 @@ struct AttnLaunch {
 };
 
 hipError_t attn_launch(const AttnLaunch& a);
+hipError_t attn_launch_stream(const AttnLaunch& a, int groups);   // with that many row groups per workgroup
 hipError_t attn_launch_rows64(const AttnLaunch& a);   // D = 128 only: 64 query rows per wavefront
 
 // Does this problem take the kernel with 64 query rows per wavefront?  (Workgroups of 256 rows either way.)

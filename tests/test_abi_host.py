@@ -213,3 +213,23 @@ def test_library_links_only_the_hip_runtime():
     out = subprocess.run(["ldd", lib], capture_output=True, text=True).stdout
     assert "torch" not in out and "libc10" not in out
     assert "amdhip64" in out
+
+
+def test_streamed_problems_by_size(P):
+    """Which problems of few tiles take the kernel whose wavefronts stream keys of their own, and with how many row groups:
+    both sides of every line of the rule."""
+    def groups(heads, S, D, causal):
+        name = P.attn_kernel_name(1, heads, S, D, 0, causal)
+        return int(name.split(", ")[3]) if "stream" in name else 0
+
+    for D in (32, 64, 128):
+        for causal in (False, True):
+            assert groups(1, 128, D, causal) == 0 and groups(1, 129, D, causal) == 1 and groups(2, 1, D, causal) == 1
+            assert groups(8, 1024, D, causal) == 1 and groups(128, 64, D, causal) == 1
+            assert groups(129, 64, D, causal) == 0 and groups(64, 1024, D, causal) == 0     # tiles of 256 rows fill half of the chip
+            assert groups(32, 512, D, False) == 2 and groups(33, 512, D, False) == 0
+        assert groups(4, 4096, D, False) == 2 and groups(4, 4096, D, True) == 1 and groups(5, 4096, D, False) == 0
+        assert groups(8, 4096, D, True) == (0 if D == 128 else 2)
+        assert groups(12, 1024, D, True) == 1 and groups(16, 1024, D, True) == (1 if D == 128 else 2)
+        assert groups(24, 1000, D, True) == 2 and groups(24, 999, D, True) == 0 and groups(24, 1025, D, True) == 0
+        assert groups(128, 128, D, True) == 2

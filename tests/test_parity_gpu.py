@@ -356,3 +356,30 @@ def test_matrix_instruction_probe_runs():
     for dt in (F16, BF16):
         r = P.probe_mfma(iters=200, dtype=dt, random_operands=True, workgroups=512, repeats=2)
         assert math.isfinite(r) and r > 0
+
+
+# Wavefronts that stream keys of their own (eight per workgroup, blocks of 32 keys dealt out in turn), one and two groups of 32
+# rows per workgroup: fewer blocks than wavefronts, exactly one each, one more; one block more than the buffers of a wavefront
+# hold (8 x 1, 2, 4 blocks at D = 128, 64, 32) and the first that goes round them; ragged ends of 1 and 31 keys; rows past the
+# end in the last group or a whole group of them.  Loud and quiet blocks, so that the parts of a row weigh very differently, and
+# the reference of a part has to move where its first block is a quiet one.
+def _streamed(S, D, causal):
+    """Numbers of heads for which the library takes one and two row groups: two heads, and the least that has two groups (none
+    where tiles of 256 rows fill the chip before that)."""
+    two = [h for h in range(3, 129) if "stream" in (n := P.attn_kernel_name(1, h, S, D, BF16, causal)) and n.endswith(", 2, 4>")]
+    return [(S, D, causal, 1, 2)] + [(S, D, causal, 2, two[0])] * bool(two)
+
+
+@pytest.mark.parametrize("S,D,causal,groups,H", [
+    c for S, D in [(33, 32), (65, 64), (161, 128), (256, 64), (257, 128), (287, 32), (513, 64), (545, 128), (1025, 32), (1087, 64), (1300, 32)]
+    for causal in (False, True) for c in _streamed(S, D, causal)])
+def test_streamed_keys(S, D, causal, groups, H):
+    for dtype in (F16, BF16):
+        assert P.attn_kernel_name(1, H, S, D, dtype, causal) == f"attn_fwd_halves_stream_kernel<{dtype}, {D}, {str(causal).lower()}, {groups}, 4>"
+        q, k, v = I.gen_tensors(1, H, S, D, dtype, workload_id=950 + S)
+        loud = (np.arange(S) // 32 // 3) % 2 == 1
+        step = np.where(loud[None, None, :, None], 2, -3) << (7 if dtype == BF16 else 10)     # of the exponent field: x 4, x 1/8
+        room = ((k >> 7) & 0xFF) > 16 if dtype == BF16 else (((k >> 10) & 0x1F) > 4) & (((k >> 10) & 0x1F) < 28)
+        k = np.where(room, k.astype(np.int64) + step, k).astype(np.uint16)
+        for scale in (1 / math.sqrt(D), -1.0, 1e-4):
+            check_full(q, k, v, dtype, causal, scale, f"B1 H{H} S{S} D{D} dt{dtype} causal{causal} groups{groups} scale{scale}")
