@@ -367,7 +367,7 @@ def _streamed(S, D, causal):
     """Numbers of heads for which the library takes one and two row groups: two heads, and the least that has two groups (none
     where tiles of 256 rows fill the chip before that)."""
     two = [h for h in range(3, 129) if "stream" in (n := P.attn_kernel_name(1, h, S, D, BF16, causal)) and n.endswith(", 2, 4>")]
-    return [(S, D, causal, 1, 2)] + [(S, D, causal, 2, two[0])] * bool(two)
+    return [(S, D, causal, 1, 2)] + [(S, D, causal, 2, h) for h in two[:1]]
 
 
 @pytest.mark.parametrize("S,D,causal,groups,H", [
