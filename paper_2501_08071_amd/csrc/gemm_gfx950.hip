@@ -47,6 +47,10 @@ __device__ __forceinline__ void wait_tile_loads() { wait_lds_dma<N>(); }
 // that a wavefront reads together land in different banks both for the 16-byte row reads and for
 // the transposing 8-byte reads.
 __device__ __forceinline__ constexpr int swz_a(int row) { return (row >> 2) & 3; }
+// The same for 16-byte reads of 16 rows and 4 chunks (lane = chunk * 16 + row).  LDS serves such a read in four parts, lanes 0-3,
+// 12-15, 20-27 the first and 4-11, 16-19, 28-31 the second, the other half alike: with this swizzle the sixteen lanes of each
+// lie in different banks.
+__device__ __forceinline__ constexpr int swz_a16(int row) { return (row >> 2) & 2; }
 template <int CHUNKS>
 __device__ __forceinline__ constexpr int swz_b(int row) {
     return CHUNKS >= 16 ? (((row & 3) << 2) | ((row >> 2) & 3))   // the low four chunk bits = 256 bytes = all banks
@@ -292,12 +296,13 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 //   * v_mfma_f32_16x16x32 with 8 x 8 accumulators: an operand read from LDS feeds eight instructions, 64 KiB of LDS reads
 //     per 32 of K and workgroup instead of 96 KiB with eight wavefronts of 64 x 128;
 //   * the accumulators are visited in a snake, so that only one of an instruction's two operands changes.
-// 4096 x 4096 x 4096, N(0,1): 96 to 107 us over the boxes seen = 1290 to 1430 TFLOP/s, 8192 cubed 785 to 801 us = 1370 to
-// 1400 TFLOP/s (113 to 121 and 844 us with eight wavefronts of 64 x 128, two groups alternating between LDS reads and matrix
-// instructions).  A wavefront lives 173.5 k cycles at 4096 cubed: 1260 per block of 32 of K, 1024 of them matrix instructions (130 with
-// an LDS bank conflict), and 8.6 k for the way out.
-// Nothing but the order of issue keeps the matrix pipe fed: the operands of block kb + 1 are read under the 64 matrix
-// instructions of block kb, one LDS read per two of them, then the loads of block kb + NST - 1.
+// Nothing but the order of issue keeps the matrix pipe fed: under the 64 matrix instructions of block kb the operands of block
+// kb + 1 are read, one LDS read per two of them, and the eight loads of block kb + NST - 1 issued, one per eight of them, evenly over
+// the block.  (All within the first sixteen instructions, where the reads are too, they come in bursts from all compute units at
+// once: 4096 cubed 104.5 us in bursts, 99.2 evenly; 8192 cubed 817 and 749; 2 x 3000 cubed 154 and 138; 5000 x 4104, K = 1000, 65.5 and 59.4,
+// bfloat16.  A fifth stage: 0.5 to 3 % slower.  v_mfma_f32_32x32x16 with 4 x 4 accumulators instead: 109 and 826, 147, 62.)
+// N(0,1), over the boxes seen: 4096 cubed 92 to 104 us = 1320 to 1490 TFLOP/s, 8192 cubed 749 to 763 = 1440 to 1470 (in bursts 96 to
+// 107 and 785 to 817; with eight wavefronts of 64 x 128 113 to 121 and 844).
 template <int DT, bool KTAIL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, uint16_t* __restrict__ C, int M,
@@ -307,7 +312,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     // LDS: the a tiles of all stages, then the b tiles: every read is one base register plus a 16-bit immediate
     constexpr int A_TILE = 256 * 64, B_ROWB = 512, B_TILE = 32 * B_ROWB, B_BASE = NST * A_TILE;
     constexpr int LA = 4, LB = 4, IPS = LA + LB;   // load instructions (1 KiB) per stage and wavefront
-    static_assert(NST >= 3 && NST % 2 == 0 && NST * (A_TILE + B_TILE) <= 160 * 1024, "stages");
+    static_assert(NST >= 3 && NST % 2 == 0 && IPS == 8 && NST * (A_TILE + B_TILE) <= 160 * 1024, "stages");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -333,8 +338,8 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
         for (int j = 0; j < LA; ++j) {
             const int r = 16 * (wave * LA + j) + lane / 4, pos = lane % 4;
             const int rr = r < M - 1 - m0 ? r : M - 1 - m0;
-            goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a(r)) << 3)) * 2u;
-            if constexpr (KTAIL) tail_a[j] = 8 * (pos ^ swz_a(r)) < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
+            goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a16(r)) << 3)) * 2u;
+            if constexpr (KTAIL) tail_a[j] = 8 * (pos ^ swz_a16(r)) < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
         }
 #pragma unroll
         for (int j = 0; j < LB; ++j) {
@@ -369,7 +374,7 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
     // a: row l16 of a block of 16, chunk g.  b^T: lane addresses 8 bytes of row (k) 8 g + 4 hi + x, elements (n) 4 y .. +3
     // of a block of 16 columns; the transposing read hands lane l the four k of column l % 16.  Two neighbouring blocks
     // of columns differ in one bit of the swizzled chunk index, further ones by a constant.
-    const uint32_t a_addr = lds0 + (wm * 128 + l16) * 64 + ((g ^ swz_a(l16)) << 4);
+    const uint32_t a_addr = lds0 + (wm * 128 + l16) * 64 + ((g ^ swz_a16(l16)) << 4);
     uint32_t b_addr[2][8];
     {
         const int x = l16 >> 2, y = l16 & 3;
@@ -428,9 +433,10 @@ void gemm_lrelu_wide_kernel(const uint16_t* __restrict__ A, const uint16_t* __re
             constexpr int U = decltype(un)::value;
             constexpr int i = U / 8, j = i % 2 == 0 ? U % 8 : 7 - U % 8;
             acc[i][j] = E::mfma16(ops[PH % 2].b[i], ops[PH % 2].a[j], acc[i][j]);
+            __builtin_amdgcn_sched_barrier(0);
             if constexpr (U % 2 == 1 && U < 48) read_one(ops[(PH + 1) % 2], std::integral_constant<int, U / 2>{}, (PH + 1) % NST);
-            if constexpr (U % 2 == 0 && U / 2 < IPS) {
-                constexpr int P = U / 2;
+            if constexpr (U % 8 == 4) {
+                constexpr int P = U / 8;
                 if constexpr (P < LA) issue_a(kc, P, (PH + NST - 1) % NST);
                 else issue_b(kc, P - LA, (PH + NST - 1) % NST);
             }

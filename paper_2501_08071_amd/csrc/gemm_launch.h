@@ -22,6 +22,9 @@ constexpr int gemm_pieces(int x, int t) { return (int)(((unsigned)x + (unsigned)
 // 27 35; K = 2048 the same way).  Except few rows with a long K, where what counts is how often a is read, once per column of
 // tiles (us with 128 and 64: 4 x 64 x 8192, K = 512 9.5 9.1, 1024 14.6 15.0, 4096 54 69; 232 x 33 x 232, K = 1024 29 33).  A problem that fits the chip in one round of 32 x 32 tiles and has a K worth splitting
 // takes those.
+// And 256 x 256 already where 128 x 128 tiles would begin a second round of the chip (two to a compute unit, 512) and K is
+// long enough to matter (us with 128 and 256: 2816 x 3072, K = 1024, 528 of them, 29.0 26.1; 3072 x 3072, K = 2048, 50 43, K = 4096, 93 75; 2 x 2048 x 2304, K =
+// 3000, 86 66; but 4096 x 2048, K = 1024, 512 of them, 22.9 25.5; 3072 x 3584, K = 256, 14.0 14.4).
 #ifndef GEMM_SK_TILES
 #define GEMM_SK_TILES 256
 #endif
@@ -29,7 +32,7 @@ inline int gemm_tile_of(int batch, int M, int N, int K) {
     auto tiles = [&](int t) { return (long long)batch * gemm_pieces(M, t) * gemm_pieces(N, t); };
     if (tiles(32) <= GEMM_SK_TILES && K >= 256) return 5;
     const int largest = N <= 64 || (M <= 64 && K < 768) ? 64 : N <= 128 || M <= 128 ? 128 : 256;
-    return largest == 256 && tiles(256) >= 192 ? 1 : largest >= 128 && tiles(128) >= 192 ? 2 : 3;
+    return largest == 256 && (tiles(256) >= 192 || (tiles(128) > 512 && K >= 512)) ? 1 : largest >= 128 && tiles(128) >= 192 ? 2 : 3;
 }
 
 // 64 x 64 tiles: six LDS stages instead of four?  A block is two matrix instructions per wavefront, so the loads' latency

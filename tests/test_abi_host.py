@@ -233,3 +233,11 @@ def test_streamed_problems_by_size(P):
         assert groups(12, 1024, D, True) == 1 and groups(16, 1024, D, True) == (1 if D == 128 else 2)
         assert groups(24, 1000, D, True) == 2 and groups(24, 999, D, True) == 0 and groups(24, 1025, D, True) == 0
         assert groups(128, 128, D, True) == 2
+
+
+def test_gemm_second_round_of_middle_tiles(P):
+    """256 x 256 tiles as soon as 128 x 128 ones would begin a second round of the chip, if K is long."""
+    for dt in (0, 1):
+        assert P.gemm_path(1, 2816, 3072, 1024, dt) == 1 and P.gemm_path(1, 4096, 2048, 1024, dt) == 2      # 528 and 512 of them
+        assert P.gemm_path(1, 2816, 3072, 512, dt) == 1 and P.gemm_path(1, 2816, 3072, 480, dt) == 2
+        assert P.gemm_path(4, 1300, 1536, 1024, dt) == 1 and P.gemm_path(8, 8192, 128, 1024, dt) == 2        # a tile of 256 would be half empty
