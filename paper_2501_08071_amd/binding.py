@@ -1,5 +1,8 @@
 """Thin Python binding of the C-ABI library (include/attn.h): argument marshalling only.
 
+The entry points on torch tensors go through a small module of C++ (csrc/binding_fast.cpp) where the arguments are the usual
+ones; the Python below it is for the rest, and says what is wrong with a call.
+
 PyTorch supplies device memory and the stream; every step of the attention path runs inside
 the HIP kernel.  There is no CPU or PyTorch fallback: if the shared library is missing the
 import fails loudly.
@@ -79,6 +82,21 @@ def _load() -> ctypes.CDLL:
 
 
 lib = _load()
+
+
+def _load_fast():
+    if not os.path.exists(_build.BINDING):
+        try:
+            _build.build_binding()
+        except Exception as e:
+            raise ImportError(f"{_build.BINDING} is missing and could not be built: {e}") from e
+    from . import _binding_fast
+    _binding_fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                         (lib.attn_fwd, lib.attn_fwd_o16, lib.softmax_rows_fwd, lib.rmsnorm_fwd, lib.gemm_leakyrelu_fwd)))
+    return _binding_fast
+
+
+_fast = _load_fast()
 
 
 def attn_status_str(status: int) -> str:
@@ -231,6 +249,9 @@ def attn_fwd(q, k, v, causal: bool, scale: float, o=None, lse=None, stream=None,
     stream  : a torch.cuda.Stream (default: the current stream).
     Returns (o, lse).  Asynchronous, like the C call.
     """
+    done = _fast.attn_fwd(q, k, v, causal, scale, o, lse, stream, want_lse, _o16)
+    if done is not None:
+        return done
     if q.dtype == torch.float16:
         dtype = F16
     elif q.dtype == torch.bfloat16:
@@ -309,6 +330,9 @@ def _row_args(x, y):
 
 def softmax_rows_fwd(x, y=None, stream=None):
     """softmax_rows_fwd on a torch device tensor: softmax over the last dimension, result in x's dtype."""
+    done = _fast.softmax_rows_fwd(x, y, stream)
+    if done is not None:
+        return done
     dtype, y, n_rows, n = _row_args(x, y)
     st = (stream or torch.cuda.current_stream(x.device)).cuda_stream
     rc = softmax_rows_fwd_raw(x.data_ptr(), y.data_ptr(), n_rows, n, dtype, st)
@@ -319,6 +343,9 @@ def softmax_rows_fwd(x, y=None, stream=None):
 
 def rmsnorm_fwd(x, w, eps: float, y=None, stream=None):
     """rmsnorm_fwd on torch device tensors: x [..., d], w [d] of one dtype; result in x's dtype."""
+    done = _fast.rmsnorm_fwd(x, w, eps, y, stream)
+    if done is not None:
+        return done
     dtype, y, n_rows, n = _row_args(x, y)
     if w.dtype != x.dtype or tuple(w.shape) != (n,) or not w.is_cuda or not w.is_contiguous():
         raise ValueError("w must be a contiguous device tensor [d] of x's dtype")
@@ -354,6 +381,9 @@ def gemm_leakyrelu_fwd_raw(a_ptr, b_ptr, c_ptr, batch, M, N, K, slope, dtype, st
 def gemm_leakyrelu_fwd(a, b, slope: float = 0.01, c=None, stream=None):
     """gemm_leakyrelu_fwd on torch device tensors: a [batch, M, K] (or [M, K]), b [batch, K, N] (or [K, N])
     of one 16-bit dtype; returns c [batch, M, N] (or [M, N]) in that dtype."""
+    done = _fast.gemm_leakyrelu_fwd(a, b, slope, c, stream)
+    if done is not None:
+        return done
     if a.dtype == torch.float16:
         dtype = F16
     elif a.dtype == torch.bfloat16:

@@ -10,6 +10,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattn_gfx950.so")
+BINDING = os.path.join(HERE, "_binding_fast.so")   # a Python module: torch tensors to the C ABI of LIB
 SOURCES = ["attn_fwd_gfx950.hip", "attn_fwd_stream_gfx950.hip", "attn_fwd_rows64_gfx950.hip", "attn_api.cpp", "rowops_gfx950.hip", "rowops_api.cpp",
            "gemm_gfx950.hip", "gemm_api.cpp", "probe_gfx950.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -30,7 +31,7 @@ def _run(cmd):
     res = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in res.stderr.splitlines() if NOISE not in l)
     if res.returncode != 0:
-        raise RuntimeError(f"hipcc failed:\n{' '.join(cmd)}\n{err}")
+        raise RuntimeError(f"the compiler failed:\n{' '.join(cmd)}\n{err}")
     return err
 
 
@@ -54,13 +55,30 @@ def build_lib(extra_flags=(), out: str = LIB, verbose: bool = False, jobs: int =
     return out
 
 
+def build_binding(out: str = BINDING, verbose: bool = False) -> str:
+    """The module behind the Python entry points (host code only, against torch's headers)."""
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
+           sysconfig.get_paths()["include"]]
+    # (no path to torch's libraries is recorded: the process that imports the module has loaded them)
+    err = _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+                *[a for d in inc for a in ("-isystem", d)], os.path.join(CSRC, "binding_fast.cpp"),
+                "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", out])
+    if verbose and err.strip():
+        print(err)
+    return out
+
+
 def lib_is_stale() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(BINDING):
         return True
-    t = os.path.getmtime(LIB)
+    t = min(os.path.getmtime(LIB), os.path.getmtime(BINDING))
     deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", h) for h in ("attn.h", "rowops.h", "gemm.h", "probe.h")]
     return any(os.path.getmtime(d) > t for d in deps)
 
 
 if __name__ == "__main__":
-    print(build_lib(verbose=True))
+    print(build_lib(verbose=True), build_binding(verbose=True))
