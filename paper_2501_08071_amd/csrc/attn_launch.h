@@ -103,9 +103,6 @@ inline bool attn_splits_keys(long long BH, int S, int D) {
 // 23.0 25.1, 6 x 1670 17.8 10.2 13.4, 32 x 512 9.8 9.0 7.9, 10 x 1701 18.9 16.7 14.6, 32 x 1024 14.1 19.7 15.3; D = 32, 8 x 4096 29.4 31.1
 // 23.9, 32 x 1024 11.2 15.4 11.6.  (A single tile of 128 rows keeps the kernel that attn_kernel_name has always named for it.)
 inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
-#ifdef EXP_RG
-    return EXP_RG;
-#endif
     if (attn_pick_nw(BH, S) == ATTN_NW || (BH == 1 && S <= 128)) return 0;
     const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
     if (n32 <= 256 || (causal && n32 <= 512 && (S >= 2048 || (D == 128 ? S >= 256 : n32 <= 400 && S >= 640)))) return 1;

@@ -3,13 +3,14 @@
 //
 // Matrix-core kernel (K % 8 == 0, N % 8 == 0):
 //   * a workgroup of four wavefronts (2 x 2) owns a 64 TM x 64 TN tile of c, a wavefront 32 TM x 32 TN of
-//     it as TM x TN accumulator blocks of v_mfma_f32_32x32x16; TM = TN = 2 (128 x 128) or 1 (64 x 64); larger
-//     problems: 256 x 256 tiles, gemm_lrelu_wide_kernel; gemm_tile_of chooses;
+//     it as TM x TN accumulator blocks of v_mfma_f32_32x32x16: 128 x 128, 64 x 128 or 64 x 64; eight wavefronts own 128 x 256 or
+//     256 x 256, or 128 x 128 in two parts, each with half of every block of K; larger problems: 256 x 256 tiles,
+//     gemm_lrelu_wide_kernel; gemm_tile_of chooses, and the rules behind it;
 //   * computed transposed, c^T = b^T a^T: the first operand is a 32 x 16 piece of b^T, fetched from the
 //     row-major b tile in LDS with transposing reads (ds_read_b64_tr_b16), the second 16 contiguous bytes
 //     of a row of a; a lane then holds four consecutive n of one row m of c, and the tile of c goes out
 //     through LDS so that the stores write whole rows of it;
-//   * K runs in steps of 32 through four LDS stages (64 x 64 tiles: four or six); tiles come straight from
+//   * K runs in blocks of 32 or 64 through four to six LDS stages; tiles come straight from
 //     global memory into LDS (global_load_lds_dwordx4, 16 bytes per lane, 1 KiB of consecutive LDS per
 //     instruction), all stages but one ahead, with the bank-conflict swizzle applied to the global address of each lane;
 //   * rows past M repeat the last row and column chunks past N the last chunk (results masked at the
@@ -28,7 +29,8 @@
 #include "gfx950_common.h"
 
 // LDS stages of 32 in K; all but one of them in flight ahead of the one in use.  128 x 128 tiles: 2048 cubed 21.7 us with four
-// and six, 22.4 with eight.  64 x 64 tiles take four or six (gemm_deep).
+// and six, 22.4 with eight.  64 x 64 tiles take four or six (gemm_deep), or five of 64 (gemm_long_blocks: 1024 x 1024, K = 1024 7.0 with
+// four and 6.8 with five, 512 x 1024, K = 4096 16.7 and 14.9); 64 x 128 tiles four of 64 (1000 x 1000 x 1000 9.9, with six 10.8).
 #ifndef GEMM_NST128
 #define GEMM_NST128 4
 #endif
@@ -47,6 +49,8 @@ __device__ __forceinline__ void wait_tile_loads() { wait_lds_dma<N>(); }
 // that a wavefront reads together land in different banks both for the 16-byte row reads and for
 // the transposing 8-byte reads.
 __device__ __forceinline__ constexpr int swz_a(int row) { return (row >> 2) & 3; }
+// The same for rows of a of eight chunks (blocks of 64 in K).
+__device__ __forceinline__ constexpr int swz_a8(int row) { return (row >> 1) & 7; }
 // The same for 16-byte reads of 16 rows and 4 chunks (lane = chunk * 16 + row).  LDS serves such a read in four parts, lanes 0-3,
 // 12-15, 20-27 the first and 4-11, 16-19, 28-31 the second, the other half alike: with this swizzle the sixteen lanes of each
 // lie in different banks.
@@ -79,36 +83,42 @@ __device__ __forceinline__ float leaky(float t, float slope) { return t >= 0.f ?
 
 extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
-// dynamic LDS of a kernel instance: the stages of the loop, or (if larger) the padded blocks of c on their way out
-template <int WM, int WN, int TM, int TN, int NST>
+// dynamic LDS of a kernel instance: the stages of the loop, or (if larger) the padded blocks of c on their way out and, behind
+// them, the other parts' sums
+template <int WM, int WN, int TM, int TN, int BK, int NST, int KS>
 struct GemmLds {
-    static constexpr int STAGES = NST * (32 * TM * WM * 64 + 32 * 2 * 32 * TN * WN);
+    static constexpr int STAGES = NST * 2 * BK * (32 * TM * WM + 32 * TN * WN);
     static constexpr int OUT = WM * WN * (32 * TM) * (64 * TN + 16);
-    static constexpr int BYTES = STAGES > OUT ? STAGES : OUT;
+    static constexpr int SUMS = WM * WN * TM * TN * 4096;
+    static constexpr int BYTES = STAGES > OUT + (KS - 1) * SUMS ? STAGES : OUT + (KS - 1) * SUMS;
     static_assert(BYTES <= 160 * 1024, "LDS");
 };
 
-template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
+template <int DT, int WM, int WN, int TM, int TN, int BK, int NST, int KS, bool KTAIL>
+__global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                         uint16_t* __restrict__ C, int M, int N, int K, int tiles_m,
                                                         int tiles_n, long long total, int order, float slope) {
     using E = Elem<DT>;
-    constexpr int NW = WM * WN;               // wavefronts, WM x WN over the tile
+    constexpr int NW = WM * WN;               // wavefronts of a part, WM x WN over the tile
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-    constexpr int A_TILE = BM * 64;          // BM rows of 32 elements
+    constexpr int A_ROWB = 2 * BK, A_TILE = BM * A_ROWB;   // BM rows of BK elements
     constexpr int B_ROWB = 2 * BN;           // bytes per row of the b tile
-    constexpr int B_TILE = 32 * B_ROWB;      // 32 rows (k) of BN elements
+    constexpr int B_TILE = BK * B_ROWB;      // BK rows (k) of BN elements
     constexpr int STAGE = A_TILE + B_TILE;
+    constexpr int NKS = BK / 16 / KS;        // k steps of 16 of a block per part
+    constexpr int A_LPR = BK / 8, A_RPI = 64 / A_LPR;   // as below, for the a tile
     constexpr int B_LPR = B_ROWB / 16;       // lanes (16-byte chunks) per row of the b tile
     constexpr int B_RPI = 64 / B_LPR;        // rows per load instruction
-    constexpr int LA = A_TILE / 1024 / NW, LB = B_TILE / 1024 / NW;   // load instructions per stage and wavefront
+    constexpr int LA = A_TILE / 1024 / (KS * NW), LB = B_TILE / 1024 / (KS * NW);   // load instructions per stage and wavefront
     constexpr int IPS = LA + LB;
-    static_assert(LA * NW * 1024 == A_TILE && LB * NW * 1024 == B_TILE && LA >= 1 && LB >= 1, "the wavefronts share the loads evenly");
+    static_assert(LA * KS * NW * 1024 == A_TILE && LB * KS * NW * 1024 == B_TILE && LA >= 1 && LB >= 1, "the wavefronts share the loads evenly");
     static_assert(NST * STAGE <= 160 * 1024, "LDS");
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int loader = __builtin_amdgcn_readfirstlane(tid >> 6);   // its share of the loads
+    const int part = KS == 1 ? 0 : loader / NW;                    // its k steps of every block
+    const int wave = loader - part * NW;                           // its piece of the tile
     const int l32 = lane & 31, h = lane >> 5;
     const int wm = wave % WM, wn = wave / WM;
 
@@ -117,25 +127,26 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     const uint16_t* Ab = A + ((size_t)bi * M + m0) * K;
     const uint16_t* Bb = B + (size_t)bi * K * N + n0;
     uint16_t* Cb = C + (size_t)bi * M * N;
-    const int nk = gemm_pieces(K, 32);
+    const int nk = gemm_pieces(K, BK);
+    auto swz = [](int row) { return BK == 64 ? swz_a8(row) : swz_a(row); };
 
     const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
 
     // ---- loads: byte offset of this lane's source chunk inside the tile's rows ----
-    const int kr = K - 32 * (nk - 1);   // valid k of the last block (KTAIL: 8, 16 or 24, else 32)
+    const int kr = K - BK * (nk - 1);   // valid k of the last block (KTAIL: a multiple of 8, else BK)
     uint32_t goff_a[LA], goff_b[LB], tail_a[LA], tail_b[LB];   // tail: the same for the last block, chunks past K replaced
 #pragma unroll
     for (int j = 0; j < LA; ++j) {
-        const int r = 16 * (wave * LA + j) + lane / 4, pos = lane % 4;
+        const int r = A_RPI * (loader * LA + j) + lane / A_LPR, pos = lane % A_LPR;
         const int rr = r < M - 1 - m0 ? r : M - 1 - m0;
-        goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz_a(r)) << 3)) * 2u;
-        if constexpr (KTAIL) tail_a[j] = 8 * (pos ^ swz_a(r)) < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
+        goff_a[j] = (uint32_t)(rr * K + ((pos ^ swz(r)) << 3)) * 2u;
+        if constexpr (KTAIL) tail_a[j] = 8 * (pos ^ swz(r)) < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
     }
     {
         const int nvalid = (N - n0) / 8 < BN / 8 ? (N - n0) / 8 : BN / 8;   // chunks of this tile inside the matrix
 #pragma unroll
         for (int j = 0; j < LB; ++j) {
-            const int r = B_RPI * (wave * LB + j) + lane / B_LPR, pos = lane % B_LPR;
+            const int r = B_RPI * (loader * LB + j) + lane / B_LPR, pos = lane % B_LPR;
             int ch = pos ^ swz_b<B_LPR>(r);
             ch = ch < nvalid - 1 ? ch : nvalid - 1;
             goff_b[j] = (uint32_t)(r * N + (ch << 3)) * 2u;
@@ -146,22 +157,22 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     // issues the same number of loads and the wait count is a constant
     auto issue = [&](int kb, int st) {
         const int kc = kb < nk - 1 ? kb : nk - 1;
-        const uint16_t* sa = Ab + (size_t)kc * 32;
-        const uint16_t* sb = Bb + (size_t)kc * 32 * N;
+        const uint16_t* sa = Ab + (size_t)kc * BK;
+        const uint16_t* sb = Bb + (size_t)kc * BK * N;
         const bool tail = KTAIL && kc == nk - 1;
 #pragma unroll
-        for (int j = 0; j < LA; ++j) lds_dma16(lds0 + st * STAGE + (wave * LA + j) * 1024, sa, tail ? tail_a[j] : goff_a[j]);
+        for (int j = 0; j < LA; ++j) lds_dma16(lds0 + st * STAGE + (loader * LA + j) * 1024, sa, tail ? tail_a[j] : goff_a[j]);
 #pragma unroll
-        for (int j = 0; j < LB; ++j) lds_dma16(lds0 + st * STAGE + A_TILE + (wave * LB + j) * 1024, sb, tail ? tail_b[j] : goff_b[j]);
+        for (int j = 0; j < LB; ++j) lds_dma16(lds0 + st * STAGE + A_TILE + (loader * LB + j) * 1024, sb, tail ? tail_b[j] : goff_b[j]);
     };
 
     // ---- operand addresses (stage 0, k step 0 of the b tile) ----
-    uint32_t a_addr[TM][2];
+    uint32_t a_addr[TM][NKS];
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-            a_addr[tm][ks] = lds0 + ((wm * TM + tm) * 32 + l32) * 64 + (((2 * ks + h) ^ swz_a(l32)) << 4);
+        for (int ks = 0; ks < NKS; ++ks)
+            a_addr[tm][ks] = lds0 + ((wm * TM + tm) * 32 + l32) * A_ROWB + (((2 * (part * NKS + ks) + h) ^ swz(l32)) << 4);
     // b^T operand: lane addresses 8 bytes of row (k) 8 h + 4 hi + x, elements (n) 16 g1 + 4 y .. +3 of the
     // 32-wide block; the transposing read hands lane l the four k of element n = l % 32
     uint32_t b_addr[2][TN];
@@ -173,7 +184,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
             for (int tn = 0; tn < TN; ++tn) {
                 const int row = 8 * h + 4 * hi + x;
                 const int chunk = 4 * (wn * TN + tn) + 2 * g1 + (y >> 1);
-                b_addr[hi][tn] = lds0 + A_TILE + row * B_ROWB + ((chunk ^ swz_b<B_LPR>(row)) << 4) + ((y & 1) << 3);
+                b_addr[hi][tn] = lds0 + A_TILE + (part * NKS * 16 + row) * B_ROWB + ((chunk ^ swz_b<B_LPR>(row)) << 4) + ((y & 1) << 3);
             }
     }
 
@@ -188,7 +199,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
 #pragma unroll
     for (int s = 0; s < NST - 1; ++s) issue(s, s);
 
-    // The operands of one k step (16 of the 32 of a block) of stage st
+    // The operands of one k step (16 k of a block) of stage st
     struct Ops {
         u32x4 a[TM], b[TN];
     };
@@ -202,14 +213,19 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
             o.b[tn] = u32x4{lo[0], lo[1], hi[0], hi[1]};
         }
     };
-    // the last block of a K that is not a multiple of 32: both operands' k past the end become zero (whatever was
-    // loaded in their place may be infinite)
-    auto cut_tail = [&](Ops& o, int ks) {
-        const bool past = 16 * ks + 8 * h >= kr;
+    // The last block of a K that is not a multiple of BK: both operands' k past the end become zero (whatever was loaded in their
+    // place may be infinite).  Every wavefront clears what its own loads brought, once they have landed and before the barrier
+    // behind which the block may be read: nothing of it is left in the loop.
+    auto clear_tail = [&](int st) {
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) o.a[tm] = past ? u32x4{0u, 0u, 0u, 0u} : o.a[tm];
+        for (int j = 0; j < LA; ++j) {
+            const int r = A_RPI * (loader * LA + j) + lane / A_LPR, pos = lane % A_LPR;
+            if (8 * (pos ^ swz(r)) >= kr) lds_write_b128(lds0 + st * STAGE + (loader * LA + j) * 1024 + 16 * lane, u32x4{0u, 0u, 0u, 0u});
+        }
 #pragma unroll
-        for (int tn = 0; tn < TN; ++tn) o.b[tn] = past ? u32x4{0u, 0u, 0u, 0u} : o.b[tn];
+        for (int j = 0; j < LB; ++j)
+            if (B_RPI * (loader * LB + j) + lane / B_LPR >= kr) lds_write_b128(lds0 + st * STAGE + A_TILE + (loader * LB + j) * 1024 + 16 * lane, u32x4{0u, 0u, 0u, 0u});
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
     auto multiply = [&](const Ops& o) {
 #pragma unroll
@@ -218,34 +234,32 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
             for (int tm = 0; tm < TM; ++tm) acc[tn][tm] = E::mfma(o.b[tn], o.a[tm], acc[tn][tm]);
     };
 
-    // Block kb: its first k step runs on operands read during block kb-1 (`ahead`), its second on operands
-    // read under the first, and under the second the first operands of block kb+1 are read: the matrix
+    // Block kb: its first k step runs on operands read during block kb-1 (`ahead`), every other on operands
+    // read under the one before, and under the last the first operands of block kb+1 are read: the matrix
     // pipe never waits for an LDS round trip behind a barrier.  For that, block kb+1 must be complete one
     // barrier early: every wavefront checks its share of it before the barrier of block kb.
     Ops ahead;
     wait_tile_loads<(NST - 2) * IPS>();
+    if (KTAIL && nk == 1) clear_tail(0);
     __syncthreads();
     read_ops(ahead, 0, 0);
     auto step = [&](int kb, auto phase) {
         constexpr int PH = decltype(phase)::value;
         // blocks up to kb+1 have landed when at most the loads of the NST-3 later blocks are still out
         wait_tile_loads<(NST - 3) * IPS>();
+        if (KTAIL && kb == nk - 2) clear_tail((PH + 1) % NST);
         asm volatile("s_barrier" ::: "memory");
         // ... for everybody, and everybody is done with block kb-1: its stage takes block kb+NST-1
         issue(kb + NST - 1, (PH + NST - 1) % NST);
-        Ops second;
-        read_ops(second, PH * STAGE, 1);
-        if (KTAIL && kb == nk - 1) {
-            cut_tail(ahead, 0);
-            cut_tail(second, 1);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(ahead);
-        __builtin_amdgcn_sched_barrier(0);
-        read_ops(ahead, ((PH + 1) % NST) * STAGE, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(second);
-        __builtin_amdgcn_sched_barrier(0);
+        [&]<int... S>(std::integer_sequence<int, S...>) {
+            ([&] {
+                const Ops now = ahead;
+                read_ops(ahead, (S + 1 < NKS ? PH : (PH + 1) % NST) * STAGE, (S + 1) % NKS);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(now);
+                __builtin_amdgcn_sched_barrier(0);
+            }(), ...);
+        }(std::make_integer_sequence<int, NKS>{});
     };
     static_assert(NST >= 3, "one block in use, one read ahead, at least one in flight");
     for (int k0 = 0; k0 < nk; k0 += NST) {
@@ -262,9 +276,32 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_lrelu_kernel(const uint16_t
     // bank conflicts, and reads it back with 4 TN lanes side by side on a row: a store instruction then writes
     // whole rows of the block, 64 TN bytes each.
     __syncthreads();
+    if constexpr (KS > 1) {
+        // the sums of the other parts go through LDS, 16 bytes per lane and access, and are added in the order of the parts
+        using Lds = GemmLds<WM, WN, TM, TN, BK, NST, KS>;
+        auto at = [&](int p, int i) { return (f32x4*)(smem + Lds::OUT + (p - 1) * Lds::SUMS + ((wave * TM * TN * 4 + i) * 64 + lane) * 16); };
+        if (part > 0) {
+#pragma unroll
+            for (int i = 0; i < TM * TN * 4; ++i) {
+                const f32x16& t = acc[i / 4 / TM][i / 4 % TM];
+                const int r = 4 * (i % 4);
+                *at(part, i) = f32x4{t[r], t[r + 1], t[r + 2], t[r + 3]};
+            }
+        }
+        __syncthreads();
+        if (part > 0) return;
+#pragma unroll
+        for (int p = 1; p < KS; ++p)
+#pragma unroll
+            for (int i = 0; i < TM * TN * 4; ++i) {
+                const f32x4 u = *at(p, i);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[i / 4 / TM][i / 4 % TM][4 * (i % 4) + e] += u[e];
+            }
+    }
     {
         constexpr int RW = 32 * TM, RB = 64 * TN, RS = RB + 16;
-        static_assert(NW * RW * RS <= GemmLds<WM, WN, TM, TN, NST>::BYTES, "LDS for the way out");
+        static_assert(NW * RW * RS <= GemmLds<WM, WN, TM, TN, BK, NST, KS>::BYTES, "LDS for the way out");
         uint8_t* reg = smem + wave * (RW * RS);
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
@@ -765,11 +802,11 @@ hipError_t launch_grid(const GemmLaunch& g, const void* fn, int bm, int bn, int 
     return hipLaunchKernel(fn, dim3(grid.x, grid.y), dim3(threads), args, lds_bytes, (hipStream_t)g.stream);
 }
 
-template <int DT, int WM, int WN, int TM, int TN, int NST, bool KTAIL>
+template <int DT, int WM, int WN, int TM, int TN, int BK, int NST, int KS, bool KTAIL>
 hipError_t launch_tiles(const GemmLaunch& g) {
     static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
-    return launch_grid(g, reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN, NST, KTAIL>), 32 * TM * WM, 32 * TN * WN,
-                       WM * WN * 64, (unsigned)GemmLds<WM, WN, TM, TN, NST>::BYTES, told);
+    return launch_grid(g, reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN, BK, NST, KS, KTAIL>), 32 * TM * WM, 32 * TN * WN,
+                       KS * WM * WN * 64, (unsigned)GemmLds<WM, WN, TM, TN, BK, NST, KS>::BYTES, told);
 }
 
 // 256 x 256 tiles
@@ -789,10 +826,16 @@ template <int DT, bool KTAIL>
 hipError_t launch_tile_size(const GemmLaunch& g) {
     switch (gemm_tile_of(g.batch, g.M, g.N, g.K)) {
         case 1:                                                                // 256 x 256, eight wavefronts of 64 x 128 or four of 128 x 128
-            return gemm_eight_waves(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 4, 2, 2, 4, 4, KTAIL>(g) : launch_wide<DT, KTAIL>(g);
-        case 2: return launch_tiles<DT, 2, 2, 2, 2, GEMM_NST128, KTAIL>(g);   // 128 x 128, four wavefronts of 64 x 64
-        case 3:                                                               // 64 x 64, four wavefronts of 32 x 32
-            return gemm_deep(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 2, 2, 1, 1, 6, KTAIL>(g) : launch_tiles<DT, 2, 2, 1, 1, 4, KTAIL>(g);
+            return gemm_eight_waves(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 4, 2, 2, 4, 32, 4, 1, KTAIL>(g) : launch_wide<DT, KTAIL>(g);
+        case 2:
+            if (gemm_tiles_128x256(g.batch, g.M, g.N, g.K)) return launch_tiles<DT, 2, 4, 2, 2, 32, 4, 1, KTAIL>(g);   // eight wavefronts of 64 x 64
+            if (gemm_two_parts(g.batch, g.M, g.N, g.K)) return launch_tiles<DT, 2, 2, 2, 2, 64, 4, 2, KTAIL>(g);       // twice four of 64 x 64
+            return launch_tiles<DT, 2, 2, 2, 2, 32, GEMM_NST128, 1, KTAIL>(g);                                         // four of 64 x 64
+        case 3:
+            if (gemm_tiles_64x128(g.batch, g.M, g.N, g.K))                                                            // four of 32 x 64
+                return g.K % 64 != 0 ? launch_tiles<DT, 2, 2, 1, 2, 64, 4, 1, true>(g) : launch_tiles<DT, 2, 2, 1, 2, 64, 4, 1, false>(g);
+            if (gemm_long_blocks(g.batch, g.M, g.N, g.K)) return launch_tiles<DT, 2, 2, 1, 1, 64, 5, 1, false>(g);    // four of 32 x 32
+            return gemm_deep(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 2, 2, 1, 1, 32, 6, 1, KTAIL>(g) : launch_tiles<DT, 2, 2, 1, 1, 32, 4, 1, KTAIL>(g);
         default: return launch_splitk<DT, KTAIL ? 1 : 0>(g);                  // 32 x 32, K split over the four wavefronts
     }
 }

@@ -15,6 +15,16 @@ struct GemmLaunch {
 // Pieces of t that cover x, for any x >= 0 (as int, x + t - 1 would overflow where x is near 2^31).
 constexpr int gemm_pieces(int x, int t) { return (int)(((unsigned)x + (unsigned)(t - 1)) / (unsigned)t); }
 
+// 128 x 128 with fewer than 192 of them, too?  Where tiles of 64 x 128 (below) would begin a second round and K is long enough (us with 128 and
+// 64, 140 to 191 of them: 1536 x 1536, K = 4096 32 50; 1599 x 1696, K = 1408 14.7 20.4; 2 x 3476 x 288, K = 560 9.5 11.1; 2370 x 1216, K = 384
+// 7.3 7.9; but 4 x 846 x 576, K = 384, 140 of them, 6.7 5.5; 4 x 324 x 1408, K = 448, 132, 7.2 6.9; 2761 x 704, K = 608,
+// 132, 8.6 7.3), unless a quarter more of them lies outside c
+// (8 x 556 x 448, K = 1536 14.9 13.7; 8 x 398 x 544, K = 1560 16.5 15.7.)
+inline bool gemm_middle_round(int batch, int M, int N, int K) {
+    auto tiles = [&](int bm, int bn) { return (long long)batch * gemm_pieces(M, bm) * gemm_pieces(N, bn); };
+    return K >= 384 && tiles(64, 128) > 256 && (K >= 640 || tiles(128, 128) >= 152) && 16 * tiles(128, 128) <= 5 * tiles(64, 64);
+}
+
 // Tiles of c for a problem whose rows are 16-byte aligned: 1: 256 x 256, 2: 128 x 128, 3: 64 x 64, 5: 32 x 32 with K
 // split over the wavefronts of a workgroup.  The largest tile that still gives three quarters of the 256 compute units
 // a workgroup, and that is not more than half empty: a tile costs the same however little of it lies inside c (us with 256,
@@ -32,7 +42,48 @@ inline int gemm_tile_of(int batch, int M, int N, int K) {
     auto tiles = [&](int t) { return (long long)batch * gemm_pieces(M, t) * gemm_pieces(N, t); };
     if (tiles(32) <= GEMM_SK_TILES && K >= 256) return 5;
     const int largest = N <= 64 || (M <= 64 && K < 768) ? 64 : N <= 128 || M <= 128 ? 128 : 256;
-    return largest == 256 && (tiles(256) >= 192 || (tiles(128) > 512 && K >= 512)) ? 1 : largest >= 128 && tiles(128) >= 192 ? 2 : 3;
+    return largest == 256 && (tiles(256) >= 192 || (tiles(128) > 512 && K >= 512)) ? 1 : largest >= 128 && (tiles(128) >= 192 || gemm_middle_round(batch, M, N, K)) ? 2 : 3;
+}
+
+// The loads of a tile, not its matrix instructions, are what most problems of one or two rounds of the chip wait for: a compute unit
+// takes 16 bytes per lane into LDS at 35 to 60 bytes per cycle, half of that where the rows are short and not aligned to cache lines (measured
+// with the loads alone).  So: as few bytes as possible for a round, and rows of a in pieces of 128 bytes (blocks of 64 in K) where
+// they start at multiples of that.
+
+// Instead of 128 x 128: 128 x 256 with eight wavefronts, where the first begin a second round and the second do not?  (us with 128 x 128 and 128 x
+// 256: 3072 x 1536, K = 3072 50 40; 2 x 2048 x 2048, K = 1000 26 23; 2703 x 2432, K = 448 12.3 11.6; 4 x 522 x 2784, K = 416 11.7 11.1; 3770 x
+// 864 x 2, K = 480 13.1 12.2.  Short sums are start and end: 2 x 1292 x 3680, K = 96 10.8 12.3.  A
+// single column of them, where nobody shares rows of a, pays for a larger part of the second round only: 8 x 2297 x 256, K = 3200, 288 of 128 x 128, 53 61; 4 x 4271 x
+// 256, K = 2400, 272, 42 45; 8 x 2531 x 256, K = 2816, 320, 0.84 of the time.)
+inline bool gemm_tiles_128x256(int batch, int M, int N, int K) {
+    const long long columns = (long long)batch * gemm_pieces(M, 128);
+    return N > 128 && K >= 384 && columns * gemm_pieces(N, 128) > (N > 256 ? 256 : 300) && columns * gemm_pieces(N, 256) <= 256;
+}
+
+// 128 x 128 in one round: eight wavefronts in two parts, each with half of every block of 64 in K, instead of four with blocks of 32?  The
+// parts' sums are added at the end, worth it for a long K (us with four and eight: 2 x 3374 x 384, K = 3328 30.5 25.4; 3978 x 216 x 4, K =
+// 2896 48.6 42.0; 3000 x 1024, K = 2040 23.3 20.6; 2644 x 1440, K = 1472 17.0 16.2; 2285 x 1280, K = 1248 14.1 15.1).  Not for odd multiples of 32,
+// whose last block is half empty (4 x 224 x 3168, K = 1312 14.6 15.5; 4 x 1912 x 512, K = 3872 34.2 35.9).
+inline bool gemm_two_parts(int batch, int M, int N, int K) {
+    return (long long)batch * gemm_pieces(M, 128) * gemm_pieces(N, 128) <= 256 && K >= 1280 && K % 64 != 32;
+}
+
+// Instead of 64 x 64: 64 x 128, blocks of 64 in K, where the first begin a second round and the second do not (gemm_tile_of takes 128 x
+// 128 where they would, from K = 640 on)?  (us with 64 x 64 and 64 x 128: 2 x 777 x 1000, K = 1000 13.2 10.4; 1304 x 1304, K = 1304 16.5 12.5; 2107 x 720, K =
+// 2968 31.7 21.2; 2 x 338 x 2688, K = 640 7.8 7.1; 456 x 2304, K = 576 5.9 6.2; 4 x 594 x 416, K = 512 5.5 5.9;
+// 802 x 1536, K = 608, whose last block is half empty, 6.7 7.1.)  Where it takes three columns for five and the like, only for a long K (N = 320: 4071, K = 704 6.3
+// 6.8; 8 x 431, K = 2016 11.5 13.7; 4 x 1272 x 312, K = 3968 0.73 of the time; N = 152, K = 1848 0.77).
+inline bool gemm_tiles_64x128(int batch, int M, int N, int K) {
+    const long long columns = (long long)batch * gemm_pieces(M, 64);
+    if (N > 192 && 12 * gemm_pieces(N, 128) > 7 * gemm_pieces(N, 64) && K < 2560) return false;
+    return N > 64 && (M > 64 || K >= 768) && K >= (K % 64 == 32 ? 800 : 600) && columns * gemm_pieces(N, 64) > 256 && columns * gemm_pieces(N, 128) <= 256;
+}
+
+// 64 x 64 with at most one tile per compute unit: five stages of 64 in K instead of six of 32?  (us with 32 and 64: 512 x 1024, K =
+// 4096 18.1 14.9; 4 x 512 x 512, K = 2048 11.6 9.7; 4 x 242 x 832, K = 3328 14.2 12.6; 1024 x 1024, K = 1024 7.4 6.8; 248 x 2688, K = 640 4.8
+// 4.7.  K not a multiple of 64 gains nothing: 896 x 424, K = 1712, and 1724 x 160, K = 3600, 1.00; 1100 x 640, K = 928 6.1 6.6.)
+inline bool gemm_long_blocks(int batch, int M, int N, int K) {
+    return K >= 640 && K % 64 == 0 && (long long)batch * gemm_pieces(M, 64) * gemm_pieces(N, 64) <= 256;
 }
 
 // 64 x 64 tiles: six LDS stages instead of four?  A block is two matrix instructions per wavefront, so the loads' latency

@@ -102,6 +102,7 @@ __device__ __forceinline__ u32x2 lds_read_tr16(uint32_t addr) {
     return __builtin_bit_cast(u32x2, t);
 }
 __device__ __forceinline__ u32x4 lds_read_b128(uint32_t addr) { return *(const LDS_AS u32x4*)(uintptr_t)addr; }
+__device__ __forceinline__ void lds_write_b128(uint32_t addr, u32x4 v) { *(LDS_AS u32x4*)(uintptr_t)addr = v; }
 
 // 16 bytes per lane from global memory straight into LDS: lane l's data lands at lds_base + 16 l
 // (lds_base wave-uniform, a multiple of 16).  Written as asm so that the compiler's wait-count

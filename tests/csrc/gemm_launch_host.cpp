@@ -18,6 +18,10 @@ int tile_in_list(int t, int tiles_m, int tiles_n, int join) {
 int in_order(int N, int K, int total) { return gemm_in_order(N, K, total); }
 int order_of(int batch, int M, int N, int K) { return gemm_order_of(gemm_grid_of(batch, M, N, 256, 256), N, K); }
 int eight_waves(int batch, int M, int N, int K) { return gemm_eight_waves(batch, M, N, K); }
+int tiles_128x256(int batch, int M, int N, int K) { return gemm_tiles_128x256(batch, M, N, K); }
+int two_parts(int batch, int M, int N, int K) { return gemm_two_parts(batch, M, N, K); }
+int tiles_64x128(int batch, int M, int N, int K) { return gemm_tiles_64x128(batch, M, N, K); }
+int long_blocks(int batch, int M, int N, int K) { return gemm_long_blocks(batch, M, N, K); }
 int deep(int batch, int M, int N, int K) { return gemm_deep(batch, M, N, K); }
 int per_element(int batch, int M, int N, int K) { return gemm_per_element(batch, M, N, K); }
 }

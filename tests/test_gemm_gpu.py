@@ -190,6 +190,34 @@ def test_sizes_that_fit_no_tile(P, shape, dtype):
     run(P, *shape, dtype)
 
 
+# the tiles between the square ones, ragged in M and N, whole and cut last blocks of 32 and 64 in K (remainders 0, 8, 16, 24, 32, 40 and 56 of 64): 64 x 128,
+# 128 x 128 in two parts, 128 x 256, 64 x 64 with blocks of 64 (K a multiple of it)
+BETWEEN = [(1, 1090, 1000, 600), (1, 1090, 968, 800), (2, 577, 1032, 640), (1, 1089, 1000, 616), (1, 1500, 1416, 1288), (1, 1537, 1480, 1280), (1, 1500, 1416, 1336),
+           (2, 1700, 1288, 400), (1, 2049, 2056, 384), (1, 2049, 2056, 392), (1, 520, 520, 640), (2, 300, 520, 704)]
+
+
+@pytest.mark.parametrize("dtype", [I.F16, I.BF16])
+@pytest.mark.parametrize("shape", BETWEEN)
+def test_tiles_between_the_square_ones(P, shape, dtype):
+    run(P, *shape, dtype)
+
+
+@pytest.mark.parametrize("shape", [(1, 576, 520, 264), (1, 1090, 1000, 600), (1, 1500, 1416, 1288), (2, 1700, 1288, 400)])
+def test_an_infinite_element_stays_in_its_row_and_column(P, shape):
+    """What a cut last block reads in place of k past the end is the rows' own first elements of the block, and the next row's: none of
+    it may count."""
+    batch, M, N, K = shape
+    first = K // 64 * 64       # the last block's first k (of 32: the same where the remainder is below 32)
+    a, b = torch.ones((batch, M, K), dtype=torch.float16, device="cuda"), torch.ones((batch, K, N), dtype=torch.float16, device="cuda")
+    a[0, 5, first] = float("inf")
+    b[0, first, 9] = float("inf")
+    c = P.gemm_leakyrelu_fwd(a, b, 0.01)
+    want = torch.full((batch, M, N), float(K), dtype=torch.float16, device="cuda")
+    want[0, 5, :] = float("inf")
+    want[0, :, 9] = float("inf")
+    assert torch.equal(c, want)
+
+
 @pytest.mark.parametrize("K,N", [(40, 64), (37, 33)])
 def test_what_lies_past_a_cut_k_is_not_read_into_the_sums(P, K, N):
     """Rows of a and b next to each other in memory: an infinite element in one row shows in that row of c only."""

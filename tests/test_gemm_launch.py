@@ -117,6 +117,22 @@ def test_deep_pipelines_are_for_long_sums(L):
         assert L.deep(*shape) == want, shape
 
 
+def test_one_round_of_larger_tiles(L):
+    """Tiles between the square ones, on either side of each condition."""
+    for shape, want in (((1, 1536, 1536, 4096), 2), ((1, 1536, 1536, 640), 2), ((1, 1536, 1536, 632), 3), ((1, 1664, 1536, 384), 2), ((1, 1664, 1536, 376), 3),
+                        ((8, 556, 448, 1536), 3), ((1, 1536, 1280, 4096), 3), ((2, 777, 1000, 1000), 3)):
+        assert L.tile_of(*shape) == want, shape
+    for shape, want in (((1, 3072, 1536, 3072), 1), ((1, 3072, 1536, 376), 0), ((1, 2048, 2048, 2048), 0), ((1, 2176, 4096, 1000), 0), ((20, 1792, 128, 1024), 0)):
+        assert L.tiles_128x256(*shape) == want, shape
+    for shape, want in (((1, 1536, 1536, 1280), 1), ((1, 1536, 1536, 1272), 0), ((1, 1536, 1536, 1288), 1), ((1, 1536, 1536, 1312), 0), ((1, 2176, 2048, 2048), 0)):
+        assert L.two_parts(*shape) == want, shape
+    for shape, want in (((2, 777, 1000, 1000), 1), ((2, 777, 1000, 592), 0), ((2, 777, 1000, 600), 1), ((2, 777, 1000, 608), 0), ((20, 1792, 128, 1024), 0), ((1, 1000, 1000, 1000), 0), ((1, 1536, 1536, 1024), 0), ((1, 20000, 64, 1024), 0),
+                        ((8, 64, 4096, 760), 0), ((5, 64, 4096, 768), 1), ((1, 4071, 320, 704), 0), ((1, 4071, 320, 2560), 1)):
+        assert L.tiles_64x128(*shape) == want, shape
+    for shape, want in (((4, 512, 512, 2048), 1), ((4, 512, 512, 2056), 0), ((4, 512, 512, 576), 0), ((1, 1024, 1088, 1024), 0)):
+        assert L.long_blocks(*shape) == want, shape
+
+
 def test_few_products_take_one_thread_per_element(L):
     """Sizes that fit no tile, on either side by a factor in the time measured."""
     for shape in ((4000, 1, 9, 3), (4000, 1, 35, 17), (1, 1, 65537, 7), (1, 33, 33, 1), (1, 1500, 1500, 8), (16384, 8, 64, 8), (1, 1 << 20, 8, 8),
