@@ -54,8 +54,8 @@ int gemm_leakyrelu_fwd(const void* a, const void* b, void* c, int batch, int M, 
 /* Which code path serves this shape: 1, 2, 3 = matrix cores with tiles of 256 x 256, 128 x 128 (or 128 x
  * 256), 64 x 64 (or 64 x 128): about the largest that still gives most of the chip a workgroup and is at least half filled by c; 5 = matrix cores with tiles of 32 x 32 and K split over
  * the wavefronts of a workgroup (small problems with K >= 256, the paper's 512 x 512 x 2048 among them); 4 = sizes
- * that fit no tile: K % 32 != 0 or N % 8 != 0 (one of those kernels with the last block of K cut, or the 32 x 32 one
- * with unaligned loads, or one thread per element of c); 0 = the shape or dtype is not accepted. */
+ * that fit no tile: K % 32 != 0 or N % 8 != 0 (one of those kernels with the last block of K cut, or 64 x 64 or 32 x 32
+ * tiles with unaligned loads, or one thread per element of c); 0 = the shape or dtype is not accepted. */
 int gemm_path(int batch, int M, int N, int K, int dtype);
 
 /* Static, NUL-terminated description of a status code; never NULL. */

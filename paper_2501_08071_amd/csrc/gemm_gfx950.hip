@@ -18,7 +18,7 @@
 // Small problems (at most 256 tiles of 32 x 32, K >= 256): 32 x 32 tiles with K split over the four wavefronts of
 // the workgroup, see gemm_lrelu_splitk_kernel.
 // K % 32 != 0: the same kernels with the last block cut (K % 8 == 0), or, where rows of a or b do not start at 16-byte
-// aligned addresses, the 32 x 32 kernel with its loads through registers; either way one thread per element where there are
+// aligned addresses, 64 x 64 tiles or the 32 x 32 kernel with their loads through registers; either way one thread per element where there are
 // too few products to pay for tiles, see gemm_lrelu_element_kernel.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -94,7 +94,13 @@ struct GemmLds {
     static_assert(BYTES <= 160 * 1024, "LDS");
 };
 
-template <int DT, int WM, int WN, int TM, int TN, int BK, int NST, int KS, bool KTAIL>
+// ANY: rows of a and b that start at any even address (N >= 8; offsets in a tile below 2^32).  Loads into LDS need aligned addresses, so the
+// blocks go through registers, 16 bytes per lane as they come, NST blocks ahead, and from there to the same places in LDS.  Bound by
+// those loads: a piece of a row that begins inside a cache line costs two lines (2 x 320 x 2426, K = 1288: 17.7 us; 32 x 32 tiles with K
+// split 27.7).  Four stages of LDS and registers: 12 % slower, fewer workgroups fit; 64 x 128 tiles 25 %, 128 x 128 60 %.
+// What follows a row's end is the next row's and counts for columns of c that are not stored; in the last block, the only one with k
+// past the end, it is zeroed in the registers, and nothing past a matrix's end is read.
+template <int DT, int WM, int WN, int TM, int TN, int BK, int NST, int KS, bool KTAIL, bool ANY>
 __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B,
                                                         uint16_t* __restrict__ C, int M, int N, int K, int tiles_m,
                                                         int tiles_n, long long total, int order, float slope) {
@@ -143,7 +149,8 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
         if constexpr (KTAIL) tail_a[j] = 8 * (pos ^ swz(r)) < kr ? goff_a[j] : (uint32_t)(rr * K) * 2u;
     }
     {
-        const int nvalid = (N - n0) / 8 < BN / 8 ? (N - n0) / 8 : BN / 8;   // chunks of this tile inside the matrix
+        const int inside = ANY ? (N - n0 + 7) / 8 : (N - n0) / 8;
+        const int nvalid = inside < BN / 8 ? inside : BN / 8;   // chunks of this tile inside the matrix
 #pragma unroll
         for (int j = 0; j < LB; ++j) {
             const int r = B_RPI * (loader * LB + j) + lane / B_LPR, pos = lane % B_LPR;
@@ -165,6 +172,52 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
 #pragma unroll
         for (int j = 0; j < LB; ++j) lds_dma16(lds0 + st * STAGE + A_TILE + (loader * LB + j) * 1024, sb, tail ? tail_b[j] : goff_b[j]);
     };
+
+    // ANY: the same by way of registers
+    struct Blk {
+        u32x4 a[LA], b[LB];
+    };
+    auto load_block = [&](Blk& x, int kb) {
+        if (kb >= nk) return;
+        const char* sa = (const char*)(Ab + (size_t)kb * BK);
+        const char* sb = (const char*)(Bb + (size_t)kb * BK * N);
+        if (kb < nk - 1) {
+#pragma unroll
+            for (int j = 0; j < LA; ++j) __builtin_memcpy(&x.a[j], sa + goff_a[j], 16);
+#pragma unroll
+            for (int j = 0; j < LB; ++j) __builtin_memcpy(&x.b[j], sb + goff_b[j], 16);
+            return;
+        }
+        // 16 bytes at p, of which the first n elements (any number) count
+        auto cut_load = [](const char* p, long long n) {
+            u32x4 v = {0u, 0u, 0u, 0u};
+            if (n >= 8) {
+                __builtin_memcpy(&v, p, 16);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (e < n) v[e / 2] |= (uint32_t)((const uint16_t*)p)[e] << (16 * (e % 2));
+            }
+            return v;
+        };
+#pragma unroll
+        for (int j = 0; j < LA; ++j) {
+            const int row = A_RPI * (loader * LA + j) + lane / A_LPR;
+            x.a[j] = cut_load(sa + goff_a[j], kr - 8 * ((lane % A_LPR) ^ swz(row)));
+        }
+#pragma unroll
+        for (int j = 0; j < LB; ++j) {
+            const int row = B_RPI * (loader * LB + j) + lane / B_LPR;
+            x.b[j] = cut_load(sb + goff_b[j], row < kr ? (long long)kr * N - n0 - (long long)(goff_b[j] / 2) : 0);   // up to the matrix's end
+        }
+    };
+    auto store_block = [&](const Blk& x, int st) {
+#pragma unroll
+        for (int j = 0; j < LA; ++j) lds_write_b128(lds0 + st * STAGE + (loader * LA + j) * 1024 + 16 * lane, x.a[j]);
+#pragma unroll
+        for (int j = 0; j < LB; ++j) lds_write_b128(lds0 + st * STAGE + A_TILE + (loader * LB + j) * 1024 + 16 * lane, x.b[j]);
+    };
+    Blk x[ANY ? NST : 1];
 
     // ---- operand addresses (stage 0, k step 0 of the b tile) ----
     uint32_t a_addr[TM][NKS];
@@ -196,8 +249,13 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[tn][tm][r] = 0.f;
 
+    if constexpr (ANY) {
 #pragma unroll
-    for (int s = 0; s < NST - 1; ++s) issue(s, s);
+        for (int s = 0; s < NST; ++s) load_block(x[s], s);
+    } else {
+#pragma unroll
+        for (int s = 0; s < NST - 1; ++s) issue(s, s);
+    }
 
     // The operands of one k step (16 k of a block) of stage st
     struct Ops {
@@ -239,18 +297,30 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
     // pipe never waits for an LDS round trip behind a barrier.  For that, block kb+1 must be complete one
     // barrier early: every wavefront checks its share of it before the barrier of block kb.
     Ops ahead;
-    wait_tile_loads<(NST - 2) * IPS>();
-    if (KTAIL && nk == 1) clear_tail(0);
+    if constexpr (ANY) {
+        store_block(x[0], 0);
+        load_block(x[0], NST);
+    } else {
+        wait_tile_loads<(NST - 2) * IPS>();
+        if (KTAIL && nk == 1) clear_tail(0);
+    }
     __syncthreads();
     read_ops(ahead, 0, 0);
     auto step = [&](int kb, auto phase) {
         constexpr int PH = decltype(phase)::value;
-        // blocks up to kb+1 have landed when at most the loads of the NST-3 later blocks are still out
-        wait_tile_loads<(NST - 3) * IPS>();
-        if (KTAIL && kb == nk - 2) clear_tail((PH + 1) % NST);
-        asm volatile("s_barrier" ::: "memory");
-        // ... for everybody, and everybody is done with block kb-1: its stage takes block kb+NST-1
-        issue(kb + NST - 1, (PH + NST - 1) % NST);
+        if constexpr (ANY) {
+            // block kb+1 to its stage, last read (block kb+1-NST) two barriers ago or more, and the registers to block kb+1+NST
+            if (kb + 1 < nk) store_block(x[(PH + 1) % NST], (PH + 1) % NST);
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            load_block(x[(PH + 1) % NST], kb + 1 + NST);
+        } else {
+            // blocks up to kb+1 have landed when at most the loads of the NST-3 later blocks are still out
+            wait_tile_loads<(NST - 3) * IPS>();
+            if (KTAIL && kb == nk - 2) clear_tail((PH + 1) % NST);
+            asm volatile("s_barrier" ::: "memory");
+            // ... for everybody, and everybody is done with block kb-1: its stage takes block kb+NST-1
+            issue(kb + NST - 1, (PH + NST - 1) % NST);
+        }
         [&]<int... S>(std::integer_sequence<int, S...>) {
             ([&] {
                 const Ops now = ahead;
@@ -320,7 +390,17 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
             const int row = p * RPP + lane / LPR, ch = lane % LPR;
             const u32x4 v = *(const u32x4*)(reg + row * RS + ch * 16);
             const int m = m0 + wm * RW + row, n = n0 + wn * (32 * TN) + ch * 8;
-            if (m < M && n < N) *(u32x4*)(Cb + (size_t)m * N + n) = v;
+            if (m >= M || n >= N) continue;
+            uint16_t* cp = Cb + (size_t)m * N + n;
+            if constexpr (!ANY) {
+                *(u32x4*)cp = v;
+            } else if (n <= N - 8) {
+                __builtin_memcpy(cp, &v, 16);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    if (n + e < N) cp[e] = (uint16_t)(v[e / 2] >> (16 * (e % 2)));
+            }
         }
     }
 }
@@ -802,10 +882,10 @@ hipError_t launch_grid(const GemmLaunch& g, const void* fn, int bm, int bn, int 
     return hipLaunchKernel(fn, dim3(grid.x, grid.y), dim3(threads), args, lds_bytes, (hipStream_t)g.stream);
 }
 
-template <int DT, int WM, int WN, int TM, int TN, int BK, int NST, int KS, bool KTAIL>
+template <int DT, int WM, int WN, int TM, int TN, int BK, int NST, int KS, bool KTAIL, bool ANY = false>
 hipError_t launch_tiles(const GemmLaunch& g) {
     static std::atomic<uint64_t> told{0};   // per kernel instance: the devices whose runtime knows its LDS size
-    return launch_grid(g, reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN, BK, NST, KS, KTAIL>), 32 * TM * WM, 32 * TN * WN,
+    return launch_grid(g, reinterpret_cast<const void*>(&gemm_lrelu_kernel<DT, WM, WN, TM, TN, BK, NST, KS, KTAIL, ANY>), 32 * TM * WM, 32 * TN * WN,
                        KS * WM * WN * 64, (unsigned)GemmLds<WM, WN, TM, TN, BK, NST, KS>::BYTES, told);
 }
 
@@ -844,7 +924,9 @@ hipError_t dispatch(const GemmLaunch& g) {
     const bool aligned = gemm_rows_aligned(g.N, g.K);
     if (aligned && g.K % 32 == 0) return launch_tile_size<DT, false>(g);
     if (gemm_per_element(g.batch, g.M, g.N, g.K)) return launch_element<DT>(g);
-    return aligned ? launch_tile_size<DT, true>(g) : launch_splitk<DT, 2>(g);
+    if (aligned) return launch_tile_size<DT, true>(g);
+    if (!gemm_unaligned_64(g.batch, g.M, g.N, g.K)) return launch_splitk<DT, 2>(g);
+    return gemm_unaligned_blocks_64(g.batch, g.M, g.N, g.K) ? launch_tiles<DT, 2, 2, 1, 1, 64, 3, 1, false, true>(g) : launch_tiles<DT, 2, 2, 1, 1, 32, 3, 1, false, true>(g);
 }
 
 }  // namespace

@@ -119,6 +119,21 @@ inline bool gemm_eight_waves(int batch, int M, int N, int K) {
 // blocks of K go straight from global memory into LDS.
 inline bool gemm_rows_aligned(int N, int K) { return K > 0 && K % 8 == 0 && N % 8 == 0 && K <= (1 << 22) && N <= (1 << 22); }
 
+// Rows that are not aligned: 64 x 64 tiles by way of registers instead of 32 x 32 with K split over the wavefronts?  Where the second are more
+// than two to a compute unit, a little later for a long K, which they split (us with 32 and 64: 1049 x 565, K = 76 6.5 4.6; 4 x 142 x 2905, K =
+// 201 13.5 7.5; 660 x 3283, K = 112 12.3 5.8; 2 x 320 x 2426, K = 1288 27.7 17.7; 4 x 395 x 475, K = 2659, 780 of 32 x 32, 37.4 32.7; 540 of them 0.71 of the time
+// at K = 128, 0.89 at 1200, 1.08 above; 648 of them, K = 3087,
+// 33.3 34.8; 468 of them, K = 400, 1.19).  The kernel wants N >= 8 and 32-bit offsets in a tile.
+inline bool gemm_unaligned_64(int batch, int M, int N, int K) {
+    const long long tiles = (long long)batch * gemm_pieces(M, 32) * gemm_pieces(N, 32);
+    return tiles > (K > 2400 ? 768 : K > 1200 ? 640 : 512) && N >= 8 && N <= (1 << 22) && K >= 1 && K <= (1 << 22);
+}
+// Its blocks: 64 in K instead of 32?  With a long K, where the loads' latency shows, unless many more workgroups than fit at once hide it (us with 32 and
+// 64: 2 x 320 x 2426, K = 1288 22.4 17.7; 560 x 1415, K = 296 6.3 6.1; 1888 x 1381, K = 184 6.9 7.1; with 836 tiles, K = 400, 64 takes 1.25 of the time).
+inline bool gemm_unaligned_blocks_64(int batch, int M, int N, int K) {
+    return K > 700 || (K > 256 && (long long)batch * gemm_pieces(M, 64) * gemm_pieces(N, 64) <= 600);
+}
+
 // A size that fits no tile (K % 32 != 0, or rows that are not aligned): one thread per element of c instead?  The tile
 // kernels compute whole tiles and whole blocks of 32 in K and begin with a chain of LDS stages; with few products per element that
 // is mostly waste.  Both times are estimated, in us, from constants fitted to 495 measured sizes of this kind (1 to 70000 in
@@ -143,6 +158,8 @@ inline bool gemm_per_element(int batch, int M, int N, int K) {
     } else {
         const double tiles = 1e-3 * batch * gemm_pieces(M, 32) * gemm_pieces(N, 32);
         tiled = 4.3 + 3.6 * tiles > 5.2 * tiles ? 4.3 + 3.6 * tiles : 5.2 * tiles;
+        // (64 x 64, from 60 sizes with K = 64 to 120: 660 x 3283, K = 112 5.8; 2 x 2318 x 2350, K = 86 14.0, one thread per element 47)
+        if (K > 32 && gemm_unaligned_64(batch, M, N, K)) tiled = 4.0 + 3.7e-3 * batch * gemm_pieces(M, 64) * gemm_pieces(N, 64);
     }
     return each < (K > 24 ? 0.9 : 1.0) * tiled;   // the estimate for one thread per element is the less certain one the longer K is
 }

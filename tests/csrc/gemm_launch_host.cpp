@@ -22,6 +22,8 @@ int tiles_128x256(int batch, int M, int N, int K) { return gemm_tiles_128x256(ba
 int two_parts(int batch, int M, int N, int K) { return gemm_two_parts(batch, M, N, K); }
 int tiles_64x128(int batch, int M, int N, int K) { return gemm_tiles_64x128(batch, M, N, K); }
 int long_blocks(int batch, int M, int N, int K) { return gemm_long_blocks(batch, M, N, K); }
+int unaligned_64(int batch, int M, int N, int K) { return gemm_unaligned_64(batch, M, N, K); }
+int unaligned_blocks_64(int batch, int M, int N, int K) { return gemm_unaligned_blocks_64(batch, M, N, K); }
 int deep(int batch, int M, int N, int K) { return gemm_deep(batch, M, N, K); }
 int per_element(int batch, int M, int N, int K) { return gemm_per_element(batch, M, N, K); }
 }

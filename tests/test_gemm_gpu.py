@@ -196,13 +196,19 @@ BETWEEN = [(1, 1090, 1000, 600), (1, 1090, 968, 800), (2, 577, 1032, 640), (1, 1
            (2, 1700, 1288, 400), (1, 2049, 2056, 384), (1, 2049, 2056, 392), (1, 520, 520, 640), (2, 300, 520, 704)]
 
 
+# rows that are not aligned, more than 512 tiles of 32 x 32: 64 x 64 tiles with blocks of 32 and 64 in K, one, two, as many as stages and more of them; last
+# blocks of one k, all and all but one; N of one element past a tile and one short, odd and even, and the smallest; a single row
+BETWEEN += [(1, 737, 801, 33), (1, 737, 833, 64), (2, 575, 767, 65), (1, 769, 705, 95), (1, 736, 833, 97), (1, 737, 801, 161), (1, 737, 801, 257), (3, 415, 481, 320),
+            (2, 577, 703, 383), (1, 800, 766, 385), (1, 777, 1001, 1003), (1, 20500, 8, 101), (1, 20500, 9, 104), (1, 1, 20500, 99), (1, 65, 12002, 66)]
+
+
 @pytest.mark.parametrize("dtype", [I.F16, I.BF16])
 @pytest.mark.parametrize("shape", BETWEEN)
 def test_tiles_between_the_square_ones(P, shape, dtype):
     run(P, *shape, dtype)
 
 
-@pytest.mark.parametrize("shape", [(1, 576, 520, 264), (1, 1090, 1000, 600), (1, 1500, 1416, 1288), (2, 1700, 1288, 400)])
+@pytest.mark.parametrize("shape", [(1, 576, 520, 264), (1, 1090, 1000, 600), (1, 1500, 1416, 1288), (2, 1700, 1288, 400), (2, 737, 801, 353), (1, 700, 1001, 201)])
 def test_an_infinite_element_stays_in_its_row_and_column(P, shape):
     """What a cut last block reads in place of k past the end is the rows' own first elements of the block, and the next row's: none of
     it may count."""

@@ -133,6 +133,16 @@ def test_one_round_of_larger_tiles(L):
         assert L.long_blocks(*shape) == want, shape
 
 
+def test_unaligned_rows(L):
+    """64 x 64 tiles from more than 512 (640) tiles of 32 x 32 on, in blocks of 64 for a long K or a middling one with few tiles."""
+    for shape, want in (((2, 512, 511, 100), 0), ((2, 513, 511, 100), 1), ((2, 640, 511, 1201), 0), ((2, 641, 511, 1201), 1), ((1, 1 << 20, 7, 100), 0), ((1, 1 << 20, 8, 100), 1),
+                        ((1, 20000, 9, (1 << 22) + 1), 0), ((65535, 1, TOP, 1), 0)):
+        assert L.unaligned_64(*shape) == want, shape
+    for shape, want in (((1, 1500, 1501, 256), 0), ((1, 1500, 1501, 257), 1), ((1, 1600, 1601, 257), 0), ((1, 1600, 1601, 701), 1)):
+        assert L.unaligned_blocks_64(*shape) == want, shape
+    assert L.per_element(2, 2318, 2350, 86) == 0 and L.per_element(1, 660, 3283, 33) == 0
+
+
 def test_few_products_take_one_thread_per_element(L):
     """Sizes that fit no tile, on either side by a factor in the time measured."""
     for shape in ((4000, 1, 9, 3), (4000, 1, 35, 17), (1, 1, 65537, 7), (1, 33, 33, 1), (1, 1500, 1500, 8), (16384, 8, 64, 8), (1, 1 << 20, 8, 8),
