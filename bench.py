@@ -37,44 +37,44 @@ CSRC = os.path.join(ROOT, "paper_2501_08071_amd", "csrc")
 # scaled by what the same counter reads for a plain 1 GiB copy: 2.0 and 1.0), keyed by workload, with the
 # summary under profiles/ that holds the counter values; valid only for the kernel source they were taken
 # with (sha256 over the kernel's sources), otherwise reported as null.
-ATTN_FILES = ("attn_fwd_gfx950.hip", "attn_fwd_rows64_gfx950.hip", "attn_launch.h", "attn_device.h", "gfx950_common.h")
+ATTN_FILES = ("attn_fwd_gfx950.hip", "attn_fwd_stream_gfx950.hip", "attn_fwd_rows64_gfx950.hip", "attn_launch.h", "attn_device.h", "gfx950_common.h")
 ROW_FILES = ("rowops_gfx950.hip", "rowops_launch.h", "gfx950_common.h")
 GEMM_FILES = ("gemm_gfx950.hip", "gemm_launch.h", "gfx950_common.h")
 TRAFFIC = {
-    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 147310 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 148961 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
      "source": "profiles/attn_fwd_kernel_S4096_D128_bf16_causal.md"},
-    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 907667 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 897807 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
      "source": "profiles/attn_fwd_kernel_all_workloads.md"},
-    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98513.5 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98513.6 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
      "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
-    "B4_H16_S1024_D64_f16": {"fetch_kib": 12459.7 * 2.0, "write_kib": 16640 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
+    "B4_H16_S1024_D64_f16": {"fetch_kib": 12460 * 2.0, "write_kib": 16640 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
      "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
-    "B1_H4_S4096_D32_f16_paper": {"fetch_kib": 2690.1 * 2.0, "write_kib": 2112 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "d991abe05397b01f5d015e4ee52eba4982cfdf0873d4928af6af6dd795f00345",
-     "source": "profiles/attn_fwd_halves_kernel.md"},
+    "B1_H4_S4096_D32_f16_paper": {"fetch_kib": 2611.3 * 2.0, "write_kib": 2112 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
+     "source": "profiles/attn_fwd_halves_stream_kernel.md"},
     # the row kernels (workload name as rowop_run reports it)
     "softmax_512x4096_f16 x16 rows": {"fetch_kib": 32798.0 * 2.0, "write_kib": 65536.0 * 1.0, "files": ROW_FILES,
-     "kernel_sha256": "12992ce88316b0f94604d49962a30775d2c085beaabd0a6ce5e590ceaaaf33d6",
+     "kernel_sha256": "7f933e1f3eb6d0313213ec96a09ad1dd1e0805961ede815938a5601f9b5de2a3",
      "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
     "rmsnorm_1x32x4096x64_f16 x16 rows": {"fetch_kib": 131106.1 * 2.0, "write_kib": 262144.0 * 1.0, "files": ROW_FILES,
-     "kernel_sha256": "12992ce88316b0f94604d49962a30775d2c085beaabd0a6ce5e590ceaaaf33d6",
+     "kernel_sha256": "7f933e1f3eb6d0313213ec96a09ad1dd1e0805961ede815938a5601f9b5de2a3",
      "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
     # the GEMM + LeakyReLU kernels (the paper's shapes; the 256 x 256 tile's launches)
     "mmLeakyReLu_1x512x512x2048_f16": {"fetch_kib": 6188.0 * 2.0, "write_kib": 512.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
+     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "bmm_4x512x512x2048_f16": {"fetch_kib": 12334.5 * 2.0, "write_kib": 2048.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
+    "bmm_4x512x512x2048_f16": {"fetch_kib": 12333.0 * 2.0, "write_kib": 2048.0 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 98454.5 * 2.0, "write_kib": 32768.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
+    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 98441.5 * 2.0, "write_kib": 32768.1 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "mmLeakyReLu_1x8192x8192x8192_f16": {"fetch_kib": 786803.6 * 2.0, "write_kib": 131073.6 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "f12d1c1f4e13e630beeb6a396a0e8911267912bd1225f461745ea5f82afd71fb",
+    "mmLeakyReLu_1x8192x8192x8192_f16": {"fetch_kib": 786629.8 * 2.0, "write_kib": 131074.3 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
 }
 
