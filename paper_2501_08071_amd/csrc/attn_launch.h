@@ -97,17 +97,38 @@ inline bool attn_splits_keys(long long BH, int S, int D) {
 // compute units, two while that is; beyond it the larger workgroups above read less of K and V per row.  Under the mask, where
 // the workgroups of a second round are the short ones, a little further.  Measured, us as before / one group / two (heads x S, 8
 // wavefronts of the other kernels before): D = 128, 8 x 333 11.6 6.6 9.7, 8 x 1024 17.6 10.8 15.7, 1 x 4096 44.6 23.8 39.0,
-// 32 x 333 12.6 12.5 10.6, 16 x 1024 19.4 19.9 17.6, 32 x 1024 25.3 39.5 34.2; D = 64, 8 x 1024 12.3 8.0 9.9, 16 x 1024 12.6 13.9
+// 16 x 1024 19.4 19.9 17.6, 32 x 1024 25.3 39.5 34.2; D = 64, 8 x 1024 12.3 8.0 9.9, 16 x 1024 12.6 13.9
 // 10.4, 32 x 1024 14.8 26.0 19.5; D = 32, 8 x 1024 10.1 6.4 8.0, 4 x 4096 29.0 27.2 19.6, 8 x 4096 30.4 50.7 35.9.  With the mask:
-// D = 128, 4 x 4096 46.6 32.0 40.3, 8 x 2887 37.6 37.1 33.5, 16 x 2048 31.5 38.2 33.8, 128 x 128 9.9 10.3 9.5; D = 64, 4 x 4096 32.4
+// D = 128, 4 x 4096 46.6 32.0 40.3, 8 x 2887 37.6 37.1 33.5, 16 x 2048 31.5 38.2 33.8; D = 64, 4 x 4096 32.4
 // 23.0 25.1, 6 x 1670 17.8 10.2 13.4, 32 x 512 9.8 9.0 7.9, 10 x 1701 18.9 16.7 14.6, 32 x 1024 14.1 19.7 15.3; D = 32, 8 x 4096 29.4 31.1
 // 23.9, 32 x 1024 11.2 15.4 11.6.  (A single tile of 128 rows keeps the kernel that attn_kernel_name has always named for it.)
+inline bool attn_stream_wide_heads(long long BH, int S, bool causal, int groups);
 inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
     if (attn_pick_nw(BH, S) == ATTN_NW || (BH == 1 && S <= 128)) return 0;
     const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
-    if (n32 <= 256 || (causal && n32 <= 512 && (S >= 2048 || (D == 128 ? S >= 256 : n32 <= 400 && S >= 640)))) return 1;
-    if (n64 <= 256 || (causal && (D != 128 && S >= 2048 ? n64 <= 512 : S >= 1000 && n64 <= 384))) return 2;
+    if (n32 <= 256) return 1;
+    if (D == 128) return attn_stream_wide_heads(BH, S, causal, 1) ? 1 : attn_stream_wide_heads(BH, S, causal, 2) ? 2 : 0;
+    if (causal && n32 <= 512 && (S >= 2048 || (n32 <= 400 && S >= 640))) return 1;
+    if (n64 <= 256 || (causal && (S >= 2048 ? n64 <= 512 : S >= 1000 && n64 <= 384))) return 2;
     return 0;
+}
+
+// The same at D = 128 past one round of single groups.  A key costs the most bytes there, so it counts how many XCDs read a head's K and
+// V: workgroup b runs on XCD b % 8 and works on head b % BH, so one XCD does where BH is a multiple of 8, two where it is one of 4, all
+// eight where it is odd.  Even numbers of heads are better off streaming from 320 keys on, shorter sequences only where few XCDs
+// share a head, odd numbers only while the workgroups are few or the sequence is long.  Measured, us as before / one group / two, on
+// either side: 60 x 256 11.7 12.6 11.6, 62 x 256 11.8 16.0 13.3; 24 x 512 13.9 14.0 12.4, 27 x 512 14.6 20.7 16.2; 17 x 600 15.2 16.7 14.0, 25 x
+// 576 15.6 22.3 16.5; 15 x 1000 20.2 25.4 19.3; 110 x 100 9.1 11.2 10.2.  With the mask: 64 x 256 11.9 11.4 11.0, 55 x 256 11.6 13.0 11.8; 36 x 333 12.6
+// 11.5 11.6, 33 x 333 12.6 13.1 12.5; 24 x 640 15.6 13.2 13.3, 25 x 640 15.9 17.2 15.3; 64 x 200 10.8 10.6 10.0, 62 x 200 11.0 12.3 11.6; 18 x 1000
+// 19.5 20.3 18.6, 20 x 1000 19.7 20.8 20.4, 23 x 1000 20.8 29.9 24.1; 11 x 2000 29.7 33.0 28.0.
+inline bool attn_stream_wide_heads(long long BH, int S, bool causal, int groups) {
+    const long long tiles = BH * ((S + 32 * groups - 1) / (32 * groups));
+    const bool even = BH % 2 == 0;
+    if (groups == 1) return causal && S >= 256 && tiles <= (S >= 900 || (even && S > 320) ? 512 : S >= 480 ? 440 : even ? 340 : S > 320 ? 352 : 300);
+    if (!causal)
+        return tiles <= 256 && (S >= 780 || (S > 320 && tiles <= (even ? 256 : S > 512 ? 210 : 165)) || (S > 256 && even && tiles <= 170) || (S > 128 && BH % 4 == 0));
+    if (tiles <= 256) return S >= 480 || (S >= 90 && S <= 160 && BH % 8 == 0) || (S > 192 && (BH % 4 == 0 || (even && tiles <= 140)));
+    return S >= 1000 && tiles <= (S >= 2000 ? 384 : S >= 1400 ? 340 : S >= 1200 ? 320 : S >= 1100 ? 310 : 300);
 }
 
 struct AttnLaunch {
