@@ -15,14 +15,18 @@ struct GemmLaunch {
 // Pieces of t that cover x, for any x >= 0 (as int, x + t - 1 would overflow where x is near 2^31).
 constexpr int gemm_pieces(int x, int t) { return (int)(((unsigned)x + (unsigned)(t - 1)) / (unsigned)t); }
 
-// 128 x 128 with fewer than 192 of them, too?  Where tiles of 64 x 128 (below) would begin a second round and K is long enough (us with 128 and
-// 64, 140 to 191 of them: 1536 x 1536, K = 4096 32 50; 1599 x 1696, K = 1408 14.7 20.4; 2 x 3476 x 288, K = 560 9.5 11.1; 2370 x 1216, K = 384
-// 7.3 7.9; but 4 x 846 x 576, K = 384, 140 of them, 6.7 5.5; 4 x 324 x 1408, K = 448, 132, 7.2 6.9; 2761 x 704, K = 608,
-// 132, 8.6 7.3), unless a quarter more of them lies outside c
-// (8 x 556 x 448, K = 1536 14.9 13.7; 8 x 398 x 544, K = 1560 16.5 15.7.)
+// 128 x 128 with fewer than 192 of them, too?  Where tiles of 64 x 128 (below) would begin a second round, 64 x 64 tiles are more than two
+// to a compute unit (512), and K is long enough (us with 128 and 64, 140 to 191 of them: 1536 x 1536, K = 4096 32 50; 1599 x 1696, K = 1408 14.7
+// 20.4; 2 x 3476 x 288, K = 560 9.5 11.1; 2370 x 1216, K = 384 7.3 7.9; 4 x 576 x 904, K = 512 8.2 10.9; 4 x 846 x 576, K = 384, 140 of
+// them, 6.7 5.5; 4 x 324 x 1408, K = 448, 132, 7.2 6.9; 2761 x 704, K = 608, 132, 8.6 7.3).  Up to 512 of 64 x 64 only for a long K, sooner where rows of b do not
+// begin at cache lines (6395 x 264, K = 2048, 500 of 64 x 64, 18.5 19.7; 4224 x 440, K = 1344, 462, 14.3 15.1; 2 x 2784 x 288, K = 1440, 440, 15.8 14.6; 5952 x
+// 264, K = 704, 465, 10.4 9.8; but 2 x 2176 x 448, K = 1024 12.7 11.4; 5952 x 320, K = 1024 12.7 11.3; 2 x 1728 x 576, K = 2048 19.3 18.1; 4 x 704 x
+// 704, K = 3368 28.6 31.8, but 2 x 2171 x 448, K = 3616 30.9 27.5).  Not where a quarter more of them lies outside c (8 x 556 x 448, K = 1536 14.9 13.7; 8 x 398 x 544, K = 1560 16.5 15.7.)
 inline bool gemm_middle_round(int batch, int M, int N, int K) {
     auto tiles = [&](int bm, int bn) { return (long long)batch * gemm_pieces(M, bm) * gemm_pieces(N, bn); };
-    return K >= 384 && tiles(64, 128) > 256 && (K >= 640 || tiles(128, 128) >= 152) && 16 * tiles(128, 128) <= 5 * tiles(64, 64);
+    const long long t64 = tiles(64, 64), t128 = tiles(128, 128);
+    if (K < 384 || tiles(64, 128) <= 256 || 16 * t128 > 5 * t64) return false;
+    return t64 > 512 ? K >= 640 || t128 >= 152 : K >= (t64 > 448 && N % 64 != 0 ? 1200 : 3000);
 }
 
 // Tiles of c for a problem whose rows are 16-byte aligned: 1: 256 x 256, 2: 128 x 128, 3: 64 x 64, 5: 32 x 32 with K
