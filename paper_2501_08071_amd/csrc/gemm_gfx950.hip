@@ -119,6 +119,7 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
     constexpr int IPS = LA + LB;
     static_assert(LA * KS * NW * 1024 == A_TILE && LB * KS * NW * 1024 == B_TILE && LA >= 1 && LB >= 1, "the wavefronts share the loads evenly");
     static_assert(NST * STAGE <= 160 * 1024, "LDS");
+    constexpr bool CLEAR = KTAIL && BK != 32;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -272,8 +273,10 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
         }
     };
     // The last block of a K that is not a multiple of BK: both operands' k past the end become zero (whatever was loaded in their
-    // place may be infinite).  Every wavefront clears what its own loads brought, once they have landed and before the barrier
-    // behind which the block may be read: nothing of it is left in the loop.
+    // place may be infinite).  Blocks of 64: every wavefront clears what its own loads brought, once they have landed and before the
+    // barrier behind which the block may be read: nothing of it is left in the loop, whose four k steps would each have to ask.  Blocks of
+    // 32: in the operands' registers, which takes a product of 128 x 128 tiles with K = 48 6.3 us where clearing takes 6.7 (4664 x 776), one
+    // of 64 x 64 tiles with K = 424 7.1 and 7.7 (4 x 123 x 3968).
     auto clear_tail = [&](int st) {
 #pragma unroll
         for (int j = 0; j < LA; ++j) {
@@ -284,6 +287,13 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
         for (int j = 0; j < LB; ++j)
             if (B_RPI * (loader * LB + j) + lane / B_LPR >= kr) lds_write_b128(lds0 + st * STAGE + A_TILE + (loader * LB + j) * 1024 + 16 * lane, u32x4{0u, 0u, 0u, 0u});
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    };
+    auto cut_tail = [&](Ops& o, int ks) {
+        const bool past = 16 * ks + 8 * h >= kr;
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) o.a[tm] = past ? u32x4{0u, 0u, 0u, 0u} : o.a[tm];
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) o.b[tn] = past ? u32x4{0u, 0u, 0u, 0u} : o.b[tn];
     };
     auto multiply = [&](const Ops& o) {
 #pragma unroll
@@ -302,7 +312,7 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
         load_block(x[0], NST);
     } else {
         wait_tile_loads<(NST - 2) * IPS>();
-        if (KTAIL && nk == 1) clear_tail(0);
+        if (CLEAR && nk == 1) clear_tail(0);
     }
     __syncthreads();
     read_ops(ahead, 0, 0);
@@ -316,15 +326,19 @@ __global__ __launch_bounds__(KS * WM * WN * 64) void gemm_lrelu_kernel(const uin
         } else {
             // blocks up to kb+1 have landed when at most the loads of the NST-3 later blocks are still out
             wait_tile_loads<(NST - 3) * IPS>();
-            if (KTAIL && kb == nk - 2) clear_tail((PH + 1) % NST);
+            if (CLEAR && kb == nk - 2) clear_tail((PH + 1) % NST);
             asm volatile("s_barrier" ::: "memory");
             // ... for everybody, and everybody is done with block kb-1: its stage takes block kb+NST-1
             issue(kb + NST - 1, (PH + NST - 1) % NST);
         }
         [&]<int... S>(std::integer_sequence<int, S...>) {
             ([&] {
-                const Ops now = ahead;
+                Ops now = ahead;
                 read_ops(ahead, (S + 1 < NKS ? PH : (PH + 1) % NST) * STAGE, (S + 1) % NKS);
+                if (KTAIL && !CLEAR && S == 0 && kb == nk - 1) {
+                    cut_tail(now, 0);
+                    cut_tail(ahead, 1);
+                }
                 __builtin_amdgcn_sched_barrier(0);
                 multiply(now);
                 __builtin_amdgcn_sched_barrier(0);
