@@ -10,6 +10,7 @@ import fails loudly.
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 # torch first: it carries its own copy of the HIP runtime (same soname as the system one), and the
@@ -85,15 +86,17 @@ lib = _load()
 
 
 def _load_fast():
-    if not os.path.exists(_build.BINDING):
+    path = _build.binding_path()
+    if not os.path.exists(path):
         try:
-            _build.build_binding()
+            _build.build_binding(path)
         except Exception as e:
-            raise ImportError(f"{_build.BINDING} is missing and could not be built: {e}") from e
-    from . import _binding_fast
-    _binding_fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
-                         (lib.attn_fwd, lib.attn_fwd_o16, lib.softmax_rows_fwd, lib.rmsnorm_fwd, lib.gemm_leakyrelu_fwd)))
-    return _binding_fast
+            raise ImportError(f"{path} is missing and could not be built: {e}") from e
+    spec = importlib.util.spec_from_file_location(__package__ + "._binding_fast", path)
+    fast = importlib.util.module_from_spec(spec)
+    fast.bind(*(ctypes.cast(f, ctypes.c_void_p).value for f in
+                (lib.attn_fwd, lib.attn_fwd_o16, lib.softmax_rows_fwd, lib.rmsnorm_fwd, lib.gemm_leakyrelu_fwd)))
+    return fast
 
 
 _fast = _load_fast()

@@ -1,6 +1,7 @@
 """Compile the HIP sources into the in-tree C-ABI shared library (gfx950 only)."""
 from __future__ import annotations
 
+import hashlib
 import os
 import shutil
 import subprocess
@@ -10,7 +11,6 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libattn_gfx950.so")
-BINDING = os.path.join(HERE, "_binding_fast.so")   # a Python module: torch tensors to the C ABI of LIB
 SOURCES = ["attn_fwd_gfx950.hip", "attn_fwd_stream_gfx950.hip", "attn_fwd_rows64_gfx950.hip", "attn_api.cpp", "rowops_gfx950.hip", "rowops_api.cpp",
            "gemm_gfx950.hip", "gemm_api.cpp", "probe_gfx950.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -35,6 +35,18 @@ def _run(cmd):
     return err
 
 
+def _whole(out: str, make):
+    """make(path) writes a file; it takes the name `out` only when it is complete, so that another process never loads half of one."""
+    part = f"{out[:-3]}.{os.getpid()}.part.so"
+    try:
+        res = make(part)
+        os.replace(part, out)
+        return res
+    finally:
+        if os.path.exists(part):
+            os.remove(part)
+
+
 def build_lib(extra_flags=(), out: str = LIB, verbose: bool = False, jobs: int = 4) -> str:
     """Every source to an object of its own (with its own flags), then one link."""
     tmp = tempfile.mkdtemp(prefix="attn_build_")
@@ -47,7 +59,7 @@ def build_lib(extra_flags=(), out: str = LIB, verbose: bool = False, jobs: int =
         with ThreadPoolExecutor(max_workers=jobs) as ex:
             done = list(ex.map(compile_one, SOURCES))
         err = "".join(e for _, e in done)
-        err += _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for o, _ in done], "-o", out])
+        err += _whole(out, lambda part: _run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *[o for o, _ in done], "-o", part]))
         if verbose and err.strip():
             print(err)
     finally:
@@ -55,29 +67,39 @@ def build_lib(extra_flags=(), out: str = LIB, verbose: bool = False, jobs: int =
     return out
 
 
-def build_binding(out: str = BINDING, verbose: bool = False) -> str:
-    """The module behind the Python entry points (host code only, against torch's headers)."""
+BINDING_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1"]
+
+
+def binding_path() -> str:
+    """The module behind the Python entry points: torch tensors to the C ABI of LIB.  It is compiled against the insides of torch and
+    Python and calls LIB by address, so its name carries all it was made from: one left from another torch, another Python or other
+    sources has another name and is not loaded."""
     import sysconfig
 
     import torch
+    h = hashlib.sha256(repr((torch.__version__, torch.version.git_version, sysconfig.get_config_var("EXT_SUFFIX"), BINDING_FLAGS)).encode())
+    for f in (os.path.join(CSRC, "binding_fast.cpp"), *(os.path.join(HERE, "..", "include", x) for x in ("attn.h", "gemm.h", "rowops.h"))):
+        with open(f, "rb") as fh:
+            h.update(hashlib.sha256(fh.read()).digest())
+    return os.path.join(HERE, f"_binding_fast_{h.hexdigest()[:16]}.so")
+
+
+def build_binding(out: str | None = None, verbose: bool = False) -> str:
+    """That module (host code only, against torch's headers)."""
+    import sysconfig
+
+    import torch
+    out = out or binding_path()
     t = os.path.dirname(torch.__file__)
     inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
            sysconfig.get_paths()["include"]]
     # (no path to torch's libraries is recorded: the process that imports the module has loaded them)
-    err = _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-                *[a for d in inc for a in ("-isystem", d)], os.path.join(CSRC, "binding_fast.cpp"),
-                "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", out])
+    err = _whole(out, lambda part: _run([os.environ.get("CXX", "g++"), *BINDING_FLAGS, *[a for d in inc for a in ("-isystem", d)],
+                                         os.path.join(CSRC, "binding_fast.cpp"), "-L" + os.path.join(t, "lib"), "-ltorch_python",
+                                         "-ltorch_cpu", "-lc10", "-lc10_hip", "-o", part]))
     if verbose and err.strip():
         print(err)
     return out
-
-
-def lib_is_stale() -> bool:
-    if not os.path.exists(LIB) or not os.path.exists(BINDING):
-        return True
-    t = min(os.path.getmtime(LIB), os.path.getmtime(BINDING))
-    deps = [os.path.join(CSRC, f) for f in os.listdir(CSRC)] + [os.path.join(HERE, "..", "include", h) for h in ("attn.h", "rowops.h", "gemm.h", "probe.h")]
-    return any(os.path.getmtime(d) > t for d in deps)
 
 
 if __name__ == "__main__":
