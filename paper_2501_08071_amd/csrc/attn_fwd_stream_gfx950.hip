@@ -87,6 +87,12 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
     constexpr int XM = D == 128 ? 3 : D == 64 ? 1 : 0;
     const uint32_t off0 = (uint32_t)((lane / CPR) * ROWB + (((lane % CPR) ^ swz<D>(lane / CPR)) << 4));
     auto load_rows = [&](const uint16_t* base, int row0, int i, uint32_t dst) {
+        if constexpr (ATTN_DEBUG_POISON != 0) {
+            // Debug build: NaN patterns where this load will land, so that an operand read before its block has landed (a wait that
+            // counts too few loads), or after its buffer was given away, shows in the output.
+            lds_write_b128(dst + 16 * lane, u32x4{0x7fff7fffu, 0x7fff7fffu, 0x7fff7fffu, 0x7fff7fffu});
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
         const int over = row0 + i * RPI + lane / CPR - (S - 1);
         lds_dma16(dst, base + (size_t)row0 * D, (off0 ^ ((i & XM) << 4)) + (uint32_t)((i * RPI - (over > 0 ? over : 0)) * ROWB));
     };
