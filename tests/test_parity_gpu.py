@@ -55,8 +55,9 @@ def test_small_problems_take_half_size_workgroups():
     assert P.attn_launch_rows(2, 32, 4096, 128, BF16, True) == 256 and P.attn_launch_rows(4, 16, 1024, 64, F16, False) == 256
 
 
-# Half-size workgroups that split the keys of every block between two halves of their wavefronts.  Lengths at the first it
-# is done for, at the edges of a half (32 keys at D = 32 and 128, 64 at D = 64) and of a block, with logits that differ between
+# (Two heads of these lengths stream keys of their own in every wavefront, one row group per workgroup; the kernel that splits every
+# block between two halves is tested with the numbers of heads that take it, test_split_keys below.)  Lengths at the first the
+# halves are done for, at the edges of a half (32 keys at D = 32 and 128, 64 at D = 64) and of a block, with logits that differ between
 # the halves by far more than a weight can hold, so that one half's sums vanish in the final addition: first the one, then the other.
 @pytest.mark.parametrize("loud", [0, 1])
 @pytest.mark.parametrize("causal", [False, True])
@@ -101,6 +102,63 @@ def test_key_halves_with_logits_near_the_lowest_number(S, D, causal):
     q[..., 0] = (64 + 127) << 7              # 2^64
     k[..., 0] = 0x8000 | ((63 + 127) << 7)   # -2^63
     check_full(q, k, v, BF16, causal, 1.25, f"S{S} D{D} causal{causal} logits -2^127")
+
+
+def _heads(kernel, S, D, causal):
+    """The least number of heads above one for which the library takes `kernel`."""
+    return next(h for h in range(2, 129) if P.attn_kernel_name(1, h, S, D, F16, causal) == kernel.replace("DT", "0").replace("MASK", str(causal).lower()))
+
+
+HALVES = "attn_fwd_halves_kernel<DT, {}, MASK, 4>"
+SPLIT = [(257, 32), (288, 32), (319, 32), (385, 128), (416, 128), (449, 128), (129, 64), (192, 64), (321, 64), (1100, 32), (1100, 64), (1100, 128)]
+
+
+# The kernel that splits the keys of every block between two halves of a workgroup's wavefronts, which serves what lies between the
+# streaming kernel and tiles of 256 rows: the same lengths (and one of several rounds of the LDS buffers, ragged), the same loud and
+# quiet halves in both element types, the same lowest logits, at the least number of heads that takes it.
+@pytest.mark.parametrize("loud", [0, 1])
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("S,D", SPLIT)
+def test_split_keys(S, D, dtype, causal, loud):
+    kernel = HALVES.format(D)
+    H = _heads(kernel, S, D, causal)
+    assert P.attn_kernel_name(1, H, S, D, dtype, causal) == kernel.replace("DT", str(dtype)).replace("MASK", str(causal).lower())
+    q, k, v = I.gen_tensors(1, H, S, D, dtype, workload_id=900 + S)
+    half = 64 if D == 64 else 32
+    quiet = ((np.arange(S) // half) % 2 != loud)[None, None, :, None]
+    if dtype == BF16:
+        k = np.where(((k >> 7) & 0xFF) > 16, k.astype(np.int64) + np.where(quiet, -6, 3) * 128, k).astype(np.uint16)
+    else:
+        k = np.ascontiguousarray(k.view(np.float16) * np.where(quiet, np.float16(1 / 64), np.float16(2.0))).view(np.uint16)
+    for scale in (1 / math.sqrt(D), 3.0, 1e-4):
+        check_full(q, k, v, dtype, causal, scale, f"{kernel} H{H} S{S} dt{dtype} causal{causal} loud{loud} scale{scale}")
+
+
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("S,D", [(320, 32), (300, 32), (256, 64), (300, 64), (448, 128), (450, 128)])
+def test_split_keys_with_logits_near_the_lowest_number(S, D, causal):
+    H = _heads(HALVES.format(D), S, D, causal)
+    _, _, v = I.gen_tensors(1, H, S, D, BF16, workload_id=901)
+    q, k = np.zeros_like(v), np.zeros_like(v)
+    q[..., 0] = (64 + 127) << 7              # 2^64
+    k[..., 0] = 0x8000 | ((63 + 127) << 7)   # -2^63
+    check_full(q, k, v, BF16, causal, 1.25, f"H{H} S{S} D{D} causal{causal} logits -2^127")
+
+
+# Four wavefronts per workgroup, each with query rows of its own: more than one head takes them at D = 32 and 128 (short sequences
+# that are more than a round of the streaming kernel), a single tile at every D.
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("S,D,heads", [(129, 32, None), (161, 32, None), (255, 32, None), (65, 128, None), (127, 128, None), (200, 128, None), (320, 128, None),
+                                       (1, 64, 1), (33, 64, 1), (100, 64, 1), (128, 64, 1), (95, 32, 1), (97, 128, 1)])
+def test_four_wavefronts(S, D, heads, dtype, causal):
+    kernel = f"attn_fwd_kernel<DT, {D}, MASK, 4>"
+    H = heads or _heads(kernel, S, D, causal)
+    assert P.attn_kernel_name(1, H, S, D, dtype, causal) == kernel.replace("DT", str(dtype)).replace("MASK", str(causal).lower())
+    q, k, v = I.gen_tensors(1, H, S, D, dtype, workload_id=910 + S)
+    for scale in (1 / math.sqrt(D), -1.0):
+        check_full(q, k, v, dtype, causal, scale, f"{kernel} H{H} S{S} dt{dtype} causal{causal} scale{scale}")
 
 
 def test_workload_1_full():
