@@ -199,7 +199,7 @@ def attn_bounds(P, w, probes):
     issue_port   the vector work of the softmax plus what the matrix instructions take from the issue of the other
                  wavefront on their SIMD (two wavefronts per SIMD, one port), at 2.4 GHz
     launch_floor what a kernel that does nothing costs per launch, back to back"""
-    rows = P.attn_launch_rows(w.B, w.H, w.S, w.D, w.dtype, w.causal)
+    rows = P.attn_workgroup_rows(w.B, w.H, w.S, w.D, w.dtype, w.causal)
     nqt = (w.S + rows - 1) // rows
     scores = w.B * w.H * (w.S * (w.S + 1) // 2 if w.causal else w.S * w.S)
     if w.causal:

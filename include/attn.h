@@ -92,7 +92,7 @@ const char *attn_status_str(int status);
 /*
  * Name of the kernel attn_fwd launches for this very problem (the symbol a
  * profiler reports; it depends on B and H because small problems take the
- * instance with half the query rows, see attn_launch_rows), or NULL if
+ * instance with fewer query rows, see attn_workgroup_rows), or NULL if
  * unsupported.  A string constant: no HIP call, safe from any thread.
  */
 const char *attn_kernel_name(int B, int H, int S, int D, int dtype, int causal);
@@ -105,13 +105,17 @@ int attn_tile_rows(int D, int dtype, int causal);
 int attn_tile_keys(int D, int dtype, int causal);
 
 /*
- * Query rows per tile attn_fwd uses for this very problem: attn_tile_rows, or half of it ("..., 4>" in the
- * kernel's name) when the problem has so few tiles that the larger ones would leave half of the chip idle.  A tile is
- * a workgroup's; of the smaller ones, where the halves of a workgroup's wavefronts split the keys, it is shared by
- * several workgroups while those fit the chip at once ("attn_fwd_halves_stream_kernel": 32 or 64 rows each, the last
- * template argument but one).  0 if unsupported.
+ * attn_tile_rows, or half of it ("..., 4>" in the kernel's name) when this very problem has so few tiles of that many rows that
+ * half of the chip would be idle.  0 if unsupported.
  */
 int attn_launch_rows(int B, int H, int S, int D, int dtype, int causal);
+
+/*
+ * Query rows a workgroup of attn_kernel_name's kernel owns for this very problem: attn_launch_rows, but 32 or 64 (32 times the last
+ * template argument but one) in "attn_fwd_halves_stream_kernel", whose wavefronts each stream keys of their own.  Every workgroup
+ * reads all the keys its rows see.  0 if unsupported.  For harnesses that pick rows at the edges or count what is read.
+ */
+int attn_workgroup_rows(int B, int H, int S, int D, int dtype, int causal);
 
 #ifdef __cplusplus
 }

@@ -50,8 +50,9 @@ def _load() -> ctypes.CDLL:
     for f in (lib.attn_tile_rows, lib.attn_tile_keys):
         f.argtypes = [ctypes.c_int] * 3
         f.restype = ctypes.c_int
-    lib.attn_launch_rows.argtypes = [ctypes.c_int] * 6
-    lib.attn_launch_rows.restype = ctypes.c_int
+    for f in (lib.attn_launch_rows, lib.attn_workgroup_rows):
+        f.argtypes = [ctypes.c_int] * 6
+        f.restype = ctypes.c_int
     # include/probe.h
     lib.probe_mfma.argtypes = [vp] + [ctypes.c_int] * 4 + [vp]
     lib.probe_mfma.restype = ctypes.c_longlong
@@ -125,6 +126,10 @@ def attn_tile_keys(D: int, dtype: int, causal: bool) -> int:
 
 def attn_launch_rows(B: int, H: int, S: int, D: int, dtype: int, causal: bool) -> int:
     return int(lib.attn_launch_rows(int(B), int(H), int(S), int(D), int(dtype), int(bool(causal))))
+
+
+def attn_workgroup_rows(B: int, H: int, S: int, D: int, dtype: int, causal: bool) -> int:
+    return int(lib.attn_workgroup_rows(int(B), int(H), int(S), int(D), int(dtype), int(bool(causal))))
 
 
 # ---- include/probe.h: measuring aids (no product path calls them) -------------------------------

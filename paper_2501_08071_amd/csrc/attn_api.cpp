@@ -82,6 +82,12 @@ extern "C" int attn_launch_rows(int B, int H, int S, int D, int dtype, int causa
     return 32 * attn_pick_nw((long long)B * H, S);
 }
 
+extern "C" int attn_workgroup_rows(int B, int H, int S, int D, int dtype, int causal) {
+    const int rows = attn_launch_rows(B, H, S, D, dtype, causal);
+    const int groups = rows == 0 || attn_takes_rows64((long long)B * H, S, D) ? 0 : attn_stream_groups((long long)B * H, S, D, causal != 0);
+    return groups != 0 ? 32 * groups : rows;
+}
+
 extern "C" int attn_tile_keys(int D, int dtype, int causal) {
     return attn_supported(1, D, dtype, causal) ? attn_block_keys(D) : 0;
 }

@@ -236,6 +236,27 @@ def test_streamed_problems_by_size(P):
         assert groups(128, 128, D, True) == 2
 
 
+def test_rows_per_workgroup(P):
+    """What a workgroup owns: 32 or 64 rows where the kernel streams (its row groups, as its name has them), else the rows of the tile;
+    and the benchmark's count of the K and V bytes that its workgroups read."""
+    import sys
+    for D in (32, 64, 128):
+        for causal in (False, True):
+            for heads in (1, 2, 8, 25, 32, 60, 64, 110, 129):
+                for S in (1, 100, 129, 257, 512, 1024, 4096):
+                    name = P.attn_kernel_name(1, heads, S, D, 0, causal)
+                    want = 32 * int(name.split(",")[3]) if "stream" in name else 32 * int(name.split(",")[-1][:-1])
+                    assert P.attn_workgroup_rows(1, heads, S, D, 0, causal) == want, name
+    assert P.attn_workgroup_rows(1, 4, 4096, 32, 0, False) == 64 and P.attn_workgroup_rows(1, 4, 4096, 32, 0, True) == 32
+    assert P.attn_workgroup_rows(1, 1, 128, 96, 0, False) == 0 and P.attn_workgroup_rows(0, 1, 128, 64, 0, False) == 0
+    sys.path.insert(0, ROOT)
+    import bench
+    from paper_2501_08071_amd import inputs as I
+    # 64 workgroups a head, each 4096 keys of 32 elements twice; with the mask 128 of them, half of the keys and half a tile
+    assert bench.attn_bounds(P, I.workload(6), None)["l2_to_lds_bytes"] == 4 * 64 * 4096 * 32 * 2 * 2
+    assert bench.attn_bounds(P, I.workload(7), None)["l2_to_lds_bytes"] == 4 * sum(32 * (t + 1) for t in range(128)) * 32 * 2 * 2
+
+
 def test_streamed_problems_with_wide_heads(P):
     """D = 128 past one round of single row groups: (heads, S, mask) -> row groups, on either side of every line.  Those with
     0 and the short or odd ones next to them were 3 to 17 % slower when they streamed."""
