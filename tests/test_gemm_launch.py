@@ -138,6 +138,29 @@ def test_one_round_of_larger_tiles(L):
         assert L.long_blocks(*shape) == want, shape
 
 
+def test_the_shapes_of_the_gpu_tests_take_the_tiles_they_are_for(L):
+    """test_gemm_gpu.py's shapes between the square tiles, and of rows that are not aligned, by the tile and the block of K they take."""
+    from test_gemm_gpu import BETWEEN
+
+    def route(batch, M, N, K):
+        s = (batch, M, N, K)
+        if L.per_element(*s) and (K % 32 or N % 8):
+            return "element"
+        if K % 8 or N % 8:
+            return ("any 64, %d" % (64 if L.unaligned_blocks_64(*s) else 32)) if L.unaligned_64(*s) else "any 32"
+        tile = L.tile_of(*s)
+        if tile == 2:
+            return "128 x 256" if L.tiles_128x256(*s) else "two parts" if L.two_parts(*s) else "128"
+        if tile == 3:
+            return "64 x 128" if L.tiles_64x128(*s) else "64, long" if L.long_blocks(*s) else "64"
+        return str(tile)
+
+    want = ["64 x 128"] * 4 + ["two parts"] * 3 + ["128 x 256"] * 3 + ["64, long"] * 2
+    assert [route(*s) for s in BETWEEN[:12]] == want
+    rest = [route(*s) for s in BETWEEN[12:]]
+    assert set(rest) == {"any 64, 32", "any 64, 64"} and rest.count("any 64, 32") >= 5 and rest.count("any 64, 64") >= 5
+
+
 def test_unaligned_rows(L):
     """64 x 64 tiles from more than 512 (640) tiles of 32 x 32 on, in blocks of 64 for a long K or a middling one with few tiles."""
     for shape, want in (((2, 512, 511, 100), 0), ((2, 513, 511, 100), 1), ((2, 640, 511, 1201), 0), ((2, 641, 511, 1201), 1), ((1, 1 << 20, 7, 100), 0), ((1, 1 << 20, 8, 100), 1),
