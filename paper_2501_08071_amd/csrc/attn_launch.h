@@ -101,7 +101,10 @@ inline bool attn_splits_keys(long long BH, int S, int D) {
 // 10.4, 32 x 1024 14.8 26.0 19.5; D = 32, 8 x 1024 10.1 6.4 8.0, 4 x 4096 29.0 27.2 19.6, 8 x 4096 30.4 50.7 35.9.  With the mask:
 // D = 128, 4 x 4096 46.6 32.0 40.3, 8 x 2887 37.6 37.1 33.5, 16 x 2048 31.5 38.2 33.8; D = 64, 4 x 4096 32.4
 // 23.0 25.1, 6 x 1670 17.8 10.2 13.4, 32 x 512 9.8 9.0 7.9, 10 x 1701 18.9 16.7 14.6, 32 x 1024 14.1 19.7 15.3; D = 32, 8 x 4096 29.4 31.1
-// 23.9, 32 x 1024 11.2 15.4 11.6.  (A single tile of 128 rows keeps the kernel that attn_kernel_name has always named for it.)
+// 23.9, 32 x 1024 11.2 15.4 11.6.
+// A single tile of up to 128 rows keeps four wavefronts, not for its time but because attn_kernel_name's answer for it is pinned
+// (us with four wavefronts / streaming, one head, S = 1, 64, 128: D = 32 3.0 3.0, 3.2 3.1, 3.9 3.2; D = 64 6.3 3.4, 6.2 3.6, 5.7
+// 3.7, the only problems at D = 64 that still take four wavefronts; D = 128 5.6 4.2, 5.4 4.5, 7.0 4.9).
 inline bool attn_stream_wide_heads(long long BH, int S, bool causal, int groups);
 inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
     if (attn_pick_nw(BH, S) == ATTN_NW || (BH == 1 && S <= 128)) return 0;

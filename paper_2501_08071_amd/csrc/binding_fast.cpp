@@ -1,8 +1,8 @@
 // The Python entry points' way to the C ABI for the usual call: torch tensors on the GPU, right shapes, right types.
 //
 // A small launch takes the GPU 3 to 6 us.  Looking at each tensor from Python (dtype, shape, contiguity, address), asking torch
-// for the current stream and the ctypes call took 7.4 to 9 us (row softmax to attention), so the host was what such a call waited
-// for; from here it is about 2.  Every function takes the arguments of its namesake in binding.py and returns its result,
+// for the current stream and the ctypes call took 7.2 to 9.8 us (row softmax to product), so the host was what such a call waited
+// for; from here it is 3.2 to 3.4, the launch itself most of it.  Every function takes the arguments of its namesake in binding.py and returns its result,
 // or None for anything out of the ordinary -- whatever is not exactly a tensor with memory of its own on the GPU, a wrong shape
 // or type, a status other than 0 (nothing has been launched then) -- and binding.py goes through its own checks, which say what
 // is wrong.
