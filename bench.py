@@ -41,20 +41,20 @@ ATTN_FILES = ("attn_fwd_gfx950.hip", "attn_fwd_stream_gfx950.hip", "attn_fwd_row
 ROW_FILES = ("rowops_gfx950.hip", "rowops_launch.h", "gfx950_common.h")
 GEMM_FILES = ("gemm_gfx950.hip", "gemm_launch.h", "gfx950_common.h")
 TRAFFIC = {
-    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 148961 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
+    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 146681 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "06d06df999277c75a0aa8294c590cd3caff5766ec233d36af1b0a0417cfe4e9c",
      "source": "profiles/attn_fwd_kernel_S4096_D128_bf16_causal.md"},
-    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 897807 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
+    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 900706 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "06d06df999277c75a0aa8294c590cd3caff5766ec233d36af1b0a0417cfe4e9c",
      "source": "profiles/attn_fwd_kernel_all_workloads.md"},
-    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98513.6 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
+    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98513.4 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "06d06df999277c75a0aa8294c590cd3caff5766ec233d36af1b0a0417cfe4e9c",
      "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
     "B4_H16_S1024_D64_f16": {"fetch_kib": 12460 * 2.0, "write_kib": 16640 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
+     "kernel_sha256": "06d06df999277c75a0aa8294c590cd3caff5766ec233d36af1b0a0417cfe4e9c",
      "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
     "B1_H4_S4096_D32_f16_paper": {"fetch_kib": 2611.3 * 2.0, "write_kib": 2112 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "04d3cb7a792462b586763ff67acdfbe1978e247dcdd08ee1e89bb50271c96d1a",
+     "kernel_sha256": "06d06df999277c75a0aa8294c590cd3caff5766ec233d36af1b0a0417cfe4e9c",
      "source": "profiles/attn_fwd_halves_stream_kernel.md"},
     # the row kernels (workload name as rowop_run reports it)
     "softmax_512x4096_f16 x16 rows": {"fetch_kib": 32798.0 * 2.0, "write_kib": 65536.0 * 1.0, "files": ROW_FILES,
@@ -65,16 +65,16 @@ TRAFFIC = {
      "source": "profiles/rowop_reg_kernel_softmax_rmsnorm.md"},
     # the GEMM + LeakyReLU kernels (the paper's shapes; the 256 x 256 tile's launches)
     "mmLeakyReLu_1x512x512x2048_f16": {"fetch_kib": 6188.0 * 2.0, "write_kib": 512.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
+     "kernel_sha256": "66be41ed70ac50d2667705968432f7ca4cb0408e74d2d268a65b62501a5f40ec",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
     "bmm_4x512x512x2048_f16": {"fetch_kib": 12333.0 * 2.0, "write_kib": 2048.0 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
+     "kernel_sha256": "66be41ed70ac50d2667705968432f7ca4cb0408e74d2d268a65b62501a5f40ec",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 98441.5 * 2.0, "write_kib": 32768.1 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
+    "mmLeakyReLu_1x4096x4096x4096_f16": {"fetch_kib": 98441.5 * 2.0, "write_kib": 32768.0 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "66be41ed70ac50d2667705968432f7ca4cb0408e74d2d268a65b62501a5f40ec",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
-    "mmLeakyReLu_1x8192x8192x8192_f16": {"fetch_kib": 786629.8 * 2.0, "write_kib": 131074.3 * 1.0, "files": GEMM_FILES,
-     "kernel_sha256": "50996b712bc302c16937238fe70bf5dd596fd800cdd3b443072640f0b042fda8",
+    "mmLeakyReLu_1x8192x8192x8192_f16": {"fetch_kib": 786620.0 * 2.0, "write_kib": 131075.6 * 1.0, "files": GEMM_FILES,
+     "kernel_sha256": "66be41ed70ac50d2667705968432f7ca4cb0408e74d2d268a65b62501a5f40ec",
      "source": "profiles/gemm_lrelu_kernel_mmLeakyReLu.md"},
 }
 

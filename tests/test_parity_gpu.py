@@ -34,7 +34,7 @@ def test_small_shapes_full_compare(B, H, S, D, dtype, causal):
 
 
 # The same edge lengths with so many (b,h) pairs that the library takes its full-size workgroups (256 query rows,
-# eight wavefronts): with few tiles it launches the same kernel with four wavefronts per workgroup.
+# eight wavefronts): with few tiles it launches other kernels, with fewer rows per workgroup.
 WIDE = [(3, 43, 1, 64), (3, 43, 33, 128), (3, 43, 65, 32), (3, 43, 129, 64), (3, 43, 200, 128), (3, 43, 257, 64),
         (3, 43, 300, 128), (3, 43, 257, 32)]
 
