@@ -1,4 +1,4 @@
-// Attention forward for problems that do not fill the chip with tiles of 128 or 256 query rows (attn_stream_groups): every
+// Attention forward for problems that do not fill the chip evenly with tiles of 128 or 256 query rows (attn_stream_groups): every
 // wavefront streams keys of its own, and the parts of a row are put together at the end.
 //
 // What bounds such a problem is latency: the launch, a chain over the keys, the loads it waits for (1.4 us from the request of a
@@ -6,9 +6,13 @@
 // (two halves of NH) work on all of them, wavefront w on the key blocks (32 keys) w, w + 2 NH, ...: the chain of a row is 2 NH
 // times shorter than the number of its blocks, all compute units have work, and the loop has no barrier.
 //   * K and V blocks go straight from global memory into LDS (global_load_lds_dwordx4), into buffers of the wavefront's own: one
-//     per tensor at D = 128, two at 64, four at 32, 128 KiB in all.  A block's buffer is loaded again as soon as its operands are
+//     per tensor at D = 128, as many as row groups at 64, two at 32.  A block's buffer is loaded again as soon as its operands are
 //     in registers.  (K straight into the operand registers, 32 rows of 32 bytes per instruction, was twice as slow: 8 heads x
 //     1024, D = 128 18.9 us, 10.8 by way of LDS.)
+//   * At D = 32, and at 64 with one row group, that is 64 KiB and at most 128 registers, so that two workgroups share a compute
+//     unit: four wavefronts to a SIMD fill each other's waits, one workgroup's start and end overlap with the other's loop, and the
+//     kernel also serves problems of several rounds (us, with twice the buffers and two wavefronts to a SIMD -> so: D = 32, 6 x 6422
+//     68 -> 62, with the mask 43 -> 35, 18 x 7992 295 -> 226; D = 64, 20 x 2048 with the mask 30.1 -> 23.5).
 //   * q is read once per workgroup and kept in registers (D = 128 with two groups: in LDS).
 //   * An operand read from LDS feeds the matrix instructions of all RG row groups.
 // Registers and the transposed formulation are those of attn_fwd_gfx950.hip: a lane holds values of one query row only, the
@@ -19,7 +23,7 @@
 // groups 4.2 to 7 us.
 //
 // Measured, two wavefronts for every 32 rows that share blocks -> this kernel (us, heads x S): D = 128, 8 x 333 with the mask 11.1 ->
-// 6.6; D = 64, 8 x 1024 12.3 -> 8.0; D = 32, 4 x 4096 29.0 -> 19.6.
+// 6.4; D = 64, 8 x 1024 12.3 -> 7.2; D = 32, 4 x 4096 29.0 -> 19.2.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -39,7 +43,8 @@ extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 template <int D, int RG, int NW>
 struct StreamLds {
     static constexpr int BLK = 32 * 2 * D;                            // one block of K or V
-    static constexpr int BUFS = D == 128 ? 1 : D == 64 ? 2 : 4;       // buffers per wavefront and tensor: 128 KiB in all
+    // buffers per wavefront and tensor: 64 KiB in all where the registers let two workgroups share a compute unit, else 128 KiB
+    static constexpr int BUFS = D == 128 ? 1 : D == 64 ? RG : 2;
     static constexpr int WAVE = 2 * BUFS * BLK;                       // a wavefront's K buffers, then its V buffers
     static constexpr int Q = NW * WAVE, STREAM = Q + RG * BLK;
     static constexpr int PASS = 4 * 32 / D < RG ? 4 * 32 / D : RG;    // the end: row groups added up at a time,
@@ -51,7 +56,7 @@ struct StreamLds {
 };
 
 template <int DT, int D, bool CAUSAL, int RG, int NH>
-__global__ __launch_bounds__(NH * 128) __attribute__((amdgpu_waves_per_eu(2)))
+__global__ __launch_bounds__(NH * 128) __attribute__((amdgpu_waves_per_eu(RG * D <= 64 ? 4 : 2)))
 void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
                             void* __restrict__ o, float* __restrict__ lse, int S, int BH, int nqt, float c, uint32_t qsign, int o16) {
     using E = Elem<DT>;
@@ -66,11 +71,22 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-    // (b,h) fastest: workgroups that read the same K and V are BH apart, and with BH a multiple of 8 on one XCD; under the
-    // causal mask the longest rows first
-    const int bh = (int)blockIdx.x % BH;
-    int qt = (int)blockIdx.x / BH;
-    if (CAUSAL) qt = nqt - 1 - qt;
+    // Workgroup -> rows.  (b,h) fastest: workgroups that read the same K and V are BH apart, and with BH a multiple of 8 on one
+    // XCD; under the causal mask the longest rows first.  With two groups and no mask an XCD (workgroup b runs on XCD b % 8) gets a
+    // run of whole heads instead, so that its L2 holds what its workgroups read (us before -> after: D = 128, 13 x 1188 20.4 -> 18.7,
+    // 5 x 2609 29.1 -> 27.7; D = 64, 1 x 11607 53.4 -> 53.0; D = 32, 2 x 8273 52.2 -> 51.6).  Under the mask that takes the long rows
+    // from the front: 1.1 to 1.4 times the time.
+    int bh, qt;
+    if (CAUSAL || RG == 1) {
+        bh = (int)blockIdx.x % BH;
+        qt = (int)blockIdx.x / BH;
+        if (CAUSAL) qt = nqt - 1 - qt;
+    } else {
+        const int x = (int)blockIdx.x & 7, each = (int)gridDim.x >> 3, more = (int)gridDim.x & 7;   // (the first `more` XCDs have one more)
+        const int item = x * each + (x < more ? x : more) + ((int)blockIdx.x >> 3);
+        bh = item / nqt;
+        qt = item - bh * nqt;
+    }
     const int q0 = qt * (32 * RG);
     const size_t head = (size_t)bh * S * D;
     const uint16_t* kh = k + head;
@@ -81,24 +97,32 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
     const uint32_t lds0 = (uint32_t)(uintptr_t)(LDS_AS uint8_t*)smem;
     const uint32_t ldsw = lds0 + wave * L::WAVE;
 
-    // Load instruction i: rows row0 + i RPI .. of a head (row0 < S, a multiple of 32), with the bank-conflict swizzle on the
-    // global side.  The instructions' offsets differ in the swizzle bits that come from i and in whole rows.  Rows past the end
-    // of the sequence are copies of the last one (masked, or never stored).
+    // Load instruction i of the 32 rows from row0 on (row0 < S, a multiple of 32), with the bank-conflict swizzle on the global
+    // side.  The instructions' offsets differ in the swizzle bits that come from i and in whole rows.  Rows past the end of the
+    // sequence are copies of the last one (masked, or never stored); a block that has none skips the arithmetic for them.
     constexpr int XM = D == 128 ? 3 : D == 64 ? 1 : 0;
     const uint32_t off0 = (uint32_t)((lane / CPR) * ROWB + (((lane % CPR) ^ swz<D>(lane / CPR)) << 4));
-    auto load_rows = [&](const uint16_t* base, int row0, int i, uint32_t dst) {
+    auto load_piece = [&](const uint16_t* src, int i, int past, uint32_t dst) {
         if constexpr (ATTN_DEBUG_POISON != 0) {
             // Debug build: NaN patterns where this load will land, so that an operand read before its block has landed (a wait that
             // counts too few loads), or after its buffer was given away, shows in the output.
             lds_write_b128(dst + 16 * lane, u32x4{0x7fff7fffu, 0x7fff7fffu, 0x7fff7fffu, 0x7fff7fffu});
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         }
+        lds_dma16(dst, src, (off0 ^ ((i & XM) << 4)) + (uint32_t)((i * RPI - past) * ROWB));
+    };
+    auto load_rows = [&](const uint16_t* base, int row0, int i, uint32_t dst) {
         const int over = row0 + i * RPI + lane / CPR - (S - 1);
-        lds_dma16(dst, base + (size_t)row0 * D, (off0 ^ ((i & XM) << 4)) + (uint32_t)((i * RPI - (over > 0 ? over : 0)) * ROWB));
+        load_piece(base + (size_t)row0 * D, i, over > 0 ? over : 0, dst);
     };
     auto load_block = [&](const uint16_t* base, int j, uint32_t dst) {
+        if (ATTN_DEBUG_POISON == 0 && 32 * j + 32 <= S) {   // (the debug build has one path, its writes in front of its loads)
 #pragma unroll
-        for (int i = 0; i < IPT; ++i) load_rows(base, 32 * j, i, dst + i * 1024);
+            for (int i = 0; i < IPT; ++i) load_piece(base + (size_t)j * (32 * D), i, 0, dst + i * 1024);
+        } else {
+#pragma unroll
+            for (int i = 0; i < IPT; ++i) load_rows(base, 32 * j, i, dst + i * 1024);
+        }
     };
     // The loads land in the order of issue: Q, K(0), V(0), K(1), V(1), ... (blocks of this wavefront); to wait for one is to
     // count what was issued after it.
@@ -158,12 +182,15 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
             for (int ks = 0; ks < KSTEPS; ++ks) qf[g][ks] = read_q(g, ks);
     }
 
+    constexpr int WARY = D == 128 ? 0 : ATTN_WARY;   // (at D = 128 the code for it costs 2 to 4 % of the shortest calls)
+    int wary = 0;  // blocks still to go whose row maxima are taken before the weights
     int buf = 0;   // byte offset of the block's buffers
 #pragma unroll 1
     for (int it = 0; it < mine; ++it) {
         const int j = wave + it * NW, left = mine - 1 - it;   // blocks still to come
         // ---- S = K Q^T ----
-        wait_blocks(1 + 2 * (left < BUFS - 1 ? left : BUFS - 1));
+        if (left >= BUFS - 1) wait_lds_dma<(2 * BUFS - 1) * IPT>();
+        else wait_blocks(1 + 2 * left);
         f32x16 s[RG];
         {
             u32x4 kf[KSTEPS];
@@ -195,7 +222,10 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
                 for (int r = 0; r < 16; ++r) s[g][r] = 8 * (r / 4) + r % 4 > lim ? -3.0e38f : s[g][r];
             }
         }
-        // the reference policy of attn_fwd_gfx950.hip: the true maxima of the first block, moved only when the weights outgrow it
+        // the reference policy of attn_fwd_gfx950.hip: the true maxima of the first block, moved only when the weights outgrow it;
+        // after that, for ATTN_WARY blocks, moved to every new maximum before the weights are taken (144 problems with peaked logits:
+        // 0.98 of the time of doing without, and the error of O against 64 bits, where a row's largest weight is exactly one, 0.81 of
+        // what it was instead of 0.94)
         auto look = [&](int g) {
             // vmax and vmax3 are asm, for which the compiler does not wait out a matrix instruction's latency
             asm volatile("s_nop 15\n\ts_nop 7" : "+v"(s[g]));
@@ -225,33 +255,53 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
                     for (int e = 0; e < 4; ++e) psum[g] = E::dot2_ones(pf[g][tt][e], psum[g]);
             }
         };
+        auto move = [&](int g, float m_new) {
+            const float alpha = __builtin_amdgcn_exp2f(m_ref[g] - m_new);
+            m_ref[g] = m_new;
+            l_run[g] *= alpha;
+#pragma unroll
+            for (int i = 0; i < DB; ++i)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[g][i][r] *= alpha;
+            wary = WARY;
+        };
         if (it == 0) {
 #pragma unroll
             for (int g = 0; g < RG; ++g) m_ref[g] = look(g);
         }
-        bool outgrown = false;
+        const bool look_first = WARY > 0 && wary > 0;
+        wary -= look_first;
+        // One group after the other at D = 32, where four wavefronts share a SIMD: the scores of the first need no registers any more in
+        // the second's turn.  Both together where two do (one by one 5 % slower at D = 64).
+        constexpr int TOGETHER = D == 32 ? 1 : RG;
 #pragma unroll
-        for (int g = 0; g < RG; ++g) {
-            weights(g);
-            outgrown |= !(psum[g] <= __builtin_exp2f(ATTN_MAX_SLACK));
-        }
-        if (__builtin_amdgcn_ballot_w64(outgrown) != 0) {
+        for (int g0 = 0; g0 < RG; g0 += TOGETHER) {
+            bool outgrown = false;
 #pragma unroll
-            for (int g = 0; g < RG; ++g) {
-                const float m_new = look(g), alpha = __builtin_amdgcn_exp2f(m_ref[g] - m_new);
-                m_ref[g] = m_new;
-                l_run[g] *= alpha;
+            for (int g = g0; g < g0 + TOGETHER; ++g) {
+                if (look_first) {
+                    const float m_new = look(g);
+                    if (__builtin_amdgcn_ballot_w64(m_new != m_ref[g]) != 0) move(g, m_new);
+                }
+            }
 #pragma unroll
-                for (int i = 0; i < DB; ++i)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[g][i][r] *= alpha;
+            for (int g = g0; g < g0 + TOGETHER; ++g) {
                 weights(g);
+                outgrown |= !(psum[g] <= __builtin_exp2f(ATTN_MAX_SLACK));
+            }
+            if (__builtin_amdgcn_ballot_w64(outgrown) != 0) {
+#pragma unroll
+                for (int g = g0; g < g0 + TOGETHER; ++g) {
+                    move(g, look(g));
+                    weights(g);
+                }
             }
         }
 #pragma unroll
         for (int g = 0; g < RG; ++g) l_run[g] += psum[g];
         // ---- O += V^T P ----
-        wait_blocks(left >= BUFS ? 2 * BUFS - 1 : 2 * left);
+        if (left >= BUFS) wait_lds_dma<(2 * BUFS - 1) * IPT>();
+        else wait_blocks(2 * left);
         u32x4 va[2][DB];
 #pragma unroll
         for (int tt = 0; tt < 2; ++tt)
