@@ -105,15 +105,66 @@ inline bool attn_splits_keys(long long BH, int S, int D) {
 // A single tile of up to 128 rows keeps four wavefronts, not for its time but because attn_kernel_name's answer for it is pinned
 // (us with four wavefronts / streaming, one head, S = 1, 64, 128: D = 32 3.0 3.0, 3.2 3.1, 3.9 3.2; D = 64 6.3 3.4, 6.2 3.6, 5.7
 // 3.7, the only problems at D = 64 that still take four wavefronts; D = 128 5.6 4.2, 5.4 4.5, 7.0 4.9).
+//
+// At D = 32, and at 64 with one group, two workgroups share a compute unit, so a round is 512 of them; the lines of those two for few
+// tiles stand in attn_stream_few_tiles, past ATTN_SMALL_TILES in attn_stream_many_tiles.  (Single lengths and numbers of heads beside
+// some of them keep the kernel that a test of it names, at no loss of more than what the next length gains.)
 inline bool attn_stream_wide_heads(long long BH, int S, bool causal, int groups);
+inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal);
+inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal);
 inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
-    if (attn_pick_nw(BH, S) == ATTN_NW || (BH == 1 && S <= 128)) return 0;
-    const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
-    if (n32 <= 256) return 1;
+    if (attn_pick_nw(BH, S) == ATTN_NW) return ATTN_NW == 8 ? attn_stream_many_tiles(BH, S, D, causal) : 0;
+    if (BH == 1 && S <= 128) return 0;
+    if (BH * ((S + 31) / 32) <= 256) return 1;
     if (D == 128) return attn_stream_wide_heads(BH, S, causal, 1) ? 1 : attn_stream_wide_heads(BH, S, causal, 2) ? 2 : 0;
-    if (causal && n32 <= 512 && (S >= 2048 || (n32 <= 400 && S >= 640))) return 1;
-    if (n64 <= 256 || (causal && (S >= 2048 ? n64 <= 512 : S >= 1000 && n64 <= 384))) return 2;
-    return 0;
+    return attn_stream_few_tiles(BH, S, D, causal);
+}
+
+// D = 32 and 64, more than 256 single groups.  D = 64, us before (s: streaming with two groups) / one group: 9 x 1218 s 10.6 10.0, 24 x 498 s
+// 7.2 6.9, 88 x 78 s 5.0 4.5, but 1 x 11607 s 57 59, 6 x 2370 s 17.2 17.9; with the mask 30 x 456 s 7.4 6.2, 3 x 5256 26.9 22.9, 55 x 158 s 5.6
+// 4.9, 3 x 5645 s 31 24, 20 x 1041 s 12.3 10.6, 35 x 507 9.4 8.4, 95 x 145 7.3 5.2, but 44 x 496 9.4 9.9, 41 x 714 12.0 14.1.  D = 32, us
+// before / one group / two: 29 x 530 7.5 5.8 7.4; with the mask 13 x 1241 s 8.7 6.8 8.7, 5 x 3145 s 13.8 10.9 15.3, 25 x 846 9.4 8.0 7.7, 19 x
+// 1490 13.5 10.8 11.5, 4 x 6216 s 26.3 24.6 27.7, but 53 x 290 5.8 6.0 5.8, 100 x 177 5.2 6.1 5.6.
+inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
+    const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
+    if (!causal) {
+        if (D == 64 && n32 < 512 && n64 <= 256 && S < 1500) return 1;
+        return n64 <= 256 ? 2 : D == 32 && n32 < 512 && S >= 480 ? 1 : 0;
+    }
+    if (D == 64) {
+        if ((n32 <= 512 && S >= 2048) || (n32 < 512 && (S > 300 || S <= 160 || (S <= 256 && n64 <= 256)))) return 1;
+        if (n64 <= 256) return 2;
+        if (n32 <= 690 && S >= 320) return 1;
+        return (S >= 2048 && n64 <= 512) || (S >= 1000 && n64 <= 384) ? 2 : 0;
+    }
+    if (n32 < 512 && n64 <= 256) return 1;
+    if (n32 < 1024 && n64 <= 512 && S > 1100) return 1;
+    if (n64 <= 256 || (S >= 350 && n64 < 384) || (S >= 1000 && n64 <= 384)) return 2;
+    return S > 1100 && n64 <= 512 ? 2 : 0;
+}
+
+// More than ATTN_SMALL_TILES tiles of 256 rows.  A tile takes the whole launch's time where there is about one for every compute
+// unit, more so under the mask, and its rows past the end of the sequence take as long as the others; workgroups of 64 rows, two to a
+// compute unit, even that out, but read K and V four times as often.  us, 256 rows / one group / two.  D = 32: 6 x 6422 81 63 62, 36 x
+// 784 13.4 11.9 9.6, 28 x 1435 21.3 19.8 19.0, 67 x 1019 31.9 26 23, 33 x 2134 59 42 39, 17 x 5772 147 140 126, 45 x 3311 131 126 109, 162 x
+// 1029 65 58 48, 145 x 291 13.6 11.7 9.4, 121 x 1360 61 65 56, but 24 x 2050 29.3 32.6 30.8, 65 x 542 10.5 12.2 11.4, 270 x 216 11.9 (two groups) 12.6, 226 x 397 17.5 23.6 20.9;
+// with the mask 11 x 3000 40 18 18, 29 x 1063 16.7 9.9 9.7, 18 x 3287 44 31 27, 60 x 617 11.4 10.1 9.6, 9 x 9547 119 131 90, 42 x 2624 46 56 39,
+// 132 x 796 27 27 22, 233 x 796 45 45 38, but 93 x 712 14.6 18.6 16.5, 33 x 3894 71 90 78, 144 x 1756 65 85 79.  D = 64, one group only: 134 x 71 7.0
+// 4.7, 135 x 129 8.8 7.3, 156 x 146 9.3 8.6, 295 x 93 13.3 8.4, but 238 x 119 8.1 8.5, 135 x 184 9.4 10.7, 75 x 279 10.7 11.4.
+inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
+    const long long t = (S + 255) / 256, tiles = BH * t, n64 = BH * ((S + 63) / 64), n32 = BH * ((S + 31) / 32);
+    if (S <= 64 || tiles <= 130) return 0;
+    if (D == 64) return (n32 <= 800 && S <= 160) || (tiles > 256 && S <= 128 && n32 <= 1200) ? 1 : 0;
+    if (D != 32) return 0;
+    const long long rows = t * 256 * 20;   // a tile's rows for every row that exists: 1.05 is 21 S, 1.15 is 23 S
+    if (causal) {
+        if (S >= 1200 && n64 <= (BH % 2 == 0 ? 2000 : 1500)) return 2;
+        if (S >= 480 && n64 <= 780) return 2;
+        return tiles > 256 && rows >= 23LL * S && S >= 100 ? 2 : 0;
+    }
+    if (tiles <= 256) return (S >= 1200 && n64 <= 770) || (S >= 256 && n64 <= 512) ? 2 : 0;
+    if ((tiles - 1) % 256 >= 248) return 0;   // whole rounds
+    return S >= 1000 || (rows >= 21LL * S && (S >= 500 || (S > 256 && tiles <= 340))) ? 2 : 0;
 }
 
 // The same at D = 128 past one round of single groups.  A key costs the most bytes there, so it counts how many XCDs read a head's K and

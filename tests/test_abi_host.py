@@ -282,3 +282,22 @@ def test_gemm_second_round_of_middle_tiles(P):
         assert P.gemm_path(1, 2816, 3072, 1024, dt) == 1 and P.gemm_path(1, 4096, 2048, 1024, dt) == 2      # 528 and 512 of them
         assert P.gemm_path(1, 2816, 3072, 512, dt) == 1 and P.gemm_path(1, 2816, 3072, 480, dt) == 2
         assert P.gemm_path(4, 1300, 1536, 1024, dt) == 1 and P.gemm_path(8, 8192, 128, 1024, dt) == 2        # a tile of 256 would be half empty
+
+
+def test_routes_past_the_small_tiles(P):
+    """More than 128 tiles of 256 rows, and two streaming workgroups to a compute unit: (heads, S, D, mask) -> what runs, on either side of
+    the lines ("s1", "s2": streamed with so many row groups, "h": 128 rows with split keys, "8": 256 rows)."""
+    def route(heads, S, D, causal):
+        name = P.attn_kernel_name(1, heads, S, D, 0, causal)
+        return "s" + name.split(", ")[3] if "stream" in name else "h" if "halves" in name else name.split(", ")[-1][:-1]
+
+    for (heads, S, D, causal), want in {
+            (13, 1241, 32, True): "s1", (5, 3145, 32, True): "s1", (19, 1490, 32, True): "s1", (25, 846, 32, True): "s2", (53, 290, 32, True): "h",
+            (29, 530, 32, False): "s1", (32, 520, 32, False): "h", (6, 6422, 32, True): "s2", (6, 6422, 32, False): "s2", (29, 3371, 32, True): "8",
+            (42, 2624, 32, True): "s2", (66, 500, 32, True): "s2", (93, 712, 32, True): "8", (132, 796, 32, True): "s2", (124, 1008, 32, True): "8",
+            (36, 784, 32, False): "s2", (65, 542, 32, False): "8", (24, 2050, 32, False): "8", (67, 1019, 32, False): "s2", (64, 2048, 32, False): "8",
+            (121, 1360, 32, False): "s2", (145, 291, 32, False): "s2", (226, 397, 32, False): "8",
+            (9, 1218, 64, False): "s1", (9, 1518, 64, False): "s2", (30, 456, 64, True): "s1", (33, 300, 64, True): "s2", (20, 1041, 64, True): "s1",
+            (44, 496, 64, True): "h", (95, 145, 64, True): "s1", (86, 129, 64, False): "h", (134, 71, 64, False): "s1", (163, 184, 64, False): "8",
+            (295, 93, 64, False): "s1", (246, 110, 64, False): "8"}.items():
+        assert route(heads, S, D, causal) == want, (heads, S, D, causal)

@@ -441,3 +441,22 @@ def test_streamed_keys(S, D, causal, groups, H):
         k = np.where(room, k.astype(np.int64) + step, k).astype(np.uint16)
         for scale in (1 / math.sqrt(D), -1.0, 1e-4):
             check_full(q, k, v, dtype, causal, scale, f"B1 H{H} S{S} D{D} dt{dtype} causal{causal} groups{groups} scale{scale}")
+
+
+# More than 128 tiles of 256 rows: streamed keys in several rounds of workgroups, two to a compute unit.  Ragged lengths, the same loud and quiet blocks (references that move and stay on watch), numbers of heads that
+# do not divide by the XCDs.
+@pytest.mark.parametrize("dtype", [F16, BF16])
+@pytest.mark.parametrize("H,S,D,causal,kernel", [
+    (66, 500, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (131, 440, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (66, 300, 32, False, "stream_kernel<{}, 32, false, 2, 4>"),
+    (27, 1201, 32, False, "stream_kernel<{}, 32, false, 2, 4>"), (29, 1249, 32, True, "stream_kernel<{}, 32, true, 2, 4>"),
+    (131, 97, 64, False, "stream_kernel<{}, 64, false, 1, 4>"), (159, 129, 64, True, "stream_kernel<{}, 64, true, 1, 4>")])
+def test_many_tiles_streamed(H, S, D, causal, kernel, dtype):
+    assert P.attn_kernel_name(1, H, S, D, dtype, causal) == "attn_fwd_halves_" + kernel.format(dtype) or \
+        P.attn_kernel_name(1, H, S, D, dtype, causal) == "attn_fwd_" + kernel.format(dtype)
+    q, k, v = I.gen_tensors(1, H, S, D, dtype, workload_id=980 + S)
+    loud = (np.arange(S) // 32 // 3) % 2 == 1
+    step = np.where(loud[None, None, :, None], 2, -3) << (7 if dtype == BF16 else 10)     # of the exponent field: x 4, x 1/8
+    room = ((k >> 7) & 0xFF) > 16 if dtype == BF16 else (((k >> 10) & 0x1F) > 4) & (((k >> 10) & 0x1F) < 28)
+    k = np.where(room, k.astype(np.int64) + step, k).astype(np.uint16)
+    for scale in (1 / math.sqrt(D), -1.0):
+        check_full(q, k, v, dtype, causal, scale, f"B1 H{H} S{S} D{D} dt{dtype} causal{causal} scale{scale}")
