@@ -69,7 +69,7 @@ extern "C" const char* attn_kernel_name(int B, int H, int S, int D, int dtype, i
     const long long bh = (long long)B * H;
     const int di = D == 32 ? 0 : D == 64 ? 1 : 2;
     if (const int groups = attn_stream_groups(bh, S, D, causal != 0)) return kStreamNames[groups - 1][dtype][di][causal != 0];
-    const int mode = attn_pick_nw(bh, S) == ATTN_NW ? 0 : attn_splits_keys(bh, S, D) ? 2 : 1;
+    const int mode = attn_splits_keys(bh, S, D, causal != 0) ? 2 : attn_pick_nw(bh, S) == ATTN_NW ? 0 : 1;
     return kKernelNames[mode][dtype][di][causal != 0];
 }
 
@@ -79,7 +79,8 @@ extern "C" int attn_tile_rows(int D, int dtype, int causal) {
 
 extern "C" int attn_launch_rows(int B, int H, int S, int D, int dtype, int causal) {
     if (B <= 0 || H <= 0 || !attn_supported(S, D, dtype, causal)) return 0;
-    return 32 * attn_pick_nw((long long)B * H, S);
+    const long long bh = (long long)B * H;
+    return 32 * (!attn_takes_rows64(bh, S, D) && attn_splits_keys(bh, S, D, causal != 0) ? ATTN_NW / 2 : attn_pick_nw(bh, S));
 }
 
 extern "C" int attn_workgroup_rows(int B, int H, int S, int D, int dtype, int causal) {

@@ -811,7 +811,7 @@ hipError_t attn_launch(const AttnLaunch& a) {
     // instruction reaches it)
     if (attn_takes_rows64(a.BH, a.S, a.D) && a.qsign == 0) return attn_launch_rows64(a);
     if (const int groups = attn_stream_groups(a.BH, a.S, a.D, a.causal != 0)) return attn_launch_stream(a, groups);
-    const bool full = attn_pick_nw(a.BH, a.S) == ATTN_NW, halves = attn_splits_keys(a.BH, a.S, a.D);
+    const bool halves = attn_splits_keys(a.BH, a.S, a.D, a.causal != 0), full = !halves && attn_pick_nw(a.BH, a.S) == ATTN_NW;
 #define ATTN_CASE(DT, DD, CZ)                                       \
     if (a.dtype == DT && a.D == DD && (a.causal != 0) == CZ) {   \
         if (full) return launch<DT, DD, CZ, ATTN_NW, 1>(a);         \

@@ -88,8 +88,24 @@ inline int attn_pick_nw(long long BH, int S) {
 // D = 128: S = 128 7.2 -> 8.3, 333 causal 10.9 -> 10.9, 512 12.7 -> 11.9, 2048 35.2 -> 27.9.  Over 488 problems it is done for (1
 // to 128 heads, S up to 16384, with and without the causal mask) the time is 0.63 to 1.01 of the unsplit kernel's, the error
 // of O against 64 bits (97 problems) 0.67 to 1.001 of it.
-inline bool attn_splits_keys(long long BH, int S, int D) {
-    return attn_can_split(D) && attn_pick_nw(BH, S) != ATTN_NW && S > (D == 128 ? 384 : D == 64 ? 128 : 256);
+//
+// Past ATTN_SMALL_TILES, D = 64 and 128.  With the mask the workgroup of a head's last rows takes as long as the whole launch while
+// there is one for every compute unit at most: half the rows with twice the wavefronts each are 0.6 of that.  Without it, where a second
+// round of 256-row tiles would hold a few only.  Measured, us with 256 rows / split: D = 64 with the mask, 6 x 5392 66 43, 22 x 1325 21.7 15.9,
+// 12 x 4071 52 37, 19 x 3162 48.2 38.4, 14 x 5193 74 70, but 58 x 937 21.0 21.6, 43 x 1375 26.4 26.7, 33 x 2528 43 48; D = 128, 14 x 2797 53 40,
+// 30 x 1500 34.4 32.4, 20 x 2949 60 56, but 40 x 1421 33.4 35.2, 26 x 2491 57 62.  Without the mask, D = 64, 55 x 1056 42.5 35.5, 10 x 7496 208 187,
+// 141 x 363 21.7 19.3, but 297 x 233 19.0 23.7, 95 x 671 38.2 42.0, 33 x 2715 88 99; D = 128, 10 x 6495 276 205, 16 x 4380 194 186, 88 x 633 38.8 33.1, but 265 x 224 28 36.
+inline bool attn_splits_wide(long long BH, int S, int D, bool causal) {
+    const long long tiles = BH * ((S + 255) / 256), n128 = BH * ((S + 127) / 128);
+    if (causal) return D == 64 ? (tiles <= 256 && S >= 1150) || (tiles <= 320 && S >= 5000)
+                               : D == 128 && ((tiles <= 190 && S >= 1450) || (tiles <= 250 && S >= 2000));
+    if (tiles <= 256) return false;
+    return D == 64 ? (n128 <= 512 && S >= 360) || (tiles <= 300 && S >= 3500) : D == 128 && ((n128 <= 512 && S >= 500) || (tiles <= 310 && S >= 4000));
+}
+inline bool attn_splits_keys(long long BH, int S, int D, bool causal) {
+    if (!attn_can_split(D)) return false;
+    if (attn_pick_nw(BH, S) == ATTN_NW) return ATTN_NW == 8 && attn_splits_wide(BH, S, D, causal);
+    return S > (D == 128 ? 384 : D == 64 ? 128 : 256);
 }
 
 // Problems that do not fill the chip with large tiles: row groups (of 32 rows) per workgroup of the kernel whose wavefronts each

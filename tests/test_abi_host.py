@@ -299,5 +299,10 @@ def test_routes_past_the_small_tiles(P):
             (121, 1360, 32, False): "s2", (145, 291, 32, False): "s2", (226, 397, 32, False): "8",
             (9, 1218, 64, False): "s1", (9, 1518, 64, False): "s2", (30, 456, 64, True): "s1", (33, 300, 64, True): "s2", (20, 1041, 64, True): "s1",
             (44, 496, 64, True): "h", (95, 145, 64, True): "s1", (86, 129, 64, False): "h", (134, 71, 64, False): "s1", (163, 184, 64, False): "8",
-            (295, 93, 64, False): "s1", (246, 110, 64, False): "8"}.items():
+            (295, 93, 64, False): "s1", (246, 110, 64, False): "8", (22, 1325, 64, True): "h", (58, 937, 64, True): "8", (14, 5193, 64, True): "h",
+            (33, 2528, 64, True): "8", (55, 1056, 64, False): "h", (95, 671, 64, False): "8", (10, 7496, 64, False): "h",
+            (14, 2797, 128, True): "h", (40, 1421, 128, True): "8", (20, 2949, 128, True): "h", (26, 2491, 128, True): "8", (88, 633, 128, False): "h",
+            (265, 224, 128, False): "8", (10, 6495, 128, False): "h"}.items():
         assert route(heads, S, D, causal) == want, (heads, S, D, causal)
+        rows = P.attn_launch_rows(1, heads, S, D, 0, causal)
+        assert want != "h" or rows == P.attn_workgroup_rows(1, heads, S, D, 0, causal) == 128

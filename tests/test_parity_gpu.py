@@ -443,14 +443,17 @@ def test_streamed_keys(S, D, causal, groups, H):
             check_full(q, k, v, dtype, causal, scale, f"B1 H{H} S{S} D{D} dt{dtype} causal{causal} groups{groups} scale{scale}")
 
 
-# More than 128 tiles of 256 rows: streamed keys in several rounds of workgroups, two to a compute unit.  Ragged lengths, the same loud and quiet blocks (references that move and stay on watch), numbers of heads that
+# More than 128 tiles of 256 rows: streamed keys in several rounds of workgroups, two to a compute unit, and keys split between two halves
+# of tiles of 128 rows.  Ragged lengths, the same loud and quiet blocks (references that move and stay on watch), numbers of heads that
 # do not divide by the XCDs.
 @pytest.mark.parametrize("dtype", [F16, BF16])
 @pytest.mark.parametrize("H,S,D,causal,kernel", [
     (66, 500, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (131, 440, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (66, 300, 32, False, "stream_kernel<{}, 32, false, 2, 4>"),
     (27, 1201, 32, False, "stream_kernel<{}, 32, false, 2, 4>"), (29, 1249, 32, True, "stream_kernel<{}, 32, true, 2, 4>"),
-    (131, 97, 64, False, "stream_kernel<{}, 64, false, 1, 4>"), (159, 129, 64, True, "stream_kernel<{}, 64, true, 1, 4>")])
-def test_many_tiles_streamed(H, S, D, causal, kernel, dtype):
+    (131, 97, 64, False, "stream_kernel<{}, 64, false, 1, 4>"), (159, 129, 64, True, "stream_kernel<{}, 64, true, 1, 4>"),
+    (33, 1153, 64, True, "halves_kernel<{}, 64, true, 4>"), (27, 1451, 128, True, "halves_kernel<{}, 128, true, 4>"),
+    (52, 1100, 64, False, "halves_kernel<{}, 64, false, 4>"), (87, 520, 128, False, "halves_kernel<{}, 128, false, 4>")])
+def test_many_tiles_streamed_and_split(H, S, D, causal, kernel, dtype):
     assert P.attn_kernel_name(1, H, S, D, dtype, causal) == "attn_fwd_halves_" + kernel.format(dtype) or \
         P.attn_kernel_name(1, H, S, D, dtype, causal) == "attn_fwd_" + kernel.format(dtype)
     q, k, v = I.gen_tensors(1, H, S, D, dtype, workload_id=980 + S)
