@@ -184,6 +184,13 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
 
     constexpr int WARY = D == 128 ? 0 : ATTN_WARY;   // (at D = 128 the code for it costs 2 to 4 % of the shortest calls)
     int wary = 0;  // blocks still to go whose row maxima are taken before the weights
+    // The largest sum of a lane's weights that leaves the reference where it is.  Besides range a move gains that the largest weight of
+    // every row is one and loses nothing to rounding.  Rows that move in groups of 32 (and not, as at D = 64 with two groups, of 64) are
+    // moved less often, and in a chain of few blocks no later move makes up for it: there they have less slack.  Error of O against 64 bits
+    // over that of rows moving in groups of 64, 2500 problems with logits peaked 1.5- to 8-fold: with ATTN_MAX_SLACK throughout 0.88 on average, 379
+    // problems above 1.001, up to 1.92 (lse 1.61), 44 % of those with two blocks to a wavefront and none with six or more; so 0.72, three
+    // above 1.001, 1.04 (lse 1.008).  Flat logits (standard normal) do not reach the limit; at 2^4 they do, for 1 to 4 % of the time.
+    const float limit = RG * D <= 64 && mine <= 6 ? __builtin_exp2f(5.0f) : __builtin_exp2f(ATTN_MAX_SLACK);
     int buf = 0;   // byte offset of the block's buffers
 #pragma unroll 1
     for (int it = 0; it < mine; ++it) {
@@ -263,14 +270,12 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
             for (int i = 0; i < DB; ++i)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[g][i][r] *= alpha;
-            wary = WARY;
+            wary = WARY + 1;   // (this block's is taken off below)
         };
         if (it == 0) {
 #pragma unroll
             for (int g = 0; g < RG; ++g) m_ref[g] = look(g);
         }
-        const bool look_first = WARY > 0 && wary > 0;
-        wary -= look_first;
         // One group after the other at D = 32, where four wavefronts share a SIMD: the scores of the first need no registers any more in
         // the second's turn.  Both together where two do (one by one 5 % slower at D = 64).
         constexpr int TOGETHER = D == 32 ? 1 : RG;
@@ -279,7 +284,7 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
             bool outgrown = false;
 #pragma unroll
             for (int g = g0; g < g0 + TOGETHER; ++g) {
-                if (look_first) {
+                if (WARY > 0 && wary > 0) {   // (also where the group before moved in this very block)
                     const float m_new = look(g);
                     if (__builtin_amdgcn_ballot_w64(m_new != m_ref[g]) != 0) move(g, m_new);
                 }
@@ -287,7 +292,7 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
 #pragma unroll
             for (int g = g0; g < g0 + TOGETHER; ++g) {
                 weights(g);
-                outgrown |= !(psum[g] <= __builtin_exp2f(ATTN_MAX_SLACK));
+                outgrown |= !(psum[g] <= limit);
             }
             if (__builtin_amdgcn_ballot_w64(outgrown) != 0) {
 #pragma unroll
@@ -297,6 +302,7 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
                 }
             }
         }
+        wary -= WARY > 0 && wary > 0;
 #pragma unroll
         for (int g = 0; g < RG; ++g) l_run[g] += psum[g];
         // ---- O += V^T P ----

@@ -443,6 +443,29 @@ def test_streamed_keys(S, D, causal, groups, H):
             check_full(q, k, v, dtype, causal, scale, f"B1 H{H} S{S} D{D} dt{dtype} causal{causal} groups{groups} scale{scale}")
 
 
+# Two blocks to a wavefront, and in the second one key that outweighs all others of its rows by 2^6 to 2^15, less than a weight can hold.
+# The reference has to follow it even so, as it does where rows move in larger groups: the largest weight is then exactly one.  Only that key
+# has a value, so what is left in O is the rounding of the other weights' sum in 32 bits: logits are exact products, |scale| log2(e) is off by
+# 2^-24 of an exponent of 15 at most (1e-6), the sum of 700 weights by as many half ulps at most (4e-5, in fact a tenth of it).  A weight
+# that is rounded away from one is off by up to 2^-9 (bfloat16) and 2^-12 (binary16: 2.4e-4).
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("D,groups,dtype", [(32, 1, F16), (32, 1, BF16), (32, 2, F16), (32, 2, BF16), (64, 1, BF16)])
+@pytest.mark.parametrize("S", [360, 456, 500])
+def test_streamed_reference_follows_the_largest_weight(S, D, groups, dtype, causal):
+    H = next(h for s, d, c, g, h in _streamed(S, D, causal) if g == groups)
+    shape = (1, H, S, D)
+    q, k, v = (np.zeros(shape, np.float32) for _ in range(3))
+    q[..., 0] = 0.75 + np.arange(S) % 113 / 128
+    blocks = (S + 31) // 32
+    for h in range(H):
+        key = min(32 * (8 + h % (blocks - 8)) + 7 * h % 32, S - 1)
+        k[0, h, key, 0], v[0, h, key] = 6.0, 1.0
+    q, k, v = (I.to_bits(t, dtype) for t in (q, k, v))
+    o, _ = run_gpu(q, k, v, dtype, causal, 1.0)
+    o_ref, _ = oracle.attn_oracle(q, k, v, causal, 1.0, dtype)
+    assert np.abs(o - o_ref).max() <= 4e-5, f"H{H} S{S} D{D} dt{dtype} causal{causal} groups{groups}"
+
+
 # More than 128 tiles of 256 rows: streamed keys in several rounds of workgroups, two to a compute unit, and keys split between two halves
 # of tiles of 128 rows.  Ragged lengths, the same loud and quiet blocks (references that move and stay on watch), numbers of heads that
 # do not divide by the XCDs.
