@@ -536,7 +536,7 @@ hipError_t launch64(const AttnLaunch& a) {
     constexpr int BR = 256;
     const int nqt = (a.S + BR - 1) / BR;
     const long long blocks = (long long)nqt * a.BH;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    if (!attn_grid_fits(blocks, 256)) return hipErrorInvalidConfiguration;
     const uint16_t* q = (const uint16_t*)a.q;
     const uint16_t* k = (const uint16_t*)a.k;
     const uint16_t* v = (const uint16_t*)a.v;

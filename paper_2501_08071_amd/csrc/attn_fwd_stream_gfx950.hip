@@ -388,7 +388,7 @@ hipError_t launch(const AttnLaunch& a) {
     constexpr int NH = ATTN_NW / 2, BR = 32 * RG;
     int nqt = (a.S + BR - 1) / BR;
     const long long blocks = (long long)nqt * a.BH;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    if (!attn_grid_fits(blocks, NH * 128)) return hipErrorInvalidConfiguration;
     const uint16_t *q = (const uint16_t*)a.q, *k = (const uint16_t*)a.k, *v = (const uint16_t*)a.v;
     void* o = a.o;
     float* lse = a.lse;

@@ -71,6 +71,9 @@ constexpr bool attn_can_split(int D) { return attn_alternating(D) ? attn_block_k
 static_assert(ATTN_PP_KEYS == 32 || ATTN_PP_KEYS == 64, "block size of the alternating-phase loop");
 static_assert(ATTN_PP_KEYS_D64 == 32 || ATTN_PP_KEYS_D64 == 64 || ATTN_PP_KEYS_D64 == 128, "block size of the alternating-phase loop at D = 64");
 
+// Can a grid of so many workgroups be launched?  The runtime takes fewer than 2^32 work-items.
+constexpr bool attn_grid_fits(long long blocks, int threads) { return blocks <= 0xffffffffLL / threads; }
+
 // Wavefronts per workgroup for a problem of BH (b,h) pairs and S rows: ATTN_NW (256 query rows per workgroup),
 // or half of that when the larger tiles would leave at least half of the 256 compute units without a
 // workgroup (the smaller workgroups also fit two to a compute unit at D = 32).
@@ -169,7 +172,7 @@ inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
 // 4.7, 135 x 129 8.8 7.3, 156 x 146 9.3 8.6, 295 x 93 13.3 8.4, but 238 x 119 8.1 8.5, 135 x 184 9.4 10.7, 75 x 279 10.7 11.4.
 inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
     const long long t = (S + 255) / 256, tiles = BH * t, n64 = BH * ((S + 63) / 64), n32 = BH * ((S + 31) / 32);
-    if (S <= 64 || tiles <= 130) return 0;
+    if (S <= 64 || tiles <= 130 || !attn_grid_fits(n64, 64 * ATTN_NW)) return 0;   // (tiles of 256 rows still fit where theirs are too many)
     if (D == 64) return (n32 <= 800 && S <= 160) || (tiles > 256 && S <= 128 && n32 <= 1200) ? 1 : 0;
     if (D != 32) return 0;
     const long long rows = t * 256 * 20;   // a tile's rows for every row that exists: 1.05 is 21 S, 1.15 is 23 S

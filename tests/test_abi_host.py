@@ -306,3 +306,13 @@ def test_routes_past_the_small_tiles(P):
         assert route(heads, S, D, causal) == want, (heads, S, D, causal)
         rows = P.attn_launch_rows(1, heads, S, D, 0, causal)
         assert want != "h" or rows == P.attn_workgroup_rows(1, heads, S, D, 0, causal) == 128
+
+
+def test_grids_past_the_launch_limit_keep_large_tiles(P):
+    """A launch takes fewer than 2^32 work-items.  Streaming workgroups of 64 rows reach that at a quarter of the rows that workgroups of 256
+    do (512 work-items either way): from there on the problem keeps the larger tiles, which can still be launched."""
+    for causal in (False, True):
+        for heads, S in ((524300, 1000), (540000, 1000), (4200000, 100), (8388600, 100), (2097000, 257), (1 << 20, 512)):
+            name, rows = P.attn_kernel_name(1, heads, S, 32, 0, causal), P.attn_workgroup_rows(1, heads, S, 32, 0, causal)
+            assert heads * -(-S // rows) * 512 < 1 << 32, (heads, S, causal, name)
+    assert "stream" in P.attn_kernel_name(1, 524000, 1000, 32, 0, False) and P.attn_workgroup_rows(1, 524300, 1000, 32, 0, False) == 256
