@@ -105,8 +105,8 @@ int attn_tile_rows(int D, int dtype, int causal);
 int attn_tile_keys(int D, int dtype, int causal);
 
 /*
- * attn_tile_rows, or half of it ("..., 4>" in the kernel's name) when this very problem has so few tiles of that many rows that
- * half of the chip would be idle, or when they would fill it unevenly.  0 if unsupported.
+ * attn_tile_rows ("..., 8>" in the kernel's name), or half of it ("..., 4>") when this very problem has so few tiles of that many
+ * rows that half of the chip would be idle, or when they would fill it unevenly.  0 if unsupported.
  */
 int attn_launch_rows(int B, int H, int S, int D, int dtype, int causal);
 

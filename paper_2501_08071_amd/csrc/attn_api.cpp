@@ -80,7 +80,9 @@ extern "C" int attn_tile_rows(int D, int dtype, int causal) {
 extern "C" int attn_launch_rows(int B, int H, int S, int D, int dtype, int causal) {
     if (B <= 0 || H <= 0 || !attn_supported(S, D, dtype, causal)) return 0;
     const long long bh = (long long)B * H;
-    return 32 * (!attn_takes_rows64(bh, S, D) && attn_splits_keys(bh, S, D, causal != 0) ? ATTN_NW / 2 : attn_pick_nw(bh, S));
+    if (attn_takes_rows64(bh, S, D)) return 32 * ATTN_NW;
+    const bool half = attn_stream_groups(bh, S, D, causal != 0) != 0 || attn_splits_keys(bh, S, D, causal != 0);
+    return 32 * (half ? ATTN_NW / 2 : attn_pick_nw(bh, S));
 }
 
 extern "C" int attn_workgroup_rows(int B, int H, int S, int D, int dtype, int causal) {

@@ -308,6 +308,17 @@ def test_routes_past_the_small_tiles(P):
         assert want != "h" or rows == P.attn_workgroup_rows(1, heads, S, D, 0, causal) == 128
 
 
+def test_launch_rows_and_the_kernel_name_agree(P):
+    """attn_launch_rows is half a tile exactly where the kernel's name ends in "..., 4>", for streamed problems of many tiles too."""
+    for D in (32, 64, 128):
+        for causal in (False, True):
+            for heads in (1, 2, 8, 25, 60, 66, 67, 129, 131, 145, 270, 295, 1000):
+                for S in (1, 64, 97, 129, 257, 291, 500, 520, 796, 1100, 1201, 1451, 3000, 4096):
+                    name = P.attn_kernel_name(1, heads, S, D, 0, causal)
+                    rows, own = P.attn_launch_rows(1, heads, S, D, 0, causal), P.attn_workgroup_rows(1, heads, S, D, 0, causal)
+                    assert rows == (128 if name.endswith(", 4>") else 256) and own == (32 * int(name.split(", ")[3]) if "stream" in name else rows), name
+
+
 def test_grids_past_the_launch_limit_keep_large_tiles(P):
     """A launch takes fewer than 2^32 work-items.  Streaming workgroups of 64 rows reach that at a quarter of the rows that workgroups of 256
     do (512 work-items either way): from there on the problem keeps the larger tiles, which can still be launched."""

@@ -36,7 +36,7 @@ def test_small_shapes_full_compare(B, H, S, D, dtype, causal):
 # The same edge lengths with so many (b,h) pairs that the library takes its full-size workgroups (256 query rows,
 # eight wavefronts): with few tiles it launches other kernels, with fewer rows per workgroup.
 WIDE = [(3, 43, 1, 64), (3, 43, 33, 128), (3, 43, 65, 32), (3, 43, 129, 64), (3, 43, 200, 128), (3, 43, 257, 64),
-        (3, 43, 300, 128), (3, 43, 257, 32)]
+        (3, 43, 300, 128), (3, 43, 500, 32)]
 
 
 @pytest.mark.parametrize("causal", [False, True])
@@ -44,6 +44,7 @@ WIDE = [(3, 43, 1, 64), (3, 43, 33, 128), (3, 43, 65, 32), (3, 43, 129, 64), (3,
 @pytest.mark.parametrize("B,H,S,D", WIDE)
 def test_small_shapes_full_size_workgroups(B, H, S, D, dtype, causal):
     assert P.attn_launch_rows(B, H, S, D, dtype, causal) == P.attn_tile_rows(D, dtype, causal) == 256
+    assert P.attn_workgroup_rows(B, H, S, D, dtype, causal) == 256 and P.attn_kernel_name(B, H, S, D, dtype, causal).endswith(", 8>")
     q, k, v = I.gen_tensors(B, H, S, D, dtype, workload_id=500 + S)
     check_full(q, k, v, dtype, causal, 1 / math.sqrt(D), f"B{B} H{H} S{S} D{D} dt{dtype} causal{causal}")
 
@@ -471,6 +472,7 @@ def test_streamed_reference_follows_the_largest_weight(S, D, groups, dtype, caus
 # do not divide by the XCDs.
 @pytest.mark.parametrize("dtype", [F16, BF16])
 @pytest.mark.parametrize("H,S,D,causal,kernel", [
+    (129, 257, 32, False, "stream_kernel<{}, 32, false, 2, 4>"), (129, 257, 32, True, "stream_kernel<{}, 32, true, 2, 4>"),
     (66, 500, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (131, 440, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (66, 300, 32, False, "stream_kernel<{}, 32, false, 2, 4>"),
     (27, 1201, 32, False, "stream_kernel<{}, 32, false, 2, 4>"), (29, 1249, 32, True, "stream_kernel<{}, 32, true, 2, 4>"),
     (131, 97, 64, False, "stream_kernel<{}, 64, false, 1, 4>"), (159, 129, 64, True, "stream_kernel<{}, 64, true, 1, 4>"),
