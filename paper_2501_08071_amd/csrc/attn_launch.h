@@ -139,26 +139,33 @@ inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
     return attn_stream_few_tiles(BH, S, D, causal);
 }
 
-// D = 32 and 64, more than 256 single groups.  D = 64, us before (s: streaming with two groups) / one group: 9 x 1218 s 10.6 10.0, 24 x 498 s
-// 7.2 6.9, 88 x 78 s 5.0 4.5, but 1 x 11607 s 57 59, 6 x 2370 s 17.2 17.9; with the mask 30 x 456 s 7.4 6.2, 3 x 5256 26.9 22.9, 55 x 158 s 5.6
-// 4.9, 3 x 5645 s 31 24, 20 x 1041 s 12.3 10.6, 35 x 507 9.4 8.4, 95 x 145 7.3 5.2, but 44 x 496 9.4 9.9, 41 x 714 12.0 14.1.  D = 32, us
-// before / one group / two: 29 x 530 7.5 5.8 7.4; with the mask 13 x 1241 s 8.7 6.8 8.7, 5 x 3145 s 13.8 10.9 15.3, 25 x 846 9.4 8.0 7.7, 19 x
-// 1490 13.5 10.8 11.5, 4 x 6216 s 26.3 24.6 27.7, but 53 x 290 5.8 6.0 5.8, 100 x 177 5.2 6.1 5.6.
+// D = 32 and 64, more than 256 single groups.  One group halves a workgroup's chain and its registers (two workgroups to a compute unit: 512
+// are a round), two read K and V half as often.  Which XCDs read a head counts for that: workgroup b runs on XCD b % 8; with one group or the mask
+// it works on head b % BH, so that with an odd number of heads every XCD reads every head, with an even one that is no multiple of
+// four every other, while without the mask two groups have whole heads to an XCD.  Times of one over the other, geometric mean (least .. most), three
+// sets of buffers in turn:
+//   D = 64, no mask, one group / two, n64 <= 256, n32 < 512, S < 1500: up to 128 keys and 384 groups 0.90 (0.86 .. 1.05); longer, multiples of four heads 0.95
+//   (0.88 .. 0.99), other even numbers 0.94 (0.90 .. 0.97) up to 320 groups and 1.04 (0.93 .. 1.17) above, odd ones 1.13 (0.89 .. 1.34).
+//   D = 64 with the mask, one group / two, n32 <= 512: 0.77 (0.61 .. 1.04), but odd numbers of heads with 192 to 384 keys 0.99 (0.84 .. 1.07).  One group /
+//   keys split, up to 690 groups: even numbers of heads from 289 keys on 0.76 (0.55 .. 1.01), odd ones from 513 on 0.75 (0.56 .. 1.00), between 1.00 (0.93 .. 1.10).
+//   D = 32 with the mask, two groups / keys split, n64 < 384: 321 to 384 keys and even numbers of heads 0.87 (0.73 .. 0.99), odd ones with 385 to 512 1.01 (0.94
+//   .. 1.07), with more 0.90 (0.76 .. 1.01).
 inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
     const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
+    const bool even = BH % 2 == 0;
     if (!causal) {
-        if (D == 64 && n32 < 512 && n64 <= 256 && S < 1500) return 1;
+        if (D == 64 && n32 < 512 && n64 <= 256 && S < 1500 && ((S <= 128 && n32 <= 384) || BH % 4 == 0 || (even && n32 <= 320))) return 1;
         return n64 <= 256 ? 2 : D == 32 && n32 < 512 && S >= 480 ? 1 : 0;
     }
     if (D == 64) {
-        if ((n32 <= 512 && S >= 2048) || (n32 < 512 && (S > 300 || S <= 160 || (S <= 256 && n64 <= 256)))) return 1;
+        if ((n32 <= 512 && S >= 2048) || (n32 < 512 && (even || S <= 192 || S > 384 || n64 > 256))) return 1;
         if (n64 <= 256) return 2;
-        if (n32 <= 690 && S >= 320) return 1;
+        if (n32 <= 690 && S > (even ? 288 : 512)) return 1;
         return (S >= 2048 && n64 <= 512) || (S >= 1000 && n64 <= 384) ? 2 : 0;
     }
     if (n32 < 512 && n64 <= 256) return 1;
     if (n32 < 1024 && n64 <= 512 && S > 1100) return 1;
-    if (n64 <= 256 || (S >= 350 && n64 < 384) || (S >= 1000 && n64 <= 384)) return 2;
+    if (n64 <= 256 || (S > 320 && n64 < 384 && (even || S <= 384 || S > 512)) || (S >= 1000 && n64 <= 384)) return 2;
     return S > 1100 && n64 <= 512 ? 2 : 0;
 }
 
