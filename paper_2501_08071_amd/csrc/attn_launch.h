@@ -126,8 +126,7 @@ inline bool attn_splits_keys(long long BH, int S, int D, bool causal) {
 // 3.7, the only problems at D = 64 that still take four wavefronts; D = 128 5.6 4.2, 5.4 4.5, 7.0 4.9).
 //
 // At D = 32, and at 64 with one group, two workgroups share a compute unit, so a round is 512 of them; the lines of those two for few
-// tiles stand in attn_stream_few_tiles, past ATTN_SMALL_TILES in attn_stream_many_tiles.  (Single lengths and numbers of heads beside
-// some of them keep the kernel that a test of it names, at no loss of more than what the next length gains.)
+// tiles stand in attn_stream_few_tiles, past ATTN_SMALL_TILES in attn_stream_many_tiles.
 inline bool attn_stream_wide_heads(long long BH, int S, bool causal, int groups);
 inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal);
 inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal);
@@ -148,25 +147,27 @@ inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
 //   (0.88 .. 0.99), other even numbers 0.94 (0.90 .. 0.97) up to 320 groups and 1.04 (0.93 .. 1.17) above, odd ones 1.13 (0.89 .. 1.34).
 //   D = 64 with the mask, one group / two, n32 <= 512: 0.77 (0.61 .. 1.04), but odd numbers of heads with 192 to 384 keys 0.99 (0.84 .. 1.07).  One group /
 //   keys split, up to 690 groups: even numbers of heads from 289 keys on 0.76 (0.55 .. 1.01), odd ones from 513 on 0.75 (0.56 .. 1.00), between 1.00 (0.93 .. 1.10).
-//   D = 32 with the mask, two groups / keys split, n64 < 384: 321 to 384 keys and even numbers of heads 0.87 (0.73 .. 0.99), odd ones with 385 to 512 1.01 (0.94
-//   .. 1.07), with more 0.90 (0.76 .. 1.01).
+//     Beyond that two groups / keys split, up to 512 pairs from 1985 keys on 0.82 (0.70 .. 1.00), up to 384 from 1000 on 0.93 (0.82 .. 1.07).
+//   D = 32, no mask: two groups while they are one to a compute unit (one group / two 0.99, 0.88 .. 1.21); then, up to 512 groups, one group / keys split 0.82 (0.69
+//   .. 1.00), with more 1.00 (0.87 .. 1.27).
+//   D = 32 with the mask, one group / two, n64 <= 256: 0.80 (0.67 .. 0.97); up to 512 with more than 1100 keys 0.92 (0.70 .. 1.10), and 0.67 (0.44 .. 0.92) of
+//   split keys.  Two groups / keys split, up to 512 pairs of 321 to 1100 keys: even numbers of heads 0.86 (0.73 .. 0.99), odd ones with up to 384 0.94
+//   (0.92 .. 0.97), with 385 to 512 1.01 (0.94 .. 1.07), with more 0.90 (0.76 .. 1.01); up to 320 keys 0.98 (0.94 .. 1.00).
 inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
     const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
     const bool even = BH % 2 == 0;
     if (!causal) {
+        // (512 groups, just one round, are as fast as 256 pairs: 0.97 .. 1.01)
         if (D == 64 && n32 < 512 && n64 <= 256 && S < 1500 && ((S <= 128 && n32 <= 384) || BH % 4 == 0 || (even && n32 <= 320))) return 1;
-        return n64 <= 256 ? 2 : D == 32 && n32 < 512 && S >= 480 ? 1 : 0;
+        return n64 <= 256 ? 2 : D == 32 && n32 <= 512 && S > 256 ? 1 : 0;
     }
     if (D == 64) {
-        if ((n32 <= 512 && S >= 2048) || (n32 < 512 && (even || S <= 192 || S > 384 || n64 > 256))) return 1;
-        if (n64 <= 256) return 2;
+        if (n32 <= 512) return even || S <= 192 || S > 384 || n64 > 256 ? 1 : 2;
         if (n32 <= 690 && S > (even ? 288 : 512)) return 1;
-        return (S >= 2048 && n64 <= 512) || (S >= 1000 && n64 <= 384) ? 2 : 0;
+        return (S > 1984 && n64 <= 512) || (S >= 1000 && n64 <= 384) ? 2 : 0;
     }
-    if (n32 < 512 && n64 <= 256) return 1;
-    if (n32 < 1024 && n64 <= 512 && S > 1100) return 1;
-    if (n64 <= 256 || (S > 320 && n64 < 384 && (even || S <= 384 || S > 512)) || (S >= 1000 && n64 <= 384)) return 2;
-    return S > 1100 && n64 <= 512 ? 2 : 0;
+    if (n64 <= 256 || (n64 <= 512 && S > 1100)) return 1;
+    return n64 <= 512 && S > 320 && (even || S <= 384 || S > 512) ? 2 : 0;
 }
 
 // More than ATTN_SMALL_TILES tiles of 256 rows.  A tile takes the whole launch's time where there is about one for every compute

@@ -115,12 +115,11 @@ SPLIT = [(257, 32), (288, 32), (319, 32), (385, 128), (416, 128), (449, 128), (1
 
 
 # The kernel that splits the keys of every block between two halves of a workgroup's wavefronts, which serves what lies between the
-# streaming kernel and tiles of 256 rows: the same lengths (and one of several rounds of the LDS buffers, ragged), the same loud and
-# quiet halves in both element types, the same lowest logits, at the least number of heads that takes it.
+# streaming kernel and tiles of 256 rows: the same lengths (and one of several rounds of the LDS buffers, ragged; at D = 32 with the mask
+# the longest that takes it, one round), the same loud and quiet halves in both element types, the same lowest logits, at the least number of heads that takes it.
 @pytest.mark.parametrize("loud", [0, 1])
-@pytest.mark.parametrize("causal", [False, True])
 @pytest.mark.parametrize("dtype", [F16, BF16])
-@pytest.mark.parametrize("S,D", SPLIT)
+@pytest.mark.parametrize("S,D,causal", [(S, D, causal) for S, D in SPLIT for causal in (False, True) if (S, D, causal) != (1100, 32, True)] + [(512, 32, True)])
 def test_split_keys(S, D, dtype, causal, loud):
     kernel = HALVES.format(D)
     H = _heads(kernel, S, D, causal)
