@@ -178,20 +178,27 @@ inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
 // with the mask 11 x 3000 40 18 18, 29 x 1063 16.7 9.9 9.7, 18 x 3287 44 31 27, 60 x 617 11.4 10.1 9.6, 9 x 9547 119 131 90, 42 x 2624 46 56 39,
 // 132 x 796 27 27 22, 233 x 796 45 45 38, but 93 x 712 14.6 18.6 16.5, 33 x 3894 71 90 78, 144 x 1756 65 85 79.  D = 64, one group only: 134 x 71 7.0
 // 4.7, 135 x 129 8.8 7.3, 156 x 146 9.3 8.6, 295 x 93 13.3 8.4, but 238 x 119 8.1 8.5, 135 x 184 9.4 10.7, 75 x 279 10.7 11.4.
+//
+// D = 32, two groups over 256 rows where the rule gives them (geometric mean, least .. most; 2600 problems, three sets of buffers in turn).  With the mask, tiles mostly
+// past the end of the sequence (waste of 15 %), more than a round of them: from 480 keys on 0.85 (0.73 .. 1.01), 257 to 384 0.80 (0.63 .. 0.96), 100 to
+// 128 0.91 (0.81 .. 0.97); 129 to 256 and 385 to 479 only where the last round of tiles is at most half full, 0.87 (0.79 .. 1.01), in a fuller one 1.07 (0.95
+// .. 1.20).  Without it, 500 to 999 keys, 5 % of waste, in a last round that is three quarters full 20 %: 0.84 (0.61 .. 1.02), others of that length 0.96 (0.83 .. 1.14).
 inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
     const long long t = (S + 255) / 256, tiles = BH * t, n64 = BH * ((S + 63) / 64), n32 = BH * ((S + 31) / 32);
     if (S <= 64 || tiles <= 130 || !attn_grid_fits(n64, 64 * ATTN_NW)) return 0;   // (tiles of 256 rows still fit where theirs are too many)
     if (D == 64) return (n32 <= 800 && S <= 160) || (tiles > 256 && S <= 128 && n32 <= 1200) ? 1 : 0;
     if (D != 32) return 0;
-    const long long rows = t * 256 * 20;   // a tile's rows for every row that exists: 1.05 is 21 S, 1.15 is 23 S
+    const long long last = (tiles - 1) % 256;                                                    // tiles of the last round, less one
+    auto waste = [&](int percent) { return t * 25600 >= (100LL + percent) * S; };                // rows of tiles past the end, of every 100
     if (causal) {
         if (S >= 1200 && n64 <= (BH % 2 == 0 ? 2000 : 1500)) return 2;
         if (S >= 480 && n64 <= 780) return 2;
-        return tiles > 256 && rows >= 23LL * S && S >= 100 ? 2 : 0;
+        return tiles > 256 && waste(15) && (S >= 480 || (S > 256 && S <= 384) || (S >= 100 && (S <= 128 || last < 128))) ? 2 : 0;
     }
     if (tiles <= 256) return (S >= 1200 && n64 <= 770) || (S >= 256 && n64 <= 512) ? 2 : 0;
     if ((tiles - 1) % 256 >= 248) return 0;   // whole rounds
-    return S >= 1000 || (rows >= 21LL * S && (S >= 500 || (S > 256 && tiles <= 340))) ? 2 : 0;
+    if (S >= 500) return S >= 1000 || waste(last < 192 ? 5 : 20) ? 2 : 0;
+    return S > 256 && waste(5) && tiles <= 340 ? 2 : 0;
 }
 
 // The same at D = 128 past one round of single groups.  A key costs the most bytes there, so it counts how many XCDs read a head's K and
