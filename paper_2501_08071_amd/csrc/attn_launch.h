@@ -183,6 +183,8 @@ inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
 // past the end of the sequence (waste of 15 %), more than a round of them: from 480 keys on 0.85 (0.73 .. 1.01), 257 to 384 0.80 (0.63 .. 0.96), 100 to
 // 128 0.91 (0.81 .. 0.97); 129 to 256 and 385 to 479 only where the last round of tiles is at most half full, 0.87 (0.79 .. 1.01), in a fuller one 1.07 (0.95
 // .. 1.20).  Without it, 500 to 999 keys, 5 % of waste, in a last round that is three quarters full 20 %: 0.84 (0.61 .. 1.02), others of that length 0.96 (0.83 .. 1.14).
+// Longer ones 0.82 (0.51 .. 1.05) past the first round, where whole rounds of whole tiles are as fast with 256 rows, which read K and V a quarter as often: 0.99 (0.92 ..
+// 1.07) with up to 5 % of waste (us, binary16: 64 x 2048 63.5 61.0, 128 x 1024 32.7 34.8, 256 x 1024 62.2 66.6, 32 x 4096 106.4 107.5, 8 x 16384 405 396; 256 x 512 21.0 24.2), with more 0.95 (0.91 .. 1.00).
 inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
     const long long t = (S + 255) / 256, tiles = BH * t, n64 = BH * ((S + 63) / 64), n32 = BH * ((S + 31) / 32);
     if (S <= 64 || tiles <= 130 || !attn_grid_fits(n64, 64 * ATTN_NW)) return 0;   // (tiles of 256 rows still fit where theirs are too many)
@@ -196,8 +198,8 @@ inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
         return tiles > 256 && waste(15) && (S >= 480 || (S > 256 && S <= 384) || (S >= 100 && (S <= 128 || last < 128))) ? 2 : 0;
     }
     if (tiles <= 256) return (S >= 1200 && n64 <= 770) || (S >= 256 && n64 <= 512) ? 2 : 0;
-    if ((tiles - 1) % 256 >= 248) return 0;   // whole rounds
-    if (S >= 500) return S >= 1000 || waste(last < 192 ? 5 : 20) ? 2 : 0;
+    if (S >= 1000) return last >= 248 && !waste(5) ? 0 : 2;
+    if (S >= 500) return waste(last < 192 ? 5 : 20) ? 2 : 0;
     return S > 256 && waste(5) && tiles <= 340 ? 2 : 0;
 }
 

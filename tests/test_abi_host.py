@@ -313,6 +313,9 @@ def test_routes_past_the_small_tiles(P):
             (230, 418, 32, True): "8", (225, 416, 32, True): "8", (494, 214, 32, True): "8", (460, 198, 32, True): "8", (236, 389, 32, True): "8", (300, 198, 32, True): "s2",
             (160, 418, 32, True): "s2", (230, 380, 32, True): "s2", (480, 128, 32, True): "s2", (480, 129, 32, True): "8", (334, 706, 32, False): "8", (150, 648, 32, False): "8",
             (300, 706, 32, False): "s2", (150, 630, 32, False): "s2",
+            # whole rounds of whole tiles only: with 5 % of the rows past the end they stream
+            (128, 2048, 32, False): "8", (128, 1951, 32, False): "8", (128, 1950, 32, False): "s2", (128, 1281, 32, False): "s2", (128, 1536, 32, False): "8", (64, 2943, 32, False): "8",
+            (256, 512, 32, False): "8", (128, 2049, 32, False): "s2",
             (14, 2797, 128, True): "h", (40, 1421, 128, True): "8", (20, 2949, 128, True): "h", (26, 2491, 128, True): "8", (88, 633, 128, False): "h",
             (265, 224, 128, False): "8", (10, 6495, 128, False): "h"}.items():
         assert route(heads, S, D, causal) == want, (heads, S, D, causal)
