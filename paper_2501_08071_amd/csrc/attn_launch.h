@@ -171,36 +171,40 @@ inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
 }
 
 // More than ATTN_SMALL_TILES tiles of 256 rows.  A tile takes the whole launch's time where there is about one for every compute
-// unit, more so under the mask, and its rows past the end of the sequence take as long as the others; workgroups of 64 rows, two to a
-// compute unit, even that out, but read K and V four times as often.  us, 256 rows / one group / two.  D = 32: 6 x 6422 81 63 62, 36 x
-// 784 13.4 11.9 9.6, 28 x 1435 21.3 19.8 19.0, 67 x 1019 31.9 26 23, 33 x 2134 59 42 39, 17 x 5772 147 140 126, 45 x 3311 131 126 109, 162 x
-// 1029 65 58 48, 145 x 291 13.6 11.7 9.4, 121 x 1360 61 65 56, but 24 x 2050 29.3 32.6 30.8, 65 x 542 10.5 12.2 11.4, 270 x 216 11.9 (two groups) 12.6, 226 x 397 17.5 23.6 20.9;
-// with the mask 11 x 3000 40 18 18, 29 x 1063 16.7 9.9 9.7, 18 x 3287 44 31 27, 60 x 617 11.4 10.1 9.6, 9 x 9547 119 131 90, 42 x 2624 46 56 39,
-// 132 x 796 27 27 22, 233 x 796 45 45 38, but 93 x 712 14.6 18.6 16.5, 33 x 3894 71 90 78, 144 x 1756 65 85 79.  D = 64, one group only: 134 x 71 7.0
-// 4.7, 135 x 129 8.8 7.3, 156 x 146 9.3 8.6, 295 x 93 13.3 8.4, but 238 x 119 8.1 8.5, 135 x 184 9.4 10.7, 75 x 279 10.7 11.4.
-//
-// D = 32, two groups over 256 rows where the rule gives them (geometric mean, least .. most; 2600 problems, three sets of buffers in turn).  With the mask, tiles mostly
-// past the end of the sequence (waste of 15 %), more than a round of them: from 480 keys on 0.85 (0.73 .. 1.01), 257 to 384 0.80 (0.63 .. 0.96), 100 to
-// 128 0.91 (0.81 .. 0.97); 129 to 256 and 385 to 479 only where the last round of tiles is at most half full, 0.87 (0.79 .. 1.01), in a fuller one 1.07 (0.95
-// .. 1.20).  Without it, 500 to 999 keys, 5 % of waste, in a last round that is three quarters full 20 %: 0.84 (0.61 .. 1.02), others of that length 0.96 (0.83 .. 1.14).
-// Longer ones 0.82 (0.51 .. 1.05) past the first round, where whole rounds of whole tiles are as fast with 256 rows, which read K and V a quarter as often: 0.99 (0.92 ..
-// 1.07) with up to 5 % of waste (us, binary16: 64 x 2048 63.5 61.0, 128 x 1024 32.7 34.8, 256 x 1024 62.2 66.6, 32 x 4096 106.4 107.5, 8 x 16384 405 396; 256 x 512 21.0 24.2), with more 0.95 (0.91 .. 1.00).
+// unit, more so under the mask, and its rows past the end of the sequence take as long as the others; workgroups of 32 or 64 rows, two to a
+// compute unit, even that out, but read K and V four or eight times as often.  So they pay while the tiles are one round, unevenly filled, while many of their
+// rows do not exist, or while the last round is mostly empty.  At the lines: time streamed over 256 rows, geometric mean (least .. most), 4500
+// problems, three sets of buffers in turn.
 inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
     const long long t = (S + 255) / 256, tiles = BH * t, n64 = BH * ((S + 63) / 64), n32 = BH * ((S + 31) / 32);
-    if (S <= 64 || tiles <= 130 || !attn_grid_fits(n64, 64 * ATTN_NW)) return 0;   // (tiles of 256 rows still fit where theirs are too many)
-    if (D == 64) return (n32 <= 800 && S <= 160) || (tiles > 256 && S <= 128 && n32 <= 1200) ? 1 : 0;
-    if (D != 32) return 0;
-    const long long last = (tiles - 1) % 256;                                                    // tiles of the last round, less one
-    auto waste = [&](int percent) { return t * 25600 >= (100LL + percent) * S; };                // rows of tiles past the end, of every 100
-    if (causal) {
-        if (S >= 1200 && n64 <= (BH % 2 == 0 ? 2000 : 1500)) return 2;
-        if (S >= 480 && n64 <= 780) return 2;
-        return tiles > 256 && waste(15) && (S >= 480 || (S > 256 && S <= 384) || (S >= 100 && (S <= 128 || last < 128))) ? 2 : 0;
+    // (past the launch limit for its workgroups a problem keeps the larger tiles)
+    if (D == 64) {
+        if (!attn_grid_fits(n32, 64 * ATTN_NW)) return 0;
+        if (S <= 96) return 1;                       // up to 32 keys 0.32 (0.26 .. 0.38), to 64 0.60 (0.50 .. 0.69), to 96 0.77 (0.60 .. 1.01)
+        // 0.97 (0.94 .. 1.02) up to 600 groups, 1.07 (0.92 .. 1.26) above; past a round of tiles 0.77 (0.73 .. 0.82) up to 1200, 0.92 (0.73 .. 1.09) above
+        if (S <= 128) return n32 <= 600 || (tiles > 256 && n32 <= 1200) ? 1 : 0;
+        return S <= 160 && n32 <= 800 ? 1 : 0;       // 0.89 (0.82 .. 0.94), with more 0.95 (0.73 .. 1.22)
     }
-    if (tiles <= 256) return (S >= 1200 && n64 <= 770) || (S >= 256 && n64 <= 512) ? 2 : 0;
+    if (D != 32 || !attn_grid_fits(n64, 64 * ATTN_NW)) return 0;
+    const long long last = (tiles - 1) % 256;                                        // tiles of the last round, less one
+    auto waste = [&](int percent) { return t * 25600 >= (100LL + percent) * S; };    // so many percent of rows past the end, at least
+    if (causal) {
+        // 0.63 (0.39 .. 0.98); an odd number of heads, which every XCD reads, up to 1500 pairs 0.57 (0.37 .. 1.03), between 0.90 (0.76 .. 1.13), beyond 1.03 (0.81 ..
+        // 1.27), even ones beyond 0.92 (0.76 .. 1.25)
+        if (S >= 1200 && n64 <= (BH % 2 == 0 ? 2000 : 1500)) return 2;
+        // up to three quarters of a round of tiles 0.54 (0.37 .. 0.94), above 0.61 (0.44 .. 1.06); shorter sequences 1.01 (0.60 .. 1.36)
+        if (tiles <= 256) return S >= (n64 <= 768 ? 480 : 512) ? 2 : 0;
+        // from 480 keys on 0.85 (0.73 .. 1.01), 257 to 384 0.80 (0.63 .. 0.96), 100 to 128 0.91 (0.81 .. 0.97); the others where the last round of tiles is at
+        // most half full 0.87 (0.79 .. 1.01), else 1.07 (0.95 .. 1.20); with less waste 0.99 (0.76 .. 1.34)
+        return waste(15) && (S >= 480 || (S > 256 && S <= 384) || (S >= 100 && (S <= 128 || last < 128))) ? 2 : 0;
+    }
+    // one round of pairs 0.75 (0.56 .. 0.89), three quarters of a round of tiles 0.78 (0.56 .. 0.90), else 1.02 (0.84 .. 1.39)
+    if (tiles <= 256) return S >= 256 && n64 <= (S >= 1200 ? 768 : 512) ? 2 : 0;
+    // 0.82 (0.51 .. 1.05).  Whole rounds of whole tiles are as fast with 256 rows, which read K and V a quarter as often: 0.99 (0.92 .. 1.07) with up to 5 % of waste, with more
+    // 0.95 (0.91 .. 1.00).  (us, binary16, 256 rows / streamed: 64 x 2048 63.5 61.0, 128 x 1024 32.7 34.8, 32 x 4096 106.4 107.5, 8 x 16384 405 396, 256 x 512 21.0 24.2.)
     if (S >= 1000) return last >= 248 && !waste(5) ? 0 : 2;
-    if (S >= 500) return waste(last < 192 ? 5 : 20) ? 2 : 0;
-    return S > 256 && waste(5) && tiles <= 340 ? 2 : 0;
+    if (S >= 500) return waste(last < 192 ? 5 : 20) ? 2 : 0;    // 0.84 (0.61 .. 1.02), others of that length 0.96 (0.83 .. 1.14)
+    return S > 256 && waste(5) && tiles <= 340 ? 2 : 0;         // 0.74 (0.65 .. 0.89); more tiles 0.93 (0.76 .. 1.20), shorter 1.03 (0.83 .. 1.38)
 }
 
 // The same at D = 128 past one round of single groups.  A key costs the most bytes there, so it counts how many XCDs read a head's K and

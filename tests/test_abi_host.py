@@ -226,7 +226,8 @@ def test_streamed_problems_by_size(P):
         for causal in (False, True):
             assert groups(1, 128, D, causal) == 0 and groups(1, 129, D, causal) == 1 and groups(2, 1, D, causal) == 1
             assert groups(8, 1024, D, causal) == 1 and groups(128, 64, D, causal) == 1
-            assert groups(129, 64, D, causal) == 0 and groups(64, 1024, D, causal) == 0     # tiles of 256 rows fill half of the chip
+            assert groups(129, 128, D, causal) == (1 if D == 64 else 0)     # tiles of 256 rows fill half of the chip
+            assert groups(64, 1024, D, causal) == (2 if D == 32 and causal else 0)
             assert groups(32, 512, D, False) == 2 and groups(33, 512, D, False) == 0
         assert groups(4, 4096, D, False) == 2 and groups(4, 4096, D, True) == 1 and groups(5, 4096, D, False) == 0
         assert groups(8, 4096, D, True) == {32: 1, 64: 2, 128: 0}[D]
@@ -316,6 +317,11 @@ def test_routes_past_the_small_tiles(P):
             # whole rounds of whole tiles only: with 5 % of the rows past the end they stream
             (128, 2048, 32, False): "8", (128, 1951, 32, False): "8", (128, 1950, 32, False): "s2", (128, 1281, 32, False): "s2", (128, 1536, 32, False): "8", (64, 2943, 32, False): "8",
             (256, 512, 32, False): "8", (128, 2049, 32, False): "s2",
+            # 129 tiles are as any other number below a round: no line of its own, nor has the shortest sequence
+            (13, 2300, 32, True): "s1", (13, 2560, 32, True): "s2", (10, 3300, 32, True): "s2", (11, 3000, 32, True): "s2", (26, 1100, 32, True): "s2", (26, 1100, 32, False): "s2",
+            (129, 1, 64, False): "s1", (129, 64, 64, True): "s1", (1000, 64, 64, True): "s1", (129, 64, 32, True): "8", (129, 129, 64, False): "s1", (161, 129, 64, False): "8",
+            (52, 939, 32, True): "s2", (65, 766, 32, True): "s2", (65, 509, 32, True): "s2", (65, 513, 32, True): "s2", (97, 500, 32, True): "8",
+            (151, 128, 64, False): "8", (172, 128, 64, False): "8", (197, 114, 64, False): "8", (196, 121, 64, True): "8", (150, 128, 64, False): "s1", (263, 128, 64, False): "s1",
             (14, 2797, 128, True): "h", (40, 1421, 128, True): "8", (20, 2949, 128, True): "h", (26, 2491, 128, True): "8", (88, 633, 128, False): "h",
             (265, 224, 128, False): "8", (10, 6495, 128, False): "h"}.items():
         assert route(heads, S, D, causal) == want, (heads, S, D, causal)

@@ -35,7 +35,7 @@ def test_small_shapes_full_compare(B, H, S, D, dtype, causal):
 
 # The same edge lengths with so many (b,h) pairs that the library takes its full-size workgroups (256 query rows,
 # eight wavefronts): with few tiles it launches other kernels, with fewer rows per workgroup.
-WIDE = [(3, 43, 1, 64), (3, 43, 33, 128), (3, 43, 65, 32), (3, 43, 129, 64), (3, 43, 200, 128), (3, 43, 257, 64),
+WIDE = [(3, 43, 1, 32), (3, 43, 1, 128), (3, 43, 33, 128), (3, 43, 65, 32), (7, 30, 97, 64), (7, 23, 129, 64), (3, 43, 200, 128), (3, 43, 257, 64),
         (3, 43, 300, 128), (3, 43, 500, 32)]
 
 
@@ -471,6 +471,9 @@ def test_streamed_reference_follows_the_largest_weight(S, D, groups, dtype, caus
 # do not divide by the XCDs.
 @pytest.mark.parametrize("dtype", [F16, BF16])
 @pytest.mark.parametrize("H,S,D,causal,kernel", [
+    (129, 1, 64, False, "stream_kernel<{}, 64, false, 1, 4>"), (129, 1, 64, True, "stream_kernel<{}, 64, true, 1, 4>"), (600, 33, 64, True, "stream_kernel<{}, 64, true, 1, 4>"),
+    (129, 129, 64, False, "stream_kernel<{}, 64, false, 1, 4>"), (129, 129, 64, True, "stream_kernel<{}, 64, true, 1, 4>"),
+    (26, 1100, 32, False, "stream_kernel<{}, 32, false, 2, 4>"), (26, 1100, 32, True, "stream_kernel<{}, 32, true, 2, 4>"),
     (129, 257, 32, False, "stream_kernel<{}, 32, false, 2, 4>"), (129, 257, 32, True, "stream_kernel<{}, 32, true, 2, 4>"),
     (66, 500, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (131, 440, 32, True, "stream_kernel<{}, 32, true, 2, 4>"), (66, 300, 32, False, "stream_kernel<{}, 32, false, 2, 4>"),
     (27, 1201, 32, False, "stream_kernel<{}, 32, false, 2, 4>"), (29, 1249, 32, True, "stream_kernel<{}, 32, true, 2, 4>"),

@@ -23,10 +23,11 @@ F16, BF16 = I.F16, I.BF16
 @pytest.mark.parametrize("dtype", [F16, BF16])
 def test_every_instance_in_both_launch_modes(dtype, D, causal, wide):
     """S = 1100: five query tiles of 256 rows (nine of 128), the last one ragged; 1100 keys are more than four
-    rounds of the 256-key buffer ring.  26 heads give 130 large tiles, which takes the eight-wavefront instance;
+    rounds of the 256-key buffer ring.  26 heads give 130 large tiles, which takes the eight-wavefront instance (at D = 32 such problems
+    stream: there it is 102 heads of 1270, two whole rounds of tiles);
     two heads take the kernel whose wavefronts stream keys of their own (its last template argument, too, is four).  The same length
     in the instances between them: test_split_keys."""
-    B, H, S = (2, 13, 1100) if wide else (1, 2, 1100)
+    B, H, S = (1, 2, 1100) if not wide else (2, 51, 1270) if D == 32 else (2, 13, 1100)
     assert P.attn_launch_rows(B, H, S, D, dtype, causal) == (256 if wide else 128)
     name = P.attn_kernel_name(B, H, S, D, dtype, causal)
     assert name.endswith(", 8>" if wide else ", 4>") or "rows64" in name
