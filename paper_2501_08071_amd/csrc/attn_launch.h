@@ -208,19 +208,20 @@ inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
 }
 
 // The same at D = 128 past one round of single groups.  A key costs the most bytes there, so it counts how many XCDs read a head's K and
-// V: workgroup b runs on XCD b % 8 and works on head b % BH, so one XCD does where BH is a multiple of 8, two where it is one of 4, all
+// V.  Without the mask two groups have a run of whole heads to an XCD (workgroup b runs on XCD b % 8), whatever the number of heads: while the pairs are one round they are
+// 0.87 of the time of 128 rows (0.82 .. 1.00; 1000 problems of more than 128 keys, odd numbers of heads 0.86, multiples of four 0.88), with up to 128 keys 1.00 (0.95 .. 1.07), in a
+// second round 1.52 (1.39 .. 1.69).  us, 128 rows / two groups: 17 x 600 14.5 12.0, 25 x 576 14.7 12.6, 23 x 700 16.3 14.8, 27 x 512 13.6 11.9, 41 x 333 12.8 10.8, 62 x 256 11.2 10.2.
+// With the mask a workgroup works on head b % BH, so one XCD reads a head where BH is a multiple of 8, two where it is one of 4, all
 // eight where it is odd.  Even numbers of heads are better off streaming from 320 keys on, shorter sequences only where few XCDs
 // share a head, odd numbers only while the workgroups are few or the sequence is long.  Measured, us as before / one group / two, on
-// either side: 60 x 256 11.7 12.6 11.6, 62 x 256 11.8 16.0 13.3; 24 x 512 13.9 14.0 12.4, 27 x 512 14.6 20.7 16.2; 17 x 600 15.2 16.7 14.0, 25 x
-// 576 15.6 22.3 16.5; 15 x 1000 20.2 25.4 19.3; 110 x 100 9.1 11.2 10.2.  With the mask: 64 x 256 11.9 11.4 11.0, 55 x 256 11.6 13.0 11.8; 36 x 333 12.6
+// either side: 64 x 256 11.9 11.4 11.0, 55 x 256 11.6 13.0 11.8; 36 x 333 12.6
 // 11.5 11.6, 33 x 333 12.6 13.1 12.5; 24 x 640 15.6 13.2 13.3, 25 x 640 15.9 17.2 15.3; 64 x 200 10.8 10.6 10.0, 62 x 200 11.0 12.3 11.6; 18 x 1000
 // 19.5 20.3 18.6, 20 x 1000 19.7 20.8 20.4, 23 x 1000 20.8 29.9 24.1; 11 x 2000 29.7 33.0 28.0.
 inline bool attn_stream_wide_heads(long long BH, int S, bool causal, int groups) {
     const long long tiles = BH * ((S + 32 * groups - 1) / (32 * groups));
     const bool even = BH % 2 == 0;
     if (groups == 1) return causal && S >= 256 && tiles <= (S >= 900 || (even && S > 320) ? 512 : S >= 480 ? 440 : even ? 340 : S > 320 ? 352 : 300);
-    if (!causal)
-        return tiles <= 256 && (S >= 780 || (S > 320 && tiles <= (even ? 256 : S > 512 ? 210 : 165)) || (S > 256 && even && tiles <= 170) || (S > 128 && BH % 4 == 0));
+    if (!causal) return tiles <= 256 && S > 128;
     if (tiles <= 256) return S >= 480 || (S >= 90 && S <= 160 && BH % 8 == 0) || (S > 192 && (BH % 4 == 0 || (even && tiles <= 140)));
     return S >= 1000 && tiles <= (S >= 2000 ? 384 : S >= 1400 ? 340 : S >= 1200 ? 320 : S >= 1100 ? 310 : 300);
 }

@@ -259,16 +259,18 @@ def test_rows_per_workgroup(P):
 
 
 def test_streamed_problems_with_wide_heads(P):
-    """D = 128 past one round of single row groups: (heads, S, mask) -> row groups, on either side of every line.  Those with
+    """D = 128 past one round of single row groups: (heads, S, mask) -> row groups, on either side of every line.  Without the mask the
+    pairs stream while they are one round, whatever the number of heads; with it those with
     0 and the short or odd ones next to them were 3 to 17 % slower when they streamed."""
     def groups(heads, S, causal):
         name = P.attn_kernel_name(1, heads, S, 128, 0, causal)
         return int(name.split(", ")[3]) if "stream" in name else 0
 
     for (heads, S, causal), want in {
-            (110, 100, False): 0, (125, 128, False): 0, (56, 129, False): 2, (66, 129, False): 0, (60, 256, False): 2, (62, 256, False): 0, (34, 257, False): 2,
-            (42, 257, False): 0, (42, 333, False): 2, (41, 333, False): 0, (25, 333, False): 2, (30, 512, False): 2, (27, 512, False): 0, (31, 512, False): 0,
-            (17, 600, False): 2, (25, 576, False): 0, (23, 700, False): 0, (15, 780, False): 2, (19, 779, False): 0, (13, 1000, False): 2, (17, 1025, False): 0,
+            (110, 100, False): 0, (125, 128, False): 0, (56, 129, False): 2, (66, 129, False): 2, (85, 129, False): 2, (86, 129, False): 0, (60, 256, False): 2, (62, 256, False): 2,
+            (64, 256, False): 2, (65, 256, False): 0, (34, 257, False): 2, (42, 257, False): 2, (52, 257, False): 0, (42, 333, False): 2, (41, 333, False): 2, (43, 333, False): 0,
+            (25, 333, False): 2, (30, 512, False): 2, (27, 512, False): 2, (31, 512, False): 2, (33, 512, False): 0, (17, 600, False): 2, (25, 576, False): 2, (23, 700, False): 2,
+            (24, 700, False): 0, (15, 780, False): 2, (19, 779, False): 2, (20, 779, False): 0, (13, 1000, False): 2, (17, 1025, False): 0,
             (110, 100, True): 0, (120, 100, True): 2, (128, 89, True): 0, (80, 192, True): 0, (62, 200, True): 0, (60, 200, True): 2, (34, 255, True): 2,
             (37, 256, True): 1, (49, 256, True): 0, (42, 256, True): 1, (62, 256, True): 0, (64, 256, True): 2, (36, 333, True): 1, (41, 333, True): 0, (25, 333, True): 1,
             (35, 448, True): 0, (32, 448, True): 1, (25, 512, True): 1, (31, 512, True): 2, (24, 640, True): 1, (25, 640, True): 2, (21, 768, True): 2, (17, 900, True): 1,
