@@ -116,7 +116,9 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
         load_piece(base + (size_t)row0 * D, i, over > 0 ? over : 0, dst);
     };
     auto load_block = [&](const uint16_t* base, int j, uint32_t dst) {
-        if (ATTN_DEBUG_POISON == 0 && 32 * j + 32 <= S) {   // (the debug build has one path, its writes in front of its loads)
+        if (32 * j + 32 <= S) {
+            // (debug build: keeps the compiler from sharing the first write with the other path, so that each path's loads have their own)
+            if constexpr (ATTN_DEBUG_POISON != 0) asm volatile("; a whole block" ::: "memory");
 #pragma unroll
             for (int i = 0; i < IPT; ++i) load_piece(base + (size_t)j * (32 * D), i, 0, dst + i * 1024);
         } else {
