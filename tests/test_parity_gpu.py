@@ -417,10 +417,15 @@ def test_matrix_instruction_probe_runs():
 
 
 # Wavefronts that stream keys of their own (eight per workgroup, blocks of 32 keys dealt out in turn), one and two groups of 32
-# rows per workgroup: fewer blocks than wavefronts, exactly one each, one more; one block more than the buffers of a wavefront
-# hold (8 x 1, 2, 4 blocks at D = 128, 64, 32) and the first that goes round them; ragged ends of 1 and 31 keys; rows past the
+# rows per workgroup: fewer blocks than wavefronts, exactly one each, one more; as many as the buffers of the wavefronts hold (8 x _buffers blocks), one more, the first
+# that goes round them, and several rounds; ragged ends of 1 and 31 keys; rows past the
 # end in the last group or a whole group of them.  Loud and quiet blocks, so that the parts of a row weigh very differently, and
 # the reference of a part has to move where its first block is a quiet one.
+def _buffers(D, groups):
+    """Buffers per wavefront and tensor."""
+    return {128: 1, 64: groups, 32: 2}[D]
+
+
 def _streamed(S, D, causal):
     """Numbers of heads for which the library takes one and two row groups: two heads, and the least that has two groups (none
     where tiles of 256 rows fill the chip before that)."""
@@ -428,9 +433,21 @@ def _streamed(S, D, causal):
     return [(S, D, causal, 1, 2)] + [(S, D, causal, 2, h) for h in two[:1]]
 
 
-@pytest.mark.parametrize("S,D,causal,groups,H", [
-    c for S, D in [(33, 32), (65, 64), (161, 128), (256, 64), (257, 128), (287, 32), (513, 64), (545, 128), (1025, 32), (1087, 64), (1300, 32)]
-    for causal in (False, True) for c in _streamed(S, D, causal)])
+STREAMED = [c for S, D in [(33, 32), (65, 64), (161, 128), (256, 64), (257, 64), (257, 128), (287, 32), (287, 64), (512, 32), (513, 32), (513, 64), (544, 32), (545, 64), (545, 128),
+                           (1025, 32), (1087, 64), (1300, 32)]
+            for causal in (False, True) for c in _streamed(S, D, causal)]
+
+
+def test_streamed_cases_reach_the_edges():
+    """Every instance has a case just past its buffers, and a ragged one that goes round them several times.  (D = 64 with the mask takes two
+    groups for up to 384 keys and from 1000 on, never just past the 512 that its buffers hold.)"""
+    every = {(D, causal, groups) for D in (32, 64, 128) for causal in (False, True) for groups in (1, 2)}
+    rounds = lambda S, D, groups: -(-S // 32) / (8 * _buffers(D, groups))     # blocks to a buffer
+    assert {(D, causal, groups) for S, D, causal, groups, _ in STREAMED if 1 < rounds(S, D, groups) <= 1.25} == every - {(64, True, 2)}
+    assert {(D, causal, groups) for S, D, causal, groups, _ in STREAMED if rounds(S, D, groups) > 2 and S % 32} == every
+
+
+@pytest.mark.parametrize("S,D,causal,groups,H", STREAMED)
 def test_streamed_keys(S, D, causal, groups, H):
     for dtype in (F16, BF16):
         assert P.attn_kernel_name(1, H, S, D, dtype, causal) == f"attn_fwd_halves_stream_kernel<{dtype}, {D}, {str(causal).lower()}, {groups}, 4>"
