@@ -186,13 +186,15 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
 
     constexpr int WARY = D == 128 ? 0 : ATTN_WARY;   // (at D = 128 the code for it costs 2 to 4 % of the shortest calls)
     int wary = 0;  // blocks still to go whose row maxima are taken before the weights
+    bool watched = false;   // is this block one of them?  (from a move on also for the row group that comes after)
     // The largest sum of a lane's weights that leaves the reference where it is.  Besides range a move gains that the largest weight of
     // every row is one and loses nothing to rounding.  Rows that move in groups of 32 (and not, as at D = 64 with two groups, of 64) are
     // moved less often, and in a chain of few blocks no later move makes up for it: there they have less slack.  Error of O against 64 bits
     // over that of rows moving in groups of 64, 2500 problems with logits peaked 1.5- to 8-fold: with ATTN_MAX_SLACK throughout 0.88 on average, 379
-    // problems above 1.001, up to 1.92 (lse 1.61), 44 % of those with two blocks to a wavefront and none with six or more; so 0.72, three
-    // above 1.001, 1.04 (lse 1.008).  Flat logits (standard normal) do not reach the limit; at 2^4 they do, for 1 to 4 % of the time.
-    const float limit = RG * D <= 64 && mine <= 6 ? __builtin_exp2f(5.0f) : __builtin_exp2f(ATTN_MAX_SLACK);
+    // problems above 1.001, up to 1.92 (lse 1.61), 44 % of those with two blocks to a wavefront and none with six or more; so 0.73, five
+    // above 1.001, 1.04 at most (lse 1.008).  Flat logits (standard normal) do not reach the limit; 2^5 they do now and then, which costs a launch of one
+    // round 5 to 8 %, and with 2^7 the error is 0.75, eleven above 1.001.
+    const float limit = RG * D <= 64 && mine <= 6 ? __builtin_exp2f(6.0f) : __builtin_exp2f(ATTN_MAX_SLACK);
     int buf = 0;   // byte offset of the block's buffers
 #pragma unroll 1
     for (int it = 0; it < mine; ++it) {
@@ -272,12 +274,15 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
             for (int i = 0; i < DB; ++i)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[g][i][r] *= alpha;
-            wary = WARY + 1;   // (this block's is taken off below)
+            wary = WARY;
+            watched = WARY > 0;
         };
         if (it == 0) {
 #pragma unroll
             for (int g = 0; g < RG; ++g) m_ref[g] = look(g);
         }
+        watched = WARY > 0 && wary > 0;
+        wary -= watched;
         // One group after the other at D = 32, where four wavefronts share a SIMD: the scores of the first need no registers any more in
         // the second's turn.  Both together where two do (one by one 5 % slower at D = 64).
         constexpr int TOGETHER = D == 32 ? 1 : RG;
@@ -286,7 +291,7 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
             bool outgrown = false;
 #pragma unroll
             for (int g = g0; g < g0 + TOGETHER; ++g) {
-                if (WARY > 0 && wary > 0) {   // (also where the group before moved in this very block)
+                if (watched) {
                     const float m_new = look(g);
                     if (__builtin_amdgcn_ballot_w64(m_new != m_ref[g]) != 0) move(g, m_new);
                 }
@@ -304,7 +309,6 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
                 }
             }
         }
-        wary -= WARY > 0 && wary > 0;
 #pragma unroll
         for (int g = 0; g < RG; ++g) l_run[g] += psum[g];
         // ---- O += V^T P ----
