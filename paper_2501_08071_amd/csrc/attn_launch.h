@@ -145,7 +145,7 @@ inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
 // sets of buffers in turn:
 //   D = 64, no mask, one group / two, n64 <= 256, n32 < 512, S < 1500: up to 128 keys and 384 groups 0.90 (0.86 .. 1.05); longer, multiples of four heads 0.95
 //   (0.88 .. 0.99), other even numbers 0.94 (0.90 .. 0.97) up to 320 groups and 1.04 (0.93 .. 1.17) above, odd ones 1.13 (0.89 .. 1.34).
-//   D = 64 with the mask, one group / two, n32 <= 512: 0.77 (0.61 .. 1.04), but odd numbers of heads with 192 to 384 keys 0.99 (0.84 .. 1.07).  One group /
+//   D = 64 with the mask, one group / two, n32 <= 512: 0.77 (0.61 .. 1.04), but odd numbers of heads with 225 to 320 keys and more than 300 groups 1.02 (1.00 .. 1.07).  One group /
 //   keys split, up to 690 groups: even numbers of heads from 289 keys on 0.76 (0.55 .. 1.01), odd ones from 513 on 0.75 (0.56 .. 1.00), between 1.00 (0.93 .. 1.10).
 //     Beyond that two groups / keys split, up to 512 pairs from 1985 keys on 0.82 (0.70 .. 1.00), up to 384 from 1000 on 0.93 (0.82 .. 1.07).
 //   D = 32, no mask: two groups while they are one to a compute unit (one group / two 0.99, 0.88 .. 1.21); then, up to 512 groups, one group / keys split 0.82 (0.69
@@ -162,7 +162,7 @@ inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
         return n64 <= 256 ? 2 : D == 32 && n32 <= 512 && S > 256 ? 1 : 0;
     }
     if (D == 64) {
-        if (n32 <= 512) return even || S <= 192 || S > 384 || n64 > 256 ? 1 : 2;
+        if (n32 <= 512) return even || S <= 224 || S > 320 || n32 <= 300 || n64 > 256 ? 1 : 2;
         if (n32 <= 690 && S > (even ? 288 : 512)) return 1;
         return (S > 1984 && n64 <= 512) || (S >= 1000 && n64 <= 384) ? 2 : 0;
     }
@@ -181,8 +181,8 @@ inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
     if (D == 64) {
         if (!attn_grid_fits(n32, 64 * ATTN_NW)) return 0;
         if (S <= 96) return 1;                       // up to 32 keys 0.32 (0.26 .. 0.38), to 64 0.60 (0.50 .. 0.69), to 96 0.77 (0.60 .. 1.01)
-        // 0.97 (0.94 .. 1.02) up to 600 groups, 1.07 (0.92 .. 1.26) above; past a round of tiles 0.77 (0.73 .. 0.82) up to 1200, 0.92 (0.73 .. 1.09) above
-        if (S <= 128) return n32 <= 600 || (tiles > 256 && n32 <= 1200) ? 1 : 0;
+        // 0.97 (0.94 .. 1.01) up to 550 groups, 1.07 (0.92 .. 1.27) above; past a round of tiles 0.77 (0.73 .. 0.82) up to 1200, 0.92 (0.73 .. 1.09) above
+        if (S <= 128) return n32 <= 550 || (tiles > 256 && n32 <= 1200) ? 1 : 0;
         return S <= 160 && n32 <= 800 ? 1 : 0;       // 0.89 (0.82 .. 0.94), with more 0.95 (0.73 .. 1.22)
     }
     if (D != 32 || !attn_grid_fits(n64, 64 * ATTN_NW)) return 0;
@@ -194,9 +194,10 @@ inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
         if (S >= 1200 && n64 <= (BH % 2 == 0 ? 2000 : 1500)) return 2;
         // up to three quarters of a round of tiles 0.54 (0.37 .. 0.94), above 0.61 (0.44 .. 1.06); shorter sequences 1.01 (0.60 .. 1.36)
         if (tiles <= 256) return S >= (n64 <= 768 ? 480 : 512) ? 2 : 0;
-        // from 480 keys on 0.85 (0.73 .. 1.01), 257 to 384 0.80 (0.63 .. 0.96), 100 to 128 0.91 (0.81 .. 0.97); the others where the last round of tiles is at
-        // most half full 0.87 (0.79 .. 1.01), else 1.07 (0.95 .. 1.20); with less waste 0.99 (0.76 .. 1.34)
-        return waste(15) && (S >= 480 || (S > 256 && S <= 384) || (S >= 100 && (S <= 128 || last < 128))) ? 2 : 0;
+        // from 480 keys on 0.85 (0.73 .. 1.01), 257 to 384 0.80 (0.63 .. 0.96), 100 to 128 0.89 (0.80 .. 0.97), 129 to
+        // 256 up to a round and a half 0.89 (0.79 .. 1.05), with more tiles 1.09 (0.94 .. 1.20), 385 to 479 where the last round is at most half full 0.88 (0.78 .. 1.01),
+        // else 1.01 (0.95 .. 1.10); with less waste 0.99 (0.76 .. 1.34)
+        return waste(15) && (S >= 480 || (S > 256 ? S <= 384 || last < 128 : S >= 100 && (S <= 128 || tiles <= 384))) ? 2 : 0;
     }
     // one round of pairs 0.75 (0.56 .. 0.89), three quarters of a round of tiles 0.78 (0.56 .. 0.90), else 1.02 (0.84 .. 1.39)
     if (tiles <= 256) return S >= 256 && n64 <= (S >= 1200 ? 768 : 512) ? 2 : 0;

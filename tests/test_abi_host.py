@@ -306,14 +306,14 @@ def test_routes_past_the_small_tiles(P):
             (33, 2528, 64, True): "8", (55, 1056, 64, False): "h", (95, 671, 64, False): "8", (10, 7496, 64, False): "h",
             # odd numbers of heads, which every XCD reads: one group to a workgroup, or streaming at all, was up to 1.2 times as slow
             (114, 128, 64, False): "s2", (113, 128, 64, False): "s2", (39, 249, 64, False): "s2", (45, 192, 64, False): "s2", (58, 192, 64, False): "s2", (11, 1384, 64, False): "s2",
-            (88, 78, 64, False): "s1", (40, 249, 64, False): "s1", (24, 498, 64, False): "s1", (57, 237, 64, True): "s2", (58, 237, 64, True): "s1", (55, 381, 64, True): "h",
+            (88, 78, 64, False): "s1", (40, 249, 64, False): "s1", (24, 498, 64, False): "s1", (57, 237, 64, True): "s2", (58, 237, 64, True): "s1", (43, 196, 64, True): "s1", (39, 320, 64, True): "s2", (39, 321, 64, True): "s1", (55, 381, 64, True): "h",
             (43, 492, 64, True): "h", (42, 492, 64, True): "s1", (47, 505, 32, True): "h", (46, 505, 32, True): "s2",
             # no length has a kernel of its own: those next to a line with the same number of workgroups are on the same side of it
             (33, 479, 32, False): "s1", (33, 480, 32, False): "s1", (33, 481, 32, False): "h", (64, 319, 64, True): "s1", (64, 320, 64, True): "s1", (64, 321, 64, True): "h",
             (16, 2047, 64, True): "s2", (16, 2048, 64, True): "s2", (16, 2049, 64, True): "h", (16, 1023, 64, True): "s1", (16, 1024, 64, True): "s1", (16, 1025, 64, True): "s1",
             (30, 257, 64, True): "s1", (30, 300, 64, True): "s1", (30, 301, 64, True): "s1", (24, 1024, 32, True): "s2", (24, 1025, 32, True): "s2", (24, 1101, 32, True): "s1",
             # tiles that the sequence ends in: a round of them that is nearly full is faster all the same (230 x 418 1.06, 494 x 214 1.20, 334 x 706 1.05 when streamed)
-            (230, 418, 32, True): "8", (225, 416, 32, True): "8", (494, 214, 32, True): "8", (460, 198, 32, True): "8", (236, 389, 32, True): "8", (300, 198, 32, True): "s2",
+            (230, 418, 32, True): "8", (225, 416, 32, True): "8", (494, 214, 32, True): "8", (460, 198, 32, True): "8", (236, 389, 32, True): "8", (300, 198, 32, True): "s2", (1284, 196, 32, True): "8",
             (160, 418, 32, True): "s2", (230, 380, 32, True): "s2", (480, 128, 32, True): "s2", (480, 129, 32, True): "8", (334, 706, 32, False): "8", (150, 648, 32, False): "8",
             (300, 706, 32, False): "s2", (150, 630, 32, False): "s2",
             # whole rounds of whole tiles only: with 5 % of the rows past the end they stream
@@ -323,7 +323,7 @@ def test_routes_past_the_small_tiles(P):
             (13, 2300, 32, True): "s1", (13, 2560, 32, True): "s2", (10, 3300, 32, True): "s2", (11, 3000, 32, True): "s2", (26, 1100, 32, True): "s2", (26, 1100, 32, False): "s2",
             (129, 1, 64, False): "s1", (129, 64, 64, True): "s1", (1000, 64, 64, True): "s1", (129, 64, 32, True): "8", (129, 129, 64, False): "s1", (161, 129, 64, False): "8",
             (52, 939, 32, True): "s2", (65, 766, 32, True): "s2", (65, 509, 32, True): "s2", (65, 513, 32, True): "s2", (97, 500, 32, True): "8",
-            (151, 128, 64, False): "8", (172, 128, 64, False): "8", (197, 114, 64, False): "8", (196, 121, 64, True): "8", (150, 128, 64, False): "s1", (263, 128, 64, False): "s1",
+            (142, 128, 64, False): "8", (172, 128, 64, False): "8", (197, 114, 64, False): "8", (196, 121, 64, True): "8", (136, 128, 64, False): "s1", (263, 128, 64, False): "s1",
             (14, 2797, 128, True): "h", (40, 1421, 128, True): "8", (20, 2949, 128, True): "h", (26, 2491, 128, True): "8", (88, 633, 128, False): "h",
             (265, 224, 128, False): "8", (10, 6495, 128, False): "h"}.items():
         assert route(heads, S, D, causal) == want, (heads, S, D, causal)
