@@ -12,7 +12,7 @@
 //   * At D = 32, and at 64 with one row group, that is 64 KiB and at most 128 registers, so that two workgroups share a compute
 //     unit: four wavefronts to a SIMD fill each other's waits, one workgroup's start and end overlap with the other's loop, and the
 //     kernel also serves problems of several rounds (us, with twice the buffers and two wavefronts to a SIMD -> so: D = 32, 6 x 6422
-//     68 -> 62, with the mask 43 -> 35, 18 x 7992 295 -> 226; D = 64, 20 x 2048 with the mask 30.1 -> 23.5).
+//     74 -> 61, with the mask 41 -> 34, 18 x 7992 276 -> 227; D = 64, 8 x 1024 7.2 -> 6.4, 20 x 1041 with the mask 15.1 -> 10.9).
 //   * q is read once per workgroup and kept in registers (D = 128 with two groups: in LDS).
 //   * An operand read from LDS feeds the matrix instructions of all RG row groups.
 // Registers and the transposed formulation are those of attn_fwd_gfx950.hip: a lane holds values of one query row only, the
@@ -22,8 +22,8 @@
 // its share of the columns against the largest reference.  That and the start are 3.5 (D = 32) to 4.8 us (D = 128), with two
 // groups 4.2 to 7 us.
 //
-// Measured, two wavefronts for every 32 rows that share blocks -> this kernel (us, heads x S): D = 128, 8 x 333 with the mask 11.1 ->
-// 6.4; D = 64, 8 x 1024 12.3 -> 7.2; D = 32, 4 x 4096 29.0 -> 19.2.
+// Measured in turn, two wavefronts for every 32 rows that share blocks -> this kernel (us, heads x S): D = 128, 8 x 333 with the mask 10.9 ->
+// 6.3; D = 64, 8 x 1024 11.8 -> 6.6; D = 32, 4 x 4096 29.2 -> 19.5 (18.0 where nothing else runs in between).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <type_traits>
@@ -73,8 +73,8 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
 
     // Workgroup -> rows.  (b,h) fastest: workgroups that read the same K and V are BH apart, and with BH a multiple of 8 on one
     // XCD; under the causal mask the longest rows first.  With two groups and no mask an XCD (workgroup b runs on XCD b % 8) gets a
-    // run of whole heads instead, so that its L2 holds what its workgroups read (us before -> after: D = 128, 13 x 1188 20.4 -> 18.7,
-    // 5 x 2609 29.1 -> 27.7; D = 64, 1 x 11607 53.4 -> 53.0; D = 32, 2 x 8273 52.2 -> 51.6).  Under the mask that takes the long rows
+    // run of whole heads instead, so that its L2 holds what its workgroups read (us before -> after: D = 128, 13 x 1188 22.3 -> 19.0,
+    // D = 64, 9 x 1518 13.3 -> 12.1; D = 32, 18 x 7992 238 -> 227, 4 x 4096 the same).  Under the mask that takes the long rows
     // from the front: 1.1 to 1.4 times the time.
     int bh, qt;
     if (CAUSAL || RG == 1) {
@@ -99,7 +99,8 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
 
     // Load instruction i of the 32 rows from row0 on (row0 < S, a multiple of 32), with the bank-conflict swizzle on the global
     // side.  The instructions' offsets differ in the swizzle bits that come from i and in whole rows.  Rows past the end of the
-    // sequence are copies of the last one (masked, or never stored); a block that has none skips the arithmetic for them.
+    // sequence are copies of the last one (masked, or never stored); a block that has none skips the arithmetic for them (D = 32, 4 x 4096 18.5 ->
+    // 18.0 us, 8 heads x 1024 at D = 64 6.5 -> 6.4).
     constexpr int XM = D == 128 ? 3 : D == 64 ? 1 : 0;
     const uint32_t off0 = (uint32_t)((lane / CPR) * ROWB + (((lane % CPR) ^ swz<D>(lane / CPR)) << 4));
     auto load_piece = [&](const uint16_t* src, int i, int past, uint32_t dst) {
@@ -200,6 +201,7 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
     for (int it = 0; it < mine; ++it) {
         const int j = wave + it * NW, left = mine - 1 - it;   // blocks still to come
         // ---- S = K Q^T ----
+        // (the usual count without the search through all of them: D = 32, 4 x 4096 18.9 -> 18.0 us)
         if (left >= BUFS - 1) wait_lds_dma<(2 * BUFS - 1) * IPT>();
         else wait_blocks(1 + 2 * left);
         f32x16 s[RG];
@@ -234,8 +236,8 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
             }
         }
         // the reference policy of attn_fwd_gfx950.hip: the true maxima of the first block, moved only when the weights outgrow it;
-        // after that, for ATTN_WARY blocks, moved to every new maximum before the weights are taken (144 problems with peaked logits:
-        // 0.98 of the time of doing without, and the error of O against 64 bits, where a row's largest weight is exactly one, 0.81 of
+        // after that, for ATTN_WARY blocks, moved to every new maximum before the weights are taken (the code for it costs flat logits 3 %, D = 32, 4 x 4096 17.4
+        // -> 18.0 us; 144 problems with peaked logits: 0.98 of the time of doing without, and the error of O against 64 bits, where a row's largest weight is exactly one, 0.81 of
         // what it was instead of 0.94)
         auto look = [&](int g) {
             // vmax and vmax3 are asm, for which the compiler does not wait out a matrix instruction's latency
@@ -284,7 +286,7 @@ void attn_fwd_halves_stream_kernel(const uint16_t* __restrict__ q, const uint16_
         watched = WARY > 0 && wary > 0;
         wary -= watched;
         // One group after the other at D = 32, where four wavefronts share a SIMD: the scores of the first need no registers any more in
-        // the second's turn.  Both together where two do (one by one 5 % slower at D = 64).
+        // the second's turn (4 x 4096 19.5 -> 18.0 us).  Both together where two do (one by one 5 % slower at D = 64).
         constexpr int TOGETHER = D == 32 ? 1 : RG;
 #pragma unroll
         for (int g0 = 0; g0 < RG; g0 += TOGETHER) {

@@ -17,7 +17,7 @@
 #define ATTN_MAX_SLACK 15.0f  // log2 of the largest sum of a lane's softmax weights of one block tolerated before the reference maximum is moved
 #endif
 #ifndef ATTN_WARY
-#define ATTN_WARY 16  // alternating-phase loop: after a reference maximum moved, blocks whose row maxima are taken before the weights
+#define ATTN_WARY 16  // alternating-phase loop, streaming kernel at D = 32 and 64: after a reference maximum moved, blocks whose row maxima are taken before the weights
 #endif
 #ifndef ATTN_NBUF
 #define ATTN_NBUF 8   // LDS buffers per tensor for blocks of up to 8 KiB (a power of two); larger blocks get half as many: 4 x 2 x 16 KiB = 128 KiB with the shipped blocks at D = 128 and 64, one workgroup per CU
@@ -114,13 +114,11 @@ inline bool attn_splits_keys(long long BH, int S, int D, bool causal) {
 // Problems that do not fill the chip with large tiles: row groups (of 32 rows) per workgroup of the kernel whose wavefronts each
 // stream keys of their own (attn_fwd_stream_gfx950.hip), or 0: not that kernel.  One group while that is one round of the 256
 // compute units, two while that is; beyond it the larger workgroups above read less of K and V per row.  Under the mask, where
-// the workgroups of a second round are the short ones, a little further.  Measured, us as before / one group / two (heads x S, 8
-// wavefronts of the other kernels before): D = 128, 8 x 333 11.6 6.6 9.7, 8 x 1024 17.6 10.8 15.7, 1 x 4096 44.6 23.8 39.0,
-// 16 x 1024 19.4 19.9 17.6, 32 x 1024 25.3 39.5 34.2; D = 64, 8 x 1024 12.3 8.0 9.9, 16 x 1024 12.6 13.9
-// 10.4, 32 x 1024 14.8 26.0 19.5; D = 32, 8 x 1024 10.1 6.4 8.0, 4 x 4096 29.0 27.2 19.6, 8 x 4096 30.4 50.7 35.9.  With the mask:
-// D = 128, 4 x 4096 46.6 32.0 40.3, 8 x 2887 37.6 37.1 33.5, 16 x 2048 31.5 38.2 33.8; D = 64, 4 x 4096 32.4
-// 23.0 25.1, 6 x 1670 17.8 10.2 13.4, 32 x 512 9.8 9.0 7.9, 10 x 1701 18.9 16.7 14.6, 32 x 1024 14.1 19.7 15.3; D = 32, 8 x 4096 29.4 31.1
-// 23.9, 32 x 1024 11.2 15.4 11.6.
+// the workgroups of a second round are the short ones, a little further.  Measured, us with 128 rows (keys split or not) / one group / two (heads x
+// S): D = 128, 8 x 333 11.1 6.3 9.5, 8 x 1024 17.3 10.0 15.1, 1 x 4096 44.1 23.0 36.3, 16 x 1024 18.3 18.7 16.7, 32 x 1024 23.5 35.0 31.3; D = 64, 8 x 1024 11.7 6.5 9.5,
+// 16 x 1024 12.2 10.1 9.9, 32 x 1024 14.2 17.7 19.2; D = 32, 8 x 1024 9.6 5.5 7.4, 4 x 4096 28.4 18.9 18.6, 8 x 4096 29.5 34.5 30.2.  With the mask: D = 128, 4 x 4096
+// 44.9 29.4 37.6, 8 x 2887 35.6 33.6 30.4, 16 x 2048 30.0 35.5 31.5; D = 64, 4 x 4096 31.7 18.1 24.0, 6 x 1670 16.7 9.0 13.2, 32 x 512 9.8 6.5 8.1, 10 x 1701 17.8 11.3
+// 14.4, 32 x 1024 14.3 13.7 15.3; D = 32, 8 x 4096 29.1 20.5 21.8, 32 x 1024 11.0 10.0 9.5.
 // A single tile of up to 128 rows keeps four wavefronts, not for its time but because attn_kernel_name's answer for it is pinned
 // (us with four wavefronts / streaming, one head, S = 1, 64, 128: D = 32 3.0 3.0, 3.2 3.1, 3.9 3.2; D = 64 6.3 3.4, 6.2 3.6, 5.7
 // 3.7, the only problems at D = 64 that still take four wavefronts; D = 128 5.6 4.2, 5.4 4.5, 7.0 4.9).
