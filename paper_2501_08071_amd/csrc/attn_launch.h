@@ -141,9 +141,10 @@ inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
 // it works on head b % BH, so that with an odd number of heads every XCD reads every head, with an even one that is no multiple of
 // four every other, while without the mask two groups have whole heads to an XCD.  Times of one over the other, geometric mean (least .. most), three
 // sets of buffers in turn:
-//   D = 64, no mask, one group / two, n64 <= 256: up to 128 keys and 384 groups 0.90 (0.86 .. 1.05).  Longer ones with fewer than 512 groups and 1500 keys are 0.95
-//   (0.88 .. 0.99) with multiples of four heads, 1.13 (0.89 .. 1.34) with odd ones, but peaked logits lose up to 9 % of that, and with two blocks to a wavefront an
-//   exact largest weight now and then (bfloat16, error of O up to 1.03 times that of two groups whose rows move together): two groups.
+//   D = 64, no mask, one group / two, n64 <= 256: up to 128 keys and 384 groups 0.90 (0.86 .. 1.05), with more 1.12 (1.05 .. 1.17), but multiples of four heads 0.91; 129 to
+//   256 keys, multiples of four heads 0.95 (0.87 .. 0.99), other even numbers 1.06 (0.93 .. 1.17), odd ones 1.15 (0.89 .. 1.34).  Longer ones, where a wavefront has more than
+//   one block: 0.95 (0.89 .. 1.02), 1.00, 1.13, but peaked logits lose up to 9 % of that, and with two blocks an exact largest weight now and
+//   then (bfloat16, error of O up to 1.03 times that of two groups, whose rows move together): two groups.
 //   D = 64 with the mask, one group / two, n32 <= 512: 0.77 (0.61 .. 1.04), but odd numbers of heads with 225 to 320 keys and more than 300 groups 1.02 (1.00 .. 1.07).  One group /
 //   keys split, up to 690 groups: even numbers of heads from 289 keys on 0.76 (0.55 .. 1.01), odd ones from 513 on 0.75 (0.56 .. 1.00), between 1.00 (0.93 .. 1.10).
 //     Beyond that two groups / keys split, up to 512 pairs from 1985 keys on 0.82 (0.70 .. 1.00), up to 384 from 1000 on 0.93 (0.82 .. 1.07).
@@ -156,7 +157,7 @@ inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
     const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
     const bool even = BH % 2 == 0;
     if (!causal) {
-        if (D == 64 && n64 <= 256 && S <= 128 && n32 <= 384) return 1;
+        if (D == 64 && n64 <= 256 && S <= 256 && ((S <= 128 && n32 <= 384) || BH % 4 == 0)) return 1;
         return n64 <= 256 ? 2 : D == 32 && n32 <= 512 && S > 256 ? 1 : 0;
     }
     if (D == 64) {
