@@ -141,8 +141,9 @@ inline int attn_stream_groups(long long BH, int S, int D, bool causal) {
 // it works on head b % BH, so that with an odd number of heads every XCD reads every head, with an even one that is no multiple of
 // four every other, while without the mask two groups have whole heads to an XCD.  Times of one over the other, geometric mean (least .. most), three
 // sets of buffers in turn:
-//   D = 64, no mask, one group / two, n64 <= 256: up to 128 keys and 384 groups 0.90 (0.86 .. 1.05), with more 1.12 (1.05 .. 1.17), but multiples of four heads 0.91; 129 to
-//   256 keys, multiples of four heads 0.95 (0.87 .. 0.99), other even numbers 1.06 (0.93 .. 1.17), odd ones 1.15 (0.89 .. 1.34).  Longer ones, where a wavefront has more than
+//   D = 64, no mask, one group / two, n64 <= 256: up to 96 keys 0.90 (0.86 .. 0.93); 97 to 128 and multiples of four heads 0.90 (0.87 .. 0.92), others up to 320 groups 0.90
+//   (0.86 .. 0.98), with more 1.10 (0.91 .. 1.18); 129 to 256 and multiples of four heads 0.95 (0.84 .. 0.99), other even numbers up to 320 groups 0.95
+//   (0.93 .. 0.99), with more 1.09 (0.90 .. 1.22), odd ones 1.15 (0.87 .. 1.36).  Longer ones, where a wavefront has more than
 //   one block: 0.95 (0.89 .. 1.02), 1.00, 1.13, but peaked logits lose up to 9 % of that, and with two blocks an exact largest weight now and
 //   then (bfloat16, error of O up to 1.03 times that of two groups, whose rows move together): two groups.
 //   D = 64 with the mask, one group / two, n32 <= 512: 0.77 (0.61 .. 1.04), but odd numbers of heads with 225 to 320 keys and more than 300 groups 1.02 (1.00 .. 1.07).  One group /
@@ -157,7 +158,7 @@ inline int attn_stream_few_tiles(long long BH, int S, int D, bool causal) {
     const long long n32 = BH * ((S + 31) / 32), n64 = BH * ((S + 63) / 64);
     const bool even = BH % 2 == 0;
     if (!causal) {
-        if (D == 64 && n64 <= 256 && S <= 256 && ((S <= 128 && n32 <= 384) || BH % 4 == 0)) return 1;
+        if (D == 64 && n64 <= 256 && S <= 256 && (S <= 96 || BH % 4 == 0 || (n32 <= 320 && (even || S <= 128)))) return 1;
         return n64 <= 256 ? 2 : D == 32 && n32 <= 512 && S > 256 ? 1 : 0;
     }
     if (D == 64) {
@@ -180,7 +181,7 @@ inline int attn_stream_many_tiles(long long BH, int S, int D, bool causal) {
     if (D == 64) {
         if (!attn_grid_fits(n32, 64 * ATTN_NW)) return 0;
         if (S <= 96) return 1;                       // up to 32 keys 0.32 (0.26 .. 0.38), to 64 0.60 (0.50 .. 0.69), to 96 0.77 (0.60 .. 1.01)
-        // 0.97 (0.94 .. 1.01) up to 550 groups, 1.07 (0.92 .. 1.27) above; past a round of tiles 0.77 (0.73 .. 0.82) up to 1200, 0.92 (0.73 .. 1.09) above
+        // 0.97 (0.94 .. 1.10) up to 550 groups, 1.07 (0.92 .. 1.27) above; past a round of tiles 0.77 (0.73 .. 0.82) up to 1200, 0.92 (0.73 .. 1.09) above
         if (S <= 128) return n32 <= 550 || (tiles > 256 && n32 <= 1200) ? 1 : 0;
         return S <= 160 && n32 <= 800 ? 1 : 0;       // 0.89 (0.82 .. 0.94), with more 0.95 (0.73 .. 1.22)
     }
