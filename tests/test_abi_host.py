@@ -306,7 +306,7 @@ def test_routes_past_the_small_tiles(P):
             (33, 2528, 64, True): "8", (55, 1056, 64, False): "h", (95, 671, 64, False): "8", (10, 7496, 64, False): "h",
             # odd numbers of heads, which every XCD reads: one group to a workgroup, or streaming at all, was up to 1.2 times as slow
             (114, 128, 64, False): "s2", (113, 128, 64, False): "s2", (39, 249, 64, False): "s2", (45, 192, 64, False): "s2", (58, 192, 64, False): "s2", (11, 1384, 64, False): "s2",
-            (88, 78, 64, False): "s1", (96, 128, 64, False): "s1", (97, 128, 64, False): "s2", (95, 128, 64, False): "s2", (79, 128, 64, False): "s1", (95, 96, 64, False): "s1", (100, 128, 64, False): "s1", (60, 129, 64, False): "s1", (62, 129, 64, False): "s2", (40, 249, 64, False): "s1", (40, 257, 64, False): "s2", (24, 498, 64, False): "s2", (57, 237, 64, True): "s2", (58, 237, 64, True): "s1", (43, 196, 64, True): "s1", (39, 320, 64, True): "s2", (39, 321, 64, True): "s1", (55, 381, 64, True): "h",
+            (88, 78, 64, False): "s1", (96, 128, 64, False): "s1", (97, 128, 64, False): "s2", (95, 128, 64, False): "s2", (79, 128, 64, False): "s1", (95, 96, 64, False): "s1", (100, 128, 64, False): "s1", (60, 129, 64, False): "s1", (62, 129, 64, False): "s1", (66, 129, 64, False): "s2", (40, 249, 64, False): "s1", (40, 257, 64, False): "s2", (24, 498, 64, False): "s2", (57, 237, 64, True): "s2", (58, 237, 64, True): "s1", (43, 196, 64, True): "s1", (39, 320, 64, True): "s2", (39, 321, 64, True): "s1", (55, 381, 64, True): "h",
             (43, 492, 64, True): "h", (42, 492, 64, True): "s1", (47, 505, 32, True): "h", (46, 505, 32, True): "s2",
             # no length has a kernel of its own: those next to a line with the same number of workgroups are on the same side of it
             (33, 479, 32, False): "s1", (33, 480, 32, False): "s1", (33, 481, 32, False): "h", (64, 319, 64, True): "s1", (64, 320, 64, True): "s1", (64, 321, 64, True): "h",
