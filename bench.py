@@ -41,20 +41,20 @@ ATTN_FILES = ("attn_fwd_gfx950.hip", "attn_fwd_stream_gfx950.hip", "attn_fwd_row
 ROW_FILES = ("rowops_gfx950.hip", "rowops_launch.h", "gfx950_common.h")
 GEMM_FILES = ("gemm_gfx950.hip", "gemm_launch.h", "gfx950_common.h")
 TRAFFIC = {
-    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 147603 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "bc15f232cad6e82bf12d043abcea82a10f69ea2f861ede8aee56be336c34cb52",
+    "B2_H32_S4096_D128_bf16_causal": {"fetch_kib": 148409 * 2.0, "write_kib": 132096 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "8bf3231e24390a908f88c5f825b4abc46af7e6f228e36311ea53e2a4c6f5a5fd",
      "source": "profiles/attn_fwd_kernel_S4096_D128_bf16_causal.md"},
-    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 909415 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "bc15f232cad6e82bf12d043abcea82a10f69ea2f861ede8aee56be336c34cb52",
+    "B1_H32_S16384_D128_bf16_causal": {"fetch_kib": 905690 * 2.0, "write_kib": 264192 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "8bf3231e24390a908f88c5f825b4abc46af7e6f228e36311ea53e2a4c6f5a5fd",
      "source": "profiles/attn_fwd_kernel_all_workloads.md"},
-    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98514.6 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "bc15f232cad6e82bf12d043abcea82a10f69ea2f861ede8aee56be336c34cb52",
+    "B16_H16_S2048_D64_f16_peaky": {"fetch_kib": 98514.2 * 2.0, "write_kib": 133120 * 1.0, "files": ATTN_FILES,
+     "kernel_sha256": "8bf3231e24390a908f88c5f825b4abc46af7e6f228e36311ea53e2a4c6f5a5fd",
      "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
     "B4_H16_S1024_D64_f16": {"fetch_kib": 12460 * 2.0, "write_kib": 16640 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "bc15f232cad6e82bf12d043abcea82a10f69ea2f861ede8aee56be336c34cb52",
+     "kernel_sha256": "8bf3231e24390a908f88c5f825b4abc46af7e6f228e36311ea53e2a4c6f5a5fd",
      "source": "profiles/attn_fwd_kernel_S2048_D64_f16.md"},
     "B1_H4_S4096_D32_f16_paper": {"fetch_kib": 2622.8 * 2.0, "write_kib": 2112 * 1.0, "files": ATTN_FILES,
-     "kernel_sha256": "bc15f232cad6e82bf12d043abcea82a10f69ea2f861ede8aee56be336c34cb52",
+     "kernel_sha256": "8bf3231e24390a908f88c5f825b4abc46af7e6f228e36311ea53e2a4c6f5a5fd",
      "source": "profiles/attn_fwd_halves_stream_kernel.md"},
     # the row kernels (workload name as rowop_run reports it)
     "softmax_512x4096_f16 x16 rows": {"fetch_kib": 32798.0 * 2.0, "write_kib": 65536.0 * 1.0, "files": ROW_FILES,
