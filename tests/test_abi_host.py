@@ -349,4 +349,7 @@ def test_grids_past_the_launch_limit_keep_large_tiles(P):
         for heads, S in ((524300, 1000), (540000, 1000), (4200000, 100), (8388600, 100), (2097000, 257), (1 << 20, 512)):
             name, rows = P.attn_kernel_name(1, heads, S, 32, 0, causal), P.attn_workgroup_rows(1, heads, S, 32, 0, causal)
             assert heads * -(-S // rows) * 512 < 1 << 32, (heads, S, causal, name)
+        for heads, S in ((2700000, 96), (2800000, 96), (4194303, 64), (4194304, 64), (8388600, 1)):
+            rows = P.attn_workgroup_rows(1, heads, S, 64, 0, causal)
+            assert heads * -(-S // rows) * 512 < 1 << 32 and (rows == 32) == (heads * -(-S // 32) * 512 < 1 << 32), (heads, S, causal, rows)
     assert "stream" in P.attn_kernel_name(1, 524000, 1000, 32, 0, False) and P.attn_workgroup_rows(1, 524300, 1000, 32, 0, False) == 256
